@@ -112,16 +112,20 @@ __host__ __device__ constexpr int unrolled_slots(int K) { return K == 29 ? 7 : (
 // ---- epilogue shared by the engines of this file ------------------------------------------------
 // The sums leave the accumulators through a wave-private LDS tile [16 rows][NT*32] (float32) so that
 // each lane finishes 8 consecutive time steps of one channel: one 16-byte residual load, one scale,
-// one shift, one 16-byte store per item (rows of out and res are 16-byte aligned: checked by the
-// host).  All of these are buffer accesses without branches: absent operands have empty descriptors
-// and read zeros, masked lanes go out of range.
+// one shift, one 16-byte store per item.  All of these are buffer accesses without branches: absent
+// operands have empty descriptors and read zeros, masked lanes go out of range.  That needs 16-byte
+// aligned rows of out and res; the ANYROW instances also serve rows of any length (`anyrow`): the same
+// items through 16-byte global accesses at 2-byte aligned addresses, element by element for the group
+// that holds the end of a row.
 template <int NT>
 struct Epilogue {
     static constexpr int TN = NT * 32;
     static constexpr int kItems = NT;  // 16 rows * (TN/8) groups / 64 lanes
     __amdgpu_buffer_rsrc_t rs_out, rs_res, rs_scale, rs_shift;
     int M, Tout;
-    bool has_scale, relu;
+    bool has_scale, relu, anyrow;
+    bf16_t *out_p;        // (anyrow) the tensors themselves
+    const bf16_t *res_p;
     const int *len_out;  // optional [B]: outputs at t >= ceil((len_out[b] - sub) / div) are written as zero
     int len_sub, len_div;
     double *stats;       // see ConvGemmParams::stats (used by the STATS instances only)
@@ -133,6 +137,7 @@ struct Epilogue {
         float scv[kItems], shv[kItems];
         uint32_t ooff[kItems];
         int tlim_rel;  // output limit of the batch item relative to the tile's first time step (wave-uniform)
+        int tout_rel;  // the same of the row's end
     };
     // first time step of batch item b that is written as zero (Tout without lengths)
     __device__ __forceinline__ int out_limit(int b) const
@@ -155,6 +160,9 @@ struct Epilogue {
         Tout = Tout_;
         has_scale = scale != nullptr;
         relu = relu_ != 0;
+        anyrow = Tout_ % 8 != 0;
+        out_p = const_cast<bf16_t *>(out);
+        res_p = res;
         rs_out = __builtin_amdgcn_make_buffer_rsrc((void *)out, 0, out_bytes, 0x00020000);
         rs_res = __builtin_amdgcn_make_buffer_rsrc((void *)res, 0, res ? out_bytes : 0, 0x00020000);
         rs_scale = __builtin_amdgcn_make_buffer_rsrc((void *)scale, 0, scale ? M_ * 4 : 0, 0x00020000);
@@ -162,10 +170,12 @@ struct Epilogue {
     }
     // operands of the 16 tile rows whose first channel is m0 (tile row r is channel m0 + r, or
     // m0 + 32*(r/8) + r%8 when `split`: eight rows from each row of blocks); el: the lane number
+    template <bool ANYROW = false>
     __device__ __forceinline__ RowLoads request_rows(int el, int b, int t0, int m0, bool split) const
     {
         RowLoads ld;
         ld.tlim_rel = out_limit(b) - t0;
+        ld.tout_rel = Tout - t0;
 #pragma unroll
         for (int q = 0; q < kItems; ++q) {
             const int idx = el + 64 * q;
@@ -175,14 +185,17 @@ struct Epilogue {
             const bool ok = m < M && t < Tout;
             ld.ooff[q] = ok ? (uint32_t)((((size_t)b * M + m) * Tout + t) * 2) : kOutOfRange;
             const uint32_t moff = ok ? (uint32_t)m * 4u : kOutOfRange;
-            ld.rvec[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_res, ld.ooff[q], 0, 0);
+            if (ANYROW && anyrow)
+                ld.rvec[q] = load8_any(res_p + ld.ooff[q] / 2, ok && res_p ? Tout - t : 0);
+            else
+                ld.rvec[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_res, ld.ooff[q], 0, 0);
             ld.scv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_scale, moff, 0, 0));
             ld.shv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_shift, moff, 0, 0));
         }
         return ld;
     }
     // affine, residual, ReLU, rounding and the stores of the 16 rows that sit in the LDS tile tp
-    template <bool STATS = false>
+    template <bool STATS = false, bool ANYROW = false>
     __device__ __forceinline__ void finish_rows(int el, float *tp, const RowLoads &ld) const
     {
 #pragma unroll
@@ -209,7 +222,10 @@ struct Epilogue {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] &= nvalid >= 2 * e + 2 ? 0xffffffffu : (nvalid == 2 * e + 1 ? 0x0000ffffu : 0u);
             }
-            __builtin_amdgcn_raw_buffer_store_b128(o, rs_out, ld.ooff[q], 0, 0);
+            if (ANYROW && anyrow)
+                store8_any(out_p + ld.ooff[q] / 2, o, ld.ooff[q] != kOutOfRange ? ld.tout_rel - c8 * 8 : 0);
+            else
+                __builtin_amdgcn_raw_buffer_store_b128(o, rs_out, ld.ooff[q], 0, 0);
             if constexpr (STATS) {  // sums of the eight stored (rounded) values; an item outside the tensor adds nothing
                 float s1 = 0.f, s2 = 0.f;
                 if (ld.ooff[q] != kOutOfRange) {
@@ -247,12 +263,12 @@ struct Epilogue {
     // A whole 64-row tile held by one wavefront (rows m_first .. m_first+63): four rounds of 16 rows
     // (row of blocks mi, accumulator registers 8*gp .. 8*gp+7) through tp; the operands of a round
     // are requested two rounds ahead.
-    template <bool STATS = false>
+    template <bool STATS = false, bool ANYROW = false>
     __device__ __forceinline__ void store_private_tile(const f32x16 (&acc)[2][NT], float *tp, int el, int b, int t0,
                                                        int m_first, int part = 0) const
     {
         const int tcol = el & 31, thalf = el >> 5;
-        RowLoads ld[2] = {request_rows(el, b, t0, m_first, false), request_rows(el, b, t0, m_first + 16, false)};
+        RowLoads ld[2] = {request_rows<ANYROW>(el, b, t0, m_first, false), request_rows<ANYROW>(el, b, t0, m_first + 16, false)};
 #pragma unroll
         for (int rd = 0; rd < 4; ++rd) {
             const int mi = rd >> 1, gp = rd & 1;
@@ -265,8 +281,8 @@ struct Epilogue {
                     for (int ni = 0; ni < NT; ++ni) tp[r * TN + ni * 32 + tcol] = acc[mi][ni][4 * (2 * gp + g) + j];
                 }
             wave_lds_fence();
-            finish_rows<STATS>(el, tp, ld[rd & 1]);
-            if (rd + 2 < 4) ld[rd & 1] = request_rows(el, b, t0, m_first + (rd + 2) * 16, false);
+            finish_rows<STATS, ANYROW>(el, tp, ld[rd & 1]);
+            if (rd + 2 < 4) ld[rd & 1] = request_rows<ANYROW>(el, b, t0, m_first + (rd + 2) * 16, false);
             wave_lds_fence();
             if constexpr (STATS) emit_row_stats(el, tp, m_first + rd * 16 + el, part, t0);
         }
@@ -287,7 +303,8 @@ struct TileCoords {
 
 // KT > 0: the number of taps is a compile-time constant and a chunk is one straight-line block
 // (see the unrolled main loop below); KT == 0: any K, tap pairs in a loop.
-// LEN: the instance for calls with per-sample lengths; it alone carries the test for tiles in the padding.
+// LEN: the instance for ragged calls -- per-sample lengths, output rows of any length; of the unrolled kernels it
+// alone carries the test for tiles in the padding and the epilogue for such rows.
 // STATS: the instance that also writes the per-tile statistics of its stored outputs (ConvGemmParams::stats).
 template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false>
 __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParams p)
@@ -296,6 +313,7 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int TN = NT * 32;
+    constexpr bool ANYROW = LEN || KT == 0;
 
     const int nitems = p.nitems;                           // staging items per lane and chunk
     const int nmy = (p.nch - wave + kWaves - 1) / kWaves;  // chunks of this wavefront (may be 0)
@@ -724,7 +742,7 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
 
         if (priv) {
             // A private tile: this wavefront holds all 64 rows.
-            epi.template store_private_tile<STATS>(acc, tp, el, tc.b, tc.t0, tc.mt * kTileM, tc.b * p.ntt + tc.t0 / TN);
+            epi.template store_private_tile<STATS, ANYROW>(acc, tp, el, tc.b, tc.t0, tc.mt * kTileM, tc.b * p.ntt + tc.t0 / TN);
 #pragma unroll
             for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -736,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
             // wave hands the other three quarters over through LDS, one row of blocks (mi) per
             // round; the scratch is the dead-parity staging buffers of all four wavefronts.  The
             // operands of this wave's 16 rows are requested before the sum.
-            const auto ld = epi.request_rows(el, tc.b, tc.t0, tc.mt * kTileM + 8 * wave, true);
+            const auto ld = epi.template request_rows<ANYROW>(el, tc.b, tc.t0, tc.mt * kTileM + 8 * wave, true);
             f32x4 *red = reinterpret_cast<f32x4 *>(smem + (size_t)dead_par * kWaves * p.buf_bytes);
             __syncthreads();  // every wavefront has left the main loop
             // One copy of the exchange per wave number, so that the accumulator quarters are named
@@ -790,7 +808,7 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
             default: exchange(std::integral_constant<int, 3>{}); break;
             }
             wave_lds_fence();
-            epi.template finish_rows<STATS>(el, tp, ld);
+            epi.template finish_rows<STATS, ANYROW>(el, tp, ld);
             wave_lds_fence();
             if constexpr (STATS) {  // this wavefront's rows: channels 8*wave .. +7 of both row blocks of the tile
                 epi.emit_row_stats(el, tp, tc.mt * kTileM + 8 * wave + (el >> 3) * 32 + (el & 7), tc.b * p.ntt + tc.t0 / TN,
@@ -834,7 +852,8 @@ struct PwShape {
     static constexpr size_t kLds = 2 * (size_t)kBufBytes + (kEpiInBuf ? 0 : kEpiBytes);
 };
 
-// LEN: the launch carries input lengths (a staged group may straddle the valid length of its item).
+// LEN: the launch carries input lengths (a staged group may straddle the valid length of its item) or has output
+// rows of any length.
 template <bool LEN, int MI, int NT, int SC>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void pointwise_gemm_kernel(const ConvGemmParams p)
 {
@@ -845,7 +864,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int T = p.Tout;                                  // == p.Tin
+    const int T = p.Tin;                                   // row_pitch(p.Tout)
     const int nmt4 = (p.nmt + kWaves * RT - 1) / (kWaves * RT);  // workgroup row tiles
     const int nst = (p.R + kPwStageCh - 1) / kPwStageCh;   // stages per tile
     const int ncols = p.ntt * p.B;                         // time tiles of all batch items
@@ -1045,7 +1064,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
             float *tp = reinterpret_cast<float *>(ebase + (size_t)wave * 16 * TN * sizeof(float));
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
-                epi.store_private_tile(acc[rt], tp, el, q.b, q.t0, ((q.mt4 * kWaves + wave) * RT + rt) * kTileM);
+                epi.template store_private_tile<false, LEN>(acc[rt], tp, el, q.b, q.t0, ((q.mt4 * kWaves + wave) * RT + rt) * kTileM);
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -1360,6 +1379,56 @@ __global__ __launch_bounds__(256) void interleave2_kernel(const u32x4 *__restric
     dx[2 * i + 1] = hi;
 }
 
+// The preparation of a call on rows that are no multiple of eight long (RowPrep): packing blocks, mask blocks (a
+// wavefront per 32 channels x 64 time steps), copy blocks (a 16-byte group of the pitched copy per thread).
+// Bound by memory: a 16 x 384 x 777 padded batch (K = 13, with residual) takes 201 us for the forward
+// pass and both gradients, 30 900 us on the plain kernels that served such rows before.
+struct PrepareRowsArgs {
+    unsigned npack, nmask;
+    const bf16_t *w;
+    u32x4 *wp;
+    int M, R, K, nch, ld, vec;
+    size_t zero_off;
+    const float *rscale;
+    int B, Cout, To, ncm, nst, nst4, relu;
+    const bf16_t *dy, *y;
+    bf16_t *gplain, *dres;
+    u32x4 *gf;
+    int Cin, T, T8;
+    size_t ngroups;
+    const int *len;
+    const bf16_t *x;
+    u32x4 *xp;
+};
+template <bool FLIP>
+__global__ __launch_bounds__(256) void prepare_rows_kernel(const PrepareRowsArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned blk = blockIdx.x;
+    if (blk < a.npack) {
+        prepack_block<FLIP>(blk, smem, a.w, a.wp, a.M, a.R, a.K, a.nch, a.ld, a.zero_off, a.vec, a.rscale);
+        return;
+    }
+    blk -= a.npack;
+    if (blk < a.nmask) {
+        const unsigned item = blk * 4 + (threadIdx.x >> 6);  // (b, cm, st4), st4 fastest
+        if (item >= (unsigned)(a.B * a.ncm * a.nst4)) return;
+        const int st4 = item % a.nst4, cm = (item / a.nst4) % a.ncm, b = item / (a.nst4 * a.ncm);
+        mask_pack_wave_any(threadIdx.x & 63, b, cm, st4, a.Cout, a.To, a.ncm, a.nst, a.dy, a.y, a.relu, a.gplain, a.dres, a.gf);
+        return;
+    }
+    const size_t i = (size_t)(blk - a.nmask) * 256 + threadIdx.x;
+    if (i >= a.ngroups) return;
+    const size_t row = i / (unsigned)a.T8;
+    const int t = 8 * (int)(i - row * (unsigned)a.T8);
+    int n = a.T;
+    if (a.len) {
+        const int l = a.len[row / (unsigned)a.Cin];
+        n = l < 0 ? 0 : (l < n ? l : n);
+    }
+    a.xp[i] = load8_any(a.x + row * a.T + t, n - t);
+}
+
 struct Plan {
     bool ok;
     int nt;       // NT template value (5 or 2)
@@ -1371,14 +1440,14 @@ struct Plan {
     size_t lds;
 };
 
-// Tin, Tout: lengths of the rows that are staged / written; both must be 16-byte aligned (% 8 == 0).
+// Tin, Tout: lengths of the rows that are staged / written; the staged ones must be 16-byte aligned (% 8 == 0).
 // R: reduction channels (cross-tile staging needs every wavefront to own the same number of chunks).
 Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
 {
     Plan pl = {};
     pl.stride = stride;
     if (stride != 1 && stride != 2) return pl;
-    if (Tin % 8 != 0 || Tout % 8 != 0) return pl;
+    if (Tin % 8 != 0) return pl;
     if ((size_t)kPackRows * pack_m_stride(K) * sizeof(bf16_t) > (size_t)kMaxLds) return pl;  // weight packing tile
     const int nch = (R + kChunk - 1) / kChunk;
     // candidate 0: the kernel with an unrolled chunk (tap counts it is built for, stride 1, wide tile,
@@ -1481,7 +1550,7 @@ hipError_t launch_pointwise(const ConvGemmParams &p, hipStream_t s)
     // its padding and last-round losses outweigh that
     const int cus = current_device_info().cus;
     const bool big = pointwise_waste<4, 4>(p, cus) <= 1.12 * pointwise_waste<2, 5>(p, cus);
-    if (p.len_in)
+    if (p.len_in || p.Tout % 8 != 0)
         return big ? launch_pointwise_shape<true, 4, 4, 64>(p, s) : launch_pointwise_shape<true, 2, 5, 128>(p, s);
     return big ? launch_pointwise_shape<false, 4, 4, 64>(p, s) : launch_pointwise_shape<false, 2, 5, 128>(p, s);
 }
@@ -1508,7 +1577,8 @@ hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s)
         return launch_few_channels(p, s);
     // one tap, no padding, wide tiles: the GEMM kernel whose wavefronts share the staged activations
     // (worth it from two 64-channel row tiles on: a single one would leave three wavefronts idle)
-    if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout) return launch_pointwise(p, s);
+    if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == row_pitch(p.Tout))
+        return launch_pointwise(p, s);
     if (p.stats) {  // (the caller has checked stats_on_engine)
         switch (p.K) {
         case 11: return launch_t<5, 1, 11, false, true>(p, pl.lds, s);
@@ -1520,7 +1590,7 @@ hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s)
         default: return hipErrorInvalidValue;
         }
     }
-    if (pl.unrolled && (p.len_in || p.len_out)) {
+    if (pl.unrolled && (p.len_in || p.len_out || p.Tout % 8 != 0)) {
         switch (p.K) {
         case 11: return launch_t<5, 1, 11, true>(p, pl.lds, s);
         case 13: return launch_t<5, 1, 13, true>(p, pl.lds, s);
@@ -1593,6 +1663,63 @@ hipError_t run_prepack(const void *w, void *wp, int M, int R, int K, bool flip, 
     return hipGetLastError();
 }
 
+}  // namespace
+hipError_t launch_prepare_rows(const Geom &g, const RowPrep &r, hipStream_t s)
+{
+    PrepareRowsArgs a = {};
+    size_t lds = 0;
+    if (r.w) {
+        a.M = r.flip ? g.Cin : g.Cout;
+        a.R = r.flip ? g.Cout : g.Cin;
+        const PackGeom q = pack_geom(r.w, a.M, a.R, g.K, r.flip);
+        a.npack = q.blocks;
+        a.w = (const bf16_t *)r.w;
+        a.wp = (u32x4 *)r.wp;
+        a.K = g.K; a.nch = q.nch; a.ld = (r.flip ? a.M : a.R) * g.K; a.vec = q.vec;
+        a.zero_off = q.zero_off;
+        a.rscale = r.rscale;
+        lds = q.lds;
+    }
+    if (r.dy) {
+        a.B = g.B; a.Cout = g.Cout; a.To = g.To;
+        a.ncm = r.gf ? r.ncm : (g.Cout + 31) / 32;
+        a.nst = r.gf ? r.nst : (g.To + 15) / 16;
+        a.nst4 = (a.nst + 3) / 4;
+        a.nmask = (unsigned)(((size_t)g.B * a.ncm * a.nst4 + 3) / 4);
+        a.dy = (const bf16_t *)r.dy;
+        a.y = (const bf16_t *)r.y;
+        a.relu = r.relu ? 1 : 0;
+        a.gplain = (bf16_t *)r.gplain;
+        a.dres = (bf16_t *)r.dres;
+        a.gf = (u32x4 *)r.gf;
+    }
+    unsigned ncopy = 0;
+    if (r.x) {
+        a.Cin = g.Cin; a.T = g.T; a.T8 = row_pitch(g.T) / 8;
+        a.ngroups = (size_t)g.B * g.Cin * a.T8;
+        a.len = g.len;
+        a.x = (const bf16_t *)r.x;
+        a.xp = (u32x4 *)r.xp;
+        ncopy = (unsigned)((a.ngroups + 255) / 256);
+    }
+    const unsigned blocks = a.npack + a.nmask + ncopy;
+    if (blocks == 0) return hipSuccess;
+    hipError_t e;
+    if (r.flip) {
+        static LdsOptIn opt_in;
+        e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(prepare_rows_kernel<true>), kMaxLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(prepare_rows_kernel<true>, dim3(blocks), dim3(256), lds, s, a);
+    } else {
+        static LdsOptIn opt_in;
+        e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(prepare_rows_kernel<false>), kMaxLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(prepare_rows_kernel<false>, dim3(blocks), dim3(256), lds, s, a);
+    }
+    return hipGetLastError();
+}
+namespace {
+
 void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin, int Tout, int K, int dil, int padL)
 {
     p.B = B; p.M = M; p.R = R; p.Tin = Tin; p.Tout = Tout; p.K = K; p.Kp = (K + 1) & ~1; p.dil = dil; p.padL = padL;
@@ -1612,17 +1739,18 @@ void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin
 // ---- forward ---------------------------------------------------------------------------
 bool mfma_fwd_supported(const Geom &g)
 {
-    if ((size_t)g.B * g.Cin * g.T * sizeof(bf16_t) > kMaxInput) return false;
-    if ((size_t)g.B * g.Cout * g.To * sizeof(bf16_t) > kMaxInput) return false;
-    return packed_bytes(g.Cout, g.Cin, g.K) < kMaxPacked && make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil).ok;
+    if ((size_t)g.B * g.Cin * row_pitch(g.T) * sizeof(bf16_t) > kMaxInput) return false;
+    if ((size_t)g.B * g.Cout * row_pitch(g.To) * sizeof(bf16_t) > kMaxInput) return false;
+    return packed_bytes(g.Cout, g.Cin, g.K) < kMaxPacked && make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil).ok;
 }
 
-size_t mfma_fwd_workspace(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K); }
+size_t mfma_fwd_workspace(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K) + pitched_x_bytes(g); }
 
 // Whether the forward pass of this geometry runs on a kernel instance that can also write the statistics of its
-// outputs, and into how many (batch item, time tile) parts: the unrolled engine, wide tile, no lengths.
+// outputs, and into how many (batch item, time tile) parts: the unrolled engine, wide tile, no lengths, 16-byte rows.
 int mfma_fwd_stats_parts(const Geom &g)
 {
+    if (!rows16(g)) return 0;
     const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !pl.unrolled || pl.nt != 5 || g.len || !mfma_fwd_supported(g)) return 0;
     if (pl.buf_bytes < Epilogue<5>::kTileBytesWithStats) return 0;
@@ -1632,17 +1760,29 @@ int mfma_fwd_stats_parts(const Geom &g)
 hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const float *scale, const float *shift,
                            const void *res, void *y, bool relu, void *ws, hipStream_t s, double *stats)
 {
-    const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
+    const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !mfma_fwd_supported(g)) return hipErrorInvalidValue;
     if (stats && mfma_fwd_stats_parts(g) == 0) return hipErrorInvalidValue;
     // a pointwise layer with a handful of output channels is a stream over x: no packing, no tiles
     if (skinny_fwd_supported(g) && ((uintptr_t)w % 16) == 0) return launch_skinny_fwd(g, x, w, scale, shift, res, y, relu, s);
-    hipError_t e = run_prepack(w, ws, g.Cout, g.Cin, g.K, false, nullptr, s);
+    hipError_t e;
+    const void *in = x;
+    if (g.T % 8 == 0) {
+        e = run_prepack(w, ws, g.Cout, g.Cin, g.K, false, nullptr, s);
+    } else {
+        RowPrep a = {};
+        a.w = w;
+        a.wp = ws;
+        a.x = x;
+        a.xp = (unsigned char *)ws + packed_bytes(g.Cout, g.Cin, g.K);
+        in = a.xp;
+        e = launch_prepare_rows(g, a, s);
+    }
     if (e != hipSuccess) return e;
     ConvGemmParams p = {};
-    fill_common(p, pl, g.B, g.Cout, g.Cin, g.T, g.To, g.K, g.dil, g.pad);
+    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad);
     p.relu = relu ? 1 : 0;
-    p.in = (const bf16_t *)x;
+    p.in = (const bf16_t *)in;
     p.len_in = g.len;
     p.wp = (const bf16x8 *)ws;
     p.scale = scale; p.shift = shift; p.res = (const bf16_t *)res;
@@ -1674,16 +1814,16 @@ Phase2 phases_of_stride2(const Geom &g)
     ph.ok = true;
     return ph;
 }
-size_t dz_bytes_of(const Geom &g) { return align_up((size_t)g.B * g.Cout * g.To * sizeof(bf16_t), 256); }
+size_t dz_bytes_of(const Geom &g) { return align_up((size_t)g.B * g.Cout * row_pitch(g.To) * sizeof(bf16_t), 256); }
 }  // namespace
 
 bool mfma_dgrad_supported(const Geom &g)
 {
-    if ((size_t)g.B * g.Cout * g.To * sizeof(bf16_t) > kMaxInput) return false;
-    if ((size_t)g.B * g.Cin * g.T * sizeof(bf16_t) > kMaxInput) return false;
+    if ((size_t)g.B * g.Cout * row_pitch(g.To) * sizeof(bf16_t) > kMaxInput) return false;
+    if ((size_t)g.B * g.Cin * row_pitch(g.T) * sizeof(bf16_t) > kMaxInput) return false;
     if (g.stride == 2) return phases_of_stride2(g).ok;
     if (g.stride != 1 || packed_bytes(g.Cin, g.Cout, g.K) >= kMaxPacked) return false;
-    return make_plan(g.To, g.T, g.Cout, g.K, 1, g.dil).ok;
+    return make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil).ok;
 }
 
 size_t mfma_dgrad_workspace(const Geom &g)
@@ -1773,7 +1913,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
 // parameters of the stride-1 input gradient as a run of the forward engine
 void fill_dgrad(ConvGemmParams &p, const Plan &pl, const Geom &g, const void *gin, const void *packed, void *dx, bool accumulate)
 {
-    fill_common(p, pl, g.B, g.Cin, g.Cout, g.To, g.T, g.K, g.dil, g.dil * (g.K - 1) - g.pad);
+    fill_common(p, pl, g.B, g.Cin, g.Cout, row_pitch(g.To), g.T, g.K, g.dil, g.dil * (g.K - 1) - g.pad);
     p.relu = 0;
     p.in = (const bf16_t *)gin;
     p.wp = (const bf16x8 *)packed;
@@ -1793,7 +1933,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
         if (accumulate) return hipErrorInvalidValue;
         return launch_mfma_dgrad_stride2(g, dy, y, scale, w, dx, dres, relu, ws, s);
     }
-    const Plan pl = make_plan(g.To, g.T, g.Cout, g.K, 1, g.dil);
+    const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;
     // g = dy*[y>0] (exact in bf16) comes from one elementwise pass, which shares a launch with the weight
     // packing when it can use 16-byte accesses (To % 8 == 0 on this path; dres aligned); the affine
@@ -1801,7 +1941,11 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
     hipError_t e;
     const void *gin = dy;
     void *gbuf = (unsigned char *)ws + packed_bytes(g.Cin, g.Cout, g.K);
-    if (!dres || ((uintptr_t)dres % 16) == 0) {
+    if (g.To % 8 != 0) {
+        const DzfLayout none = {};
+        e = launch_bwd_prepare(g, dy, y, scale, w, relu, ws, nullptr, none, dres, &gin, s);
+        if (e != hipSuccess) return e;
+    } else if (!dres || ((uintptr_t)dres % 16) == 0) {
         const int M = g.Cin, R = g.Cout;  // the engine's roles for this pass
         const PackGeom q = pack_geom(w, M, R, g.K, true);
         void *gout = dres ? dres : (relu ? gbuf : nullptr);
@@ -1831,11 +1975,31 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
 // Packs the flipped, scaled weights into ws and, in the same launch, forms g = dy*[y>0] in the two
 // layouts the gradients read: plain (into dres when the caller wants the residual gradient, else into
 // the workspace behind the packed weights; skipped when there is no ReLU and no dres) and in fragment
-// order (gf).  *g_plain receives the tensor the input-gradient engine has to contract.
+// order (gf).  *g_plain receives the tensor the input-gradient engine has to contract.  Rows of any length: g is
+// always formed, pitched, in the workspace; gf is optional; x (optional) is copied to xp in the same launch.
 hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
                               bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
-                              hipStream_t s)
+                              hipStream_t s, const void *x, void *xp)
 {
+    if (!rows16(g)) {
+        RowPrep a = {};
+        a.w = w;
+        a.wp = ws;
+        a.flip = true;
+        a.rscale = scale;
+        a.dy = dy;
+        a.y = y;
+        a.relu = relu;
+        a.gplain = (unsigned char *)ws + packed_bytes(g.Cin, g.Cout, g.K);
+        a.dres = dres;
+        a.gf = gf;
+        a.ncm = layout.ncm;
+        a.nst = layout.nst;
+        a.x = g.T % 8 == 0 ? nullptr : x;
+        a.xp = xp;
+        *g_plain = a.gplain;
+        return launch_prepare_rows(g, a, s);
+    }
     const int M = g.Cin, R = g.Cout;  // the engine's roles for the input gradient
     const PackGeom q = pack_geom(w, M, R, g.K, true);
     const size_t nfrag = (size_t)g.B * layout.ncm * ((layout.nst + 3) / 4);  // items of four fragments, one per wavefront
@@ -1853,7 +2017,7 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
 
 hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws, hipStream_t s)
 {
-    const Plan pl = make_plan(g.To, g.T, g.Cout, g.K, 1, g.dil);
+    const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, g_plain, ws, dx, accumulate);

@@ -1252,9 +1252,25 @@ hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, cons
     return hipGetLastError();
 }
 
-bool mfma_wgrad_supported(const Geom &g) { return g.K <= kMaxReduceTaps && (fast_ok(g) || make_wplan(g).ok); }
+// The kernels of this file work on 16-byte rows: where g's are not, on pitched copies of x and g (zeros behind a row
+// add nothing), which follow the kernel's own scratch in the workspace.
+bool mfma_wgrad_supported(const Geom &g0)
+{
+    const Geom g = pitched(g0);
+    return g.K <= kMaxReduceTaps && (fast_ok(g) || make_wplan(g).ok);
+}
 
+namespace {
+size_t wgrad_workspace16(const Geom &g, bool need_dz);
+}
 size_t mfma_wgrad_workspace(const Geom &g, bool need_dz)
+{
+    return wgrad_workspace16(pitched(g), need_dz || g.To % 8 != 0) + pitched_x_bytes(g);
+}
+size_t mfma_wgrad_x_offset(const Geom &g) { return mfma_wgrad_workspace(g, true) - pitched_x_bytes(g); }
+
+namespace {
+size_t wgrad_workspace16(const Geom &g, bool need_dz)
 {
     // (sized without looking at lengths: a call with lengths never takes the pointwise kernel)
     Geom g0 = g;
@@ -1273,12 +1289,14 @@ size_t mfma_wgrad_workspace(const Geom &g, bool need_dz)
     if (!w.ok) return 0;
     return part_bytes(g, w.S) + (need_dz ? dz_buf_bytes(g) : 0);
 }
+}  // namespace
 
 // ---- stride-1 kernel with dz already in fragment order (dz_pack_kernel's layout) ----------------
-bool mfma_wgrad_fast_supported(const Geom &g) { return fast_ok(g); }
+bool mfma_wgrad_fast_supported(const Geom &g) { return fast_ok(pitched(g)); }
 
-DzfLayout mfma_wgrad_dzf_layout(const Geom &g)
+DzfLayout mfma_wgrad_dzf_layout(const Geom &g0)
 {
+    const Geom g = pitched(g0);
     const FastPlan f = make_fast_plan(g);
     DzfLayout l;
     l.ncm = f.ncm;
@@ -1288,9 +1306,10 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g)
     return l;
 }
 
-hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float *scale, float *dw, bool accumulate, void *ws,
+hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float *scale, float *dw, bool accumulate, void *ws,
                                       hipStream_t s)
 {
+    const Geom g = pitched(g0);
     const FastPlan f = make_fast_plan(g);
     float *part = (float *)ws;
     const u32x4 *dzf = (const u32x4 *)((unsigned char *)ws + part_bytes(g, f.S));
@@ -1340,13 +1359,31 @@ hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float 
     return launch_wgrad_reduce(g, part, dw, scale, f.S, accumulate, s);
 }
 
-hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const void *y, const float *scale,
+hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, const void *y, const float *scale,
                              float *dw, bool relu, bool accumulate, void *ws, hipStream_t s)
 {
+    const Geom g = pitched(g0);
+    const bool copies = !rows16(g0);  // x, g or both are made into 16-byte rows first
+    RowPrep prep = {};
+    if (copies) {
+        prep.dy = dy;
+        prep.y = y;
+        prep.relu = relu;
+        if (g0.T % 8 != 0) {
+            prep.x = x;
+            prep.xp = (unsigned char *)ws + mfma_wgrad_x_offset(g0);
+            x = prep.xp;
+        }
+    }
     if (wgrad_k1_supported(g)) {
         // pointwise layers: a GEMM over rows as they lie in memory; g = dy*[y>0] only has to be formed with a ReLU
         const void *gplain = dy;
-        if (relu) {
+        if (copies) {
+            prep.gplain = (unsigned char *)ws + wgrad_k1_part_bytes(g);
+            gplain = prep.gplain;
+            hipError_t e = launch_prepare_rows(g0, prep, s);
+            if (e != hipSuccess) return e;
+        } else if (relu) {
             void *gbuf = (unsigned char *)ws + wgrad_k1_part_bytes(g);
             hipError_t e = launch_epilogue_bwd_vec8(g, dy, y, nullptr, relu, gbuf, nullptr, s);
             if (e != hipSuccess) return e;
@@ -1357,9 +1394,17 @@ hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const
     if (fast_ok(g)) {
         const FastPlan f = make_fast_plan(g);
         u32x4 *dzf = (u32x4 *)((unsigned char *)ws + part_bytes(g, f.S));
-        hipLaunchKernelGGL(dz_pack_kernel, dim3(((f.nst + 3) / 4 + 3) / 4, f.ncm, g.B), dim3(256), 0, s, g.Cout, g.To, f.ncm,
-                           f.nst, (const bf16_t *)dy, (const bf16_t *)y, relu ? 1 : 0, dzf);
-        hipError_t e = hipGetLastError();
+        hipError_t e;
+        if (copies) {
+            prep.gf = dzf;
+            prep.ncm = f.ncm;
+            prep.nst = f.nst;
+            e = launch_prepare_rows(g0, prep, s);
+        } else {
+            hipLaunchKernelGGL(dz_pack_kernel, dim3(((f.nst + 3) / 4 + 3) / 4, f.ncm, g.B), dim3(256), 0, s, g.Cout, g.To,
+                               f.ncm, f.nst, (const bf16_t *)dy, (const bf16_t *)y, relu ? 1 : 0, dzf);
+            e = hipGetLastError();
+        }
         if (e != hipSuccess) return e;
         return launch_mfma_wgrad_prepared(g, x, scale, dw, accumulate, ws, s);
     }
@@ -1367,7 +1412,12 @@ hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const
     if (!w.ok) return hipErrorInvalidValue;
     float *part = (float *)ws;
     const void *dz = dy;
-    if (relu) {
+    if (copies) {
+        prep.gplain = (unsigned char *)ws + part_bytes(g, w.S);
+        dz = prep.gplain;
+        hipError_t e = launch_prepare_rows(g0, prep, s);
+        if (e != hipSuccess) return e;
+    } else if (relu) {
         void *dzbuf = (unsigned char *)ws + part_bytes(g, w.S);
         // rows are 16-byte aligned here: To % 8 == 0 and the caller checked the pointers
         hipError_t e = launch_epilogue_bwd_vec8(g, dy, y, nullptr, relu, dzbuf, nullptr, s);

@@ -25,6 +25,17 @@ __device__ __forceinline__ int valid_len(const Geom &g, int b)
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
 
+// The matrix-core kernels stage rows in 16-byte groups.  Rows whose length is no multiple of eight are copied into
+// the workspace with this pitch, zeros behind the row (launch_prepare_rows); outputs are written in place.
+__host__ __device__ constexpr int row_pitch(int n) { return (n + 7) & ~7; }
+inline bool rows16(const Geom &g) { return g.T % 8 == 0 && g.To % 8 == 0; }
+inline Geom pitched(Geom g)  // the geometry of the copies
+{
+    g.T = row_pitch(g.T);
+    g.To = row_pitch(g.To);
+    return g;
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
 // float -> bfloat16, round to nearest, ties to even (finite inputs; NaN stays NaN).
@@ -103,6 +114,31 @@ __device__ __forceinline__ u32x4_t masked_grad8(u32x4_t g, const u32x4_t yv)
     return g;
 }
 
+// The first n (any number) of eight consecutive bf16 at any 2-byte aligned address, zeros behind them; one 16-byte
+// access where all eight are wanted (global accesses need no more alignment than their element's on this target).
+__device__ __forceinline__ u32x4_t load8_any(const bf16_t *p, int n)
+{
+    u32x4_t v = {0u, 0u, 0u, 0u};
+    if (n >= 8) {
+        __builtin_memcpy(&v, p, 16);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 7; ++e)
+            if (e < n) v[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+    }
+    return v;
+}
+__device__ __forceinline__ void store8_any(bf16_t *p, const u32x4_t v, int n)
+{
+    if (n >= 8) {
+        __builtin_memcpy(p, &v, 16);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 7; ++e)
+            if (e < n) p[e] = (bf16_t)(v[e >> 1] >> (16 * (e & 1)));
+    }
+}
+
 // One wavefront's share of the pass that forms g = dy*[y>0] for the weight-gradient kernels: 32 channels
 // (block cm) x 64 time steps (four 16-step fragments from st4*4 on) of batch item b.  Reads are whole
 // 128-byte lines (lane = 8 rows x 8 groups of 8 steps, four times); g goes out in MFMA A-fragment order
@@ -140,6 +176,43 @@ __device__ __forceinline__ void mask_pack_wave(int lane, int b, int cm, int st4,
             if (gplain && ok[i]) gplain[idx[i]] = g[i];
             gf[(((size_t)b * ncm + cm) * nst + st) * 64 + (tg & 1) * 32 + 8 * i + (lane >> 3)] = g[i];
         }
+    }
+}
+
+// The same for rows of any length: dy, y and dres in rows of To elements, gplain (optional) in rows of
+// row_pitch(To) with zeros behind the row, gf optional.
+__device__ __forceinline__ void mask_pack_wave_any(int lane, int b, int cm, int st4, int Cout, int To, int ncm, int nst,
+                                                   const bf16_t *__restrict__ dy, const bf16_t *__restrict__ y, int relu,
+                                                   bf16_t *__restrict__ gplain, bf16_t *__restrict__ dres,
+                                                   u32x4_t *__restrict__ gf)
+{
+    const int tg = lane & 7, st = st4 * 4 + (tg >> 1);
+    const int t = 64 * st4 + 8 * tg, Top = row_pitch(To);
+    u32x4_t g[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int co = cm * 32 + 8 * i + (lane >> 3);
+        const int n = co < Cout ? To - t : 0;
+        g[i] = load8_any(dy + ((size_t)b * Cout + co) * To + t, n);
+    }
+    if (relu) {
+        u32x4_t yv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int co = cm * 32 + 8 * i + (lane >> 3);
+            yv[i] = load8_any(y + ((size_t)b * Cout + co) * To + t, co < Cout ? To - t : 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] = masked_grad8(g[i], yv[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int co = cm * 32 + 8 * i + (lane >> 3);
+        if (co < Cout) {
+            if (dres) store8_any(dres + ((size_t)b * Cout + co) * To + t, g[i], To - t);
+            if (gplain && t < Top) *reinterpret_cast<u32x4_t *>(gplain + ((size_t)b * Cout + co) * Top + t) = g[i];
+        }
+        if (gf && st < nst) gf[(((size_t)b * ncm + cm) * nst + st) * 64 + (tg & 1) * 32 + 8 * i + (lane >> 3)] = g[i];
     }
 }
 
@@ -214,6 +287,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
 
 bool mfma_wgrad_supported(const Geom &g);
 size_t mfma_wgrad_workspace(const Geom &g, bool need_dz);
+size_t mfma_wgrad_x_offset(const Geom &g);  // where the pitched copy of x lies in a workspace sized with need_dz
 hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const void *y,
                              const float *scale, float *dw, bool relu, bool accumulate, void *ws,
                              hipStream_t s);
@@ -226,6 +300,30 @@ bool wgrad_k1_supported(const Geom &g);
 size_t wgrad_k1_part_bytes(const Geom &g);
 hipError_t launch_wgrad_k1(const Geom &g, const void *x, const void *gplain, const float *scale, float *dw, bool accumulate,
                            void *ws, hipStream_t s);
+
+// ---- rows of any length -------------------------------------------------------------------------
+// What a call on rows that are no multiple of eight long needs before its main kernel, in one launch; each part is
+// optional (w / dy / x NULL).
+struct RowPrep {
+    // weights in fragment order: as run_prepack, flipped times rscale for an input gradient
+    const void *w;
+    void *wp;
+    bool flip;
+    const float *rscale;
+    // g = dy*[y>0]: pitched, in the layout of dy, in fragment order (each optional)
+    const void *dy, *y;
+    bool relu;
+    void *gplain, *dres, *gf;
+    int ncm, nst;
+    // pitched copy of x, zeros behind the row and from a sample's length on
+    const void *x;
+    void *xp;
+};
+hipError_t launch_prepare_rows(const Geom &g, const RowPrep &a, hipStream_t s);
+inline size_t pitched_x_bytes(const Geom &g)  // 0 where x is read in place
+{
+    return g.T % 8 == 0 ? 0 : align_up((size_t)g.B * g.Cin * row_pitch(g.T) * sizeof(bf16_t), 256);
+}
 
 // ---- fused backward: one pass over dy / y feeds both gradients --------------------------------
 // The stride-1 weight-gradient kernels read g = dy*[y>0] in MFMA fragment order
@@ -247,7 +345,7 @@ hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float 
 // *g_plain: the tensor the input gradient contracts
 hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
                               bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
-                              hipStream_t s);
+                              hipStream_t s, const void *x = nullptr, void *xp = nullptr);
 // input gradient from a workspace prepared by launch_bwd_prepare
 hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws,
                                       hipStream_t s);

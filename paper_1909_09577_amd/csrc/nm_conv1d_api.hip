@@ -148,10 +148,10 @@ bool aligned16(const void *p) { return ((uintptr_t)p % 16) == 0; }
 
 // Whether a call with per-sample lengths may take the matrix-core kernels: the forward pass, the input
 // gradient and the stride-1 weight-gradient kernels apply them; the general weight-gradient kernel
-// does not (lengths then go to the plain kernel).
+// does not (lengths then go to the plain kernel), unless x is copied for it, with zeros for the padding.
 bool masked_on_mfma(const Geom &g, int op = NM_OP_FWD)
 {
-    return g.len == nullptr || op != NM_OP_BWD_WEIGHT || mfma_wgrad_fast_supported(g);
+    return g.len == nullptr || op != NM_OP_BWD_WEIGHT || mfma_wgrad_fast_supported(g) || g.T % 8 != 0;
 }
 
 // Scratch need of one operation on one path (mfma: matrix-core kernels, else plain kernels).
@@ -164,6 +164,21 @@ size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_
     }
     if (op == NM_OP_FWD) return 0;
     return scale_or_relu ? align_up((size_t)g.B * g.Cout * g.To * elt(dtype), kWsAlign) : 0;
+}
+
+// What nm_conv1d_workspace_bytes answers for one pass.  The query sees neither the scale pointer nor the
+// alignment of the tensors (misaligned tensors take the plain kernels); it sizes for the larger of the cases.
+size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags)
+{
+    const size_t plain = workspace_for(op, g, dtype, false, true);
+    const size_t fast = use_mfma(op, g, dtype, flags) ? workspace_for(op, g, dtype, true, true) : 0;
+    return plain > fast ? plain : fast;
+}
+// The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
+// without room for their copies too, by the plain kernels.
+size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
+{
+    return rows16(g) ? asked_workspace(op, g, dtype, flags) : workspace_for(op, g, dtype, false, true);
 }
 
 int check_workspace(const void *ws, size_t have, size_t need)
@@ -210,16 +225,10 @@ size_t nm_conv1d_workspace_bytes(int op, int B, int Cin, int Cout, int T, int K,
     if (op == NM_OP_BN_BWD)
         return bn_bwd_scratch_bytes(g.B, g.Cout) + align_up((size_t)g.B * g.Cout * g.To * elt(dtype), kWsAlign) +
                nm_conv1d_workspace_bytes(NM_OP_BWD, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags);
-    // The query sees neither the scale pointer nor the alignment of the tensors (misaligned
-    // tensors take the plain kernels); it sizes for the larger of the cases.
-    auto one = [&](int o) {
-        const size_t plain = workspace_for(o, g, dtype, false, true);
-        const size_t fast = use_mfma(o, g, dtype, flags) ? workspace_for(o, g, dtype, true, true) : 0;
-        return plain > fast ? plain : fast;
-    };
     // the fused backward keeps the two gradients' workspaces side by side
-    if (op == NM_OP_BWD) return one(NM_OP_BWD_DATA) + one(NM_OP_BWD_WEIGHT);
-    return one(op);
+    if (op == NM_OP_BWD)
+        return asked_workspace(NM_OP_BWD_DATA, g, dtype, flags) + asked_workspace(NM_OP_BWD_WEIGHT, g, dtype, flags);
+    return asked_workspace(op, g, dtype, flags);
 }
 
 int nm_conv1d_time_next_main_kernel(void *start_event, void *stop_event)
@@ -271,9 +280,13 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
     if (overlap(y, ny, x, (size_t)g.B * g.Cin * g.T * e) || overlap(y, ny, w, (size_t)g.Cout * g.Cin * g.K * e) ||
         overlap(y, ny, residual, ny))
         return NM_ERR_BAD_ARG;
-    const bool mfma = use_mfma(NM_OP_FWD, g, dtype, flags) && aligned16(x) && aligned16(y) && aligned16(residual) &&
-                      masked_on_mfma(g);
-    const size_t need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
+    bool mfma = use_mfma(NM_OP_FWD, g, dtype, flags) && aligned16(x) && aligned16(y) && aligned16(residual) &&
+                masked_on_mfma(g);
+    size_t need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
+    if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
+        mfma = false;  // no room for the copies
+        need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
+    }
     st = check_workspace(workspace, workspace_bytes, need);
     if (st != NM_OK) return st;
     if (overlap(y, ny, workspace, need)) return NM_ERR_BAD_ARG;
@@ -311,10 +324,14 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
         return NM_ERR_BAD_ARG;
     const bool accum = (flags & NM_ACCUM_DX) != 0;
     // accumulation into dx: the matrix-core engine adds the old value in its epilogue (stride 1, no lengths)
-    const bool mfma = use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && aligned16(dy) && aligned16(dx) &&
-                      (!relu || aligned16(y)) && masked_on_mfma(g) && !(accum && (g.stride != 1 || g.len));
+    bool mfma = use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && aligned16(dy) && aligned16(dx) &&
+                (!relu || aligned16(y)) && masked_on_mfma(g) && !(accum && (g.stride != 1 || g.len));
     const bool dzneeded = needs_dz(flags, scale);
-    const size_t need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
+    size_t need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
+    if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
+        mfma = false;  // no room for the copies
+        need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
+    }
     st = check_workspace(workspace, workspace_bytes, need);
     if (st != NM_OK) return st;
     if (overlap(dx, ndx, workspace, need) || overlap(dres, ndy, workspace, need)) return NM_ERR_BAD_ARG;
@@ -350,10 +367,15 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
     const size_t ndy = (size_t)g.B * g.Cout * g.To * e, ndw = (size_t)g.Cout * g.Cin * g.K * sizeof(float);
     if (overlap(dw, ndw, dy, ndy) || overlap(dw, ndw, y, ndy) || overlap(dw, ndw, x, (size_t)g.B * g.Cin * g.T * e))
         return NM_ERR_BAD_ARG;
-    const bool mfma = use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && aligned16(x) && aligned16(dy) &&
-                      (!relu || aligned16(y)) && masked_on_mfma(g, NM_OP_BWD_WEIGHT);
+    bool mfma = use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && aligned16(x) && aligned16(dy) &&
+                (!relu || aligned16(y)) && masked_on_mfma(g, NM_OP_BWD_WEIGHT);
     const bool dzneeded = needs_dz(flags, scale);
-    const size_t need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded);
+    // (with copies x lies behind room for g whether g is formed or not)
+    size_t need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded || (mfma && !rows16(g)));
+    if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
+        mfma = false;  // no room for the copies
+        need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded);
+    }
     st = check_workspace(workspace, workspace_bytes, need);
     if (st != NM_OK) return st;
     if (overlap(dw, ndw, workspace, need)) return NM_ERR_BAD_ARG;
@@ -388,8 +410,12 @@ int nm_conv1d_block_fwd_static(int B, int Cin, int Cout, int T, int K, int strid
     // implementation below then reports them, before any device call).
     const size_t need = nm_conv1d_workspace_bytes(NM_OP_FWD, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags);
     if (need > NM_STATIC_SCRATCH_BYTES) {
-        DisarmOnExit disarm;
-        return NM_ERR_SCRATCH_LIMIT;
+        Geom g;  // (need > 0: the arguments are valid)
+        check_geometry(B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags, kAllFlags, &g);
+        if (least_workspace(NM_OP_FWD, g, dtype, flags) > NM_STATIC_SCRATCH_BYTES) {
+            DisarmOnExit disarm;
+            return NM_ERR_SCRATCH_LIMIT;
+        }
     }
     void *ptr = nullptr;
     if (need > 0 && x && w && y) {  // (missing tensors: no device call before the argument error)
@@ -458,21 +484,28 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     if (st == NM_OK && (flags & NM_RELU) && !y) st = NM_ERR_BAD_ARG;
     const size_t need =
         st == NM_OK ? nm_conv1d_workspace_bytes(NM_OP_BWD, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags) : 0;
-    if (st == NM_OK) st = check_workspace(workspace, workspace_bytes, need);
+    bool whole = true;  // the workspace has the size nm_conv1d_workspace_bytes asks for
+    if (st == NM_OK) {
+        st = check_workspace(workspace, workspace_bytes, need);
+        whole = st == NM_OK;
+        if (!whole)
+            st = check_workspace(workspace, workspace_bytes, least_workspace(NM_OP_BWD_DATA, g, dtype, flags) +
+                                                                 least_workspace(NM_OP_BWD_WEIGHT, g, dtype, flags));
+    }
     if (st != NM_OK) {
         DisarmOnExit disarm;  // an armed timer is consumed by this call whatever happens
         return st;
     }
     const bool relu = (flags & NM_RELU) != 0;
     g.len = lengths;
-    const bool fused = !(lengths && (flags & NM_ACCUM_DX)) &&
+    const bool fused = whole && !(lengths && (flags & NM_ACCUM_DX)) &&
                        use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) &&
-                       g.stride == 1 && mfma_wgrad_fast_supported(g) && !wgrad_k1_supported(g) && aligned16(x) && aligned16(dy) &&
+                       g.stride == 1 && mfma_wgrad_fast_supported(g) && !wgrad_k1_supported(pitched(g)) && aligned16(x) && aligned16(dy) &&
                        aligned16(dx) && (!relu || aligned16(y)) && (!dres || aligned16(dres));
     const size_t ws_data = mfma_dgrad_workspace(g);  // only meaningful when fused
     // pointwise layers: the input gradient's masked g = dy*[y>0] also feeds the K=1 weight-gradient GEMM
-    const bool fused_k1 = !lengths && g.stride == 1 && use_mfma(NM_OP_BWD_DATA, g, dtype, flags) &&
-                          use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && wgrad_k1_supported(g) && aligned16(x) &&
+    const bool fused_k1 = whole && !lengths && g.stride == 1 && use_mfma(NM_OP_BWD_DATA, g, dtype, flags) &&
+                          use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && wgrad_k1_supported(pitched(g)) && aligned16(x) &&
                           aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
     if (fused_k1) {
         DisarmOnExit disarm;
@@ -487,15 +520,29 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
             return NM_ERR_BAD_ARG;
         hipStream_t s = (hipStream_t)hip_stream;
         const void *g_plain = nullptr;
+        hipError_t err;
+        if (!rows16(g)) {  // (K = 1 without padding: To == T)
+            unsigned char *ws_w = (unsigned char *)workspace + ws_data;
+            void *xp = ws_w + mfma_wgrad_x_offset(g);
+            const DzfLayout none = {};
+            err = launch_bwd_prepare(g, dy, y, scale, w, relu, workspace, nullptr, none, dres, &g_plain, s, x, xp);
+            if (err != hipSuccess) return NM_ERR_DEVICE;
+            t_current_op = NM_OP_BWD_DATA;
+            err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, s);
+            if (err != hipSuccess) return NM_ERR_DEVICE;
+            t_current_op = NM_OP_BWD_WEIGHT;
+            return dev(launch_wgrad_k1(pitched(g), xp, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
+        }
         t_current_op = NM_OP_BWD_DATA;
-        hipError_t err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, (flags & NM_ACCUM_DX) != 0, workspace, s, &g_plain);
+        err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, (flags & NM_ACCUM_DX) != 0, workspace, s, &g_plain);
         if (err != hipSuccess || !g_plain) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s));
     }
     if (!fused) {
         // two calls sharing the workspace one after the other (their own argument checks apply)
-        const size_t w1 = nm_conv1d_workspace_bytes(NM_OP_BWD_DATA, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags);
+        const size_t w1 = whole ? nm_conv1d_workspace_bytes(NM_OP_BWD_DATA, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags)
+                                : workspace_bytes;
         // a timer armed for the weight-gradient kernel outlives the first of the two calls
         hipEvent_t keep_start = t_start_event, keep_stop = t_stop_event;
         const bool keep = t_timed_op == NM_OP_BWD_WEIGHT;
@@ -523,14 +570,15 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     void *ws_w = (unsigned char *)workspace + ws_data;  // the weight gradient's workspace: partials, then dz fragments
     const DzfLayout layout = mfma_wgrad_dzf_layout(g);
     const void *g_plain = nullptr;
+    void *xp = g.T % 8 == 0 ? nullptr : (unsigned char *)ws_w + mfma_wgrad_x_offset(g);  // pitched copy of x
     hipError_t err = launch_bwd_prepare(g, dy, y, scale, w, relu, workspace, (unsigned char *)ws_w + layout.offset, layout,
-                                        dres, &g_plain, s);
+                                        dres, &g_plain, s, x, xp);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_DATA;
     err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, s);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
-    return dev(launch_mfma_wgrad_prepared(g, x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
+    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
 }
 
 int nm_conv1d_bwd(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const void *x,
@@ -566,8 +614,11 @@ int nm_conv1d_bn_fwd(int B, int Cin, int Cout, int T, int K, int stride, int dil
         st = NM_ERR_BAD_ARG;
     const size_t need =
         st == NM_OK ? nm_conv1d_workspace_bytes(NM_OP_BN_FWD, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags) : 0;
-    if (st == NM_OK) st = check_workspace(workspace, workspace_bytes, need);
-    if (st == NM_OK && (overlap(y, ny, workspace, need) || overlap(z, ny, workspace, need))) st = NM_ERR_BAD_ARG;
+    if (st == NM_OK && check_workspace(workspace, workspace_bytes, need) != NM_OK)
+        st = check_workspace(workspace, workspace_bytes, bn_fwd_scratch_bytes(g.B, g.Cout, g.To) + least_workspace(NM_OP_FWD, g, dtype, flags));
+    if (st == NM_OK && (overlap(y, ny, workspace, need < workspace_bytes ? need : workspace_bytes) ||
+                        overlap(z, ny, workspace, need < workspace_bytes ? need : workspace_bytes)))
+        st = NM_ERR_BAD_ARG;
     if (st != NM_OK) {
         DisarmOnExit disarm;
         return st;
@@ -598,8 +649,11 @@ int nm_conv1d_bn_bwd(int B, int Cin, int Cout, int T, int K, int stride, int dil
     if (st == NM_OK && (overlap(dres, ny, dy, ny) || overlap(dres, ny, y, ny) || overlap(dres, ny, z, ny))) st = NM_ERR_BAD_ARG;
     const size_t need =
         st == NM_OK ? nm_conv1d_workspace_bytes(NM_OP_BN_BWD, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags) : 0;
-    if (st == NM_OK) st = check_workspace(workspace, workspace_bytes, need);
-    if (st == NM_OK && overlap(dres, ny, workspace, need)) st = NM_ERR_BAD_ARG;
+    if (st == NM_OK && check_workspace(workspace, workspace_bytes, need) != NM_OK)
+        st = check_workspace(workspace, workspace_bytes, bn_bwd_scratch_bytes(g.B, g.Cout) + align_up(ny, kWsAlign) +
+                                                             least_workspace(NM_OP_BWD_DATA, g, dtype, flags) +
+                                                             least_workspace(NM_OP_BWD_WEIGHT, g, dtype, flags));
+    if (st == NM_OK && overlap(dres, ny, workspace, need < workspace_bytes ? need : workspace_bytes)) st = NM_ERR_BAD_ARG;
     if (st != NM_OK) {
         DisarmOnExit disarm;
         return st;
