@@ -1,6 +1,6 @@
 // Plain one-thread-per-output kernels for the conv1d sub-block (any stride, dilation,
 // padding; float or bfloat16 storage; float32 arithmetic).  They serve the float32
-// mode and every geometry the matrix-core kernels do not cover.  The sums are taken
+// mode where NM_FORCE_DIRECT asks for them or a layer is too small, too wide or strided, and every geometry the matrix-core kernels do not cover.  The sums are taken
 // in short float32 blocks that are then added together, which keeps the rounding
 // error of an n-term sum near sqrt(n)^(1/2) ulp instead of sqrt(n) ulp.
 #include "nm_common.h"

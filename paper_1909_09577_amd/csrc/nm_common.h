@@ -260,6 +260,20 @@ hipError_t launch_direct_dgrad(const Geom &g, bool is_bf16, const void *dz, cons
 hipError_t launch_direct_wgrad(const Geom &g, bool is_bf16, const void *x, const void *dz, const float *scale, float *dw,
                                bool accumulate, hipStream_t s);
 
+// ---- float32 storage on the matrix cores (f32_conv.hip) ---------------------------------
+bool f32_fwd_supported(const Geom &g);
+bool f32_dgrad_supported(const Geom &g);
+bool f32_wgrad_supported(const Geom &g);
+hipError_t launch_f32_fwd(const Geom &g, const float *x, const float *w, const float *scale, const float *shift,
+                          const float *res, float *y, bool relu, hipStream_t s);
+// gy = dy*[y>0] for both gradients (scale[co] is folded into the weights, resp. multiplies the sums);
+// part: f32_wgrad_part_bytes(g) bytes
+hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, const float *w, float *dx, bool accumulate,
+                            hipStream_t s);
+size_t f32_wgrad_part_bytes(const Geom &g);
+hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *gy, const float *scale, float *dw, bool accumulate,
+                            void *part, hipStream_t s);
+
 // ---- matrix-core kernels (mfma_*.hip), bf16 storage only -------------------------------
 // Each *_supported says whether the matrix-core path can serve the geometry; the
 // *_workspace functions give its scratch need; launches return hipSuccess or the error.

@@ -144,6 +144,19 @@ bool use_mfma(int op, const Geom &g, int dtype, unsigned flags)
 // the plain weight-gradient kernel contracts dy*[y>0] and applies scale to its sums).
 bool needs_dz(unsigned flags, const float *scale) { return (flags & NM_RELU) || scale != nullptr; }
 
+// float32 storage on the matrix cores (no copies, any alignment)
+bool use_f32(bool supported, int dtype, unsigned flags) { return dtype == NM_F32 && !(flags & NM_FORCE_DIRECT) && supported; }
+
+// g = dy*[y>0] of a float32 call, written once: into dres when that is wanted, else (with a ReLU) into buf
+hipError_t f32_mask_pass(const Geom &g, const void *dy, const void *y, bool relu, void *buf, void *dres, const void **gy,
+                         hipStream_t s)
+{
+    *gy = dy;
+    if (!relu && !dres) return hipSuccess;
+    if (relu) *gy = dres ? dres : buf;
+    return launch_epilogue_bwd(g, false, dy, y, nullptr, relu, dres ? nullptr : buf, dres, s);
+}
+
 bool aligned16(const void *p) { return ((uintptr_t)p % 16) == 0; }
 
 // Whether a call with per-sample lengths may take the matrix-core kernels: the forward pass, the input
@@ -172,13 +185,14 @@ size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
     const size_t plain = workspace_for(op, g, dtype, false, true);
     const size_t fast = use_mfma(op, g, dtype, flags) ? workspace_for(op, g, dtype, true, true) : 0;
+    if (op == NM_OP_BWD_WEIGHT && use_f32(f32_wgrad_supported(g), dtype, flags)) return plain + f32_wgrad_part_bytes(g);
     return plain > fast ? plain : fast;
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
-// without room for their copies too, by the plain kernels.
+// without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels.
 size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
-    return rows16(g) ? asked_workspace(op, g, dtype, flags) : workspace_for(op, g, dtype, false, true);
+    return rows16(g) && dtype != NM_F32 ? asked_workspace(op, g, dtype, flags) : workspace_for(op, g, dtype, false, true);
 }
 
 int check_workspace(const void *ws, size_t have, size_t need)
@@ -299,6 +313,8 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
         if (err == hipSuccess && parts > 0) *stats_parts = parts;
         return dev(err);
     }
+    if (use_f32(f32_fwd_supported(g), dtype, flags))
+        return dev(launch_f32_fwd(g, (const float *)x, (const float *)w, scale, shift, (const float *)residual, (float *)y, relu, s));
     MainKernelTimer timer(s);
     return dev(launch_direct_fwd(g, dtype == NM_BF16, x, w, scale, shift, residual, y, relu, s));
 }
@@ -338,6 +354,12 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
     hipStream_t s = (hipStream_t)hip_stream;
     t_current_op = NM_OP_BWD_DATA;
     if (mfma) return dev(launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, accum, workspace, s));
+    if (use_f32(f32_dgrad_supported(g), dtype, flags)) {
+        const void *gy = dy;
+        hipError_t err = f32_mask_pass(g, dy, y, relu, workspace, dres, &gy, s);
+        if (err != hipSuccess) return NM_ERR_DEVICE;
+        return dev(launch_f32_dgrad(g, (const float *)gy, scale, (const float *)w, (float *)dx, accum, s));
+    }
     const bool bf = dtype == NM_BF16;
     const void *dz = dy;
     if (dzneeded || dres) {
@@ -376,6 +398,13 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
         mfma = false;  // no room for the copies
         need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded);
     }
+    // float32: the partial sums follow the masked gradient
+    const size_t part_at = need;
+    bool f32 = use_f32(f32_wgrad_supported(g), dtype, flags);
+    if (f32) {
+        f32 = check_workspace(workspace, workspace_bytes, need + f32_wgrad_part_bytes(g)) == NM_OK;
+        if (f32) need += f32_wgrad_part_bytes(g);
+    }
     st = check_workspace(workspace, workspace_bytes, need);
     if (st != NM_OK) return st;
     if (overlap(dw, ndw, workspace, need)) return NM_ERR_BAD_ARG;
@@ -390,6 +419,8 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
         if (err != hipSuccess) return NM_ERR_DEVICE;
         dz = workspace;
     }
+    if (f32)
+        return dev(launch_f32_wgrad(g, (const float *)x, (const float *)dz, scale, dw, accum, (unsigned char *)workspace + part_at, s));
     MainKernelTimer timer(s);
     return dev(launch_direct_wgrad(g, bf, x, dz, scale, dw, accum, s));
 }
@@ -498,6 +529,16 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     }
     const bool relu = (flags & NM_RELU) != 0;
     g.len = lengths;
+    const size_t e = elt(dtype);
+    const size_t ndy = (size_t)g.B * g.Cout * g.To * e, nx = (size_t)g.B * g.Cin * g.T * e;
+    const size_t nw = (size_t)g.Cout * g.Cin * g.K * e, ndw = (size_t)g.Cout * g.Cin * g.K * sizeof(float);
+    const bool clash = overlap(dx, nx, dy, ndy) || overlap(dx, nx, y, ndy) || overlap(dx, nx, w, nw) || overlap(dx, nx, x, nx) ||
+                       overlap(dres, ndy, dy, ndy) || overlap(dres, ndy, y, ndy) || overlap(dres, ndy, dx, nx) ||
+                       overlap(dw, ndw, dy, ndy) || overlap(dw, ndw, y, ndy) || overlap(dw, ndw, x, nx) || overlap(dw, ndw, dx, nx) ||
+                       overlap(dw, ndw, dres, ndy) || overlap(dx, nx, workspace, need) || overlap(dres, ndy, workspace, need) ||
+                       overlap(dw, ndw, workspace, need);
+    // the geometries that once were two calls keep those calls' own checks where tensors overlap
+    whole = whole && !(clash && (dtype == NM_F32 || !rows16(g)));
     const bool fused = whole && !(lengths && (flags & NM_ACCUM_DX)) &&
                        use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) &&
                        g.stride == 1 && mfma_wgrad_fast_supported(g) && !wgrad_k1_supported(pitched(g)) && aligned16(x) && aligned16(dy) &&
@@ -509,15 +550,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
                           aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
     if (fused_k1) {
         DisarmOnExit disarm;
-        const size_t e = elt(dtype);
-        const size_t ndy = (size_t)g.B * g.Cout * g.To * e, nx = (size_t)g.B * g.Cin * g.T * e;
-        const size_t nw = (size_t)g.Cout * g.Cin * g.K * e, ndw = (size_t)g.Cout * g.Cin * g.K * sizeof(float);
-        if (overlap(dx, nx, dy, ndy) || overlap(dx, nx, y, ndy) || overlap(dx, nx, w, nw) || overlap(dx, nx, x, nx) ||
-            overlap(dres, ndy, dy, ndy) || overlap(dres, ndy, y, ndy) || overlap(dres, ndy, dx, nx) ||
-            overlap(dw, ndw, dy, ndy) || overlap(dw, ndw, y, ndy) || overlap(dw, ndw, x, nx) || overlap(dw, ndw, dx, nx) ||
-            overlap(dw, ndw, dres, ndy) || overlap(dx, nx, workspace, need) || overlap(dres, ndy, workspace, need) ||
-            overlap(dw, ndw, workspace, need))
-            return NM_ERR_BAD_ARG;
+        if (clash) return NM_ERR_BAD_ARG;
         hipStream_t s = (hipStream_t)hip_stream;
         const void *g_plain = nullptr;
         hipError_t err;
@@ -539,6 +572,21 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s));
     }
+    // float32 on the matrix cores: the masked gradient is formed once for both
+    const bool fused_f32 = whole && use_f32(f32_dgrad_supported(g) && f32_wgrad_supported(g), dtype, flags);
+    if (fused_f32) {
+        DisarmOnExit disarm;
+        hipStream_t s = (hipStream_t)hip_stream;
+        const void *gy = dy;
+        hipError_t err = f32_mask_pass(g, dy, y, relu, workspace, dres, &gy, s);
+        if (err != hipSuccess) return NM_ERR_DEVICE;
+        t_current_op = NM_OP_BWD_DATA;
+        err = launch_f32_dgrad(g, (const float *)gy, scale, (const float *)w, (float *)dx, (flags & NM_ACCUM_DX) != 0, s);
+        if (err != hipSuccess) return NM_ERR_DEVICE;
+        t_current_op = NM_OP_BWD_WEIGHT;
+        return dev(launch_f32_wgrad(g, (const float *)x, (const float *)gy, scale, dw, (flags & NM_ACCUM_DW) != 0,
+                                    (unsigned char *)workspace + workspace_for(NM_OP_BWD_DATA, g, dtype, false, true), s));
+    }
     if (!fused) {
         // two calls sharing the workspace one after the other (their own argument checks apply)
         const size_t w1 = whole ? nm_conv1d_workspace_bytes(NM_OP_BWD_DATA, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags)
@@ -557,15 +605,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
                                dtype, workspace, workspace_bytes, hip_stream);
     }
     DisarmOnExit disarm;
-    const size_t e = elt(dtype);
-    const size_t ndy = (size_t)g.B * g.Cout * g.To * e, nx = (size_t)g.B * g.Cin * g.T * e;
-    const size_t nw = (size_t)g.Cout * g.Cin * g.K * e, ndw = (size_t)g.Cout * g.Cin * g.K * sizeof(float);
-    if (overlap(dx, nx, dy, ndy) || overlap(dx, nx, y, ndy) || overlap(dx, nx, w, nw) || overlap(dx, nx, x, nx) ||
-        overlap(dres, ndy, dy, ndy) || overlap(dres, ndy, y, ndy) || overlap(dres, ndy, dx, nx) ||
-        overlap(dw, ndw, dy, ndy) || overlap(dw, ndw, y, ndy) || overlap(dw, ndw, x, nx) || overlap(dw, ndw, dx, nx) ||
-        overlap(dw, ndw, dres, ndy) || overlap(dx, nx, workspace, need) || overlap(dres, ndy, workspace, need) ||
-        overlap(dw, ndw, workspace, need))
-        return NM_ERR_BAD_ARG;
+    if (clash) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     void *ws_w = (unsigned char *)workspace + ws_data;  // the weight gradient's workspace: partials, then dz fragments
     const DzfLayout layout = mfma_wgrad_dzf_layout(g);
