@@ -72,6 +72,8 @@ struct ConvGemmParams {
     const float *shift;     // epilogue (may be NULL)
     const bf16_t *res;      // epilogue (may be NULL)
     bf16_t *out;            // [B][M][Tout]
+    int nsplit;             // conv_split_kernel: parts the reduction channels are split into
+    f32x4 *part;            // their partial sums (nsplit > 1)
     double *stats;          // optional [B*ntt][M][3]: count, mean and centred second moment of the stored outputs of
                             // every (batch item, time tile, channel) -- the partial statistics of a BatchNorm over out
 };
@@ -259,6 +261,16 @@ struct Epilogue {
         o[0] = n;
         o[1] = n > 0 ? a / n : 0.0;
         o[2] = n > 0 ? b2 - a * a / n : 0.0;
+    }
+    // the 16 rows of a wavefront's quarter of a tile (eight from each row of blocks) to the LDS tile
+    __device__ __forceinline__ void put_quarter(float *tp, int el, const f32x4 (&own)[2][NT]) const
+    {
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni) tp[(mi * 8 + 4 * (el >> 5) + j) * TN + ni * 32 + (el & 31)] = own[mi][ni][j];
     }
     // A whole 64-row tile held by one wavefront (rows m_first .. m_first+63): four rounds of 16 rows
     // (row of blocks mi, accumulator registers 8*gp .. 8*gp+7) through tp; the operands of a round
@@ -738,7 +750,6 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
         const int el = fresh_lane();  // nothing lane-dependent is kept alive across the main loop for this
         const int dead_par = next_ok ? ((cc & 1) ^ 1) : 0;
         float *tp = reinterpret_cast<float *>(smem + ((size_t)dead_par * kWaves + wave) * p.buf_bytes);
-        const int tcol = el & 31, thalf = el >> 5;
 
         if (priv) {
             // A private tile: this wavefront holds all 64 rows.
@@ -792,14 +803,7 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
                     }
                     __syncthreads();  // scratch is reused by the next round / the transpose tile / the next tile's staging
                 }
-#pragma unroll
-                for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int r = mi * 8 + 4 * thalf + j;
-#pragma unroll
-                        for (int ni = 0; ni < NT; ++ni) tp[r * TN + ni * 32 + tcol] = own[mi][ni][j];
-                    }
+                epi.put_quarter(tp, el, own);
             };
             switch (wave) {
             case 0: exchange(std::integral_constant<int, 0>{}); break;
@@ -817,6 +821,236 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
             }
         }
     }
+}
+
+// ---- calls whose tiles do not fill the chip ------------------------------------------------------
+// conv_gemm_kernel gives a workgroup one tile of 160 time steps at a time, four chunks of reduction channels side by
+// side: one utterance (600 steps, 768 channels) is 48 tiles on 256 CUs, and a layer with 64 input channels
+// keeps two of its four wavefronts busy.  Here the reduction channels are also split over `nsplit` workgroups, the
+// four wavefronts of a workgroup share ONE staged window and split the taps and halves of a chunk between them
+// (wavefront w: channel half w & 1 of the taps w >> 1, (w >> 1) + 2, ...), so that a chunk of 32 channels is enough
+// work for a workgroup; two workgroups fit a CU and cover each other's waits.  Tiles are 64 channels x NT*32
+// steps, NT chosen for little padding.  The wavefronts add their sums through LDS as in conv_gemm_kernel; with
+// nsplit > 1 the sums go to the workspace and split_reduce_kernel adds the parts in a fixed order and finishes.
+// Workgroups that read the same weights sit on one XCD (blockIdx % 8) where the counts divide.
+constexpr int kSplitRows = 256;   // staged rows of a window at most
+constexpr int kSplitItems = kSplitRows / 8 * 16 / kThreads;  // staging items (8 steps x 2 channels) per lane and chunk
+
+template <int NT>
+constexpr size_t split_exchange_bytes() { return (size_t)kWaves * 3 * NT * 64 * sizeof(f32x4); }
+
+template <int NT, int STRIDE>
+__global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const ConvGemmParams p)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int TN = NT * 32;
+    const int ncombo = p.nmt * p.nsplit, ncols = p.ntt * p.B;
+    int combo, col;
+    if (ncombo % 8 == 0) {
+        const int j = (int)blockIdx.x >> 3;
+        col = j % ncols;
+        combo = (j / ncols) * 8 + ((int)blockIdx.x & 7);
+    } else {
+        combo = (int)blockIdx.x % ncombo;
+        col = (int)blockIdx.x / ncombo;
+    }
+    const int mt = combo / p.nsplit, split = combo - mt * p.nsplit;
+    const int b = col / p.ntt, t0 = (col - b * p.ntt) * TN;
+    const int c0 = (int)((long)split * p.nch / p.nsplit), c1 = (int)((long)(split + 1) * p.nch / p.nsplit);
+
+    Epilogue<NT> epi;
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div);
+    const __amdgpu_buffer_rsrc_t rs_in =
+        __builtin_amdgcn_make_buffer_rsrc((void *)p.in, 0, (int)((size_t)p.B * p.R * p.Tin * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)p.wp, 0, (int)p.wp_bytes, 0x00020000);
+
+    const int ws = t0 * STRIDE - p.padL;
+    const int ws_al = (ws >> 3) * 8;
+    const int tlen = __builtin_amdgcn_readfirstlane(clipped_len(p.len_in, b, p.Tin));
+    const int ngroups = p.nitems;  // 8-row groups of the window
+
+    u32x4 sxa[kSplitItems], sxb[kSplitItems];
+    auto stage_load = [&](int c) {
+        const uint32_t soff = (uint32_t)(((size_t)b * p.R + (size_t)c * kChunk) * p.Tin * 2);
+        const int rem = p.R - c * kChunk;
+#pragma unroll
+        for (int q = 0; q < kSplitItems; ++q) {
+            const int idx = (int)threadIdx.x + kThreads * q;
+            const int pp = idx & 15, grp = idx >> 4;
+            const int t = ws_al + 8 * grp;
+            const bool ok = grp < ngroups && (unsigned)t < (unsigned)tlen;
+            const uint32_t at = (uint32_t)(((2 * pp) * p.Tin + t) * 2);
+            sxa[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, ok && 2 * pp < rem ? at : kOutOfRange, soff, 0);
+            sxb[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, ok && 2 * pp + 1 < rem ? at + (uint32_t)(p.Tin * 2) : kOutOfRange, soff, 0);
+        }
+    };
+    auto stage_write = [&](unsigned char *buf) {
+#pragma unroll
+        for (int q = 0; q < kSplitItems; ++q) {
+            const int idx = (int)threadIdx.x + kThreads * q;
+            const int pp = idx & 15, grp = idx >> 4;
+            if (grp >= ngroups) continue;
+            const int nv = tlen - (ws_al + 8 * grp);  // valid steps of the group (a group before the row holds zeros)
+            uint32_t *dst = reinterpret_cast<uint32_t *>(buf + (size_t)(8 * grp) * kRowBytes + pp * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t keep = nv >= 2 * j + 2 ? 0xffffffffu : (nv == 2 * j + 1 ? 0x0000ffffu : 0u);
+                const uint32_t a = sxa[q][j] & keep, c = sxb[q][j] & keep;
+                dst[(2 * j) * kRowDwords] = zip_lo16(a, c);
+                dst[(2 * j + 1) * kRowDwords] = zip_hi16(a, c);
+            }
+        }
+    };
+
+    // this wavefront's units of a chunk: j -> tap (wave>>1) + 2j, channel half wave & 1; four register sets of two
+    // fragments in rotation, each reloaded right after its use with the unit that uses it next, across chunks
+    const int nu = (p.K + 1 - (wave >> 1)) >> 1;
+    constexpr uint32_t kUnitStep = 4 * 2 * 1024;
+    const uint32_t chunk_bytes = (uint32_t)p.Kp * 4096u;
+    const uint32_t w_lane = (uint32_t)lane * 16 + (uint32_t)wave * 2048u;
+    auto chunk_off = [&](int c) { return (uint32_t)(mt * p.nch + c) * chunk_bytes; };
+    bf16x8 wf[4][2];
+    auto w_load = [&](uint32_t soff, int mi) {
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_lane + (uint32_t)mi * 1024u, soff, 0));
+    };
+    f32x16 acc[2][NT];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+    // a tile that lies wholly in the padding of its batch item: its sums are zero
+    bool dead = p.len_in && ws >= tlen;
+    dead = dead || (p.len_out && t0 >= epi.out_limit(b));
+    if (!dead) {
+        stage_load(c0);
+        uint32_t w_cur = chunk_off(c0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) wf[j][mi] = w_load(w_cur + (uint32_t)(j < nu ? j : 0) * kUnitStep, mi);  // (K = 1: the zero tap)
+        stage_write(smem);
+        __syncthreads();
+        const uint32_t tap_step = 2u * (uint32_t)p.dil * kRowBytes;
+        const uint32_t lane_off = (uint32_t)(((lane & 31) * STRIDE + ws - ws_al + (wave >> 1) * p.dil) * kRowBytes +
+                                             (lane >> 5) * 16 + (wave & 1) * 32);
+        for (int c = c0; c < c1; ++c) {
+            const bool more = c + 1 < c1;
+            const uint32_t w_nxt = more ? chunk_off(c + 1) : w_cur;
+            const unsigned char *bbase = smem + (size_t)((c - c0) & 1) * p.buf_bytes + lane_off;
+            if (more) stage_load(c + 1);
+            bf16x8 bf[2][NT];
+            auto read_b = [&](bf16x8(&dst)[NT], int j) {
+                const unsigned char *at = bbase + (uint32_t)j * tap_step;
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni) dst[ni] = *reinterpret_cast<const bf16x8 *>(at + ni * 32 * STRIDE * kRowBytes);
+            };
+            auto step = [&](auto set_c, int j) {
+                constexpr int set = decltype(set_c)::value;
+                read_b(bf[(set & 1) ^ 1], j + 1 < nu ? j + 1 : j);
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NT; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][mi], bf[set & 1][ni], acc[mi][ni], 0, 0, 0);
+                const uint32_t src = j + 4 < nu ? w_cur + (uint32_t)(j + 4) * kUnitStep : w_nxt + (uint32_t)set * kUnitStep;
+                wf[set][0] = w_load(src, 0);
+                wf[set][1] = w_load(src, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if (nu > 0) read_b(bf[0], 0);
+            for (int j = 0; j < nu; j += 4) {
+                step(std::integral_constant<int, 0>{}, j);
+                if (j + 1 >= nu) break;
+                step(std::integral_constant<int, 1>{}, j + 1);
+                if (j + 2 >= nu) break;
+                step(std::integral_constant<int, 2>{}, j + 2);
+                if (j + 3 >= nu) break;
+                step(std::integral_constant<int, 3>{}, j + 3);
+            }
+            if (more) stage_write(smem + (size_t)((c + 1 - c0) & 1) * p.buf_bytes);
+            w_cur = w_nxt;
+            __syncthreads();
+        }
+    }
+
+    // sum over the wavefronts: wavefront g finishes accumulator rows 4g .. 4g+3 of every block, one row of blocks a round
+    f32x4 *red = reinterpret_cast<f32x4 *>(smem);
+    f32x4 own[2][NT];
+    auto exchange = [&](auto wave_const) {
+        constexpr int Gw = decltype(wave_const)::value;
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) {
+#pragma unroll
+            for (int g = 0; g < kWaves; ++g) {
+                if (g == Gw) continue;
+                const int slot = Gw < g ? Gw : Gw - 1;
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+                    red[((g * 3 + slot) * NT + ni) * 64 + lane] =
+                        f32x4{acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
+            }
+            __syncthreads();
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni)
+                own[mi][ni] = f32x4{acc[mi][ni][4 * Gw], acc[mi][ni][4 * Gw + 1], acc[mi][ni][4 * Gw + 2], acc[mi][ni][4 * Gw + 3]};
+#pragma unroll
+            for (int slot = 0; slot < 3; ++slot)
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni) own[mi][ni] += red[((Gw * 3 + slot) * NT + ni) * 64 + lane];
+            __syncthreads();
+        }
+    };
+    switch (wave) {
+    case 0: exchange(std::integral_constant<int, 0>{}); break;
+    case 1: exchange(std::integral_constant<int, 1>{}); break;
+    case 2: exchange(std::integral_constant<int, 2>{}); break;
+    default: exchange(std::integral_constant<int, 3>{}); break;
+    }
+    if (p.nsplit > 1) {
+        f32x4 *dst = p.part + ((((size_t)split * ncols + col) * p.nmt + mt) * kWaves + wave) * (2 * NT) * 64 + lane;
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NT; ++ni) dst[(mi * NT + ni) * 64] = own[mi][ni];
+        return;
+    }
+    const auto ld = epi.template request_rows<true>(lane, b, t0, mt * kTileM + 8 * wave, true);
+    float *tp = reinterpret_cast<float *>(smem) + wave * 16 * TN;
+    epi.put_quarter(tp, lane, own);
+    wave_lds_fence();
+    epi.template finish_rows<false, true>(lane, tp, ld);
+}
+
+// Adds the nsplit parts of 16 rows x 32 steps in order and finishes them: a wavefront of its own for each of the
+// kWaves x nt such pieces of a tile (with whole 16-row quarters, a quarter of the wavefronts: 11 us instead of 4 for
+// 768 channels x 600 steps in four parts, too few loads in flight).
+__global__ __launch_bounds__(64) void split_reduce_kernel(const ConvGemmParams p, int nt)
+{
+    __shared__ __align__(16) float tp[16 * 32];
+    const int lane = threadIdx.x;
+    const int ni = (int)blockIdx.x % nt, quarter = (int)blockIdx.x / nt;
+    const int wave = quarter & 3, tile = quarter >> 2;
+    const int col = tile / p.nmt, mt = tile - col * p.nmt;
+    const int b = col / p.ntt, t0 = ((col - b * p.ntt) * nt + ni) * 32;
+    Epilogue<1> epi;
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div);
+    const auto ld = epi.template request_rows<true>(lane, b, t0, mt * kTileM + 8 * wave, true);
+    const size_t pitch = (size_t)p.nmt * p.ntt * p.B * kWaves * 2 * nt * 64;
+    const f32x4 *src = p.part + ((size_t)quarter * 2 * nt + ni) * 64 + lane;
+    f32x4 own[2][1] = {};
+#pragma unroll 8
+    for (int s = 0; s < p.nsplit; ++s) {
+        own[0][0] += src[(size_t)s * pitch];
+        own[1][0] += src[(size_t)s * pitch + (size_t)nt * 64];
+    }
+    epi.put_quarter(tp, lane, own);
+    wave_lds_fence();
+    epi.template finish_rows<false, true>(lane, tp, ld);
 }
 
 // ---- K = 1 (pointwise convolution: a plain GEMM  out[b] = W' . in[b]) ----------------------------
@@ -1483,6 +1717,75 @@ Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
     return pl;
 }
 
+// ---- which calls take conv_split_kernel ---------------------------------------------------------
+// Its time and the other engines' are estimated in microseconds from measured rates (256 CUs assumed: the workspace
+// query has no device).  A wavefront's MFMA costs 18 ns in the unrolled engine, 20.5 ns here with two or more workgroups
+// per CU; a chunk costs 0.3 us more there for staging and the barrier (27 ns and 0.6 us alone on the CU), parts
+// 10 us for the second launch (its host time counts where calls are this short) and 0.42 us per MB of float32 outputs and
+// part.  Both sides of the line, forward, weight packing
+// included (split / other engine): 768 channels K=25, 600 steps, B=1 40 / 65 us, B=2 55 / 67, B=4 83 / 76; 512 channels
+// K=17, 400 steps, B=4 34 / 40, B=8 46 / 42; 512 channels K=1, 400 steps, B=4 15 / 21, 800 steps, B=16 48 / 24;
+// 64 -> 256 channels, stride 2, 1600 steps, B=32 28 / 46.
+struct SplitPlan {
+    int nt, nsplit, ngroups;  // nt = 0: another engine
+    size_t lds, part_bytes;
+};
+
+double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
+{
+    const long cus = 256;
+    const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
+    if (K == 1 && nmt >= 2 && pl.nt == 5 && pl.stride == 1) {  // pointwise_gemm_kernel: 3 us per stage of 128 channels
+        const long tiles = (long)((nmt + 3) / 4) * ((Tout + 159) / 160) * B;
+        const long tiles_big = (long)((nmt + 7) / 8) * ((Tout + 127) / 128) * B;
+        const double a = (double)((tiles + cus - 1) / cus) * (3.0 * ((R + 127) / 128) + 4.0);
+        const double c = (double)((tiles_big + cus - 1) / cus) * (1.8 * ((R + 63) / 64) + 4.0);
+        return a < c ? a : c;
+    }
+    const long tiles = (long)nmt * ((Tout + pl.nt * 32 - 1) / (pl.nt * 32)) * B;
+    const long grid = tiles < cus ? tiles : cus;
+    const double chunk = 0.018 * 4 * pl.nt * (pl.unrolled ? K : (K + 1) & ~1);
+    const long full = pl.unrolled ? tiles / (kWaves * grid) + (tiles % (kWaves * grid) > 2 * grid ? 1 : 0) : 0;
+    const long left = tiles - full * kWaves * grid;
+    const long shared = left > 0 ? (left + grid - 1) / grid : 0;
+    return full * (nch * chunk + 2.0) + shared * (((nch + kWaves - 1) / kWaves) * chunk + 4.0);
+}
+
+SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil)
+{
+    SplitPlan best = {};
+    const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
+    if (!pl.ok || (K == 1 && nch == 1)) return best;
+    const double mb = 4e-6 * B * M * (double)Tout;
+    double best_cost = 0.95 * engine_cost(pl, B, M, R, Tout, K);
+    // (whatever the shape, the MFMAs at 256 CUs' full rate: most large calls need not be looked at any further)
+    if (0.0205 / 4096 * nmt * 2 * (double)B * ((Tout + 31) / 32) * nch * 2 * K > best_cost) return best;
+    for (int nt = pl.stride == 1 ? 4 : 3; nt >= 2; --nt) {
+        const long rows = (long)(nt * 32 - 1) * pl.stride + (long)(K - 1) * dil + 1 + 7;
+        if (rows > kSplitRows) continue;
+        const long tiles_l = (long)nmt * ((Tout + nt * 32 - 1) / (nt * 32)) * B;
+        if (tiles_l > (1 << 20)) continue;
+        const unsigned tiles = (unsigned)tiles_l;
+        for (const int ns : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            const unsigned wgs = tiles * ns, rounds = (wgs + 255) / 256;
+            if (ns > nch || (ns > 1 && wgs > 1024)) break;
+            const unsigned chunks = (unsigned)(nch + ns - 1) / (unsigned)ns;
+            const double cost = (double)(rounds * chunks) * ((rounds > 1 ? 0.0205 : 0.027) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.3 : 0.6)) +
+                                (ns > 1 ? 10.0 + 0.42 * ns * mb : 0.0);
+            if (cost >= best_cost) continue;
+            best_cost = cost;
+            best.nt = nt;
+            best.nsplit = ns;
+            best.ngroups = (int)((rows + 7) / 8);
+            const size_t stage = 2 * (size_t)best.ngroups * 8 * kRowBytes;
+            const size_t red = (size_t)kWaves * 3 * nt * 64 * sizeof(f32x4);
+            best.lds = stage > red ? stage : red;
+            best.part_bytes = ns > 1 ? align_up((size_t)wgs * kTileM * nt * 32 * sizeof(float), 256) : 0;
+        }
+    }
+    return best;
+}
+
 size_t packed_bytes(int M, int R, int K)
 {
     const size_t nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
@@ -1569,12 +1872,45 @@ hipError_t launch_few_channels(const ConvGemmParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s)
+template <int NT, int STRIDE>
+hipError_t launch_split_t(const ConvGemmParams &p, size_t lds, hipStream_t s)
+{
+    MainKernelTimer timer(s);
+    hipLaunchKernelGGL((conv_split_kernel<NT, STRIDE>), dim3(p.num_tiles * p.nsplit), dim3(kThreads), lds, s, p);
+    if (p.nsplit > 1) hipLaunchKernelGGL(split_reduce_kernel, dim3(p.num_tiles * kWaves * NT), dim3(64), 0, s, p, NT);
+    return hipGetLastError();
+}
+
+// sp.part_bytes bytes at `part`
+hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int stride, void *part, hipStream_t s)
+{
+    ConvGemmParams p = p0;
+    p.ntt = (p.Tout + sp.nt * 32 - 1) / (sp.nt * 32);
+    p.num_tiles = p.nmt * p.ntt * p.B;
+    p.nsplit = sp.nsplit;
+    p.nitems = sp.ngroups;
+    p.buf_bytes = sp.ngroups * 8 * kRowBytes;
+    p.part = (f32x4 *)part;
+    if (stride == 1) {
+        if (sp.nt == 4) return launch_split_t<4, 1>(p, sp.lds, s);
+        if (sp.nt == 3) return launch_split_t<3, 1>(p, sp.lds, s);
+        return launch_split_t<2, 1>(p, sp.lds, s);
+    }
+    if (sp.nt == 3) return launch_split_t<3, 2>(p, sp.lds, s);
+    return launch_split_t<2, 2>(p, sp.lds, s);
+}
+
+// [part, part + part_room): room for the partial sums of the split engine
+hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room)
 {
     // one tap, at most one chunk of reduction channels, nothing to do after the sums: the store-bound kernel
     if (p.K == 1 && p.R <= kChunk && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout && p.Tout % 8 == 0 && !p.res &&
         !p.scale && !p.shift && !p.relu && !p.len_in && !p.len_out)
         return launch_few_channels(p, s);
+    if (!p.stats) {
+        const SplitPlan sp = split_plan(pl, p.B, p.M, p.R, p.Tout, p.K, p.dil);
+        if (sp.nt && sp.part_bytes <= part_room) return launch_split(sp, p, pl.stride, part, s);
+    }
     // one tap, no padding, wide tiles: the GEMM kernel whose wavefronts share the staged activations
     // (worth it from two 64-channel row tiles on: a single one would leave three wavefronts idle)
     if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == row_pitch(p.Tout))
@@ -1744,7 +2080,12 @@ bool mfma_fwd_supported(const Geom &g)
     return packed_bytes(g.Cout, g.Cin, g.K) < kMaxPacked && make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil).ok;
 }
 
-size_t mfma_fwd_workspace(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K) + pitched_x_bytes(g); }
+size_t mfma_fwd_workspace_least(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K) + pitched_x_bytes(g); }
+size_t mfma_fwd_workspace(const Geom &g)
+{
+    const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
+    return mfma_fwd_workspace_least(g) + split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil).part_bytes;
+}
 
 // Whether the forward pass of this geometry runs on a kernel instance that can also write the statistics of its
 // outputs, and into how many (batch item, time tile) parts: the unrolled engine, wide tile, no lengths, 16-byte rows.
@@ -1754,11 +2095,12 @@ int mfma_fwd_stats_parts(const Geom &g)
     const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !pl.unrolled || pl.nt != 5 || g.len || !mfma_fwd_supported(g)) return 0;
     if (pl.buf_bytes < Epilogue<5>::kTileBytesWithStats) return 0;
+    if (split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil).nt) return 0;  // few tiles: z is small and read again instead
     return g.B * ((g.To + 159) / 160);
 }
 
 hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const float *scale, const float *shift,
-                           const void *res, void *y, bool relu, void *ws, hipStream_t s, double *stats)
+                           const void *res, void *y, bool relu, void *ws, size_t ws_bytes, hipStream_t s, double *stats)
 {
     const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !mfma_fwd_supported(g)) return hipErrorInvalidValue;
@@ -1788,7 +2130,8 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     p.scale = scale; p.shift = shift; p.res = (const bf16_t *)res;
     p.out = (bf16_t *)y;
     p.stats = stats;
-    return launch_plan(pl, p, s);
+    const size_t least = mfma_fwd_workspace_least(g);
+    return launch_plan(pl, p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
 }
 
 // ---- input gradient (stride 1 only; other strides use the plain kernels) ----------------
@@ -1826,7 +2169,7 @@ bool mfma_dgrad_supported(const Geom &g)
     return make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil).ok;
 }
 
-size_t mfma_dgrad_workspace(const Geom &g)
+size_t mfma_dgrad_workspace_least(const Geom &g)
 {
     if (g.stride == 2) {
         const Phase2 ph = phases_of_stride2(g);
@@ -1837,6 +2180,20 @@ size_t mfma_dgrad_workspace(const Geom &g)
         return n;
     }
     return packed_bytes(g.Cin, g.Cout, g.K) + dz_bytes_of(g);
+}
+size_t mfma_dgrad_workspace(const Geom &g)
+{
+    size_t part = 0;
+    if (g.stride == 2) {  // (the two phases run one after the other)
+        const Phase2 ph = phases_of_stride2(g);
+        for (int r = 0; r < 2; ++r) {
+            const SplitPlan sp = split_plan(make_plan(g.To, ph.U, g.Cout, ph.K[r], 1, 1), g.B, g.Cin, g.Cout, ph.U, ph.K[r], 1);
+            if (sp.part_bytes > part) part = sp.part_bytes;
+        }
+    } else {
+        part = split_plan(make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil), g.B, g.Cin, g.Cout, g.T, g.K, g.dil).part_bytes;
+    }
+    return mfma_dgrad_workspace_least(g) + part;
 }
 
 namespace {
@@ -1863,7 +2220,7 @@ hipError_t mask_pass(const Geom &g, const void *dy, const void *y, bool relu, vo
 }
 
 hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
-                                     void *dx, void *dres, bool relu, void *ws, hipStream_t s)
+                                     void *dx, void *dres, bool relu, void *ws, void *part, size_t part_room, hipStream_t s)
 {
     const Phase2 ph = phases_of_stride2(g);
     if (!ph.ok) return hipErrorInvalidValue;
@@ -1901,7 +2258,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
         p.len_out = g.len;  // dx[2u+r] is padding from 2u+r >= len on: u >= ceil((len - r) / 2)
         p.len_out_sub = r;
         p.len_out_div = 2;
-        e = launch_plan(pl, p, s);  // the first of the two carries the one-shot timer
+        e = launch_plan(pl, p, s, part, part_room);  // the first of the two carries the one-shot timer
         if (e != hipSuccess) return e;
     }
     const size_t n8 = (size_t)g.B * g.Cin * ph.U / 8;
@@ -1926,12 +2283,16 @@ void fill_dgrad(ConvGemmParams &p, const Plan &pl, const Geom &g, const void *gi
 
 // accumulate (stride 1 only): dx = bf16(dx + gradient), one rounding.
 hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
-                             void *dx, void *dres, bool relu, bool accumulate, void *ws, hipStream_t s, const void **g_used)
+                             void *dx, void *dres, bool relu, bool accumulate, void *ws, size_t ws_bytes, hipStream_t s,
+                             const void **g_used)
 {
+    const size_t least = mfma_dgrad_workspace_least(g);
+    void *part = (unsigned char *)ws + least;
+    const size_t part_room = ws_bytes > least ? ws_bytes - least : 0;
     if (g_used) *g_used = nullptr;
     if (g.stride == 2) {
         if (accumulate) return hipErrorInvalidValue;
-        return launch_mfma_dgrad_stride2(g, dy, y, scale, w, dx, dres, relu, ws, s);
+        return launch_mfma_dgrad_stride2(g, dy, y, scale, w, dx, dres, relu, ws, part, part_room, s);
     }
     const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;
@@ -1968,7 +2329,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
     if (g_used) *g_used = gin;
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, gin, ws, dx, accumulate);
-    return launch_plan(pl, p, s);
+    return launch_plan(pl, p, s, part, part_room);
 }
 
 // ---- fused backward -------------------------------------------------------------------------
@@ -2015,13 +2376,15 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws, hipStream_t s)
+hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws, size_t ws_bytes,
+                                      hipStream_t s)
 {
     const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, g_plain, ws, dx, accumulate);
-    return launch_plan(pl, p, s);
+    const size_t least = mfma_dgrad_workspace_least(g);
+    return launch_plan(pl, p, s, (unsigned char *)ws + least, ws_bytes - least);
 }
 
 }  // namespace nm

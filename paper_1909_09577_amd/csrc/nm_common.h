@@ -278,12 +278,14 @@ hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *gy, cons
 // Each *_supported says whether the matrix-core path can serve the geometry; the
 // *_workspace functions give its scratch need; launches return hipSuccess or the error.
 bool mfma_fwd_supported(const Geom &g);
+// (the least is what a call needs; with the full size calls of few tiles run on the split engine)
 size_t mfma_fwd_workspace(const Geom &g);
+size_t mfma_fwd_workspace_least(const Geom &g);
 // stats (optional, only where mfma_fwd_stats_parts(g) > 0): [parts][Cout][3] doubles that receive count, mean and
 // centred second moment of the stored outputs of every (batch item, 160-step time tile) part and channel
 hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const float *scale,
                            const float *shift, const void *res, void *y, bool relu, void *ws,
-                           hipStream_t s, double *stats = nullptr);
+                           size_t ws_bytes, hipStream_t s, double *stats = nullptr);
 int mfma_fwd_stats_parts(const Geom &g);
 
 // pointwise forward with at most 32 output channels: bound by reading x once (decoder_logsoftmax.hip)
@@ -293,11 +295,12 @@ hipError_t launch_skinny_fwd(const Geom &g, const void *x, const void *w, const 
 
 bool mfma_dgrad_supported(const Geom &g);
 size_t mfma_dgrad_workspace(const Geom &g);
+size_t mfma_dgrad_workspace_least(const Geom &g);
 // g_used (optional, stride 1): receives the tensor the kernel contracted, g = dy*[y>0] -- dy itself without
 // ReLU, else dres or a buffer inside ws -- so that a weight gradient launched next need not form it again
 hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const float *scale,
                              const void *w, void *dx, void *dres, bool relu, bool accumulate, void *ws,
-                             hipStream_t s, const void **g_used = nullptr);
+                             size_t ws_bytes, hipStream_t s, const void **g_used = nullptr);
 
 bool mfma_wgrad_supported(const Geom &g);
 size_t mfma_wgrad_workspace(const Geom &g, bool need_dz);
@@ -361,7 +364,7 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
                               bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
                               hipStream_t s, const void *x = nullptr, void *xp = nullptr);
 // input gradient from a workspace prepared by launch_bwd_prepare
-hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws,
+hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws, size_t ws_bytes,
                                       hipStream_t s);
 
 // ---- training-mode BatchNorm passes (bn_train.hip) ---------------------------------------------

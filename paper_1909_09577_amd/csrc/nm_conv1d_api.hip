@@ -168,11 +168,12 @@ bool masked_on_mfma(const Geom &g, int op = NM_OP_FWD)
 }
 
 // Scratch need of one operation on one path (mfma: matrix-core kernels, else plain kernels).
-size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_relu)
+// least: without room for the partial sums of the split engine.
+size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_relu, bool least = false)
 {
     if (mfma) {
-        if (op == NM_OP_FWD) return mfma_fwd_workspace(g);
-        if (op == NM_OP_BWD_DATA) return mfma_dgrad_workspace(g);
+        if (op == NM_OP_FWD) return least ? mfma_fwd_workspace_least(g) : mfma_fwd_workspace(g);
+        if (op == NM_OP_BWD_DATA) return least ? mfma_dgrad_workspace_least(g) : mfma_dgrad_workspace(g);
         return mfma_wgrad_workspace(g, scale_or_relu);
     }
     if (op == NM_OP_FWD) return 0;
@@ -181,18 +182,19 @@ size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_
 
 // What nm_conv1d_workspace_bytes answers for one pass.  The query sees neither the scale pointer nor the
 // alignment of the tensors (misaligned tensors take the plain kernels); it sizes for the larger of the cases.
-size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags)
+size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool least = false)
 {
     const size_t plain = workspace_for(op, g, dtype, false, true);
-    const size_t fast = use_mfma(op, g, dtype, flags) ? workspace_for(op, g, dtype, true, true) : 0;
+    const size_t fast = use_mfma(op, g, dtype, flags) ? workspace_for(op, g, dtype, true, true, least) : 0;
     if (op == NM_OP_BWD_WEIGHT && use_f32(f32_wgrad_supported(g), dtype, flags)) return plain + f32_wgrad_part_bytes(g);
     return plain > fast ? plain : fast;
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
-// without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels.
+// without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels;
+// calls of few tiles without room for the split engine's partial sums by the other engines.
 size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
-    return rows16(g) && dtype != NM_F32 ? asked_workspace(op, g, dtype, flags) : workspace_for(op, g, dtype, false, true);
+    return rows16(g) && dtype != NM_F32 ? asked_workspace(op, g, dtype, flags, true) : workspace_for(op, g, dtype, false, true);
 }
 
 int check_workspace(const void *ws, size_t have, size_t need)
@@ -297,6 +299,7 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
     bool mfma = use_mfma(NM_OP_FWD, g, dtype, flags) && aligned16(x) && aligned16(y) && aligned16(residual) &&
                 masked_on_mfma(g);
     size_t need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
+    if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_FWD, g, dtype, mfma, true, true);
     if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
         mfma = false;  // no room for the copies
         need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
@@ -309,7 +312,7 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
     t_current_op = NM_OP_FWD;
     if (mfma) {
         const int parts = (stats && stats_parts) ? mfma_fwd_stats_parts(g) : 0;
-        const hipError_t err = launch_mfma_fwd(g, x, w, scale, shift, residual, y, relu, workspace, s, parts > 0 ? stats : nullptr);
+        const hipError_t err = launch_mfma_fwd(g, x, w, scale, shift, residual, y, relu, workspace, workspace_bytes, s, parts > 0 ? stats : nullptr);
         if (err == hipSuccess && parts > 0) *stats_parts = parts;
         return dev(err);
     }
@@ -344,6 +347,7 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
                 (!relu || aligned16(y)) && masked_on_mfma(g) && !(accum && (g.stride != 1 || g.len));
     const bool dzneeded = needs_dz(flags, scale);
     size_t need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
+    if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded, true);
     if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
         mfma = false;  // no room for the copies
         need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
@@ -353,7 +357,7 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
     if (overlap(dx, ndx, workspace, need) || overlap(dres, ndy, workspace, need)) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     t_current_op = NM_OP_BWD_DATA;
-    if (mfma) return dev(launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, accum, workspace, s));
+    if (mfma) return dev(launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, accum, workspace, workspace_bytes, s));
     if (use_f32(f32_dgrad_supported(g), dtype, flags)) {
         const void *gy = dy;
         hipError_t err = f32_mask_pass(g, dy, y, relu, workspace, dres, &gy, s);
@@ -561,13 +565,13 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
             err = launch_bwd_prepare(g, dy, y, scale, w, relu, workspace, nullptr, none, dres, &g_plain, s, x, xp);
             if (err != hipSuccess) return NM_ERR_DEVICE;
             t_current_op = NM_OP_BWD_DATA;
-            err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, s);
+            err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
             if (err != hipSuccess) return NM_ERR_DEVICE;
             t_current_op = NM_OP_BWD_WEIGHT;
             return dev(launch_wgrad_k1(pitched(g), xp, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
         }
         t_current_op = NM_OP_BWD_DATA;
-        err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, (flags & NM_ACCUM_DX) != 0, workspace, s, &g_plain);
+        err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s, &g_plain);
         if (err != hipSuccess || !g_plain) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s));
@@ -615,7 +619,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
                                         dres, &g_plain, s, x, xp);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_DATA;
-    err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, s);
+    err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
     return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));

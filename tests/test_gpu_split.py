@@ -1,0 +1,133 @@
+"""Calls of few tiles: the engine that splits the reduction channels over workgroups, its second pass, and the other
+engines that serve such a call when the workspace has no room for partial sums."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import _util as U
+from oracle import conv1d_oracle as orc
+from paper_1909_09577_amd import binding as nm
+from paper_1909_09577_amd import inputs as syn
+from paper_1909_09577_amd.inputs import LayerCfg
+
+
+def L(name, B, Cin, Cout, T, K, stride=1, dilation=1, pad=0, affine=True, relu=True, residual=False, seed=43):
+    return LayerCfg(name, B, Cin, Cout, T, K, stride, dilation, pad, affine, relu, residual, seed,
+                    T_out=orc.out_len(T, K, stride, dilation, pad))
+
+
+CASES = [
+    L("s_parts", 1, 512, 256, 200, 17, pad=8, residual=True),            # reduction in parts, a ragged last tile
+    L("s_parts_odd", 2, 328, 200, 131, 11, pad=5, residual=True),        # channels of no whole chunk or tile, odd rows
+    L("s_one_part", 1, 64, 640, 264, 13, pad=6, residual=True),          # two chunks
+    L("s_stride2", 3, 64, 256, 400, 11, stride=2, pad=5),
+    L("s_dil2", 1, 256, 136, 144, 29, dilation=2, pad=28),               # the longest window
+    L("s_k1", 2, 384, 512, 192, 1, relu=False),                          # half of the wavefronts idle
+    L("s_k2", 1, 160, 192, 64, 2, pad=1),
+    L("s_short", 2, 256, 256, 16, 11, pad=5, residual=True),             # shorter than a tile
+]
+
+
+def _least(cfg, M, R):
+    """Bytes of the packed weights of a pass with M output and R reduction channels (128-step tap pairs, zero pair)."""
+    n = -(-M // 64) * -(-R // 32) * (cfg.K + cfg.K % 2) * 256 + 512
+    return (n * 16 + 255) // 256 * 256
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_few_tiles(cfg, masked):
+    import torch
+    inp = syn.make_inputs(cfg, "bf16")
+    kw = U.geom_kw(cfg)
+    lens = np.full(cfg.B, cfg.T, dtype=np.int32)
+    x_bits = inp["x_bits"].copy()
+    if masked:
+        lens[0] = max(1, cfg.T - 45)  # a dead tail; poison behind it
+        x_bits[0, :, lens[0]:] = 0x7FC0
+    ld = torch.from_numpy(lens).cuda() if masked else None
+    x = torch.from_numpy(x_bits.view(np.int16)).cuda().view(torch.bfloat16)
+    w, dy = U.to_dev(inp, "w", "bf16"), U.to_dev(inp, "dy", "bf16")
+    scale, shift = U.to_dev(inp, "scale", "bf16"), U.to_dev(inp, "shift", "bf16")
+    res = U.to_dev(inp, "residual", "bf16") if cfg.residual else None
+    y = nm.nm_conv1d_block_fwd(x, w, scale, shift, res, relu=cfg.relu, lengths=ld, **kw)
+    y_ref = orc.block_fwd_masked(inp["x"], inp["w"], lens, inp["scale"], inp["shift"],
+                                 inp["residual"] if cfg.residual else None, cfg.relu, **kw)
+    U.assert_close(U.to_host_f64(y), y_ref, "bf16", f"{cfg.name} y")
+    y_saved = U.round_to_storage(y_ref, "bf16")
+    ysv = U.arr_to_dev(y_saved, "bf16") if cfg.relu else None
+    dx = nm.nm_conv1d_bwd_data(dy, w, cfg.T, y=ysv, scale=scale, relu=cfg.relu, lengths=ld, **kw)[0]
+    dz, _ = orc.epilogue_bwd(inp["dy"], y_saved.astype(np.float64) if cfg.relu else None, inp["scale"], cfg.relu)
+    dx_ref = orc.bwd_data_masked(dz, inp["w"], cfg.T, lens, **kw)
+    U.assert_close(U.to_host_f64(dx), dx_ref, "bf16", f"{cfg.name} dx")
+    dx1, _, dw1 = nm.nm_conv1d_bwd(x, dy, w, y=ysv, scale=scale, relu=cfg.relu, lengths=ld, **kw)
+    assert torch.equal(dx1, dx)
+    if not masked and cfg.stride == 1:  # accumulation into dx, in the second pass too
+        old = torch.randn(cfg.B, cfg.Cin, cfg.T, device="cuda").bfloat16()
+        acc = old.clone()
+        nm.nm_conv1d_bwd_data(dy, w, cfg.T, y=ysv, scale=scale, dx=acc, relu=cfg.relu, accumulate_dx=True, **kw)
+        U.assert_close(U.to_host_f64(acc), U.to_host_f64(old) + dx_ref, "bf16", f"{cfg.name} dx accumulated")
+    # poisoned scratch of exactly the size asked for, then without room for partial sums: the other engines
+    full = nm.nm_conv1d_workspace_bytes(nm.NM_OP_FWD, *cfg.dims(), nm.NM_BF16, nm.NM_RELU)
+    for n in {full, _least(cfg, cfg.Cout, cfg.Cin) + (0 if cfg.T % 8 == 0 else 2 * cfg.B * cfg.Cin * ((cfg.T + 135) // 8 * 8))}:
+        guard = torch.full((n + 256,), 255, dtype=torch.uint8, device="cuda")
+        y1 = nm.nm_conv1d_block_fwd(x, w, scale, shift, res, relu=cfg.relu, lengths=ld, workspace=guard[:n], **kw)
+        U.assert_close(U.to_host_f64(y1), y_ref, "bf16", f"{cfg.name} y, workspace of {n}")
+        assert bool((guard[n:] == 255).all())
+
+
+@pytest.mark.gpu
+def test_batchnorm_statistics_of_few_tiles():
+    import torch
+    from oracle import bn_oracle
+    cfg = CASES[0]
+    inp = syn.make_inputs(cfg, "bf16")
+    x, w = U.to_dev(inp, "x", "bf16"), U.to_dev(inp, "w", "bf16")
+    g, b = U.to_dev(inp, "scale", "bf16"), U.to_dev(inp, "shift", "bf16")
+    z, y, mean, invstd = nm.nm_conv1d_bn_fwd(x, w, g, b, relu=True, **U.geom_kw(cfg))
+    zf = z.double()
+    assert torch.allclose(mean.double(), zf.mean(dim=(0, 2)), rtol=0, atol=1e-6)
+    assert torch.allclose(invstd.double(), 1 / torch.sqrt(zf.var(dim=(0, 2), unbiased=False) + 1e-3), rtol=1e-5, atol=0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(2, 1024, 29, 265), (1, 64, 29, 9), (3, 48, 32, 129), (1, 272, 7, 127), (2, 32, 29, 8), (1, 32, 5, 33)],
+                         ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("shifted", [0, 1], ids=["", "odd_address"])
+def test_decoder_rows_of_any_length(case, shifted):
+    """float32 sums of exact products: the gate of the decoder's other parity tests (5e-5)."""
+    import torch
+    from oracle import decoder_oracle as dorc
+    B, Cin, Ncls, T = case
+    gen = np.random.default_rng(5)
+    x = syn.bf16_bits_to_f32(syn.f32_to_bf16_bits(gen.standard_normal((B, Cin, T), dtype=np.float32)))
+    w = syn.bf16_bits_to_f32(syn.f32_to_bf16_bits(gen.standard_normal((Ncls, Cin), dtype=np.float32) / np.float32(np.sqrt(Cin))))
+    n = x.size
+    buf = torch.full((n + 16 + shifted,), float("nan"), dtype=torch.bfloat16, device="cuda")  # poison around x
+    xd = buf[8 + shifted:8 + shifted + n].view(B, Cin, T)
+    xd.copy_(U.arr_to_dev(x, "bf16"))
+    got = nm.nm_decoder_logsoftmax_fwd(xd, U.arr_to_dev(w, "bf16"), None).cpu().numpy().astype(np.float64)
+    mx, _ = U.err_metrics(got, dorc.decoder_logsoftmax(x, w))
+    assert mx <= 5e-5, mx
+
+
+FAKE = [ctypes.c_void_p(0x100000000000 + (i << 36)) for i in range(6)]
+
+
+def test_room_for_partial_sums_is_asked_for_but_not_required():
+    """A workspace of the packed weights alone still serves a call of few tiles (it ends at the launch, which has no
+    device here); a smaller one is refused as before; calls of many tiles ask for nothing more."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("addresses without memory: not on a device")
+    few = L("few", 1, 768, 768, 600, 25, pad=12)
+    least = _least(few, 768, 768)
+    assert nm.nm_conv1d_workspace_bytes(nm.NM_OP_FWD, *few.dims()) > least
+    f = nm.lib().nm_conv1d_block_fwd
+    args = (FAKE[0], FAKE[1], None, None, None, FAKE[2], 0, 0, FAKE[3])
+    assert f(*few.dims(), *args, least, None) == nm.NM_ERR_DEVICE
+    assert f(*few.dims(), *args, least - 1, None) == nm.NM_ERR_WORKSPACE
+    many = L("many", 32, 512, 512, 800, 17, pad=8)
+    assert nm.nm_conv1d_workspace_bytes(nm.NM_OP_FWD, *many.dims()) == _least(many, 512, 512)
