@@ -32,6 +32,7 @@
 // for any other K (KT == 0) tap pairs run in a loop with staging in out-of-line blocks.
 #include "nm_common.h"
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -1577,40 +1578,53 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(unsigned npack, const 
     mask_pack_wave(threadIdx.x & 63, b, cm, st4, Cout, To, ncm, nst, dy, y, relu, gplain, gf);
 }
 
-// ---- input gradient of a stride-2 convolution (the encoder's first layer) -------------------------
-// dx[ci, s] only receives taps k with s + pad - k even, so the samples of each parity r form a
-// stride-1 correlation of dz with every second tap:  dx[ci, 2u+r] = sum_co sum_k' w[co,ci,kp_r+2k'] *
-// dz[co, u + c_r - k'],  kp_r = (r+pad) mod 2,  c_r = (r+pad-kp_r)/2.  Each phase runs through the
-// stride-1 engine on its own sub-filter; two small kernels cut the sub-filters out of w and
-// interleave the two phase outputs into dx.
-__global__ __launch_bounds__(256) void tap_subsample_kernel(const bf16_t *__restrict__ w, bf16_t *__restrict__ w0,
-                                                            bf16_t *__restrict__ w1, size_t rows, int K, int kp0, int K0,
-                                                            int kp1, int K1)
+// ---- stride-2 input gradient --------------------------------------------------------------------
+// dx[ci][2u + r] only receives the taps k with 2u + r + pad - k even, so each parity r of the sample is a stride-1
+// correlation of g with every second tap.  The two are one contraction with 2*Cin output rows (parity, ci): their
+// filters are cut out side by side, aligned to the same window with zero taps where they differ, and
+// interleave_phases_kernel merges the rows.  64 <- 256 channels, K=11, B=32, T=1600: one contraction over shared windows
+// in place of one per parity.
+struct Phases {
+    int K, padL;            // taps and left padding of the joint contraction
+    int kp[2], Kr[2], off[2];  // parity r: taps kp, kp+2, ... (Kr of them) lie at off .. of its filter
+    int U, Up;              // outputs per parity, row pitch
+    bool ok;
+};
+__global__ __launch_bounds__(256) void phase_filters_kernel(const bf16_t *__restrict__ w, bf16_t *__restrict__ wsub, unsigned rows,
+                                                            int Cin, int K, const Phases ph)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const unsigned i = blockIdx.x * 256 + threadIdx.x;  // (co, ci)
     if (i >= rows) return;
-    const bf16_t *src = w + i * K;
-    for (int j = 0; j < K0; ++j) w0[i * K0 + j] = src[kp0 + 2 * j];
-    for (int j = 0; j < K1; ++j) w1[i * K1 + j] = src[kp1 + 2 * j];
+    const unsigned co = i / (unsigned)Cin, ci = i - co * (unsigned)Cin;
+    const bf16_t *src = w + (size_t)i * K;
+    for (int r = 0; r < 2; ++r) {
+        bf16_t *dst = wsub + ((size_t)(2 * co + r) * Cin + ci) * ph.K;
+        for (int t = 0; t < ph.K; ++t) {
+            const int k = t - ph.off[r];
+            dst[t] = k >= 0 && k < ph.Kr[r] ? src[ph.kp[r] + 2 * k] : (bf16_t)0;
+        }
+    }
 }
 
-// dx[row][2u] = a0[row][u], dx[row][2u+1] = a1[row][u]; 8 values of u per thread (U % 8 == 0)
-__global__ __launch_bounds__(256) void interleave2_kernel(const u32x4 *__restrict__ a0, const u32x4 *__restrict__ a1,
-                                                          u32x4 *__restrict__ dx, size_t n8)
+// dx[b][ci][2u + r] = a[b][r][ci][u], zero from a sample's length on; eight samples per thread, rows of any length
+__global__ __launch_bounds__(256) void interleave_phases_kernel(const bf16_t *__restrict__ a, bf16_t *__restrict__ dx, int Cin, int T,
+                                                                int Up, unsigned n, const int *__restrict__ len)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n8) return;
-    const u32x4 e = a0[i], o = a1[i];
-    u32x4 lo, hi;
+    const unsigned i = blockIdx.x * 256 + threadIdx.x;
+    const unsigned T8 = (unsigned)(T + 7) / 8;
+    if (i >= n) return;
+    const unsigned row = i / T8, grp = i - row * T8, b = row / (unsigned)Cin, ci = row - b * (unsigned)Cin;
+    const bf16_t *e = a + ((size_t)(2 * b) * Cin + ci) * Up + 4 * grp;
+    uint32_t ev[2], ov[2];
+    __builtin_memcpy(ev, e, 8);
+    __builtin_memcpy(ov, e + (size_t)Cin * Up, 8);
+    u32x4 v = {zip_lo16(ev[0], ov[0]), zip_hi16(ev[0], ov[0]), zip_lo16(ev[1], ov[1]), zip_hi16(ev[1], ov[1])};
+    if (len) {
+        const int nv = len[b] - 8 * (int)grp;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        lo[2 * j] = zip_lo16(e[j], o[j]);
-        lo[2 * j + 1] = zip_hi16(e[j], o[j]);
-        hi[2 * j] = zip_lo16(e[2 + j], o[2 + j]);
-        hi[2 * j + 1] = zip_hi16(e[2 + j], o[2 + j]);
+        for (int j = 0; j < 4; ++j) v[j] &= nv >= 2 * j + 2 ? 0xffffffffu : (nv == 2 * j + 1 ? 0x0000ffffu : 0u);
     }
-    dx[2 * i] = lo;
-    dx[2 * i + 1] = hi;
+    store8_any(dx + (size_t)row * T + 8 * grp, v, T - 8 * (int)grp);
 }
 
 // The preparation of a call on rows that are no multiple of eight long (RowPrep): packing blocks, mask blocks (a
@@ -1720,9 +1734,10 @@ Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
 // ---- which calls take conv_split_kernel ---------------------------------------------------------
 // Its time and the other engines' are estimated in microseconds from measured rates (256 CUs assumed: the workspace
 // query has no device).  A wavefront's MFMA costs 18 ns in the unrolled engine, 20.5 ns here with two or more workgroups
-// per CU; a chunk costs 0.3 us more there for staging and the barrier (27 ns and 0.6 us alone on the CU), parts
-// 10 us for the second launch (its host time counts where calls are this short) and 0.42 us per MB of float32 outputs and
-// part.  Both sides of the line, forward, weight packing
+// per CU; a chunk costs 0.3 us more there for staging and the barrier (27 ns and 0.8 us alone on the CU), parts
+// 6 us for the second launch and 0.42 us per MB of float32 outputs and part, and no less than 15 us in all (a call of three
+// launches is bound by the host below that: 256 channels, K=11, 200 steps 21.0 us in eight parts, 19.2 in the other engine).
+// Both sides of the line, forward, weight packing
 // included (split / other engine): 768 channels K=25, 600 steps, B=1 40 / 65 us, B=2 55 / 67, B=4 83 / 76; 512 channels
 // K=17, 400 steps, B=4 34 / 40, B=8 46 / 42; 512 channels K=1, 400 steps, B=4 15 / 21, 800 steps, B=16 48 / 24;
 // 64 -> 256 channels, stride 2, 1600 steps, B=32 28 / 46.
@@ -1757,7 +1772,7 @@ SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int d
     const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
     if (!pl.ok || (K == 1 && nch == 1)) return best;
     const double mb = 4e-6 * B * M * (double)Tout;
-    double best_cost = 0.95 * engine_cost(pl, B, M, R, Tout, K);
+    double best_cost = 0.9 * engine_cost(pl, B, M, R, Tout, K);
     // (whatever the shape, the MFMAs at 256 CUs' full rate: most large calls need not be looked at any further)
     if (0.0205 / 4096 * nmt * 2 * (double)B * ((Tout + 31) / 32) * nch * 2 * K > best_cost) return best;
     for (int nt = pl.stride == 1 ? 4 : 3; nt >= 2; --nt) {
@@ -1770,8 +1785,9 @@ SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int d
             const unsigned wgs = tiles * ns, rounds = (wgs + 255) / 256;
             if (ns > nch || (ns > 1 && wgs > 1024)) break;
             const unsigned chunks = (unsigned)(nch + ns - 1) / (unsigned)ns;
-            const double cost = (double)(rounds * chunks) * ((rounds > 1 ? 0.0205 : 0.027) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.3 : 0.6)) +
-                                (ns > 1 ? 10.0 + 0.42 * ns * mb : 0.0);
+            double cost = (double)(rounds * chunks) *
+                          ((rounds > 1 ? 0.0205 : 0.027) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.3 : 0.8));
+            if (ns > 1) cost = std::max(cost + 6.0 + 0.42 * ns * mb, 15.0);
             if (cost >= best_cost) continue;
             best_cost = cost;
             best.nt = nt;
@@ -2137,25 +2153,32 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
 // ---- input gradient (stride 1 only; other strides use the plain kernels) ----------------
 // Workspace: packed (flipped, transposed) weights, then dz when it differs from dy.
 namespace {
-// stride 2 as two stride-1 phases (see tap_subsample_kernel)
-struct Phase2 {
-    int kp[2], K[2], c[2], U;  // first tap, taps, dz offset of each phase; outputs per phase
-    bool ok;
-};
-Phase2 phases_of_stride2(const Geom &g)
+// (16-byte rows of T % 16 == 8 keep the plain kernel, whose smaller workspace they were always served with)
+Phases phases_of_stride2(const Geom &g)
 {
-    Phase2 ph = {};
-    if (g.stride != 2 || g.dil != 1 || g.T % 16 != 0 || g.To % 8 != 0) return ph;
-    ph.U = g.T / 2;
+    Phases ph = {};
+    if (g.stride != 2 || g.dil != 1 || (rows16(g) && g.T % 16 != 0)) return ph;
+    int padL[2];
     for (int r = 0; r < 2; ++r) {
         ph.kp[r] = (r + g.pad) & 1;
-        ph.K[r] = g.K > ph.kp[r] ? (g.K - ph.kp[r] + 1) / 2 : 0;
-        ph.c[r] = (r + g.pad - ph.kp[r]) / 2;
-        if (ph.K[r] < 1) return ph;
-        if (!make_plan(g.To, ph.U, g.Cout, ph.K[r], 1, 1).ok || packed_bytes(g.Cin, g.Cout, ph.K[r]) >= kMaxPacked) return ph;
+        ph.Kr[r] = g.K > ph.kp[r] ? (g.K - ph.kp[r] + 1) / 2 : 0;
+        if (ph.Kr[r] < 1) return ph;
+        // out[u] = sum_j W'[j] * g[u - padL + j] with j = Kr-1-k'
+        padL[r] = ph.Kr[r] - 1 - (r + g.pad - ph.kp[r]) / 2;
     }
-    ph.ok = true;
+    ph.padL = std::max(padL[0], padL[1]);
+    for (int r = 0; r < 2; ++r) ph.K = std::max(ph.K, ph.Kr[r] + ph.padL - padL[r]);
+    for (int r = 0; r < 2; ++r) ph.off[r] = ph.K - ph.Kr[r] - (ph.padL - padL[r]);
+    ph.U = (g.T + 1) / 2;
+    ph.Up = row_pitch(ph.U);
+    ph.ok = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1).ok && packed_bytes(2 * g.Cin, g.Cout, ph.K) < kMaxPacked &&
+            (size_t)g.B * 2 * g.Cin * ph.Up * sizeof(bf16_t) <= kMaxInput;
     return ph;
+}
+// the parities' outputs; until they are written, their filters
+size_t phase_bytes(const Geom &g, const Phases &ph)
+{
+    return align_up(std::max((size_t)g.B * 2 * g.Cin * ph.Up, (size_t)g.Cout * 2 * g.Cin * ph.K) * sizeof(bf16_t), 256);
 }
 size_t dz_bytes_of(const Geom &g) { return align_up((size_t)g.B * g.Cout * row_pitch(g.To) * sizeof(bf16_t), 256); }
 }  // namespace
@@ -2172,24 +2195,17 @@ bool mfma_dgrad_supported(const Geom &g)
 size_t mfma_dgrad_workspace_least(const Geom &g)
 {
     if (g.stride == 2) {
-        const Phase2 ph = phases_of_stride2(g);
-        size_t n = dz_bytes_of(g);
-        for (int r = 0; r < 2; ++r)
-            n += align_up((size_t)g.Cout * g.Cin * ph.K[r] * sizeof(bf16_t), 256) + packed_bytes(g.Cin, g.Cout, ph.K[r]) +
-                 align_up((size_t)g.B * g.Cin * ph.U * sizeof(bf16_t), 256);
-        return n;
+        const Phases ph = phases_of_stride2(g);
+        return dz_bytes_of(g) + packed_bytes(2 * g.Cin, g.Cout, ph.K) + phase_bytes(g, ph);
     }
     return packed_bytes(g.Cin, g.Cout, g.K) + dz_bytes_of(g);
 }
 size_t mfma_dgrad_workspace(const Geom &g)
 {
     size_t part = 0;
-    if (g.stride == 2) {  // (the two phases run one after the other)
-        const Phase2 ph = phases_of_stride2(g);
-        for (int r = 0; r < 2; ++r) {
-            const SplitPlan sp = split_plan(make_plan(g.To, ph.U, g.Cout, ph.K[r], 1, 1), g.B, g.Cin, g.Cout, ph.U, ph.K[r], 1);
-            if (sp.part_bytes > part) part = sp.part_bytes;
-        }
+    if (g.stride == 2) {
+        const Phases ph = phases_of_stride2(g);
+        part = split_plan(make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1), g.B, 2 * g.Cin, g.Cout, ph.Up, ph.K, 1).part_bytes;
     } else {
         part = split_plan(make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil), g.B, g.Cin, g.Cout, g.T, g.K, g.dil).part_bytes;
     }
@@ -2220,50 +2236,50 @@ hipError_t mask_pass(const Geom &g, const void *dy, const void *y, bool relu, vo
 }
 
 hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
-                                     void *dx, void *dres, bool relu, void *ws, void *part, size_t part_room, hipStream_t s)
+                                     void *dx, void *dres, bool relu, void *ws, void *part, size_t part_room, hipStream_t s,
+                                     const void **g_used)
 {
-    const Phase2 ph = phases_of_stride2(g);
+    const Phases ph = phases_of_stride2(g);
     if (!ph.ok) return hipErrorInvalidValue;
     unsigned char *cur = (unsigned char *)ws;
     void *gbuf = cur;
     cur += dz_bytes_of(g);
-    void *wsub[2], *packed[2], *phase_out[2];
-    for (int r = 0; r < 2; ++r) {
-        wsub[r] = cur;
-        cur += align_up((size_t)g.Cout * g.Cin * ph.K[r] * sizeof(bf16_t), 256);
-        packed[r] = cur;
-        cur += packed_bytes(g.Cin, g.Cout, ph.K[r]);
-        phase_out[r] = cur;
-        cur += align_up((size_t)g.B * g.Cin * ph.U * sizeof(bf16_t), 256);
-    }
+    void *packed = cur;
+    cur += packed_bytes(2 * g.Cin, g.Cout, ph.K);
+    bf16_t *phase_out = (bf16_t *)cur, *wsub = phase_out;
     const void *gin = dy;
-    hipError_t e = mask_pass(g, dy, y, relu, gbuf, dres, &gin, s);
-    if (e != hipSuccess) return e;
-    const size_t rows = (size_t)g.Cout * g.Cin;
-    hipLaunchKernelGGL(tap_subsample_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, (const bf16_t *)w,
-                       (bf16_t *)wsub[0], (bf16_t *)wsub[1], rows, g.K, ph.kp[0], ph.K[0], ph.kp[1], ph.K[1]);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    for (int r = 0; r < 2; ++r) {
-        const Plan pl = make_plan(g.To, ph.U, g.Cout, ph.K[r], 1, 1);
-        e = run_prepack(wsub[r], packed[r], g.Cin, g.Cout, ph.K[r], true, scale, s);
-        if (e != hipSuccess) return e;
-        ConvGemmParams p = {};
-        // out[u] = sum_j W'[j] * g[u - padL + j] with j = K_r-1-k'  ->  padL = K_r - 1 - c_r
-        fill_common(p, pl, g.B, g.Cin, g.Cout, g.To, ph.U, ph.K[r], 1, ph.K[r] - 1 - ph.c[r]);
-        p.relu = 0;
-        p.in = (const bf16_t *)gin;
-        p.wp = (const bf16x8 *)packed[r];
-        p.out = (bf16_t *)phase_out[r];
-        p.len_out = g.len;  // dx[2u+r] is padding from 2u+r >= len on: u >= ceil((len - r) / 2)
-        p.len_out_sub = r;
-        p.len_out_div = 2;
-        e = launch_plan(pl, p, s, part, part_room);  // the first of the two carries the one-shot timer
-        if (e != hipSuccess) return e;
+    hipError_t e;
+    if (g.To % 8 == 0) {
+        e = mask_pass(g, dy, y, relu, gbuf, dres, &gin, s);
+    } else {
+        RowPrep a = {};
+        a.dy = dy;
+        a.y = y;
+        a.relu = relu;
+        a.gplain = gbuf;
+        a.dres = dres;
+        gin = gbuf;
+        e = launch_prepare_rows(g, a, s);
     }
-    const size_t n8 = (size_t)g.B * g.Cin * ph.U / 8;
-    hipLaunchKernelGGL(interleave2_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, (const u32x4 *)phase_out[0],
-                       (const u32x4 *)phase_out[1], (u32x4 *)dx, n8);
+    if (e != hipSuccess) return e;
+    if (g_used) *g_used = gin;
+    const unsigned rows = (unsigned)g.Cout * (unsigned)g.Cin;
+    hipLaunchKernelGGL(phase_filters_kernel, dim3((rows + 255) / 256), dim3(256), 0, s, (const bf16_t *)w, wsub, rows, g.Cin, g.K, ph);
+    e = run_prepack(wsub, packed, 2 * g.Cin, g.Cout, ph.K, true, scale, s);
+    if (e != hipSuccess) return e;
+    const Plan pl = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1);
+    ConvGemmParams p = {};
+    fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL);
+    p.in = (const bf16_t *)gin;
+    p.wp = (const bf16x8 *)packed;
+    p.out = phase_out;
+    p.len_out = g.len;  // both parities are padding from 2u >= len on (the merging pass clears an odd length's last one)
+    p.len_out_div = 2;
+    e = launch_plan(pl, p, s, part, part_room);
+    if (e != hipSuccess) return e;
+    const unsigned n = (unsigned)g.B * g.Cin * ((g.T + 7) / 8);
+    hipLaunchKernelGGL(interleave_phases_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const bf16_t *)phase_out, (bf16_t *)dx,
+                       g.Cin, g.T, ph.Up, n, g.len);
     return hipGetLastError();
 }
 
@@ -2292,7 +2308,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
     if (g_used) *g_used = nullptr;
     if (g.stride == 2) {
         if (accumulate) return hipErrorInvalidValue;
-        return launch_mfma_dgrad_stride2(g, dy, y, scale, w, dx, dres, relu, ws, part, part_room, s);
+        return launch_mfma_dgrad_stride2(g, dy, y, scale, w, dx, dres, relu, ws, part, part_room, s, g_used);
     }
     const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;

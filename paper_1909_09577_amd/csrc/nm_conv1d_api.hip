@@ -190,11 +190,12 @@ size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool le
     return plain > fast ? plain : fast;
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
-// without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels;
+// without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels, so are stride-2 input gradients;
 // calls of few tiles without room for the split engine's partial sums by the other engines.
 size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
-    return rows16(g) && dtype != NM_F32 ? asked_workspace(op, g, dtype, flags, true) : workspace_for(op, g, dtype, false, true);
+    const bool strided = op == NM_OP_BWD_DATA && g.stride == 2;
+    return rows16(g) && dtype != NM_F32 && !strided ? asked_workspace(op, g, dtype, flags, true) : workspace_for(op, g, dtype, false, true);
 }
 
 int check_workspace(const void *ws, size_t have, size_t need)
@@ -348,7 +349,7 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
     const bool dzneeded = needs_dz(flags, scale);
     size_t need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
     if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded, true);
-    if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
+    if (mfma && (!rows16(g) || g.stride == 2) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
         mfma = false;  // no room for the copies
         need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
     }
@@ -575,6 +576,21 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         if (err != hipSuccess || !g_plain) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s));
+    }
+    // stride 2: the input gradient's g is plain too, and what the general weight-gradient kernel reads
+    const bool fused_s2 = whole && !clash && g.stride == 2 && rows16(g) && !(flags & NM_ACCUM_DX) && use_mfma(NM_OP_BWD_DATA, g, dtype, flags) &&
+                          use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && masked_on_mfma(g, NM_OP_BWD_WEIGHT) && aligned16(x) &&
+                          aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
+    if (fused_s2) {
+        DisarmOnExit disarm;
+        hipStream_t s = (hipStream_t)hip_stream;
+        const void *g_plain = nullptr;
+        t_current_op = NM_OP_BWD_DATA;
+        hipError_t err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, false, workspace, ws_data, s, &g_plain);
+        if (err != hipSuccess || !g_plain) return NM_ERR_DEVICE;
+        t_current_op = NM_OP_BWD_WEIGHT;
+        return dev(launch_mfma_wgrad(g, x, g_plain, nullptr, scale, dw, false, (flags & NM_ACCUM_DW) != 0,
+                                     (unsigned char *)workspace + ws_data, s));
     }
     // float32 on the matrix cores: the masked gradient is formed once for both
     const bool fused_f32 = whole && use_f32(f32_dgrad_supported(g) && f32_wgrad_supported(g), dtype, flags);

@@ -1,0 +1,49 @@
+"""Stride-2 input gradient: both parities of the samples in one contraction, rows of any length, every alignment of the
+two filters (pad and K even or odd), against the oracle at the gates of the other parity tests."""
+import numpy as np
+import pytest
+
+import _util as U
+from oracle import conv1d_oracle as orc
+from paper_1909_09577_amd import binding as nm
+from paper_1909_09577_amd import inputs as syn
+from paper_1909_09577_amd.inputs import LayerCfg
+
+CASES = [(3, 64, 256, T, K, pad) for T, K, pad in [
+    (123, 11, 5), (122, 11, 4), (121, 10, 5), (160, 12, 0), (336, 11, 5), (9, 2, 1), (65, 3, 0), (64, 5, 7), (331, 7, 12)]]
+CASES += [(2, 40, 72, 97, 11, 5), (20, 64, 256, 1002, 11, 5)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_stride2_gradients(case, masked):
+    import torch
+    B, Cin, Cout, T, K, pad = case
+    cfg = LayerCfg("stride2", B, Cin, Cout, T, K, 2, 1, pad, True, True, True, 47, T_out=orc.out_len(T, K, 2, 1, pad))
+    inp = syn.make_inputs(cfg, "bf16")
+    kw = U.geom_kw(cfg)
+    lens = np.full(B, T, dtype=np.int32)
+    if masked:
+        lens[:2] = [T - 1, (T + 1) // 2]
+    ld = torch.from_numpy(lens).cuda() if masked else None
+    x, w, dy = (U.to_dev(inp, n, "bf16") for n in ("x", "w", "dy"))
+    scale = U.to_dev(inp, "scale", "bf16")
+    ysv = U.to_dev(inp, "y_saved", "bf16")
+    y_saved = U.to_host_f64(ysv)
+    buf = torch.full((B * Cin * T + 128,), -7.0, dtype=torch.bfloat16, device="cuda")
+    dx = buf[64:64 + B * Cin * T].view(B, Cin, T)
+    dx1, dres1 = nm.nm_conv1d_bwd_data(dy, w, T, y=ysv, scale=scale, dx=dx, want_dres=True, relu=True, lengths=ld, **kw)
+    dz, dres_ref = orc.epilogue_bwd(inp["dy"], y_saved, inp["scale"], True)
+    dx_ref = orc.bwd_data_masked(dz, inp["w"], T, lens, **kw)
+    U.assert_close(U.to_host_f64(dx), dx_ref, "bf16", "dx")
+    np.testing.assert_array_equal(U.to_host_f64(dres1), dres_ref)
+    assert bool((buf[:64] == -7).all()) and bool((buf[-64:] == -7).all())
+    # one call for both gradients (one masked gradient feeds both), and the least workspace: the plain kernels
+    dw = nm.nm_conv1d_bwd_weight(x, dy, K, y=ysv, scale=scale, relu=True, lengths=ld, **kw)
+    dx2, dres2, dw2 = nm.nm_conv1d_bwd(x, dy, w, y=ysv, scale=scale, want_dres=True, relu=True, lengths=ld, **kw)
+    assert torch.equal(dx2, dx) and torch.equal(dres2, dres1) and torch.equal(dw2, dw)
+    if B * T < 2000:
+        small = torch.empty((2 * dy.numel() + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+        dx3, _ = nm.nm_conv1d_bwd_data(dy, w, T, y=ysv, scale=scale, relu=True, lengths=ld, workspace=small, **kw)
+        U.assert_close(U.to_host_f64(dx3), dx_ref, "bf16", "dx, small workspace")
