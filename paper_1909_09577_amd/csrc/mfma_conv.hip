@@ -32,6 +32,8 @@
 // for any other K (KT == 0) tap pairs run in a loop with staging in out-of-line blocks.
 #include "nm_common.h"
 
+#include <string.h>
+
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -1766,7 +1768,7 @@ double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
     return full * (nch * chunk + 2.0) + shared * (((nch + kWaves - 1) / kWaves) * chunk + 4.0);
 }
 
-SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil)
+SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil)
 {
     SplitPlan best = {};
     const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
@@ -1800,6 +1802,25 @@ SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int d
         }
     }
     return best;
+}
+
+// the same, remembered: a call asks several times (workspace query, checks, launch)
+SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil)
+{
+    struct Entry {
+        int key[10];
+        SplitPlan plan;
+    };
+    static thread_local Entry table[16] = {};  // (no call has B = 0)
+    const int key[10] = {B, M, R, Tout, K, dil, pl.stride, pl.nt, pl.ok, pl.unrolled};
+    unsigned h = 0;
+    for (int k : key) h = h * 31u + (unsigned)k;
+    Entry &t = table[(h ^ (h >> 7) ^ (h >> 15)) % 16];
+    if (memcmp(t.key, key, sizeof key) != 0) {
+        t.plan = make_split_plan(pl, B, M, R, Tout, K, dil);
+        memcpy(t.key, key, sizeof key);
+    }
+    return t.plan;
 }
 
 size_t packed_bytes(int M, int R, int K)

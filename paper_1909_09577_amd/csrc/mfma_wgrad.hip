@@ -24,6 +24,7 @@
 //   dw[co,ci,k] = scale[co] * sum_b sum_t g[b,co,t] * x[b,ci,tau(t,k)].
 #include "nm_common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace nm {
@@ -1065,6 +1066,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restr
     }
 }
 
+constexpr long kPlanCUs = 256;  // the planning below aims at this many CUs (a heuristic only: any count works)
 struct WPlan {
     bool ok;
     int KTg, ntg, TCH, NRX, S;
@@ -1074,7 +1076,10 @@ struct WPlan {
 };
 
 // Needs 16-byte aligned rows of both operands (T % 8 == 0 and To % 8 == 0).
-WPlan make_wplan(const Geom &g)
+// wide: a workspace with room for more parts, so that few tiles fill the chip too (64 -> 256 channels, K=11, stride 2, B=32:
+// 16 tiles; with 8 parts half of the CUs idle, kernel and sum of the
+// parts 51 + 8.5 us, with 16 33 + 15)
+WPlan make_wplan(const Geom &g, bool wide = true)
 {
     WPlan w = {};
     if (g.T % 8 != 0 || g.To % 8 != 0) return w;
@@ -1114,6 +1119,7 @@ WPlan make_wplan(const Geom &g)
     long S = (512 + ntiles - 1) / ntiles;
     if (S > 8) S = 8;
     if (S > units / kWaves) S = units / kWaves;
+    if (wide && ntiles * S < kPlanCUs) S = std::min(std::min(kPlanCUs / ntiles, 32L), units / kWaves);
     if (S < 1) S = 1;
     w.S = (int)S;
     return w;
@@ -1136,7 +1142,6 @@ struct FastPlan {
 };
 // tap-group sizes wgrad_shared_kernel is built for
 constexpr bool shared_kernel_built(int KG, int dil) { return dil == 1 ? (KG == 11 || KG == 13 || KG == 17 || KG == 21) : (dil == 2 && KG == 15); }
-constexpr int kPlanCUs = 256;  // the planning below aims at this many CUs (a heuristic only: any count works)
 FastPlan make_fast_plan(const Geom &g)
 {
     FastPlan f = {};
@@ -1261,16 +1266,16 @@ bool mfma_wgrad_supported(const Geom &g0)
 }
 
 namespace {
-size_t wgrad_workspace16(const Geom &g, bool need_dz);
+size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide);
 }
-size_t mfma_wgrad_workspace(const Geom &g, bool need_dz)
+size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, bool wide)
 {
-    return wgrad_workspace16(pitched(g), need_dz || g.To % 8 != 0) + pitched_x_bytes(g);
+    return wgrad_workspace16(pitched(g), need_dz || g.To % 8 != 0, wide) + pitched_x_bytes(g);
 }
-size_t mfma_wgrad_x_offset(const Geom &g) { return mfma_wgrad_workspace(g, true) - pitched_x_bytes(g); }
+size_t mfma_wgrad_x_offset(const Geom &g, bool wide) { return mfma_wgrad_workspace(g, true, wide) - pitched_x_bytes(g); }
 
 namespace {
-size_t wgrad_workspace16(const Geom &g, bool need_dz)
+size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide)
 {
     // (sized without looking at lengths: a call with lengths never takes the pointwise kernel)
     Geom g0 = g;
@@ -1285,7 +1290,7 @@ size_t wgrad_workspace16(const Geom &g, bool need_dz)
         const FastPlan f = make_fast_plan(g);
         return part_bytes(g, f.S) + dzf_bytes(g, f);
     }
-    const WPlan w = make_wplan(g);
+    const WPlan w = make_wplan(g, wide);
     if (!w.ok) return 0;
     return part_bytes(g, w.S) + (need_dz ? dz_buf_bytes(g) : 0);
 }
@@ -1360,10 +1365,11 @@ hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float
 }
 
 hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, const void *y, const float *scale,
-                             float *dw, bool relu, bool accumulate, void *ws, hipStream_t s)
+                             float *dw, bool relu, bool accumulate, void *ws, size_t ws_bytes, hipStream_t s)
 {
     const Geom g = pitched(g0);
     const bool copies = !rows16(g0);  // x, g or both are made into 16-byte rows first
+    const bool wide = ws_bytes >= mfma_wgrad_workspace(g0, relu || copies, true);
     RowPrep prep = {};
     if (copies) {
         prep.dy = dy;
@@ -1371,7 +1377,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
         prep.relu = relu;
         if (g0.T % 8 != 0) {
             prep.x = x;
-            prep.xp = (unsigned char *)ws + mfma_wgrad_x_offset(g0);
+            prep.xp = (unsigned char *)ws + mfma_wgrad_x_offset(g0, wide);
             x = prep.xp;
         }
     }
@@ -1408,7 +1414,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
         if (e != hipSuccess) return e;
         return launch_mfma_wgrad_prepared(g, x, scale, dw, accumulate, ws, s);
     }
-    const WPlan w = make_wplan(g);
+    const WPlan w = make_wplan(g, wide);
     if (!w.ok) return hipErrorInvalidValue;
     float *part = (float *)ws;
     const void *dz = dy;

@@ -303,11 +303,12 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
                              size_t ws_bytes, hipStream_t s, const void **g_used = nullptr);
 
 bool mfma_wgrad_supported(const Geom &g);
-size_t mfma_wgrad_workspace(const Geom &g, bool need_dz);
-size_t mfma_wgrad_x_offset(const Geom &g);  // where the pitched copy of x lies in a workspace sized with need_dz
+// wide: with room for the parts that let few tiles fill the chip (general kernel); less serves too
+size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, bool wide = true);
+size_t mfma_wgrad_x_offset(const Geom &g, bool wide = true);  // where the pitched copy of x lies in a workspace sized with need_dz
 hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const void *y,
                              const float *scale, float *dw, bool relu, bool accumulate, void *ws,
-                             hipStream_t s);
+                             size_t ws_bytes, hipStream_t s);
 
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci] (scale NULL: 1), fixed order
 hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, const float *scale, int S, bool accumulate,

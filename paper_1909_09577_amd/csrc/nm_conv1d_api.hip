@@ -168,13 +168,13 @@ bool masked_on_mfma(const Geom &g, int op = NM_OP_FWD)
 }
 
 // Scratch need of one operation on one path (mfma: matrix-core kernels, else plain kernels).
-// least: without room for the partial sums of the split engine.
+// least: without room for the partial sums of the split engine and for more than eight parts of a weight gradient.
 size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_relu, bool least = false)
 {
     if (mfma) {
         if (op == NM_OP_FWD) return least ? mfma_fwd_workspace_least(g) : mfma_fwd_workspace(g);
         if (op == NM_OP_BWD_DATA) return least ? mfma_dgrad_workspace_least(g) : mfma_dgrad_workspace(g);
-        return mfma_wgrad_workspace(g, scale_or_relu);
+        return mfma_wgrad_workspace(g, scale_or_relu, !least);
     }
     if (op == NM_OP_FWD) return 0;
     return scale_or_relu ? align_up((size_t)g.B * g.Cout * g.To * elt(dtype), kWsAlign) : 0;
@@ -399,6 +399,7 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
     const bool dzneeded = needs_dz(flags, scale);
     // (with copies x lies behind room for g whether g is formed or not)
     size_t need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded || (mfma && !rows16(g)));
+    if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded || !rows16(g), true);
     if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
         mfma = false;  // no room for the copies
         need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded);
@@ -416,7 +417,7 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
     hipStream_t s = (hipStream_t)hip_stream;
     const bool accum = (flags & NM_ACCUM_DW) != 0;
     t_current_op = NM_OP_BWD_WEIGHT;
-    if (mfma) return dev(launch_mfma_wgrad(g, x, dy, y, scale, dw, relu, accum, workspace, s));
+    if (mfma) return dev(launch_mfma_wgrad(g, x, dy, y, scale, dw, relu, accum, workspace, workspace_bytes, s));
     const bool bf = dtype == NM_BF16;
     const void *dz = dy;
     if (relu) {  // the kernel contracts dy*[y>0]; scale multiplies its float32 sums
@@ -590,7 +591,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         if (err != hipSuccess || !g_plain) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_mfma_wgrad(g, x, g_plain, nullptr, scale, dw, false, (flags & NM_ACCUM_DW) != 0,
-                                     (unsigned char *)workspace + ws_data, s));
+                                     (unsigned char *)workspace + ws_data, workspace_bytes - ws_data, s));
     }
     // float32 on the matrix cores: the masked gradient is formed once for both
     const bool fused_f32 = whole && use_f32(f32_dgrad_supported(g) && f32_wgrad_supported(g), dtype, flags);
