@@ -318,17 +318,17 @@ struct TileCoords {
 
 // KT > 0: the number of taps is a compile-time constant and a chunk is one straight-line block
 // (see the unrolled main loop below); KT == 0: any K, tap pairs in a loop.
-// LEN: the instance for ragged calls -- per-sample lengths, output rows of any length; of the unrolled kernels it
-// alone carries the test for tiles in the padding and the epilogue for such rows.
+// LEN: the instance for ragged calls (per-sample lengths); of the unrolled kernels it
+// alone carries the test for tiles in the padding.
 // STATS: the instance that also writes the per-tile statistics of its stored outputs (ConvGemmParams::stats).
-template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false>
+// ANYROW: output rows of any length (the test for them costs the other calls of few tiles about 1 %).
+template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false>
 __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParams p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int TN = NT * 32;
-    constexpr bool ANYROW = LEN || KT == 0;
 
     const int nitems = p.nitems;                           // staging items per lane and chunk
     const int nmy = (p.nch - wave + kWaves - 1) / kWaves;  // chunks of this wavefront (may be 0)
@@ -1833,10 +1833,10 @@ size_t packed_bytes(int M, int R, int K)
 constexpr size_t kMaxPacked = (size_t)1 << 31;  // the kernel addresses packed weights with 32-bit offsets
 constexpr size_t kMaxInput = (size_t)1 << 30;   // and the activation tensors through buffer descriptors
 
-template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false>
+template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false>
 hipError_t launch_t(const ConvGemmParams &p, size_t lds, hipStream_t s)
 {
-    auto kern = conv_gemm_kernel<NT, STRIDE, KT, LEN, STATS>;
+    auto kern = conv_gemm_kernel<NT, STRIDE, KT, LEN, STATS, ANYROW>;
     static LdsOptIn opt_in;
     hipError_t e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), kMaxLds);
     if (e != hipSuccess) return e;
@@ -1963,7 +1963,18 @@ hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s, v
         default: return hipErrorInvalidValue;
         }
     }
-    if (pl.unrolled && (p.len_in || p.len_out || p.Tout % 8 != 0)) {
+    if (pl.unrolled && p.Tout % 8 != 0) {
+        switch (p.K) {
+        case 11: return launch_t<5, 1, 11, true, false, true>(p, pl.lds, s);
+        case 13: return launch_t<5, 1, 13, true, false, true>(p, pl.lds, s);
+        case 21: return launch_t<5, 1, 21, true, false, true>(p, pl.lds, s);
+        case 25: return launch_t<5, 1, 25, true, false, true>(p, pl.lds, s);
+        case 29: return launch_t<5, 1, 29, true, false, true>(p, pl.lds, s);
+        case 17: return launch_t<5, 1, 17, true, false, true>(p, pl.lds, s);
+        default: return hipErrorInvalidValue;
+        }
+    }
+    if (pl.unrolled && (p.len_in || p.len_out)) {
         switch (p.K) {
         case 11: return launch_t<5, 1, 11, true>(p, pl.lds, s);
         case 13: return launch_t<5, 1, 13, true>(p, pl.lds, s);
@@ -1984,6 +1995,13 @@ hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s, v
         case 17: return launch_t<5, 1, 17>(p, pl.lds, s);
         default: return hipErrorInvalidValue;
         }
+    }
+    if (p.Tout % 8 != 0) {
+        if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0, false, false, true>(p, pl.lds, s);
+        if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0, false, false, true>(p, pl.lds, s);
+        if (pl.nt == 5 && pl.stride == 2) return launch_t<5, 2, 0, false, false, true>(p, pl.lds, s);
+        if (pl.nt == 2 && pl.stride == 2) return launch_t<2, 2, 0, false, false, true>(p, pl.lds, s);
+        return hipErrorInvalidValue;
     }
     if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0>(p, pl.lds, s);
     if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0>(p, pl.lds, s);
