@@ -27,13 +27,16 @@
  *  - `workspace` is caller-provided device memory of at least
  *    nm_conv1d_workspace_bytes(op, ...) bytes, 256-byte aligned (may be NULL when
  *    that size is 0).  Its contents are scratch: undefined before and after a call.
+ *    (A smaller one is still served where kernels that do with less can run the call: more slowly, and with
+ *    sums in another order.  NM_ERR_WORKSPACE below that.)
  *  - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Calls only enqueue work on that stream; they never synchronise the host.
  *  - Return value: an nm_status.  Argument errors are detected before any device
  *    call, so they are reported identically on a host without a GPU.  No exception,
  *    abort or message crosses the boundary.
  *  - Outputs must not overlap inputs or the workspace.  Results are deterministic:
- *    identical inputs give bit-identical outputs.
+ *    identical inputs give bit-identical outputs (with any workspace of the size asked for; with smaller
+ *    ones, for each size).
  *  - Each tensor must hold fewer than 2^31 elements.
  */
 #ifndef NM_CONV1D_H
@@ -205,11 +208,15 @@ int nm_decoder_logsoftmax_fwd(int B, int Cin, int Ncls, int T, const void *x, co
 
 /* Block forward for callers that cannot allocate device memory or size a workspace: code running under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation, arguments,
- * results (bit for bit) and error behaviour as nm_conv1d_block_fwd, without the workspace arguments: the
- * scratch its kernels need (the weights in matrix-core fragment order) lives in a fixed array of
- * NM_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held until the process ends.  The call
- * allocates and frees nothing.  A geometry whose nm_conv1d_workspace_bytes(NM_OP_FWD, ...) exceeds
- * NM_STATIC_SCRATCH_BYTES returns NM_ERR_SCRATCH_LIMIT before anything is launched.  Every call on a GPU
+ * results (bit for bit) and error behaviour as nm_conv1d_block_fwd with the workspace it asks for, without the
+ * workspace arguments: the scratch its kernels need (the weights in matrix-core fragment order, 16-byte copies of
+ * rows of other lengths, partial sums) lives in a fixed array of NM_STATIC_SCRATCH_BYTES inside the library, one
+ * copy per GPU, held until the process ends.  The call allocates and frees nothing.
+ * A geometry whose weights in fragment order exceed NM_STATIC_SCRATCH_BYTES returns NM_ERR_SCRATCH_LIMIT before
+ * anything is launched; one whose nm_conv1d_workspace_bytes(NM_OP_FWD, ...) does not exceed it is always served.
+ * (In between, partial sums are made in several rounds: slower, the same bits.)  The exception is rows whose length
+ * is no multiple of eight: where their copies and the weights exceed the array the plain kernels run, which need
+ * none; the results then are, bit for bit, those of nm_conv1d_block_fwd without a workspace.  Every call on a GPU
  * uses that GPU's one array: calls that overlap in time on one GPU (different streams or threads) race on
  * it and must be serialised by the caller.  Nothing in the array has to survive between calls. */
 #define NM_STATIC_SCRATCH_BYTES ((size_t)32 << 20)

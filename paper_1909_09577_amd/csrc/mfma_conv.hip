@@ -30,6 +30,7 @@
 // Two forms of the main loop: for the tap counts of the Jasper blocks (KT > 0) a chunk is one
 // straight-line block of 4*NT*KT MFMAs with every load, LDS write and wait placed between them;
 // for any other K (KT == 0) tap pairs run in a loop with staging in out-of-line blocks.
+#include "../../include/nm_conv1d.h"
 #include "nm_common.h"
 
 #include <string.h>
@@ -77,6 +78,7 @@ struct ConvGemmParams {
     bf16_t *out;            // [B][M][Tout]
     int nsplit;             // conv_split_kernel: parts the reduction channels are split into
     f32x4 *part;            // their partial sums (nsplit > 1)
+    int col0, ncols;        // the columns (time tiles of all batch items) of this launch
     double *stats;          // optional [B*ntt][M][3]: count, mean and centred second moment of the stored outputs of
                             // every (batch item, time tile, channel) -- the partial statistics of a BatchNorm over out
 };
@@ -834,13 +836,11 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
 // (wavefront w: channel half w & 1 of the taps w >> 1, (w >> 1) + 2, ...), so that a chunk of 32 channels is enough
 // work for a workgroup; two workgroups fit a CU and cover each other's waits.  Tiles are 64 channels x NT*32
 // steps, NT chosen for little padding.  The wavefronts add their sums through LDS as in conv_gemm_kernel; with
-// nsplit > 1 the sums go to the workspace and split_reduce_kernel adds the parts in a fixed order and finishes.
+// nsplit > 1 the sums go to the workspace and split_reduce_kernel adds the parts in a fixed order and finishes (a few
+// columns of tiles at a time where the workspace has no room for all of them: a tile's sums are the same either way).
 // Workgroups that read the same weights sit on one XCD (blockIdx % 8) where the counts divide.
 constexpr int kSplitRows = 256;   // staged rows of a window at most
 constexpr int kSplitItems = kSplitRows / 8 * 16 / kThreads;  // staging items (8 steps x 2 channels) per lane and chunk
-
-template <int NT>
-constexpr size_t split_exchange_bytes() { return (size_t)kWaves * 3 * NT * 64 * sizeof(f32x4); }
 
 template <int NT, int STRIDE>
 __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const ConvGemmParams p)
@@ -849,7 +849,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const ConvGemmP
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int TN = NT * 32;
-    const int ncombo = p.nmt * p.nsplit, ncols = p.ntt * p.B;
+    const int ncombo = p.nmt * p.nsplit, ncols = p.ncols;
     int combo, col;
     if (ncombo % 8 == 0) {
         const int j = (int)blockIdx.x >> 3;
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const ConvGemmP
         col = (int)blockIdx.x / ncombo;
     }
     const int mt = combo / p.nsplit, split = combo - mt * p.nsplit;
-    const int b = col / p.ntt, t0 = (col - b * p.ntt) * TN;
+    const int b = (p.col0 + col) / p.ntt, t0 = (p.col0 + col - b * p.ntt) * TN;
     const int c0 = (int)((long)split * p.nch / p.nsplit), c1 = (int)((long)(split + 1) * p.nch / p.nsplit);
 
     Epilogue<NT> epi;
@@ -1039,11 +1039,11 @@ __global__ __launch_bounds__(64) void split_reduce_kernel(const ConvGemmParams p
     const int ni = (int)blockIdx.x % nt, quarter = (int)blockIdx.x / nt;
     const int wave = quarter & 3, tile = quarter >> 2;
     const int col = tile / p.nmt, mt = tile - col * p.nmt;
-    const int b = col / p.ntt, t0 = ((col - b * p.ntt) * nt + ni) * 32;
+    const int b = (p.col0 + col) / p.ntt, t0 = ((p.col0 + col - b * p.ntt) * nt + ni) * 32;
     Epilogue<1> epi;
     epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div);
     const auto ld = epi.template request_rows<true>(lane, b, t0, mt * kTileM + 8 * wave, true);
-    const size_t pitch = (size_t)p.nmt * p.ntt * p.B * kWaves * 2 * nt * 64;
+    const size_t pitch = (size_t)p.nmt * p.ncols * kWaves * 2 * nt * 64;
     const f32x4 *src = p.part + ((size_t)quarter * 2 * nt + ni) * 64 + lane;
     f32x4 own[2][1] = {};
 #pragma unroll 8
@@ -1743,10 +1743,21 @@ Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
 // included (split / other engine): 768 channels K=25, 600 steps, B=1 40 / 65 us, B=2 55 / 67, B=4 83 / 76; 512 channels
 // K=17, 400 steps, B=4 34 / 40, B=8 46 / 42; 512 channels K=1, 400 steps, B=4 15 / 21, 800 steps, B=16 48 / 24;
 // 64 -> 256 channels, stride 2, 1600 steps, B=32 28 / 46.
+// The plan must not depend on the workspace a call happens to get: nm_conv1d_block_fwd_static promises the bits of
+// nm_conv1d_block_fwd and has a fixed array.  So part_limit, a function of the geometry alone, is what that array has left
+// behind the weights, and no plan has more than kSplitRounds times that: the static call makes the columns in as many rounds.
+constexpr int kSplitRounds = 4;
 struct SplitPlan {
     int nt, nsplit, ngroups;  // nt = 0: another engine
-    size_t lds, part_bytes;
+    size_t lds, part_bytes, col_bytes;  // parts of all columns, of one
 };
+
+// launches in which `cols` columns are made whose parts take col_bytes each, with room for `room` bytes of them
+unsigned split_rounds(unsigned cols, size_t col_bytes, size_t room)
+{
+    const size_t fit = room / col_bytes;
+    return fit == 0 ? ~0u : (unsigned)((cols + fit - 1) / fit);
+}
 
 double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
 {
@@ -1768,7 +1779,7 @@ double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
     return full * (nch * chunk + 2.0) + shared * (((nch + kWaves - 1) / kWaves) * chunk + 4.0);
 }
 
-SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil)
+SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil, size_t part_limit)
 {
     SplitPlan best = {};
     const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
@@ -1791,6 +1802,8 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
                           ((rounds > 1 ? 0.0205 : 0.027) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.3 : 0.8));
             if (ns > 1) cost = std::max(cost + 6.0 + 0.42 * ns * mb, 15.0);
             if (cost >= best_cost) continue;
+            const size_t col_bytes = ns > 1 ? (size_t)nmt * ns * kTileM * nt * 32 * sizeof(float) : 0;
+            if (col_bytes > 0 && split_rounds(wgs / (unsigned)(nmt * ns), col_bytes, part_limit) > kSplitRounds) continue;
             best_cost = cost;
             best.nt = nt;
             best.nsplit = ns;
@@ -1798,26 +1811,28 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
             const size_t stage = 2 * (size_t)best.ngroups * 8 * kRowBytes;
             const size_t red = (size_t)kWaves * 3 * nt * 64 * sizeof(f32x4);
             best.lds = stage > red ? stage : red;
-            best.part_bytes = ns > 1 ? align_up((size_t)wgs * kTileM * nt * 32 * sizeof(float), 256) : 0;
+            best.col_bytes = col_bytes;
+            best.part_bytes = align_up(wgs / (unsigned)(nmt * ns) * col_bytes, 256);
         }
     }
     return best;
 }
 
 // the same, remembered: a call asks several times (workspace query, checks, launch)
-SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil)
+constexpr size_t kNoLimit = (size_t)1 << 40;
+SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil, size_t part_limit = kNoLimit)
 {
     struct Entry {
-        int key[10];
+        int key[11];
         SplitPlan plan;
     };
     static thread_local Entry table[16] = {};  // (no call has B = 0)
-    const int key[10] = {B, M, R, Tout, K, dil, pl.stride, pl.nt, pl.ok, pl.unrolled};
+    const int key[11] = {B, M, R, Tout, K, dil, pl.stride, pl.nt, pl.ok, pl.unrolled, (int)(part_limit >> 8)};
     unsigned h = 0;
     for (int k : key) h = h * 31u + (unsigned)k;
     Entry &t = table[(h ^ (h >> 7) ^ (h >> 15)) % 16];
     if (memcmp(t.key, key, sizeof key) != 0) {
-        t.plan = make_split_plan(pl, B, M, R, Tout, K, dil);
+        t.plan = make_split_plan(pl, B, M, R, Tout, K, dil, part_limit);
         memcpy(t.key, key, sizeof key);
     }
     return t.plan;
@@ -1910,16 +1925,20 @@ hipError_t launch_few_channels(const ConvGemmParams &p, hipStream_t s)
 }
 
 template <int NT, int STRIDE>
-hipError_t launch_split_t(const ConvGemmParams &p, size_t lds, hipStream_t s)
+hipError_t launch_split_t(ConvGemmParams p, int cols_at_once, size_t lds, hipStream_t s)
 {
     MainKernelTimer timer(s);
-    hipLaunchKernelGGL((conv_split_kernel<NT, STRIDE>), dim3(p.num_tiles * p.nsplit), dim3(kThreads), lds, s, p);
-    if (p.nsplit > 1) hipLaunchKernelGGL(split_reduce_kernel, dim3(p.num_tiles * kWaves * NT), dim3(64), 0, s, p, NT);
+    const int cols = p.ntt * p.B;
+    for (p.col0 = 0; p.col0 < cols; p.col0 += cols_at_once) {
+        p.ncols = std::min(cols_at_once, cols - p.col0);
+        hipLaunchKernelGGL((conv_split_kernel<NT, STRIDE>), dim3(p.nmt * p.ncols * p.nsplit), dim3(kThreads), lds, s, p);
+        if (p.nsplit > 1) hipLaunchKernelGGL(split_reduce_kernel, dim3(p.nmt * p.ncols * kWaves * NT), dim3(64), 0, s, p, NT);
+    }
     return hipGetLastError();
 }
 
-// sp.part_bytes bytes at `part`
-hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int stride, void *part, hipStream_t s)
+// [part, part + part_room): room for the parts of one column of tiles at least
+hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int stride, void *part, size_t part_room, hipStream_t s)
 {
     ConvGemmParams p = p0;
     p.ntt = (p.Tout + sp.nt * 32 - 1) / (sp.nt * 32);
@@ -1928,26 +1947,26 @@ hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int strid
     p.nitems = sp.ngroups;
     p.buf_bytes = sp.ngroups * 8 * kRowBytes;
     p.part = (f32x4 *)part;
+    const int cols = p.ntt * p.B;
+    const int at_once = sp.part_bytes <= part_room ? cols : (int)(part_room / sp.col_bytes);
     if (stride == 1) {
-        if (sp.nt == 4) return launch_split_t<4, 1>(p, sp.lds, s);
-        if (sp.nt == 3) return launch_split_t<3, 1>(p, sp.lds, s);
-        return launch_split_t<2, 1>(p, sp.lds, s);
+        if (sp.nt == 4) return launch_split_t<4, 1>(p, at_once, sp.lds, s);
+        if (sp.nt == 3) return launch_split_t<3, 1>(p, at_once, sp.lds, s);
+        return launch_split_t<2, 1>(p, at_once, sp.lds, s);
     }
-    if (sp.nt == 3) return launch_split_t<3, 2>(p, sp.lds, s);
-    return launch_split_t<2, 2>(p, sp.lds, s);
+    if (sp.nt == 3) return launch_split_t<3, 2>(p, at_once, sp.lds, s);
+    return launch_split_t<2, 2>(p, at_once, sp.lds, s);
 }
 
-// [part, part + part_room): room for the partial sums of the split engine
-hipError_t launch_plan(const Plan &pl, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room)
+// [part, part + part_room): room for the partial sums of the split engine, whose plan is sp
+hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room)
 {
     // one tap, at most one chunk of reduction channels, nothing to do after the sums: the store-bound kernel
     if (p.K == 1 && p.R <= kChunk && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout && p.Tout % 8 == 0 && !p.res &&
         !p.scale && !p.shift && !p.relu && !p.len_in && !p.len_out)
         return launch_few_channels(p, s);
-    if (!p.stats) {
-        const SplitPlan sp = split_plan(pl, p.B, p.M, p.R, p.Tout, p.K, p.dil);
-        if (sp.nt && sp.part_bytes <= part_room) return launch_split(sp, p, pl.stride, part, s);
-    }
+    if (!p.stats && sp.nt && (sp.nsplit == 1 || split_rounds((unsigned)((p.Tout + sp.nt * 32 - 1) / (sp.nt * 32) * p.B), sp.col_bytes, part_room) <= kSplitRounds))
+        return launch_split(sp, p, pl.stride, part, part_room, s);
     // one tap, no padding, wide tiles: the GEMM kernel whose wavefronts share the staged activations
     // (worth it from two 64-channel row tiles on: a single one would leave three wavefronts idle)
     if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == row_pitch(p.Tout))
@@ -2136,10 +2155,16 @@ bool mfma_fwd_supported(const Geom &g)
 }
 
 size_t mfma_fwd_workspace_least(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K) + pitched_x_bytes(g); }
+namespace {
+SplitPlan fwd_split_plan(const Geom &g, const Plan &pl)
+{
+    const size_t least = mfma_fwd_workspace_least(g);
+    return split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, least <= NM_STATIC_SCRATCH_BYTES ? NM_STATIC_SCRATCH_BYTES - least : kNoLimit);
+}
+}  // namespace
 size_t mfma_fwd_workspace(const Geom &g)
 {
-    const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
-    return mfma_fwd_workspace_least(g) + split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil).part_bytes;
+    return mfma_fwd_workspace_least(g) + fwd_split_plan(g, make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil)).part_bytes;
 }
 
 // Whether the forward pass of this geometry runs on a kernel instance that can also write the statistics of its
@@ -2150,7 +2175,7 @@ int mfma_fwd_stats_parts(const Geom &g)
     const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !pl.unrolled || pl.nt != 5 || g.len || !mfma_fwd_supported(g)) return 0;
     if (pl.buf_bytes < Epilogue<5>::kTileBytesWithStats) return 0;
-    if (split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil).nt) return 0;  // few tiles: z is small and read again instead
+    if (fwd_split_plan(g, pl).nt) return 0;  // few tiles: z is small and read again instead
     return g.B * ((g.To + 159) / 160);
 }
 
@@ -2186,7 +2211,7 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     p.out = (bf16_t *)y;
     p.stats = stats;
     const size_t least = mfma_fwd_workspace_least(g);
-    return launch_plan(pl, p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
+    return launch_plan(pl, fwd_split_plan(g, pl), p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
 }
 
 // ---- input gradient (stride 1 only; other strides use the plain kernels) ----------------
@@ -2239,16 +2264,21 @@ size_t mfma_dgrad_workspace_least(const Geom &g)
     }
     return packed_bytes(g.Cin, g.Cout, g.K) + dz_bytes_of(g);
 }
-size_t mfma_dgrad_workspace(const Geom &g)
+namespace {
+SplitPlan dgrad_split_plan(const Geom &g, const Plan &pl)
 {
-    size_t part = 0;
     if (g.stride == 2) {
         const Phases ph = phases_of_stride2(g);
-        part = split_plan(make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1), g.B, 2 * g.Cin, g.Cout, ph.Up, ph.K, 1).part_bytes;
-    } else {
-        part = split_plan(make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil), g.B, g.Cin, g.Cout, g.T, g.K, g.dil).part_bytes;
+        return split_plan(pl, g.B, 2 * g.Cin, g.Cout, ph.Up, ph.K, 1);
     }
-    return mfma_dgrad_workspace_least(g) + part;
+    return split_plan(pl, g.B, g.Cin, g.Cout, g.T, g.K, g.dil);
+}
+}  // namespace
+size_t mfma_dgrad_workspace(const Geom &g)
+{
+    const Phases ph = g.stride == 2 ? phases_of_stride2(g) : Phases{};
+    const Plan pl = g.stride == 2 ? make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1) : make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
+    return mfma_dgrad_workspace_least(g) + dgrad_split_plan(g, pl).part_bytes;
 }
 
 namespace {
@@ -2314,7 +2344,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
     p.out = phase_out;
     p.len_out = g.len;  // both parities are padding from 2u >= len on (the merging pass clears an odd length's last one)
     p.len_out_div = 2;
-    e = launch_plan(pl, p, s, part, part_room);
+    e = launch_plan(pl, dgrad_split_plan(g, pl), p, s, part, part_room);
     if (e != hipSuccess) return e;
     const unsigned n = (unsigned)g.B * g.Cin * ((g.T + 7) / 8);
     hipLaunchKernelGGL(interleave_phases_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const bf16_t *)phase_out, (bf16_t *)dx,
@@ -2384,7 +2414,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
     if (g_used) *g_used = gin;
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, gin, ws, dx, accumulate);
-    return launch_plan(pl, p, s, part, part_room);
+    return launch_plan(pl, dgrad_split_plan(g, pl), p, s, part, part_room);
 }
 
 // ---- fused backward -------------------------------------------------------------------------
@@ -2439,7 +2469,7 @@ hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, g_plain, ws, dx, accumulate);
     const size_t least = mfma_dgrad_workspace_least(g);
-    return launch_plan(pl, p, s, (unsigned char *)ws + least, ws_bytes - least);
+    return launch_plan(pl, dgrad_split_plan(g, pl), p, s, (unsigned char *)ws + least, ws_bytes - least);
 }
 
 }  // namespace nm

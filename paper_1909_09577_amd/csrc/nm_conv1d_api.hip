@@ -191,7 +191,8 @@ size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool le
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
 // without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels, so are stride-2 input gradients;
-// calls of few tiles without room for the split engine's partial sums by the other engines.
+// calls of few tiles without room for the split engine's partial sums by the other engines (or, from a quarter of that
+// room on, by the split engine in rounds).
 size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
     const bool strided = op == NM_OP_BWD_DATA && g.stride == 2;
@@ -444,7 +445,8 @@ int nm_conv1d_block_fwd_static(int B, int Cin, int Cout, int T, int K, int strid
                                unsigned flags, int dtype, void *hip_stream)
 {
     // Size the scratch like nm_conv1d_workspace_bytes does (0 for invalid arguments: the shared
-    // implementation below then reports them, before any device call).
+    // implementation below then reports them, before any device call).  Where the weights fit but not the split
+    // engine's partial sums, those are made in rounds: the plan allows for this array, so the bits stay the same.
     const size_t need = nm_conv1d_workspace_bytes(NM_OP_FWD, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags);
     if (need > NM_STATIC_SCRATCH_BYTES) {
         Geom g;  // (need > 0: the arguments are valid)

@@ -78,6 +78,29 @@ def test_few_tiles(cfg, masked):
         assert bool((guard[n:] == 255).all())
 
 
+STATIC = [  # weights within the fixed array, weights and partial sums beyond it
+    L("s_static_768", 1, 768, 768, 600, 25, pad=12, residual=True),
+    L("s_static_768_odd", 1, 768, 768, 601, 25, pad=12),                 # and a copy of x
+    L("s_static_640_768", 1, 640, 768, 400, 25, pad=12),
+    L("s_static_b2", 2, 768, 640, 800, 25, pad=12),
+]
+COPIES_BEYOND = L("s_static_plain", 12, 896, 16, 3001, 3, pad=1)  # copies of x beyond the array: the plain kernels
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", STATIC + [COPIES_BEYOND], ids=lambda c: c.name)
+def test_static_entry_gives_the_same_bits_in_less_scratch(cfg):
+    import torch
+    inp = syn.make_inputs(cfg, "bf16")
+    x, w = U.to_dev(inp, "x", "bf16"), U.to_dev(inp, "w", "bf16")
+    args = (U.to_dev(inp, "scale", "bf16"), U.to_dev(inp, "shift", "bf16"), U.to_dev(inp, "residual", "bf16") if cfg.residual else None)
+    none = torch.empty(0, dtype=torch.uint8, device="cuda") if cfg is COPIES_BEYOND else None
+    y = nm.nm_conv1d_block_fwd(x, w, *args, relu=cfg.relu, workspace=none, **U.geom_kw(cfg))
+    ys = torch.full_like(y, float("nan"))
+    nm.nm_conv1d_block_fwd_static(x, w, *args, y=ys, relu=cfg.relu, **U.geom_kw(cfg))
+    assert torch.equal(ys, y)
+
+
 @pytest.mark.gpu
 def test_batchnorm_statistics_of_few_tiles():
     import torch
@@ -129,5 +152,12 @@ def test_room_for_partial_sums_is_asked_for_but_not_required():
     args = (FAKE[0], FAKE[1], None, None, None, FAKE[2], 0, 0, FAKE[3])
     assert f(*few.dims(), *args, least, None) == nm.NM_ERR_DEVICE
     assert f(*few.dims(), *args, least - 1, None) == nm.NM_ERR_WORKSPACE
+    # the entry point with the fixed array serves what it did, and refuses what it did
+    f = nm.lib().nm_conv1d_block_fwd_static
+    for cfg in STATIC + [COPIES_BEYOND]:
+        assert nm.nm_conv1d_workspace_bytes(nm.NM_OP_FWD, *cfg.dims()) > nm.NM_STATIC_SCRATCH_BYTES
+        assert f(*cfg.dims(), *args[:-1], None) == nm.NM_ERR_DEVICE, cfg.name
+    big = L("big", 1, 768, 896, 160, 29, dilation=2, pad=28)
+    assert f(*big.dims(), *args[:-1], None) == nm.NM_ERR_SCRATCH_LIMIT
     many = L("many", 32, 512, 512, 800, 17, pad=8)
     assert nm.nm_conv1d_workspace_bytes(nm.NM_OP_FWD, *many.dims()) == _least(many, 512, 512)
