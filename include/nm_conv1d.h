@@ -37,6 +37,10 @@
  *  - Outputs must not overlap inputs or the workspace.  Results are deterministic:
  *    identical inputs give bit-identical outputs (with any workspace of the size asked for; with smaller
  *    ones, for each size).
+ *  - Infinities and NaNs: a result is what the definition makes of them, except that kernels of NM_BF16 mode
+ *    also multiply the zeros they put for padding, so that an infinite weight, or, where T and T_out are
+ *    multiples of eight, an infinite sample or gradient can make a NaN of a result near it that the
+ *    definition leaves finite.
  *  - Each tensor must hold fewer than 2^31 elements.
  */
 #ifndef NM_CONV1D_H

@@ -60,6 +60,30 @@ struct F32ConvParams {
     const int *len_in, *len_out;   // optional [B]
 };
 
+// One output as the definition has it, the sums as the plain kernels take them.  The kernel below also multiplies zeros for
+// the padding: with a non-finite weight that makes a NaN of a sum that has no such product, so a NaN is made again here.
+template <bool FLIP>
+__device__ __forceinline__ float defined_sum(const F32ConvParams &p, const float *in, int len, int m, int t)
+{
+    float z = 0.f;
+#pragma clang loop unroll(disable)
+    for (int r0 = 0; r0 < p.R && z == z; r0 += 8) {
+        float part = 0.f;
+#pragma clang loop unroll(disable)
+        for (int r = r0; r < min(r0 + 8, p.R); ++r) {
+            const float *w = p.w + ((size_t)(FLIP ? r : m) * (FLIP ? p.M : p.R) + (FLIP ? m : r)) * p.K;
+            const float f = p.rscale ? p.rscale[r] : 1.f;
+#pragma clang loop unroll(disable)
+            for (int k = 0; k < p.K; ++k) {
+                const int j = FLIP ? p.K - 1 - k : k, tau = t * p.stride - p.padL + j * p.dil;
+                if (tau >= 0 && tau < len) part = fmaf(w[k], in[(size_t)r * p.Tin + tau] * f, part);
+            }
+        }
+        z += part;
+    }
+    return z;
+}
+
 // A workgroup owns 64 output channels x 32*NT time steps of one batch item.  The reduction channels are staged in chunks
 // of CC (16 up to 16 taps, 8 up to 32) and split over the eight wavefronts in pairs (lane half h takes the pair's channel
 // h, so that both operands of a tap are one LDS word at a fixed offset), with CC = 8 also by halves of the taps; their
@@ -276,6 +300,7 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
         float v = 0.f;
 #pragma unroll
         for (int q = 0; q < kConvWaves; ++q) v += lds[(size_t)q * kTileM * TN + e];
+        if (v != v && t < lim) v = defined_sum<FLIP>(p, xb, len, m, t);
         if (p.scale) v *= p.scale[m];
         if (p.shift) v += p.shift[m];
         if (t >= lim) v = 0.f;
@@ -579,7 +604,8 @@ hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *dz, cons
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return launch_wgrad_reduce(g, (const float *)part, dw, scale, q.S, accumulate, s);
+    const DefinedDw fix = {true, x, dz, nullptr};
+    return launch_wgrad_reduce(g, (const float *)part, dw, scale, q.S, accumulate, s, &g, &fix);
 }
 
 }  // namespace nm

@@ -324,7 +324,8 @@ struct TileCoords {
 // alone carries the test for tiles in the padding.
 // STATS: the instance that also writes the per-tile statistics of its stored outputs (ConvGemmParams::stats).
 // ANYROW: output rows of any length (the test for them costs the other calls of few tiles about 1 %).
-template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false>
+// PADPAIR: of the tap-pair kernels' ANYROW instances, the one where a wavefront may have an odd number of tap pairs (see do_pair).
+template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false, bool PADPAIR = false>
 __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParams p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -697,20 +698,36 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
                         if (it < nitems) stage_load(sa, it, true, sxa[it], sxb[it]);
                 }
                 const int k = 2 * pr;
+                // The second tap of an odd filter's last pair, and the pad pair: zeros times samples, a NaN where the sample
+                // is infinite.  The ANYROW instances, whose calls ran on kernels without such products before, take the
+                // last tap's samples (which the output is made of anyway), resp. zeros (in an
+                // instance of its own: clearing costs 2 of the 52 us of 32 x 256 -> 256 channels, K=7, T=801).
+                const int k1 = ANYROW ? min(k + 1, p.K - 1) : k + 1;
+                auto keep = [&](bf16x8(&bf)[NT]) {
+                    if constexpr (PADPAIR) {
+                        const uint32_t mask = real ? ~0u : 0u;
+#pragma unroll
+                        for (int ni = 0; ni < NT; ++ni) bf[ni] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, bf[ni]) & mask);
+                    }
+                };
                 read_b(b1, k, 1);
+                keep(b0);
                 mma(af[0], af[1], b0);
                 const uint32_t wn = w_next();
                 af[0] = w_load(wn, 0);
                 af[1] = w_load(wn, 1);
-                read_b(b0, k + 1, 0);
+                read_b(b0, k1, 0);
+                keep(b1);
                 mma(af[2], af[3], b1);
                 af[2] = w_load(wn, 2);
                 af[3] = w_load(wn, 3);
-                read_b(b1, k + 1, 1);
+                read_b(b1, k1, 1);
+                keep(b0);
                 mma(af[4], af[5], b0);
                 af[4] = w_load(wn, 4);
                 af[5] = w_load(wn, 5);
                 read_b(b0, min(k + 2, p.Kp - 1), 0);
+                keep(b1);
                 mma(af[6], af[7], b1);
                 af[6] = w_load(wn, 6);
                 af[7] = w_load(wn, 7);
@@ -1608,9 +1625,31 @@ __global__ __launch_bounds__(256) void phase_filters_kernel(const bf16_t *__rest
     }
 }
 
-// dx[b][ci][2u + r] = a[b][r][ci][u], zero from a sample's length on; eight samples per thread, rows of any length
+// dx[b][ci][2u + r] = a[b][r][ci][u], zero from a sample's length on; eight samples per thread, rows of any length.
+// A NaN may come from a zero tap times an infinite gradient: it is made again from the products the definition has (an
+// infinite gradient would else leave NaNs in samples that no tap connects to it).
+struct PhaseSums {
+    int Cout, To, K, pad, pitch;  // pitch of g
+    const bf16_t *g, *w;
+    const float *scale;
+};
+__device__ __forceinline__ bf16_t defined_dx(const PhaseSums &q, int Cin, unsigned b, unsigned ci, int tau)
+{
+    float z = 0.f;
+#pragma clang loop unroll(disable)
+    for (int co = 0; co < q.Cout && z == z; ++co) {
+        const bf16_t *g = q.g + ((size_t)b * q.Cout + co) * q.pitch, *w = q.w + ((size_t)co * Cin + ci) * q.K;
+#pragma clang loop unroll(disable)
+        for (int k = (tau + q.pad) & 1; k < q.K; k += 2) {
+            const int t = (tau + q.pad - k) >> 1;
+            if (t < 0 || t >= q.To) continue;
+            z = fmaf(q.scale ? bf16_to_f32(f32_to_bf16(bf16_to_f32(w[k]) * q.scale[co])) : bf16_to_f32(w[k]), bf16_to_f32(g[t]), z);
+        }
+    }
+    return f32_to_bf16(z);
+}
 __global__ __launch_bounds__(256) void interleave_phases_kernel(const bf16_t *__restrict__ a, bf16_t *__restrict__ dx, int Cin, int T,
-                                                                int Up, unsigned n, const int *__restrict__ len)
+                                                                int Up, unsigned n, const int *__restrict__ len, const PhaseSums q)
 {
     const unsigned i = blockIdx.x * 256 + threadIdx.x;
     const unsigned T8 = (unsigned)(T + 7) / 8;
@@ -1621,6 +1660,13 @@ __global__ __launch_bounds__(256) void interleave_phases_kernel(const bf16_t *__
     __builtin_memcpy(ev, e, 8);
     __builtin_memcpy(ov, e + (size_t)Cin * Up, 8);
     u32x4 v = {zip_lo16(ev[0], ov[0]), zip_hi16(ev[0], ov[0]), zip_lo16(ev[1], ov[1]), zip_hi16(ev[1], ov[1])};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int tau = 8 * (int)grp + 2 * j;
+        if ((v[j] & 0x7fffu) > 0x7f80u && tau < T) v[j] = (v[j] & 0xffff0000u) | defined_dx(q, Cin, b, ci, tau);
+        if ((v[j] >> 16 & 0x7fffu) > 0x7f80u && tau + 1 < T)
+            v[j] = (v[j] & 0xffffu) | (uint32_t)defined_dx(q, Cin, b, ci, tau + 1) << 16;
+    }
     if (len) {
         const int nv = len[b] - 8 * (int)grp;
 #pragma unroll
@@ -1848,10 +1894,10 @@ size_t packed_bytes(int M, int R, int K)
 constexpr size_t kMaxPacked = (size_t)1 << 31;  // the kernel addresses packed weights with 32-bit offsets
 constexpr size_t kMaxInput = (size_t)1 << 30;   // and the activation tensors through buffer descriptors
 
-template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false>
+template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false, bool PADPAIR = false>
 hipError_t launch_t(const ConvGemmParams &p, size_t lds, hipStream_t s)
 {
-    auto kern = conv_gemm_kernel<NT, STRIDE, KT, LEN, STATS, ANYROW>;
+    auto kern = conv_gemm_kernel<NT, STRIDE, KT, LEN, STATS, ANYROW, PADPAIR>;
     static LdsOptIn opt_in;
     hipError_t e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), kMaxLds);
     if (e != hipSuccess) return e;
@@ -2016,11 +2062,16 @@ hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
         }
     }
     if (p.Tout % 8 != 0) {
-        if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0, false, false, true>(p, pl.lds, s);
-        if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0, false, false, true>(p, pl.lds, s);
-        if (pl.nt == 5 && pl.stride == 2) return launch_t<5, 2, 0, false, false, true>(p, pl.lds, s);
-        if (pl.nt == 2 && pl.stride == 2) return launch_t<2, 2, 0, false, false, true>(p, pl.lds, s);
-        return hipErrorInvalidValue;
+        auto any = [&](auto pad_pair) {
+            constexpr bool PP = decltype(pad_pair)::value;
+            if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0, false, false, true, PP>(p, pl.lds, s);
+            if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0, false, false, true, PP>(p, pl.lds, s);
+            if (pl.nt == 5 && pl.stride == 2) return launch_t<5, 2, 0, false, false, true, PP>(p, pl.lds, s);
+            if (pl.nt == 2 && pl.stride == 2) return launch_t<2, 2, 0, false, false, true, PP>(p, pl.lds, s);
+            return hipErrorInvalidValue;
+        };
+        // (a wavefront has an odd number of pairs where both a chunk's pairs and its chunks are odd)
+        return p.Kp / 2 % 2 && p.nch % (2 * kWaves) != 0 ? any(std::true_type{}) : any(std::false_type{});
     }
     if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0>(p, pl.lds, s);
     if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0>(p, pl.lds, s);
@@ -2348,7 +2399,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
     if (e != hipSuccess) return e;
     const unsigned n = (unsigned)g.B * g.Cin * ((g.T + 7) / 8);
     hipLaunchKernelGGL(interleave_phases_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const bf16_t *)phase_out, (bf16_t *)dx,
-                       g.Cin, g.T, ph.Up, n, g.len);
+                       g.Cin, g.T, ph.Up, n, g.len, PhaseSums{g.Cout, g.To, g.K, g.pad, row_pitch(g.To), (const bf16_t *)gin, (const bf16_t *)w, scale});
     return hipGetLastError();
 }
 

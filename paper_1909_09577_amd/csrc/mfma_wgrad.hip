@@ -996,10 +996,44 @@ __global__ __launch_bounds__(kThreads) void wgrad_shared_kernel(const WgradParam
     }
 }
 
+// One sum as the definition has it (see DefinedDw), in the plain kernel's blocks.
+template <typename TS>
+__device__ __forceinline__ float defined_dw(const Geom &g, const TS *x, const TS *dy, const TS *y, int co, int ci, int k)
+{
+    const int off = k * g.dil - g.pad;
+    float z = 0.f;
+#pragma clang loop unroll(disable)
+    for (int b = 0; b < g.B && z == z; ++b) {
+        const int len = valid_len(g, b);
+        const size_t at = ((size_t)b * g.Cout + co) * g.To;
+        const TS *xr = x + ((size_t)b * g.Cin + ci) * g.T;
+#pragma clang loop unroll(disable)
+        for (int t0 = 0; t0 < g.To && z == z; t0 += 64) {
+            float part = 0.f;
+#pragma clang loop unroll(disable)
+            for (int t = t0; t < min(t0 + 64, g.To); ++t) {
+                const int tau = t * g.stride + off;
+                if (tau < 0 || tau >= len) continue;
+                const float gv = y && !(load_as_f32(y, at + t) > 0.f) ? 0.f : load_as_f32(dy, at + t);
+                part = fmaf(gv, load_as_f32(xr, (size_t)tau), part);
+            }
+            z += part;
+        }
+    }
+    return z;
+}
+__device__ __forceinline__ float defined_dw(const Geom &g, const DefinedDw &q, int co, int ci, int k)
+{
+    return q.f32 ? defined_dw(g, (const float *)q.x, (const float *)q.dy, (const float *)q.y, co, ci, k)
+                 : defined_dw(g, (const bf16_t *)q.x, (const bf16_t *)q.dy, (const bf16_t *)q.y, co, ci, k);
+}
+
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci]; one block per (co, 64 ci).
+// MEND: the instance that makes NaN sums again from the tensors of DefinedDw.
+template <bool MEND>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                            const float *__restrict__ scale, int S, int K, int Cout,
-                                                           int Cin, int accumulate)
+                                                           int Cin, int accumulate, const Geom own, const DefinedDw defined)
 {
     extern __shared__ float tile[];  // [64][K+1]
     const int co = blockIdx.y;
@@ -1013,6 +1047,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
         if (ci < Cin) {
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
             for (int sp = 0; sp < S; ++sp) s += src[(size_t)sp * K * plane];
+            if (MEND && __builtin_expect(s != s, 0)) s = defined_dw(own, defined, co, ci, k);
         }
         tile[l * (K + 1) + k] = s * factor;
     }
@@ -1030,9 +1065,10 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
 // The same for Cin % 4 == 0 and 16-byte aligned dw: one block per (co, 256 ci), 16-byte loads along ci
 // (a wavefront reads 1 KiB contiguous per partial row) and 16-byte stores of the transposed tile.
 constexpr int kReduce4Ci = 256;
+template <bool MEND>
 __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                             const float *__restrict__ scale, int S, int K, int Cout,
-                                                            int Cin, int accumulate)
+                                                            int Cin, int accumulate, const Geom own, const DefinedDw defined)
 {
     extern __shared__ float tile[];  // [256][K+1]
     const int co = blockIdx.y;
@@ -1046,6 +1082,18 @@ __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restr
         if (ci < Cin) {
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
             for (int sp = 0; sp < S; ++sp) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)sp * K * plane);
+            if constexpr (MEND) {
+                const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);  // a NaN if one of them is
+                if (__builtin_expect(all != all, 0)) {
+#pragma clang loop unroll(disable)
+                    for (int e = 0; e < 4; ++e) {
+                        const float one = e == 0 ? sum[0] : e == 1 ? sum[1] : e == 2 ? sum[2] : sum[3];
+                        if (one == one) continue;
+                        const float z = defined_dw(own, defined, co, ci + e, k);
+                        if (e == 0) sum[0] = z; else if (e == 1) sum[1] = z; else if (e == 2) sum[2] = z; else sum[3] = z;
+                    }
+                }
+            }
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) tile[(4 * l + e) * (K + 1) + k] = sum[e] * factor;
@@ -1243,17 +1291,20 @@ constexpr int kMaxReduceTaps = 64 * 1024 / (64 * (int)sizeof(float)) - 1;  // 25
 }  // namespace
 
 hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, const float *scale, int S, bool accumulate,
-                         hipStream_t s)
+                         hipStream_t s, const Geom *own, const DefinedDw *defined)
 {
+    const bool mend = own && defined;
+    const Geom og = mend ? *own : g;
+    const DefinedDw d = mend ? *defined : DefinedDw{};
     if (g.Cin % 4 == 0 && ((uintptr_t)dw % 16) == 0 && (size_t)kReduce4Ci * (g.K + 1) * sizeof(float) <= 64 * 1024) {
         dim3 grid4((g.Cin + kReduce4Ci - 1) / kReduce4Ci, g.Cout);
-        hipLaunchKernelGGL(wgrad_reduce4_kernel, grid4, dim3(256), kReduce4Ci * (g.K + 1) * sizeof(float), s, part, dw, scale,
-                           S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0);
+        hipLaunchKernelGGL(mend ? wgrad_reduce4_kernel<true> : wgrad_reduce4_kernel<false>, grid4, dim3(256),
+                           kReduce4Ci * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
         return hipGetLastError();
     }
     dim3 rgrid((g.Cin + 63) / 64, g.Cout);
-    hipLaunchKernelGGL(wgrad_reduce_kernel, rgrid, dim3(256), 64 * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K,
-                       g.Cout, g.Cin, accumulate ? 1 : 0);
+    hipLaunchKernelGGL(mend ? wgrad_reduce_kernel<true> : wgrad_reduce_kernel<false>, rgrid, dim3(256),
+                       64 * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
     return hipGetLastError();
 }
 
@@ -1312,7 +1363,7 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g0)
 }
 
 hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float *scale, float *dw, bool accumulate, void *ws,
-                                      hipStream_t s)
+                                      hipStream_t s, const DefinedDw *defined)
 {
     const Geom g = pitched(g0);
     const FastPlan f = make_fast_plan(g);
@@ -1361,7 +1412,7 @@ hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float
         }
     }
     if (e != hipSuccess) return e;
-    return launch_wgrad_reduce(g, part, dw, scale, f.S, accumulate, s);
+    return launch_wgrad_reduce(g, part, dw, scale, f.S, accumulate, s, &g0, defined);
 }
 
 hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, const void *y, const float *scale,
@@ -1370,6 +1421,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
     const Geom g = pitched(g0);
     const bool copies = !rows16(g0);  // x, g or both are made into 16-byte rows first
     const bool wide = ws_bytes >= mfma_wgrad_workspace(g0, relu || copies, true);
+    const DefinedDw tensors = {false, x, dy, relu ? y : nullptr}, *defined = copies ? &tensors : nullptr;
     RowPrep prep = {};
     if (copies) {
         prep.dy = dy;
@@ -1412,7 +1464,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
             e = hipGetLastError();
         }
         if (e != hipSuccess) return e;
-        return launch_mfma_wgrad_prepared(g, x, scale, dw, accumulate, ws, s);
+        return launch_mfma_wgrad_prepared(g0, x, scale, dw, accumulate, ws, s, defined);
     }
     const WPlan w = make_wplan(g, wide);
     if (!w.ok) return hipErrorInvalidValue;
@@ -1453,7 +1505,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
     default: e = launch_kt<6>(p, w.lds, grid, s); break;
     }
     if (e != hipSuccess) return e;
-    return launch_wgrad_reduce(g, part, dw, scale, w.S, accumulate, s);
+    return launch_wgrad_reduce(g, part, dw, scale, w.S, accumulate, s, &g0, defined);
 }
 
 }  // namespace nm

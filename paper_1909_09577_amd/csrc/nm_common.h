@@ -310,9 +310,17 @@ hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const
                              const float *scale, float *dw, bool relu, bool accumulate, void *ws,
                              size_t ws_bytes, hipStream_t s);
 
+// The tensors a weight gradient's products come from, in rows of the call's own lengths: g = dy*[y>0] (y NULL: dy).
+// A kernel that also multiplies zeros (for the padding, behind a row) makes a NaN of a sum where such a zero meets a
+// non-finite value; with these the last pass makes a NaN sum again from the products the definition has.
+struct DefinedDw {
+    bool f32;
+    const void *x, *dy, *y;
+};
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci] (scale NULL: 1), fixed order
+// (own, defined: optional; the call's geometry and tensors)
 hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, const float *scale, int S, bool accumulate,
-                               hipStream_t s);
+                               hipStream_t s, const Geom *own = nullptr, const DefinedDw *defined = nullptr);
 // pointwise (K = 1) weight gradient as a GEMM over plain rows (mfma_wgrad_k1.hip); never with lengths
 bool wgrad_k1_supported(const Geom &g);
 size_t wgrad_k1_part_bytes(const Geom &g);
@@ -355,9 +363,9 @@ struct DzfLayout {
 bool mfma_wgrad_fast_supported(const Geom &g);
 DzfLayout mfma_wgrad_dzf_layout(const Geom &g);
 // weight gradient from a workspace whose fragment-order g has been written already; scale[co] (or NULL)
-// multiplies the float32 sums
+// multiplies the float32 sums; defined: for rows of any length
 hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float *scale, float *dw, bool accumulate,
-                                      void *ws, hipStream_t s);
+                                      void *ws, hipStream_t s, const DefinedDw *defined = nullptr);
 // packs the flipped weights times scale into ws (as launch_mfma_dgrad does) and, in the same launch, forms
 // g plain (into dres, else behind the packed weights in ws, else nowhere) and in fragment order (gf);
 // *g_plain: the tensor the input gradient contracts

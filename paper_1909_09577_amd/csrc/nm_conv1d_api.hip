@@ -641,7 +641,8 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
-    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
+    const DefinedDw defined = {false, x, dy, relu ? y : nullptr};
+    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, rows16(g) ? nullptr : &defined));
 }
 
 int nm_conv1d_bwd(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const void *x,

@@ -1,0 +1,80 @@
+"""Infinities: the matrix-core kernels multiply zeros for the padding, behind a row and for absent taps.  In float32 and on rows
+of any length, which plain kernels without such products served before them, one infinite sample or gradient must leave finite
+what the definition leaves finite (in float32 one infinite weight too): results are finite where the plain kernels' are, at the
+usual gates."""
+import pytest
+
+from oracle import conv1d_oracle as orc
+from paper_1909_09577_amd import binding as nm
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, B, Cin, Cout, T, K, stride, dilation, pad)
+CASES = [
+    ("f32", 2, 40, 72, 130, 11, 1, 1, 5),
+    ("f32", 2, 24, 40, 201, 5, 2, 1, 2),
+    ("f32", 1, 24, 80, 100, 32, 1, 1, 16),
+    ("bf16", 2, 64, 96, 133, 11, 1, 1, 5),       # the engine for few tiles
+    ("bf16", 1, 256, 64, 133, 5, 1, 2, 4),       # the same in parts, a dilated filter
+    ("bf16", 20, 128, 512, 1277, 11, 1, 1, 5),   # the unrolled kernel
+    ("bf16", 16, 72, 256, 1277, 7, 1, 1, 3),     # the tap-pair loop, with its absent eighth tap
+    ("bf16", 16, 48, 256, 1277, 5, 1, 1, 2),     # the same with a pad pair
+    ("bf16", 8, 256, 1024, 1277, 1, 1, 1, 0),    # the GEMM kernel
+    ("bf16", 3, 64, 128, 175, 4, 1, 1, 2),       # only the input rows are odd
+    ("bf16", 3, 40, 72, 123, 11, 2, 1, 5),       # both parities of a stride-2 gradient: filters of five and six taps
+    ("bf16", 3, 40, 72, 160, 11, 2, 1, 5),       # the same on 16-byte rows (its gradient only)
+]
+
+
+def _same(got, ref, dtype, what):
+    import torch
+    got, ref = got.double(), ref.double()
+    ok = ref.isfinite()
+    assert torch.equal(got.isfinite(), ok), f"{what}: {int((~got.isfinite()).sum())} not finite, plain kernels {int((~ok).sum())}"
+    rms = ref[ok].square().mean().sqrt()
+    # two results within the gate of the other parity tests, so within twice the gate of each other
+    assert ((got - ref)[ok].abs() / (ref[ok].abs() + rms)).max() <= (2e-2 if dtype == "bf16" else 2e-5), what
+    assert ok.any() and not ok.all(), f"{what}: the case shows nothing"
+
+
+@pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_one_infinite_element(case, masked):
+    import torch
+    dtype, B, Cin, Cout, T, K, stride, dil, pad = case
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    To = orc.out_len(T, K, stride, dil, pad)
+    kw = dict(stride=stride, dilation=dil, pad=pad)
+    if masked:
+        kw["lengths"] = torch.tensor([T - 3 * b for b in range(B)], dtype=torch.int32, device="cuda").clamp_min(T // 2)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def randn(*shape):
+        v = torch.randn(*shape, device="cuda", generator=gen)
+        return torch.where(v == 0, 1, v).to(dt)
+
+    x, w, dy = randn(B, Cin, T), randn(Cout, Cin, K) / (Cin * K) ** 0.5, randn(B, Cout, To)
+    scale = torch.rand(Cout, device="cuda", generator=gen) + 0.5
+
+    def with_inf(t, *at):
+        t = t.clone()
+        t[at] = float("inf")
+        return t
+
+    last = int(kw["lengths"][0]) - 1 if masked else T - 1  # the last valid sample of item 0
+    rows16 = T % 8 == 0 and To % 8 == 0 and dtype == "bf16"
+    for what, xi, wi, gi in [("x start", with_inf(x, 0, 1, 0), w, dy), ("x end", with_inf(x, 0, 1, last), w, dy), ("w", x, with_inf(w, 1, 1, K // 4), dy),
+                             ("dy start", x, w, with_inf(dy, 0, 1, 0)), ("dy end", x, w, with_inf(dy, 0, 1, To - 1))]:
+        def passes(direct):
+            c = dict(kw, force_direct=direct)
+            return (nm.nm_conv1d_block_fwd(xi, wi, scale, None, None, **c), nm.nm_conv1d_bwd_data(gi, wi, T, scale=scale, **c)[0],
+                    nm.nm_conv1d_bwd_weight(xi, gi, K, scale=scale, **c), *nm.nm_conv1d_bwd(xi, gi, wi, scale=scale, **c)[::2])
+        (y, dx, dw, dx2, dw2), (yr, dxr, dwr, _, _) = passes(False), passes(True)
+        assert torch.equal(dx2.isnan(), dx.isnan()) and torch.equal(dw2.isnan(), dw.isnan())
+        in_x, in_w, in_g = what.startswith("x"), what == "w", what.startswith("dy")
+        if not rows16 and (in_x or (in_w and dtype == "f32")):
+            _same(y, yr, dtype, f"y, {what}")
+        if in_g or (in_w and dtype == "f32"):
+            _same(dx, dxr, dtype, f"dx, {what}")
+        if not rows16 and (in_x or in_g):
+            _same(dw, dwr, dtype, f"dw, {what}")
