@@ -24,6 +24,7 @@ NM_OP_FWD, NM_OP_BWD_DATA, NM_OP_BWD_WEIGHT, NM_OP_BWD, NM_OP_BN_FWD, NM_OP_BN_B
 EXPORTS = ("nm_conv1d_out_len", "nm_conv1d_workspace_bytes", "nm_strerror", "nm_conv1d_block_fwd",
            "nm_conv1d_bwd_data", "nm_conv1d_bwd_weight", "nm_conv1d_bwd", "nm_conv1d_block_fwd_masked", "nm_conv1d_bwd_data_masked",
            "nm_conv1d_bwd_weight_masked", "nm_decoder_logsoftmax_fwd", "nm_conv1d_block_fwd_static", "nm_conv1d_time_next_kernel_of", "nm_conv1d_bn_fwd", "nm_conv1d_bn_bwd", "nm_conv1d_bwd_masked", "nm_conv1d_time_next_main_kernel",
+           "nm_conv1d_kernel_name",
            "nm_fp8_row_scales", "nm_fp8_quantize_rows", "nm_conv1d_fp8_supported", "nm_conv1d_fp8_workspace_bytes",
            "nm_conv1d_block_fwd_fp8", "nm_conv1d_bwd_data_fp8", "nm_conv1d_fp8_bwd_data_workspace_bytes",
            "nm_fp8_dgrad_weight_scales", "nm_conv1d_bwd_weight_fp8", "nm_conv1d_fp8_bwd_weight_workspace_bytes",
@@ -51,6 +52,8 @@ def lib() -> ctypes.CDLL:
         L.nm_conv1d_out_len.restype = i
         L.nm_conv1d_workspace_bytes.argtypes = [i] * 9 + [i, u]
         L.nm_conv1d_workspace_bytes.restype = sz
+        L.nm_conv1d_kernel_name.argtypes = [i] * 10 + [u, i, sz, ctypes.c_char_p, sz]
+        L.nm_conv1d_kernel_name.restype = i
         L.nm_strerror.argtypes = [i]
         L.nm_strerror.restype = ctypes.c_char_p
         L.nm_conv1d_block_fwd.argtypes = [i] * 8 + [vp] * 6 + [u, i, vp, sz, vp]
@@ -120,6 +123,19 @@ def nm_conv1d_out_len(T: int, K: int, stride: int = 1, dilation: int = 1, pad: i
 def nm_conv1d_workspace_bytes(op: int, B, Cin, Cout, T, K, stride=1, dilation=1, pad=0, dtype=NM_BF16,
                               flags=0) -> int:
     return int(lib().nm_conv1d_workspace_bytes(op, B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags))
+
+
+def nm_conv1d_kernel_name(op: int, B, Cin, Cout, T, K, stride=1, dilation=1, pad=0, dtype=NM_BF16, flags=0, masked=False,
+                          workspace_bytes=None) -> str:
+    """Name of the main kernel of a pass (workspace_bytes None: of the size asked for)."""
+    dims = (B, Cin, Cout, T, K, stride, dilation, pad)
+    if workspace_bytes is None:
+        workspace_bytes = nm_conv1d_workspace_bytes(NM_OP_FWD if op == NM_OP_BN_FWD else op, *dims, dtype, flags)
+    name = ctypes.create_string_buffer(128)
+    st = lib().nm_conv1d_kernel_name(op, *dims, dtype, flags, 1 if masked else 0, workspace_bytes, name, len(name))
+    if st != NM_OK:
+        raise NmError(st, "nm_conv1d_kernel_name")
+    return name.value.decode()
 
 
 def nm_conv1d_time_next_main_kernel(start_event, stop_event) -> None:

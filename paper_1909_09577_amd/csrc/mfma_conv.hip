@@ -33,6 +33,7 @@
 #include "../../include/nm_conv1d.h"
 #include "nm_common.h"
 
+#include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
@@ -1944,14 +1945,17 @@ double pointwise_waste(const ConvGemmParams &p, int cus)
     return pad * rounds;
 }
 
-hipError_t launch_pointwise(const ConvGemmParams &p, hipStream_t s)
+bool pointwise_big_tile(const ConvGemmParams &p)
 {
     // the 512 x 128 tile does half the LDS and staging work per MFMA and has half as many epilogue rounds per
     // output (measured 1.1 to 1.2 times faster per MFMA issued at 896 <-> 1024 channels); it is taken unless
     // its padding and last-round losses outweigh that
     const int cus = current_device_info().cus;
-    const bool big = pointwise_waste<4, 4>(p, cus) <= 1.12 * pointwise_waste<2, 5>(p, cus);
-    if (p.len_in || p.Tout % 8 != 0)
+    return pointwise_waste<4, 4>(p, cus) <= 1.12 * pointwise_waste<2, 5>(p, cus);
+}
+hipError_t launch_pointwise(const ConvGemmParams &p, bool big, bool len, hipStream_t s)
+{
+    if (len)
         return big ? launch_pointwise_shape<true, 4, 4, 64>(p, s) : launch_pointwise_shape<true, 2, 5, 128>(p, s);
     return big ? launch_pointwise_shape<false, 4, 4, 64>(p, s) : launch_pointwise_shape<false, 2, 5, 128>(p, s);
 }
@@ -2004,80 +2008,102 @@ hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int strid
     return launch_split_t<2, 2>(p, at_once, sp.lds, s);
 }
 
+// Which kernel makes a contraction.
+struct ConvChoice {
+    enum Kind { kFew, kSplit, kPointwise, kGemm } kind;
+    bool big;                                // kPointwise: the 512 x 128 tile
+    int nt, stride, kt;                      // kGemm: the template arguments
+    bool len, stats, any, pad_pair;          // (len: of kPointwise too)
+};
+ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, size_t part_room)
+{
+    ConvChoice c = {};
+    c.any = p.Tout % 8 != 0;
+    // one tap, at most one chunk of reduction channels, nothing to do after the sums: the store-bound kernel
+    if (p.K == 1 && p.R <= kChunk && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout && p.Tout % 8 == 0 && !p.res &&
+        !p.scale && !p.shift && !p.relu && !p.len_in && !p.len_out) {
+        c.kind = ConvChoice::kFew;
+        return c;
+    }
+    if (!p.stats && sp.nt && (sp.nsplit == 1 || split_rounds((unsigned)((p.Tout + sp.nt * 32 - 1) / (sp.nt * 32) * p.B), sp.col_bytes, part_room) <= kSplitRounds)) {
+        c.kind = ConvChoice::kSplit;
+        return c;
+    }
+    // one tap, no padding, wide tiles: the GEMM kernel whose wavefronts share the staged activations
+    // (worth it from two 64-channel row tiles on: a single one would leave three wavefronts idle)
+    if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == row_pitch(p.Tout)) {
+        c.kind = ConvChoice::kPointwise;
+        c.big = pointwise_big_tile(p);
+        c.len = p.len_in || c.any;
+        return c;
+    }
+    c.kind = ConvChoice::kGemm;
+    c.nt = pl.nt;
+    c.stride = pl.stride;
+    c.stats = p.stats != nullptr;  // (the caller has checked that the unrolled kernel serves the call)
+    c.kt = pl.unrolled || c.stats ? p.K : 0;
+    c.len = c.kt > 0 && (c.any || p.len_in || p.len_out) && !c.stats;
+    // (a wavefront has an odd number of pairs where both a chunk's pairs and its chunks are odd)
+    c.pad_pair = c.any && c.kt == 0 && p.Kp / 2 % 2 && p.nch % (2 * kWaves) != 0;
+    return c;
+}
+
+template <bool LEN, bool STATS, bool ANY>
+hipError_t launch_unrolled(int kt, const ConvGemmParams &p, size_t lds, hipStream_t s)
+{
+    switch (kt) {
+    case 11: return launch_t<5, 1, 11, LEN, STATS, ANY>(p, lds, s);
+    case 13: return launch_t<5, 1, 13, LEN, STATS, ANY>(p, lds, s);
+    case 17: return launch_t<5, 1, 17, LEN, STATS, ANY>(p, lds, s);
+    case 21: return launch_t<5, 1, 21, LEN, STATS, ANY>(p, lds, s);
+    case 25: return launch_t<5, 1, 25, LEN, STATS, ANY>(p, lds, s);
+    case 29: return launch_t<5, 1, 29, LEN, STATS, ANY>(p, lds, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+template <bool ANY, bool PAD>
+hipError_t launch_tap_pairs(const ConvChoice &c, const ConvGemmParams &p, size_t lds, hipStream_t s)
+{
+    if (c.nt == 5 && c.stride == 1) return launch_t<5, 1, 0, false, false, ANY, PAD>(p, lds, s);
+    if (c.nt == 2 && c.stride == 1) return launch_t<2, 1, 0, false, false, ANY, PAD>(p, lds, s);
+    if (c.nt == 5 && c.stride == 2) return launch_t<5, 2, 0, false, false, ANY, PAD>(p, lds, s);
+    if (c.nt == 2 && c.stride == 2) return launch_t<2, 2, 0, false, false, ANY, PAD>(p, lds, s);
+    return hipErrorInvalidValue;
+}
+
 // [part, part + part_room): room for the partial sums of the split engine, whose plan is sp
 hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room)
 {
-    // one tap, at most one chunk of reduction channels, nothing to do after the sums: the store-bound kernel
-    if (p.K == 1 && p.R <= kChunk && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout && p.Tout % 8 == 0 && !p.res &&
-        !p.scale && !p.shift && !p.relu && !p.len_in && !p.len_out)
-        return launch_few_channels(p, s);
-    if (!p.stats && sp.nt && (sp.nsplit == 1 || split_rounds((unsigned)((p.Tout + sp.nt * 32 - 1) / (sp.nt * 32) * p.B), sp.col_bytes, part_room) <= kSplitRounds))
-        return launch_split(sp, p, pl.stride, part, part_room, s);
-    // one tap, no padding, wide tiles: the GEMM kernel whose wavefronts share the staged activations
-    // (worth it from two 64-channel row tiles on: a single one would leave three wavefronts idle)
-    if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == row_pitch(p.Tout))
-        return launch_pointwise(p, s);
-    if (p.stats) {  // (the caller has checked stats_on_engine)
-        switch (p.K) {
-        case 11: return launch_t<5, 1, 11, false, true>(p, pl.lds, s);
-        case 13: return launch_t<5, 1, 13, false, true>(p, pl.lds, s);
-        case 21: return launch_t<5, 1, 21, false, true>(p, pl.lds, s);
-        case 25: return launch_t<5, 1, 25, false, true>(p, pl.lds, s);
-        case 29: return launch_t<5, 1, 29, false, true>(p, pl.lds, s);
-        case 17: return launch_t<5, 1, 17, false, true>(p, pl.lds, s);
-        default: return hipErrorInvalidValue;
-        }
+    const ConvChoice c = choose_conv(pl, sp, p, part_room);
+    switch (c.kind) {
+    case ConvChoice::kFew: return launch_few_channels(p, s);
+    case ConvChoice::kSplit: return launch_split(sp, p, pl.stride, part, part_room, s);
+    case ConvChoice::kPointwise: return launch_pointwise(p, c.big, c.len, s);
+    case ConvChoice::kGemm: break;
     }
-    if (pl.unrolled && p.Tout % 8 != 0) {
-        switch (p.K) {
-        case 11: return launch_t<5, 1, 11, true, false, true>(p, pl.lds, s);
-        case 13: return launch_t<5, 1, 13, true, false, true>(p, pl.lds, s);
-        case 21: return launch_t<5, 1, 21, true, false, true>(p, pl.lds, s);
-        case 25: return launch_t<5, 1, 25, true, false, true>(p, pl.lds, s);
-        case 29: return launch_t<5, 1, 29, true, false, true>(p, pl.lds, s);
-        case 17: return launch_t<5, 1, 17, true, false, true>(p, pl.lds, s);
-        default: return hipErrorInvalidValue;
-        }
+    if (c.stats) return launch_unrolled<false, true, false>(c.kt, p, pl.lds, s);
+    if (c.kt > 0)
+        return c.any ? launch_unrolled<true, false, true>(c.kt, p, pl.lds, s)
+                     : c.len ? launch_unrolled<true, false, false>(c.kt, p, pl.lds, s) : launch_unrolled<false, false, false>(c.kt, p, pl.lds, s);
+    if (c.any) return c.pad_pair ? launch_tap_pairs<true, true>(c, p, pl.lds, s) : launch_tap_pairs<true, false>(c, p, pl.lds, s);
+    return launch_tap_pairs<false, false>(c, p, pl.lds, s);
+}
+
+// the kernel's name as a profiler lists it
+void name_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, size_t part_room, char *name, size_t n)
+{
+    const ConvChoice c = choose_conv(pl, sp, p, part_room);
+    auto b = [](bool v) { return v ? "true" : "false"; };
+    switch (c.kind) {
+    case ConvChoice::kFew: snprintf(name, n, "few_channels_gemm_kernel"); break;
+    case ConvChoice::kSplit: snprintf(name, n, "conv_split_kernel<%d, %d> in %d parts", sp.nt, pl.stride, sp.nsplit); break;
+    case ConvChoice::kPointwise:
+        snprintf(name, n, "pointwise_gemm_kernel<%s, %s>", b(c.len), c.big ? "4, 4, 64" : "2, 5, 128");
+        break;
+    case ConvChoice::kGemm:
+        snprintf(name, n, "conv_gemm_kernel<%d, %d, %d, %s, %s, %s, %s>", c.nt, c.stride, c.kt, b(c.len), b(c.stats), b(c.any), b(c.pad_pair));
+        break;
     }
-    if (pl.unrolled && (p.len_in || p.len_out)) {
-        switch (p.K) {
-        case 11: return launch_t<5, 1, 11, true>(p, pl.lds, s);
-        case 13: return launch_t<5, 1, 13, true>(p, pl.lds, s);
-        case 21: return launch_t<5, 1, 21, true>(p, pl.lds, s);
-        case 25: return launch_t<5, 1, 25, true>(p, pl.lds, s);
-        case 29: return launch_t<5, 1, 29, true>(p, pl.lds, s);
-        case 17: return launch_t<5, 1, 17, true>(p, pl.lds, s);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    if (pl.unrolled) {
-        switch (p.K) {
-        case 11: return launch_t<5, 1, 11>(p, pl.lds, s);
-        case 13: return launch_t<5, 1, 13>(p, pl.lds, s);
-        case 21: return launch_t<5, 1, 21>(p, pl.lds, s);
-        case 25: return launch_t<5, 1, 25>(p, pl.lds, s);
-        case 29: return launch_t<5, 1, 29>(p, pl.lds, s);
-        case 17: return launch_t<5, 1, 17>(p, pl.lds, s);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    if (p.Tout % 8 != 0) {
-        auto any = [&](auto pad_pair) {
-            constexpr bool PP = decltype(pad_pair)::value;
-            if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0, false, false, true, PP>(p, pl.lds, s);
-            if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0, false, false, true, PP>(p, pl.lds, s);
-            if (pl.nt == 5 && pl.stride == 2) return launch_t<5, 2, 0, false, false, true, PP>(p, pl.lds, s);
-            if (pl.nt == 2 && pl.stride == 2) return launch_t<2, 2, 0, false, false, true, PP>(p, pl.lds, s);
-            return hipErrorInvalidValue;
-        };
-        // (a wavefront has an odd number of pairs where both a chunk's pairs and its chunks are odd)
-        return p.Kp / 2 % 2 && p.nch % (2 * kWaves) != 0 ? any(std::true_type{}) : any(std::false_type{});
-    }
-    if (pl.nt == 5 && pl.stride == 1) return launch_t<5, 1, 0>(p, pl.lds, s);
-    if (pl.nt == 2 && pl.stride == 1) return launch_t<2, 1, 0>(p, pl.lds, s);
-    if (pl.nt == 5 && pl.stride == 2) return launch_t<5, 2, 0>(p, pl.lds, s);
-    if (pl.nt == 2 && pl.stride == 2) return launch_t<2, 2, 0>(p, pl.lds, s);
-    return hipErrorInvalidValue;
 }
 
 size_t prepack_lds(int K) { return (size_t)kPackRows * pack_m_stride(K) * sizeof(bf16_t); }
@@ -2265,6 +2291,24 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     return launch_plan(pl, fwd_split_plan(g, pl), p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
 }
 
+void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n)
+{
+    if (skinny_fwd_supported(g)) {
+        snprintf(name, n, "decoder_mfma_kernel<true, false>");
+        return;
+    }
+    static float affine;
+    static double some_stats;
+    const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
+    ConvGemmParams p = {};
+    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad);
+    p.len_in = g.len;
+    p.scale = &affine;
+    if (stats && mfma_fwd_stats_parts(g) > 0) p.stats = &some_stats;
+    const size_t least = mfma_fwd_workspace_least(g);
+    name_conv(pl, fwd_split_plan(g, pl), p, ws_bytes > least ? ws_bytes - least : 0, name, n);
+}
+
 // ---- input gradient (stride 1 only; other strides use the plain kernels) ----------------
 // Workspace: packed (flipped, transposed) weights, then dz when it differs from dy.
 namespace {
@@ -2416,6 +2460,24 @@ void fill_dgrad(ConvGemmParams &p, const Plan &pl, const Geom &g, const void *gi
     p.len_out_div = 1;
 }
 }  // namespace
+
+void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name, size_t n)
+{
+    static bf16_t dx;
+    ConvGemmParams p = {};
+    Plan pl;
+    if (g.stride == 2) {
+        const Phases ph = phases_of_stride2(g);
+        pl = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1);
+        fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL);
+        p.len_out = g.len;
+    } else {
+        pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
+        fill_dgrad(p, pl, g, nullptr, nullptr, &dx, accumulate);
+    }
+    const size_t least = mfma_dgrad_workspace_least(g);
+    name_conv(pl, dgrad_split_plan(g, pl), p, ws_bytes > least ? ws_bytes - least : 0, name, n);
+}
 
 // accumulate (stride 1 only): dx = bf16(dx + gradient), one rounding.
 hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,

@@ -24,6 +24,8 @@
 //   dw[co,ci,k] = scale[co] * sum_b sum_t g[b,co,t] * x[b,ci,tau(t,k)].
 #include "nm_common.h"
 
+#include <stdio.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -1506,6 +1508,23 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
     }
     if (e != hipSuccess) return e;
     return launch_wgrad_reduce(g, part, dw, scale, w.S, accumulate, s, &g0, defined);
+}
+
+void name_mfma_wgrad(const Geom &g0, bool relu, size_t ws_bytes, char *name, size_t n)
+{
+    const Geom g = pitched(g0);
+    if (wgrad_k1_supported(g)) {
+        snprintf(name, n, "wgrad_k1_kernel");
+    } else if (fast_ok(g)) {
+        const FastPlan f = make_fast_plan(g);
+        if (f.shared)
+            snprintf(name, n, "wgrad_shared_kernel<%d, %d, %s> in %d parts", f.KTg, g.dil, g.len ? "true" : "false", f.S);
+        else
+            snprintf(name, n, "wgrad_fast_kernel<%d, %d> in %d parts", f.KTg, g.dil, f.S);
+    } else {
+        const WPlan w = make_wplan(g, ws_bytes >= mfma_wgrad_workspace(g0, relu || !rows16(g0), true));
+        snprintf(name, n, "wgrad_kernel<%d> in %d parts", w.KTg, w.S);
+    }
 }
 
 }  // namespace nm

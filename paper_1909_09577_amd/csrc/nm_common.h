@@ -317,6 +317,12 @@ struct DefinedDw {
     bool f32;
     const void *x, *dy, *y;
 };
+// Names, as a profiler lists them, of the kernels that the three passes' launches above would run (tensors 16-byte
+// aligned, a forward pass with an affine; stats: the forward pass of a BatchNorm call).
+void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n);
+void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name, size_t n);
+void name_mfma_wgrad(const Geom &g, bool relu, size_t ws_bytes, char *name, size_t n);
+
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci] (scale NULL: 1), fixed order
 // (own, defined: optional; the call's geometry and tensors)
 hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, const float *scale, int S, bool accumulate,

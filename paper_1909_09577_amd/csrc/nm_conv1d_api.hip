@@ -5,6 +5,8 @@
 #include "../../include/nm_conv1d.h"
 #include "nm_common.h"
 
+#include <stdio.h>
+
 #include <mutex>
 
 using namespace nm;
@@ -208,6 +210,42 @@ int check_workspace(const void *ws, size_t have, size_t need)
 
 int dev(hipError_t e) { return e == hipSuccess ? NM_OK : NM_ERR_DEVICE; }
 
+// Which kernels serve one pass, and the workspace they use.
+struct Route {
+    bool mfma, f32;
+    size_t need;     // bytes of workspace in use
+    size_t part_at;  // float32 weight gradient: where the partial sums lie (behind the masked gradient)
+    int status;      // NM_ERR_WORKSPACE: the workspace is too small for all of them
+};
+// aligned: the tensors and the way dx is accumulated allow the matrix-core kernels
+Route route_pass(int op, const Geom &g, int dtype, unsigned flags, bool aligned, bool dzneeded, const void *ws, size_t have)
+{
+    Route r = {};
+    r.mfma = use_mfma(op, g, dtype, flags) && aligned && masked_on_mfma(g, op);
+    auto room = [&](bool least) {
+        // (a weight gradient's copy of x lies behind room for g whether g is formed or not)
+        const bool dz = op == NM_OP_FWD || dzneeded || (op == NM_OP_BWD_WEIGHT && r.mfma && !rows16(g));
+        return workspace_for(op, g, dtype, r.mfma, dz, least);
+    };
+    r.need = room(false);
+    if (r.mfma && have < r.need) r.need = room(true);
+    const bool plain_too = !rows16(g) || (op == NM_OP_BWD_DATA && g.stride == 2);
+    if (r.mfma && plain_too && check_workspace(ws, have, r.need) != NM_OK) {
+        r.mfma = false;  // no room for the copies
+        r.need = room(false);
+    }
+    r.part_at = r.need;
+    const bool supported = op == NM_OP_FWD ? f32_fwd_supported(g) : op == NM_OP_BWD_DATA ? f32_dgrad_supported(g) : f32_wgrad_supported(g);
+    r.f32 = use_f32(supported, dtype, flags);
+    if (r.f32 && op == NM_OP_BWD_WEIGHT) {
+        r.f32 = check_workspace(ws, have, r.need + f32_wgrad_part_bytes(g)) == NM_OK;
+        if (r.f32) r.need += f32_wgrad_part_bytes(g);
+    }
+    r.status = check_workspace(ws, have, r.need);
+    return r;
+}
+bool accumulates_on_mfma(const Geom &g, unsigned flags) { return !((flags & NM_ACCUM_DX) && (g.stride != 1 || g.len)); }
+
 // Consumes the armed event pair when an entry point returns without launching its main kernel.
 struct DisarmOnExit {
     ~DisarmOnExit()
@@ -265,6 +303,29 @@ int nm_conv1d_time_next_kernel_of(void *start_event, void *stop_event, int op)
     return NM_OK;
 }
 
+int nm_conv1d_kernel_name(int op, int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, int dtype,
+                          unsigned flags, int masked, size_t workspace_bytes, char *name, size_t name_bytes)
+{
+    static const int some_length = 0;
+    const bool bn = op == NM_OP_BN_FWD;
+    if (bn) op = NM_OP_FWD;
+    if ((op != NM_OP_FWD && op != NM_OP_BWD_DATA && op != NM_OP_BWD_WEIGHT) || !name || name_bytes == 0) return NM_ERR_BAD_ARG;
+    Geom g;
+    const int st = check_geometry(B, Cin, Cout, T, K, stride, dilation, pad, dtype, flags, kAllFlags, &g);
+    if (st != NM_OK) return st;
+    g.len = masked ? &some_length : nullptr;
+    const void *ws = (const void *)(uintptr_t)(workspace_bytes ? kWsAlign : 0);
+    const Route r = route_pass(op, g, dtype, flags, op != NM_OP_BWD_DATA || accumulates_on_mfma(g, flags), true, ws, workspace_bytes);
+    if (r.status != NM_OK) return r.status;
+    const char *pass = op == NM_OP_FWD ? "fwd" : op == NM_OP_BWD_DATA ? "dgrad" : "wgrad";
+    if (r.mfma && op == NM_OP_FWD) name_mfma_fwd(g, bn, workspace_bytes, name, name_bytes);
+    else if (r.mfma && op == NM_OP_BWD_DATA) name_mfma_dgrad(g, (flags & NM_ACCUM_DX) != 0, workspace_bytes, name, name_bytes);
+    else if (r.mfma) name_mfma_wgrad(g, (flags & NM_RELU) != 0, workspace_bytes, name, name_bytes);
+    else if (r.f32) snprintf(name, name_bytes, "%s", op == NM_OP_BWD_WEIGHT ? "f32_wgrad_kernel" : "f32_conv_kernel");
+    else snprintf(name, name_bytes, "direct_%s_kernel", pass);
+    return NM_OK;
+}
+
 const char *nm_strerror(int status)
 {
     switch (status) {
@@ -298,27 +359,19 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
     if (overlap(y, ny, x, (size_t)g.B * g.Cin * g.T * e) || overlap(y, ny, w, (size_t)g.Cout * g.Cin * g.K * e) ||
         overlap(y, ny, residual, ny))
         return NM_ERR_BAD_ARG;
-    bool mfma = use_mfma(NM_OP_FWD, g, dtype, flags) && aligned16(x) && aligned16(y) && aligned16(residual) &&
-                masked_on_mfma(g);
-    size_t need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
-    if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_FWD, g, dtype, mfma, true, true);
-    if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
-        mfma = false;  // no room for the copies
-        need = workspace_for(NM_OP_FWD, g, dtype, mfma, true);
-    }
-    st = check_workspace(workspace, workspace_bytes, need);
-    if (st != NM_OK) return st;
-    if (overlap(y, ny, workspace, need)) return NM_ERR_BAD_ARG;
+    const Route r = route_pass(NM_OP_FWD, g, dtype, flags, aligned16(x) && aligned16(y) && aligned16(residual), true, workspace, workspace_bytes);
+    if (r.status != NM_OK) return r.status;
+    if (overlap(y, ny, workspace, r.need)) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     const bool relu = (flags & NM_RELU) != 0;
     t_current_op = NM_OP_FWD;
-    if (mfma) {
+    if (r.mfma) {
         const int parts = (stats && stats_parts) ? mfma_fwd_stats_parts(g) : 0;
         const hipError_t err = launch_mfma_fwd(g, x, w, scale, shift, residual, y, relu, workspace, workspace_bytes, s, parts > 0 ? stats : nullptr);
         if (err == hipSuccess && parts > 0) *stats_parts = parts;
         return dev(err);
     }
-    if (use_f32(f32_fwd_supported(g), dtype, flags))
+    if (r.f32)
         return dev(launch_f32_fwd(g, (const float *)x, (const float *)w, scale, shift, (const float *)residual, (float *)y, relu, s));
     MainKernelTimer timer(s);
     return dev(launch_direct_fwd(g, dtype == NM_BF16, x, w, scale, shift, residual, y, relu, s));
@@ -345,22 +398,17 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
         return NM_ERR_BAD_ARG;
     const bool accum = (flags & NM_ACCUM_DX) != 0;
     // accumulation into dx: the matrix-core engine adds the old value in its epilogue (stride 1, no lengths)
-    bool mfma = use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && aligned16(dy) && aligned16(dx) &&
-                (!relu || aligned16(y)) && masked_on_mfma(g) && !(accum && (g.stride != 1 || g.len));
     const bool dzneeded = needs_dz(flags, scale);
-    size_t need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
-    if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded, true);
-    if (mfma && (!rows16(g) || g.stride == 2) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
-        mfma = false;  // no room for the copies
-        need = workspace_for(NM_OP_BWD_DATA, g, dtype, mfma, dzneeded);
-    }
-    st = check_workspace(workspace, workspace_bytes, need);
-    if (st != NM_OK) return st;
+    const Route r = route_pass(NM_OP_BWD_DATA, g, dtype, flags,
+                               aligned16(dy) && aligned16(dx) && (!relu || aligned16(y)) && accumulates_on_mfma(g, flags), dzneeded,
+                               workspace, workspace_bytes);
+    if (r.status != NM_OK) return r.status;
+    const size_t need = r.need;
     if (overlap(dx, ndx, workspace, need) || overlap(dres, ndy, workspace, need)) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     t_current_op = NM_OP_BWD_DATA;
-    if (mfma) return dev(launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, accum, workspace, workspace_bytes, s));
-    if (use_f32(f32_dgrad_supported(g), dtype, flags)) {
+    if (r.mfma) return dev(launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, accum, workspace, workspace_bytes, s));
+    if (r.f32) {
         const void *gy = dy;
         hipError_t err = f32_mask_pass(g, dy, y, relu, workspace, dres, &gy, s);
         if (err != hipSuccess) return NM_ERR_DEVICE;
@@ -395,30 +443,15 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
     const size_t ndy = (size_t)g.B * g.Cout * g.To * e, ndw = (size_t)g.Cout * g.Cin * g.K * sizeof(float);
     if (overlap(dw, ndw, dy, ndy) || overlap(dw, ndw, y, ndy) || overlap(dw, ndw, x, (size_t)g.B * g.Cin * g.T * e))
         return NM_ERR_BAD_ARG;
-    bool mfma = use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && aligned16(x) && aligned16(dy) &&
-                (!relu || aligned16(y)) && masked_on_mfma(g, NM_OP_BWD_WEIGHT);
-    const bool dzneeded = needs_dz(flags, scale);
-    // (with copies x lies behind room for g whether g is formed or not)
-    size_t need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded || (mfma && !rows16(g)));
-    if (mfma && workspace_bytes < need) need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded || !rows16(g), true);
-    if (mfma && !rows16(g) && check_workspace(workspace, workspace_bytes, need) != NM_OK) {
-        mfma = false;  // no room for the copies
-        need = workspace_for(NM_OP_BWD_WEIGHT, g, dtype, mfma, dzneeded);
-    }
-    // float32: the partial sums follow the masked gradient
-    const size_t part_at = need;
-    bool f32 = use_f32(f32_wgrad_supported(g), dtype, flags);
-    if (f32) {
-        f32 = check_workspace(workspace, workspace_bytes, need + f32_wgrad_part_bytes(g)) == NM_OK;
-        if (f32) need += f32_wgrad_part_bytes(g);
-    }
-    st = check_workspace(workspace, workspace_bytes, need);
-    if (st != NM_OK) return st;
+    const Route r = route_pass(NM_OP_BWD_WEIGHT, g, dtype, flags, aligned16(x) && aligned16(dy) && (!relu || aligned16(y)),
+                               needs_dz(flags, scale), workspace, workspace_bytes);
+    if (r.status != NM_OK) return r.status;
+    const size_t need = r.need;
     if (overlap(dw, ndw, workspace, need)) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     const bool accum = (flags & NM_ACCUM_DW) != 0;
     t_current_op = NM_OP_BWD_WEIGHT;
-    if (mfma) return dev(launch_mfma_wgrad(g, x, dy, y, scale, dw, relu, accum, workspace, workspace_bytes, s));
+    if (r.mfma) return dev(launch_mfma_wgrad(g, x, dy, y, scale, dw, relu, accum, workspace, workspace_bytes, s));
     const bool bf = dtype == NM_BF16;
     const void *dz = dy;
     if (relu) {  // the kernel contracts dy*[y>0]; scale multiplies its float32 sums
@@ -426,8 +459,8 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
         if (err != hipSuccess) return NM_ERR_DEVICE;
         dz = workspace;
     }
-    if (f32)
-        return dev(launch_f32_wgrad(g, (const float *)x, (const float *)dz, scale, dw, accum, (unsigned char *)workspace + part_at, s));
+    if (r.f32)
+        return dev(launch_f32_wgrad(g, (const float *)x, (const float *)dz, scale, dw, accum, (unsigned char *)workspace + r.part_at, s));
     MainKernelTimer timer(s);
     return dev(launch_direct_wgrad(g, bf, x, dz, scale, dw, accum, s));
 }

@@ -1,0 +1,51 @@
+"""Which kernel a call runs on (host only): the layers of the encoder, calls of few tiles, rows of any length, float32."""
+import pytest
+
+from paper_1909_09577_amd import binding as nm
+from paper_1909_09577_amd import inputs as syn
+
+FWD, DGRAD, WGRAD, BN = nm.NM_OP_FWD, nm.NM_OP_BWD_DATA, nm.NM_OP_BWD_WEIGHT, nm.NM_OP_BN_FWD
+
+
+@pytest.mark.parametrize("cfg", [syn.JASPER_B1, syn.JASPER_B3, syn.EPILOG_A], ids=lambda c: c.name)
+def test_full_size_layers_run_on_the_unrolled_kernels(cfg):
+    for op in (FWD, DGRAD):
+        assert nm.nm_conv1d_kernel_name(op, *cfg.dims()) == f"conv_gemm_kernel<5, 1, {cfg.K}, false, false, false, false>"
+        assert nm.nm_conv1d_kernel_name(op, *cfg.dims(), masked=True) == f"conv_gemm_kernel<5, 1, {cfg.K}, true, false, false, false>"
+    assert nm.nm_conv1d_kernel_name(BN, *cfg.dims()) == f"conv_gemm_kernel<5, 1, {cfg.K}, false, true, false, false>"
+    assert nm.nm_conv1d_kernel_name(WGRAD, *cfg.dims()).startswith("wgrad_shared_kernel<")
+    assert nm.nm_conv1d_kernel_name(FWD, *cfg.dims(), dtype=nm.NM_F32) == "f32_conv_kernel"
+    assert nm.nm_conv1d_kernel_name(FWD, *cfg.dims(), flags=nm.NM_FORCE_DIRECT) == "direct_fwd_kernel"
+
+
+def test_the_workspace_has_a_say():
+    few = (1, 768, 768, 600, 25, 1, 1, 12)
+    assert nm.nm_conv1d_kernel_name(FWD, *few).startswith("conv_split_kernel<")
+    full = nm.nm_conv1d_workspace_bytes(FWD, *few)
+    # from a quarter of the room for partial sums on, the same kernel in rounds; without room, the other engine
+    least = -(-768 // 64) * (768 // 32) * 26 * 256 * 16 + 512 * 16
+    assert nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least + (full - least) // 2).startswith("conv_split_kernel<")
+    assert nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least) == "conv_gemm_kernel<5, 1, 25, false, false, false, false>"
+    with pytest.raises(nm.NmError) as e:
+        nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least - 1)
+    assert e.value.status == nm.NM_ERR_WORKSPACE
+    odd = (16, 384, 384, 777, 13, 1, 1, 6)
+    for op, plain in ((FWD, "direct_fwd_kernel"), (DGRAD, "direct_dgrad_kernel"), (WGRAD, "direct_wgrad_kernel")):
+        assert not nm.nm_conv1d_kernel_name(op, *odd).startswith("direct")
+        room = 0 if op == FWD else (2 * 16 * 384 * 777 + 255) // 256 * 256
+        assert nm.nm_conv1d_kernel_name(op, *odd, workspace_bytes=room) == plain
+    f32 = (4, 256, 256, 400, 11, 1, 1, 5)
+    assert nm.nm_conv1d_kernel_name(WGRAD, *f32, dtype=nm.NM_F32) == "f32_wgrad_kernel"
+    assert nm.nm_conv1d_kernel_name(WGRAD, *f32, dtype=nm.NM_F32, workspace_bytes=4 * 4 * 256 * 400) == "direct_wgrad_kernel"
+
+
+def test_arguments_are_checked():
+    import ctypes
+    L = nm.lib()
+    dims = (2, 64, 64, 64, 3, 1, 1, 1)
+    name = ctypes.create_string_buffer(8)
+    assert L.nm_conv1d_kernel_name(FWD, *dims, 0, 0, 0, 1 << 20, None, 8) == nm.NM_ERR_BAD_ARG
+    assert L.nm_conv1d_kernel_name(FWD, *dims, 0, 0, 0, 1 << 20, name, 0) == nm.NM_ERR_BAD_ARG
+    assert L.nm_conv1d_kernel_name(nm.NM_OP_BWD, *dims, 0, 0, 0, 1 << 20, name, 8) == nm.NM_ERR_BAD_ARG
+    assert L.nm_conv1d_kernel_name(FWD, *dims[:4], 0, 1, 1, 1, 0, 0, 0, 1 << 20, name, 8) == nm.NM_ERR_BAD_ARG
+    assert L.nm_conv1d_kernel_name(FWD, *dims, 0, 0, 0, 1 << 20, name, 8) == nm.NM_OK and len(name.value) == 7
