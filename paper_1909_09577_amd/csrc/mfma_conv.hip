@@ -1459,11 +1459,19 @@ constexpr int kPackRows = 16;
 // elements between consecutive channels m of the LDS tile: 32*K plus one dword of padding, which
 // makes the stride an odd number of dwords so that lanes with different m hit different banks
 __host__ __device__ constexpr int pack_m_stride(int K) { return kChunk * K + 2; }
-template <bool FLIP>
+// The two parities' filters of a stride-2 input gradient, as one filter with twice the output rows (see there).
+struct Phases {
+    int K, padL;            // taps and left padding of the joint contraction
+    int kp[2], Kr[2], off[2];  // parity r: taps kp, kp+2, ... (Kr of them) lie at off .. of its filter
+    int U, Up;              // outputs per parity, row pitch
+    bool ok;
+};
+// PHASES: M = 2*Cin rows (parity, ci) of taps cut out of w, which is [R][Cin][ld] here (FLIP).
+template <bool FLIP, bool PHASES = false>
 __device__ __forceinline__ void prepack_block(unsigned blk, unsigned char *smem, const bf16_t *__restrict__ w,
                                               u32x4 *__restrict__ wp, int M, int R, int K, int nch,
                                               int ld /* row length of w */, size_t zero_off, int vec /* 16-byte aligned runs */,
-                                              const float *__restrict__ rscale = nullptr)
+                                              const float *__restrict__ rscale = nullptr, const Phases &ph = Phases{})
 {
     bf16_t *tile = reinterpret_cast<bf16_t *>(smem);  // [16 m][32 r][K] as m*ms + r*K + k
     const int ms = pack_m_stride(K);
@@ -1496,7 +1504,24 @@ __device__ __forceinline__ void prepack_block(unsigned blk, unsigned char *smem,
             tile[row * ms + o] = v;
         }
     };
-    if (vec) {
+    if constexpr (PHASES) {
+        const int Cin = M / 2;
+        for (int o0 = threadIdx.x; o0 < nrows * run; o0 += 256 * 4) {
+            bf16_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int o = o0 + u * 256, row = o / run, m = m0 + (o - row * run) / K, k = (o - row * run) % K;
+                const int r = m >= Cin ? 1 : 0, tap = k - ph.off[r];
+                const bool ok = o < nrows * run && row_ok(row) && m < M && tap >= 0 && tap < ph.Kr[r];
+                v[u] = ok ? w[((size_t)(r0 + row) * Cin + m - r * Cin) * ld + ph.kp[r] + 2 * tap] : (bf16_t)0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int o = o0 + u * 256, row = o / run;
+                if (o < nrows * run) put(row, o - row * run, v[u], row_factor(row));
+            }
+        }
+    } else if (vec) {
         const int vpr = run / 8, nvec = nrows * vpr;
         for (int v0 = threadIdx.x; v0 < nvec; v0 += 256 * 4) {
             u32x4 d[4];
@@ -1555,6 +1580,15 @@ __global__ __launch_bounds__(256) void prepack_kernel(const bf16_t *__restrict__
     prepack_block<FLIP>(blockIdx.x, smem, w, wp, M, R, K, nch, ld, zero_off, vec, rscale);
 }
 
+// the parities' filters of w [R][M/2][Kw]
+__global__ __launch_bounds__(256) void prepack_phases_kernel(const bf16_t *__restrict__ w, u32x4 *__restrict__ wp, int M, int R,
+                                                             int Kw, int nch, size_t zero_off, const float *__restrict__ rscale,
+                                                             const Phases ph)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    prepack_block<true, true>(blockIdx.x, smem, w, wp, M, R, ph.K, nch, Kw, zero_off, 0, rscale, ph);
+}
+
 // Everything the input-gradient engine needs, in one launch: the first npack blocks pack the
 // flipped weights times the affine factor of their output channel (a latency-bound job), the others
 // run the elementwise mask pass g = dy*[y>0] (bandwidth bound), so the two overlap instead of
@@ -1601,31 +1635,9 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(unsigned npack, const 
 // ---- stride-2 input gradient --------------------------------------------------------------------
 // dx[ci][2u + r] only receives the taps k with 2u + r + pad - k even, so each parity r of the sample is a stride-1
 // correlation of g with every second tap.  The two are one contraction with 2*Cin output rows (parity, ci): their
-// filters are cut out side by side, aligned to the same window with zero taps where they differ, and
-// interleave_phases_kernel merges the rows.  64 <- 256 channels, K=11, B=32, T=1600: one contraction over shared windows
+// filters are cut out of w while they are packed (prepack_block), side by side and aligned to the same window with zero taps
+// where they differ, and interleave_phases_kernel merges the rows.  64 <- 256 channels, K=11, B=32, T=1600: one contraction over shared windows
 // in place of one per parity.
-struct Phases {
-    int K, padL;            // taps and left padding of the joint contraction
-    int kp[2], Kr[2], off[2];  // parity r: taps kp, kp+2, ... (Kr of them) lie at off .. of its filter
-    int U, Up;              // outputs per parity, row pitch
-    bool ok;
-};
-__global__ __launch_bounds__(256) void phase_filters_kernel(const bf16_t *__restrict__ w, bf16_t *__restrict__ wsub, unsigned rows,
-                                                            int Cin, int K, const Phases ph)
-{
-    const unsigned i = blockIdx.x * 256 + threadIdx.x;  // (co, ci)
-    if (i >= rows) return;
-    const unsigned co = i / (unsigned)Cin, ci = i - co * (unsigned)Cin;
-    const bf16_t *src = w + (size_t)i * K;
-    for (int r = 0; r < 2; ++r) {
-        bf16_t *dst = wsub + ((size_t)(2 * co + r) * Cin + ci) * ph.K;
-        for (int t = 0; t < ph.K; ++t) {
-            const int k = t - ph.off[r];
-            dst[t] = k >= 0 && k < ph.Kr[r] ? src[ph.kp[r] + 2 * k] : (bf16_t)0;
-        }
-    }
-}
-
 // dx[b][ci][2u + r] = a[b][r][ci][u], zero from a sample's length on; eight samples per thread, rows of any length.
 // A NaN may come from a zero tap times an infinite gradient: it is made again from the products the definition has (an
 // infinite gradient would else leave NaNs in samples that no tap connects to it).
@@ -2334,10 +2346,9 @@ Phases phases_of_stride2(const Geom &g)
             (size_t)g.B * 2 * g.Cin * ph.Up * sizeof(bf16_t) <= kMaxInput;
     return ph;
 }
-// the parities' outputs; until they are written, their filters
-size_t phase_bytes(const Geom &g, const Phases &ph)
+size_t phase_bytes(const Geom &g, const Phases &ph)  // the parities' outputs
 {
-    return align_up(std::max((size_t)g.B * 2 * g.Cin * ph.Up, (size_t)g.Cout * 2 * g.Cin * ph.K) * sizeof(bf16_t), 256);
+    return align_up((size_t)g.B * 2 * g.Cin * ph.Up * sizeof(bf16_t), 256);
 }
 size_t dz_bytes_of(const Geom &g) { return align_up((size_t)g.B * g.Cout * row_pitch(g.To) * sizeof(bf16_t), 256); }
 }  // namespace
@@ -2410,7 +2421,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
     cur += dz_bytes_of(g);
     void *packed = cur;
     cur += packed_bytes(2 * g.Cin, g.Cout, ph.K);
-    bf16_t *phase_out = (bf16_t *)cur, *wsub = phase_out;
+    bf16_t *phase_out = (bf16_t *)cur;
     const void *gin = dy;
     hipError_t e;
     if (g.To % 8 == 0) {
@@ -2427,9 +2438,13 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
     }
     if (e != hipSuccess) return e;
     if (g_used) *g_used = gin;
-    const unsigned rows = (unsigned)g.Cout * (unsigned)g.Cin;
-    hipLaunchKernelGGL(phase_filters_kernel, dim3((rows + 255) / 256), dim3(256), 0, s, (const bf16_t *)w, wsub, rows, g.Cin, g.K, ph);
-    e = run_prepack(wsub, packed, 2 * g.Cin, g.Cout, ph.K, true, scale, s);
+    const PackGeom q = pack_geom(w, 2 * g.Cin, g.Cout, ph.K, true);
+    static LdsOptIn opt_in;
+    e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(prepack_phases_kernel), kMaxLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(prepack_phases_kernel, dim3(q.blocks), dim3(256), q.lds, s, (const bf16_t *)w, (u32x4 *)packed, 2 * g.Cin, g.Cout,
+                       g.K, q.nch, q.zero_off, scale, ph);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     const Plan pl = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1);
     ConvGemmParams p = {};

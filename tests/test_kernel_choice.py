@@ -49,3 +49,24 @@ def test_arguments_are_checked():
     assert L.nm_conv1d_kernel_name(nm.NM_OP_BWD, *dims, 0, 0, 0, 1 << 20, name, 8) == nm.NM_ERR_BAD_ARG
     assert L.nm_conv1d_kernel_name(FWD, *dims[:4], 0, 1, 1, 1, 0, 0, 0, 1 << 20, name, 8) == nm.NM_ERR_BAD_ARG
     assert L.nm_conv1d_kernel_name(FWD, *dims, 0, 0, 0, 1 << 20, name, 8) == nm.NM_OK and len(name.value) == 7
+
+
+def _align(n):
+    return (n + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("dims", [(32, 64, 256, 1600, 11, 5), (1, 64, 256, 320, 11, 5), (2, 384, 256, 112, 25, 12), (2, 64, 1024, 32, 3, 1),
+                                  (8, 256, 128, 160, 12, 5), (4, 128, 64, 96, 2, 0)], ids=lambda d: "x".join(map(str, d)))
+def test_stride2_gradient_in_the_workspace_of_one_contraction_per_parity(dims):
+    """A workspace of the size that g, each parity's taps, its packed filter and its outputs take (what the call asked for
+    while it made the parities one after the other) keeps the call on the matrix cores."""
+    B, Cin, Cout, T, K, pad = dims
+    To = nm.nm_conv1d_out_len(T, K, 2, 1, pad)
+    assert T % 16 == 0 and To % 8 == 0
+    room = _align(2 * B * Cout * To)
+    for r in (0, 1):
+        taps = (K - ((r + pad) & 1) + 1) // 2
+        packed = _align((-(-Cin // 64) * -(-Cout // 32) * (taps + taps % 2) * 256 + 512) * 16)
+        room += _align(2 * Cout * Cin * taps) + packed + _align(B * Cin * T)
+    name = nm.nm_conv1d_kernel_name(DGRAD, B, Cin, Cout, T, K, 2, 1, pad, flags=nm.NM_RELU, workspace_bytes=room)
+    assert not name.startswith("direct"), name
