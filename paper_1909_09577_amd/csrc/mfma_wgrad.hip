@@ -1031,7 +1031,8 @@ __device__ __forceinline__ float defined_dw(const Geom &g, const DefinedDw &q, i
 }
 
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci]; one block per (co, 64 ci).
-// MEND: the instance that makes NaN sums again from the tensors of DefinedDw.
+// MEND: the instance that makes NaN sums again from the tensors of DefinedDw.  Eight parts are requested at a time: one
+// after the other, 16 parts of 64 -> 256 channels, K=11, took 15 us.
 template <bool MEND>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                            const float *__restrict__ scale, int S, int K, int Cout,
@@ -1048,6 +1049,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
         float s = 0.f;
         if (ci < Cin) {
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
+#pragma unroll 8
             for (int sp = 0; sp < S; ++sp) s += src[(size_t)sp * K * plane];
             if (MEND && __builtin_expect(s != s, 0)) s = defined_dw(own, defined, co, ci, k);
         }
@@ -1083,6 +1085,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restr
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
         if (ci < Cin) {
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
+#pragma unroll 8
             for (int sp = 0; sp < S; ++sp) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)sp * K * plane);
             if constexpr (MEND) {
                 const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);  // a NaN if one of them is
@@ -1126,9 +1129,11 @@ struct WPlan {
 };
 
 // Needs 16-byte aligned rows of both operands (T % 8 == 0 and To % 8 == 0).
-// wide: a workspace with room for more parts, so that few tiles fill the chip too (64 -> 256 channels, K=11, stride 2, B=32:
-// 16 tiles; with 8 parts half of the CUs idle, kernel and sum of the
-// parts 51 + 8.5 us, with 16 33 + 15)
+// wide: a workspace with room for more parts, so that few tiles fill the chip too.  How many is weighed in microseconds: a
+// wavefront takes 3.6 per unit (80 steps, six taps); the sum of the parts is bound by latency, 0.9 per eight parts and four
+// taps of a thread, and by the parts' bytes.  Measured, kernel and sum: 64 -> 256 channels, K=11, stride 2, B=32, T=1600
+// (8 parts leave half of the CUs idle) 8 parts 60.9 us, 16 parts 44.4; 64 -> 32 channels, K=13, dilation 3, B=10,
+// T=560 8 parts 19.8, 17 parts 25.3; 64 -> 16 channels, K=11, B=31, T=304 8 parts 25.6, 20 parts 22.7.
 WPlan make_wplan(const Geom &g, bool wide = true)
 {
     WPlan w = {};
@@ -1169,8 +1174,20 @@ WPlan make_wplan(const Geom &g, bool wide = true)
     long S = (512 + ntiles - 1) / ntiles;
     if (S > 8) S = 8;
     if (S > units / kWaves) S = units / kWaves;
-    if (wide && ntiles * S < kPlanCUs) S = std::min(std::min(kPlanCUs / ntiles, 32L), units / kWaves);
     if (S < 1) S = 1;
+    if (wide) {
+        const long most = std::min(std::min(kPlanCUs / ntiles, 32L), units / kWaves);
+        double best = 1e30;
+        for (long parts = S; parts <= std::max(S, most); ++parts) {
+            const double mb = 4e-6 * parts * g.K * g.Cout * (double)g.Cin;
+            const double cost = 3.6 * w.TCH / 80 * KTg / 6 * units / (double)(parts * kWaves) +
+                                0.9 * ((g.K + 3) / 4) * ((parts + 7) / 8) + 0.4 * mb;
+            if (cost < best) {
+                best = cost;
+                S = parts;
+            }
+        }
+    }
     w.S = (int)S;
     return w;
 }

@@ -70,3 +70,10 @@ def test_stride2_gradient_in_the_workspace_of_one_contraction_per_parity(dims):
         room += _align(2 * Cout * Cin * taps) + packed + _align(B * Cin * T)
     name = nm.nm_conv1d_kernel_name(DGRAD, B, Cin, Cout, T, K, 2, 1, pad, flags=nm.NM_RELU, workspace_bytes=room)
     assert not name.startswith("direct"), name
+
+
+def test_parts_of_a_weight_gradient_where_their_sum_costs_more_than_they_save():
+    """Few rows to add the parts up, few units to share out: eight parts are enough; the strided first layer takes more."""
+    assert nm.nm_conv1d_kernel_name(WGRAD, 10, 64, 32, 560, 13, 1, 3, 18) == "wgrad_kernel<5> in 8 parts"
+    assert nm.nm_conv1d_kernel_name(WGRAD, 6, 4, 256, 408, 13, 1, 3, 18) == "wgrad_kernel<5> in 8 parts"
+    assert nm.nm_conv1d_kernel_name(WGRAD, 32, 64, 256, 1600, 11, 2, 1, 5) == "wgrad_kernel<6> in 16 parts"
