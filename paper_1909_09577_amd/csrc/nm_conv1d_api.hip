@@ -131,9 +131,36 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb)
 
 size_t elt(int dtype) { return dtype == NM_BF16 ? 2 : 4; }
 
+// Calls so small that a thread of the plain kernel is through before the two or three launches of the matrix-core kernels are:
+// its time is that of its chain of products, one after the other (0.3 to 0.4 us each, 0.08 in the weight gradient), as long
+// as there are not too many of them in all.  Only float32 weight gradients and rows that are no multiple of eight long take
+// this way (the others have run on the matrix-core kernels from the start).  Measured, plain / matrix cores: forward, chain
+// Cin*K, 8 6.7 / 10.2 us, 22 10.8 / 8.3, K=1 in the GEMM kernel 24 13.4 / 24.8; input gradient, chain Cout*K, 6 8.0 / 11.4,
+// 12 10.8 / 9.8, K=11 11 9.5 / 12.4, 22 13.1 / 12.0, stride 2 22 9.1 / 15.0; weight gradient, chain B*To, K=11 44 10.6 / 21.2,
+// 90 13.7 / 21.9, K=1 82 15.6 / 12.3; float32 K=11 44 8.9 / 18.4, K=1 66 14.4 / 12.5.
+bool tiny(int op, const Geom &g, int dtype)
+{
+    const bool wgrad = op == NM_OP_BWD_WEIGHT;
+    if (dtype == NM_F32 ? !wgrad : rows16(g)) return false;
+    const double products = (double)g.B * g.Cout * g.To * g.Cin * g.K;
+    if (products > 1.2e7) return false;
+    if (wgrad) {
+        const double plain = 7.0 + 0.08 * g.B * g.To + 0.6e-6 * products;
+        const bool gemm = g.K == 1 && g.stride == 1 && g.Cin >= 64 && g.Cout >= 64;
+        const double base = dtype == NM_F32 ? 10.5 : gemm ? 17.0 : g.stride == 1 ? 13.0 : 12.0;
+        return plain < base + 0.7 * (g.K < 14 ? g.K : 14);
+    }
+    const long chain = (long)(op == NM_OP_FWD ? g.Cin : g.Cout) * g.K;
+    const int rows = op == NM_OP_FWD ? g.Cout : g.Cin;
+    if (g.K == 1 && g.stride == 1 && g.pad == 0 && rows > 64 && g.To > 64) return chain <= (op == NM_OP_FWD ? 40 : 24);  // the GEMM kernel
+    if (op == NM_OP_FWD) return chain <= 16;
+    return chain <= (g.stride == 2 ? 22 : g.K == 1 ? 12 : g.K >= 11 ? 16 : 10);
+}
+
 bool use_mfma(int op, const Geom &g, int dtype, unsigned flags)
 {
     if (dtype != NM_BF16 || (flags & NM_FORCE_DIRECT)) return false;
+    if (tiny(op, g, dtype)) return false;
     switch (op) {
     case NM_OP_FWD: return mfma_fwd_supported(g);
     case NM_OP_BWD_DATA: return mfma_dgrad_supported(g);
@@ -147,7 +174,11 @@ bool use_mfma(int op, const Geom &g, int dtype, unsigned flags)
 bool needs_dz(unsigned flags, const float *scale) { return (flags & NM_RELU) || scale != nullptr; }
 
 // float32 storage on the matrix cores (no copies, any alignment)
-bool use_f32(bool supported, int dtype, unsigned flags) { return dtype == NM_F32 && !(flags & NM_FORCE_DIRECT) && supported; }
+bool use_f32(int op, const Geom &g, int dtype, unsigned flags)
+{
+    if (dtype != NM_F32 || (flags & NM_FORCE_DIRECT) || tiny(op, g, dtype)) return false;
+    return op == NM_OP_FWD ? f32_fwd_supported(g) : op == NM_OP_BWD_DATA ? f32_dgrad_supported(g) : f32_wgrad_supported(g);
+}
 
 // g = dy*[y>0] of a float32 call, written once: into dres when that is wanted, else (with a ReLU) into buf
 hipError_t f32_mask_pass(const Geom &g, const void *dy, const void *y, bool relu, void *buf, void *dres, const void **gy,
@@ -188,7 +219,7 @@ size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool le
 {
     const size_t plain = workspace_for(op, g, dtype, false, true);
     const size_t fast = use_mfma(op, g, dtype, flags) ? workspace_for(op, g, dtype, true, true, least) : 0;
-    if (op == NM_OP_BWD_WEIGHT && use_f32(f32_wgrad_supported(g), dtype, flags)) return plain + f32_wgrad_part_bytes(g);
+    if (op == NM_OP_BWD_WEIGHT && use_f32(op, g, dtype, flags)) return plain + f32_wgrad_part_bytes(g);
     return plain > fast ? plain : fast;
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
@@ -235,8 +266,7 @@ Route route_pass(int op, const Geom &g, int dtype, unsigned flags, bool aligned,
         r.need = room(false);
     }
     r.part_at = r.need;
-    const bool supported = op == NM_OP_FWD ? f32_fwd_supported(g) : op == NM_OP_BWD_DATA ? f32_dgrad_supported(g) : f32_wgrad_supported(g);
-    r.f32 = use_f32(supported, dtype, flags);
+    r.f32 = use_f32(op, g, dtype, flags);
     if (r.f32 && op == NM_OP_BWD_WEIGHT) {
         r.f32 = check_workspace(ws, have, r.need + f32_wgrad_part_bytes(g)) == NM_OK;
         if (r.f32) r.need += f32_wgrad_part_bytes(g);
@@ -629,7 +659,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
                                      (unsigned char *)workspace + ws_data, workspace_bytes - ws_data, s));
     }
     // float32 on the matrix cores: the masked gradient is formed once for both
-    const bool fused_f32 = whole && use_f32(f32_dgrad_supported(g) && f32_wgrad_supported(g), dtype, flags);
+    const bool fused_f32 = whole && use_f32(NM_OP_BWD_DATA, g, dtype, flags) && use_f32(NM_OP_BWD_WEIGHT, g, dtype, flags);
     if (fused_f32) {
         DisarmOnExit disarm;
         hipStream_t s = (hipStream_t)hip_stream;

@@ -77,3 +77,16 @@ def test_parts_of_a_weight_gradient_where_their_sum_costs_more_than_they_save():
     assert nm.nm_conv1d_kernel_name(WGRAD, 10, 64, 32, 560, 13, 1, 3, 18) == "wgrad_kernel<5> in 8 parts"
     assert nm.nm_conv1d_kernel_name(WGRAD, 6, 4, 256, 408, 13, 1, 3, 18) == "wgrad_kernel<5> in 8 parts"
     assert nm.nm_conv1d_kernel_name(WGRAD, 32, 64, 256, 1600, 11, 2, 1, 5) == "wgrad_kernel<6> in 16 parts"
+
+
+@pytest.mark.parametrize("dtype", [nm.NM_BF16, nm.NM_F32], ids=["bf16", "f32"])
+def test_the_smallest_calls_stay_on_the_plain_kernels(dtype):
+    """A few products per thread are done before the matrix-core kernels' launches are; rows of 16-byte groups are as ever."""
+    if dtype == nm.NM_BF16:
+        assert nm.nm_conv1d_kernel_name(FWD, 3, 1, 512, 45, 1) == "direct_fwd_kernel"
+        assert nm.nm_conv1d_kernel_name(DGRAD, 2, 45, 6, 20, 1) == "direct_dgrad_kernel"
+        assert nm.nm_conv1d_kernel_name(DGRAD, 5, 37, 1, 13, 7, 2, 1, 3) == "direct_dgrad_kernel"
+        assert not nm.nm_conv1d_kernel_name(FWD, 3, 16, 512, 45, 3, 1, 1, 1).startswith("direct")
+        assert not nm.nm_conv1d_kernel_name(FWD, 3, 1, 512, 48, 1).startswith("direct")
+    assert nm.nm_conv1d_kernel_name(WGRAD, 3, 421, 32, 23, 7, 2, 3, 9, dtype=dtype) == "direct_wgrad_kernel"
+    assert not nm.nm_conv1d_kernel_name(WGRAD, 4, 256, 256, 401, 11, 1, 1, 5, dtype=dtype).startswith("direct")
