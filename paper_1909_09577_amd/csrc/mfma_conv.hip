@@ -1796,15 +1796,18 @@ Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
 // Its time and the other engines' are estimated in microseconds from measured rates (256 CUs assumed: the workspace
 // query has no device).  A wavefront's MFMA costs 18 ns in the unrolled engine, 20.5 ns here with two or more workgroups
 // per CU; a chunk costs 0.3 us more there for staging and the barrier (27 ns and 0.8 us alone on the CU), parts
-// 6 us for the second launch and 0.42 us per MB of float32 outputs and part, and no less than 15 us in all (a call of three
-// launches is bound by the host below that: 256 channels, K=11, 200 steps 21.0 us in eight parts, 19.2 in the other engine).
-// Both sides of the line, forward, weight packing
-// included (split / other engine): 768 channels K=25, 600 steps, B=1 40 / 65 us, B=2 55 / 67, B=4 83 / 76; 512 channels
-// K=17, 400 steps, B=4 34 / 40, B=8 46 / 42; 512 channels K=1, 400 steps, B=4 15 / 21, 800 steps, B=16 48 / 24;
-// 64 -> 256 channels, stride 2, 1600 steps, B=32 28 / 46.
-// The plan must not depend on the workspace a call happens to get: nm_conv1d_block_fwd_static promises the bits of
-// nm_conv1d_block_fwd and has a fixed array.  So part_limit, a function of the geometry alone, is what that array has left
-// behind the weights, and no plan has more than kSplitRounds times that: the static call makes the columns in as many rounds.
+// 6 us for the second launch and 0.42 us per MB of float32 outputs and part.  Against another engine a call in parts counts
+// for 15 us at least: its third launch is bound by the host below that (called from Python, 256 channels, K=11, 200 steps take
+// 20.5 us in parts, 19.1 in the other engine, though the device needs 12 and 19).  Plans that tie at the floor
+// are ranked by what they take on the device (fitted to 250 geometries; the launches' replays in a graph).  Device time of a
+// forward call with its weight packing, the plan taken / best plan / other engine: 768 channels K=25, 600 steps, B=1
+// 40 / 40 / 66 us, B=2 54 / 54 / 66, B=4 77 (the other engine) / 82 / 77; 384 channels K=13, 600 steps 17.3 / 17.3 / 27.2;
+// 512 channels K=17, 400 steps, B=4 35 / 33 / 39; 768 channels K=1, 600 steps 17.9 / 17.2 / 26.2; 512 channels K=1, 400 steps,
+// B=4 21 (the other engine) / 14.6 / 21; 64 -> 256 channels, stride 2, 1600 steps, B=32 28.6 / 26.9 / 43.4; 64 -> 896
+// channels K=1, 1496 steps, B=23 41 (the other engine) / 54 / 41.
+// nm_conv1d_block_fwd_static promises the bits of nm_conv1d_block_fwd and has a fixed array.  So the plan of a call with the
+// workspace it asked for has no more parts than kSplitRounds times what that array has left behind the weights, and the
+// static call makes its columns in as many rounds.  Other calls with less room take the best plan within it.
 constexpr int kSplitRounds = 4;
 struct SplitPlan {
     int nt, nsplit, ngroups;  // nt = 0: another engine
@@ -1822,11 +1825,11 @@ double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
 {
     const long cus = 256;
     const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
-    if (K == 1 && nmt >= 2 && pl.nt == 5 && pl.stride == 1) {  // pointwise_gemm_kernel: 3 us per stage of 128 channels
+    if (K == 1 && nmt >= 2 && pl.nt == 5 && pl.stride == 1) {  // pointwise_gemm_kernel, its two tiles
         const long tiles = (long)((nmt + 3) / 4) * ((Tout + 159) / 160) * B;
         const long tiles_big = (long)((nmt + 7) / 8) * ((Tout + 127) / 128) * B;
-        const double a = (double)((tiles + cus - 1) / cus) * (3.0 * ((R + 127) / 128) + 4.0);
-        const double c = (double)((tiles_big + cus - 1) / cus) * (1.8 * ((R + 63) / 64) + 4.0);
+        const double a = (double)((tiles + cus - 1) / cus) * (5.6 * ((R + 127) / 128) + 2.9);
+        const double c = (double)((tiles_big + cus - 1) / cus) * (1.7 * ((R + 63) / 64) + 2.5);
         return a < c ? a : c;
     }
     const long tiles = (long)nmt * ((Tout + pl.nt * 32 - 1) / (pl.nt * 32)) * B;
@@ -1838,13 +1841,14 @@ double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
     return full * (nch * chunk + 2.0) + shared * (((nch + kWaves - 1) / kWaves) * chunk + 4.0);
 }
 
-SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil, size_t part_limit)
+// part_limit: room for the parts of a round, of at most `most_rounds`
+SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil, size_t part_limit, unsigned most_rounds)
 {
     SplitPlan best = {};
     const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
     if (!pl.ok || (K == 1 && nch == 1)) return best;
     const double mb = 4e-6 * B * M * (double)Tout;
-    double best_cost = 0.9 * engine_cost(pl, B, M, R, Tout, K);
+    double best_cost = 0.9 * engine_cost(pl, B, M, R, Tout, K), best_on_device = 0.0;  // (a tie with another engine goes to that)
     // (whatever the shape, the MFMAs at 256 CUs' full rate: most large calls need not be looked at any further)
     if (0.0205 / 4096 * nmt * 2 * (double)B * ((Tout + 31) / 32) * nch * 2 * K > best_cost) return best;
     for (int nt = pl.stride == 1 ? 4 : 3; nt >= 2; --nt) {
@@ -1860,10 +1864,14 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
             double cost = (double)(rounds * chunks) *
                           ((rounds > 1 ? 0.0205 : 0.027) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.3 : 0.8));
             if (ns > 1) cost = std::max(cost + 6.0 + 0.42 * ns * mb, 15.0);
-            if (cost >= best_cost) continue;
+            const double on_device = (double)(rounds * chunks) *
+                                         ((rounds > 1 ? 0.026 : 0.032) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.25 : 0.62)) +
+                                     0.78 * rounds + 1.4 + 0.79 * ns * mb;
+            if (cost > best_cost || (cost == best_cost && on_device >= best_on_device)) continue;
             const size_t col_bytes = ns > 1 ? (size_t)nmt * ns * kTileM * nt * 32 * sizeof(float) : 0;
-            if (col_bytes > 0 && split_rounds(wgs / (unsigned)(nmt * ns), col_bytes, part_limit) > kSplitRounds) continue;
+            if (col_bytes > 0 && split_rounds(wgs / (unsigned)(nmt * ns), col_bytes, part_limit) > most_rounds) continue;
             best_cost = cost;
+            best_on_device = on_device;
             best.nt = nt;
             best.nsplit = ns;
             best.ngroups = (int)((rows + 7) / 8);
@@ -1878,20 +1886,21 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
 }
 
 // the same, remembered: a call asks several times (workspace query, checks, launch)
-constexpr size_t kNoLimit = (size_t)1 << 40;
-SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil, size_t part_limit = kNoLimit)
+constexpr size_t kNoLimit = (size_t)1 << 38;  // (its number of 256-byte units is a key of the table below, an int)
+SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int dil, size_t part_limit = kNoLimit, unsigned most_rounds = 1)
 {
     struct Entry {
-        int key[11];
+        int key[12];
         SplitPlan plan;
     };
     static thread_local Entry table[16] = {};  // (no call has B = 0)
-    const int key[11] = {B, M, R, Tout, K, dil, pl.stride, pl.nt, pl.ok, pl.unrolled, (int)(part_limit >> 8)};
+    part_limit = std::min(part_limit, kNoLimit) >> 8 << 8;
+    const int key[12] = {B, M, R, Tout, K, dil, pl.stride, pl.nt, pl.ok, pl.unrolled, (int)(part_limit >> 8), (int)most_rounds};
     unsigned h = 0;
     for (int k : key) h = h * 31u + (unsigned)k;
     Entry &t = table[(h ^ (h >> 7) ^ (h >> 15)) % 16];
     if (memcmp(t.key, key, sizeof key) != 0) {
-        t.plan = make_split_plan(pl, B, M, R, Tout, K, dil, part_limit);
+        t.plan = make_split_plan(pl, B, M, R, Tout, K, dil, part_limit, most_rounds);
         memcpy(t.key, key, sizeof key);
     }
     return t.plan;
@@ -2011,6 +2020,7 @@ hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int strid
     p.part = (f32x4 *)part;
     const int cols = p.ntt * p.B;
     const int at_once = sp.part_bytes <= part_room ? cols : (int)(part_room / sp.col_bytes);
+    if (at_once < 1) return hipErrorInvalidValue;  // (no such plan is made)
     if (stride == 1) {
         if (sp.nt == 4) return launch_split_t<4, 1>(p, at_once, sp.lds, s);
         if (sp.nt == 3) return launch_split_t<3, 1>(p, at_once, sp.lds, s);
@@ -2027,7 +2037,7 @@ struct ConvChoice {
     int nt, stride, kt;                      // kGemm: the template arguments
     bool len, stats, any, pad_pair;          // (len: of kPointwise too)
 };
-ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, size_t part_room)
+ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p)
 {
     ConvChoice c = {};
     c.any = p.Tout % 8 != 0;
@@ -2037,7 +2047,7 @@ ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
         c.kind = ConvChoice::kFew;
         return c;
     }
-    if (!p.stats && sp.nt && (sp.nsplit == 1 || split_rounds((unsigned)((p.Tout + sp.nt * 32 - 1) / (sp.nt * 32) * p.B), sp.col_bytes, part_room) <= kSplitRounds)) {
+    if (!p.stats && sp.nt) {
         c.kind = ConvChoice::kSplit;
         return c;
     }
@@ -2086,7 +2096,7 @@ hipError_t launch_tap_pairs(const ConvChoice &c, const ConvGemmParams &p, size_t
 // [part, part + part_room): room for the partial sums of the split engine, whose plan is sp
 hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room)
 {
-    const ConvChoice c = choose_conv(pl, sp, p, part_room);
+    const ConvChoice c = choose_conv(pl, sp, p);
     switch (c.kind) {
     case ConvChoice::kFew: return launch_few_channels(p, s);
     case ConvChoice::kSplit: return launch_split(sp, p, pl.stride, part, part_room, s);
@@ -2102,9 +2112,9 @@ hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
 }
 
 // the kernel's name as a profiler lists it
-void name_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, size_t part_room, char *name, size_t n)
+void name_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, char *name, size_t n)
 {
-    const ConvChoice c = choose_conv(pl, sp, p, part_room);
+    const ConvChoice c = choose_conv(pl, sp, p);
     auto b = [](bool v) { return v ? "true" : "false"; };
     switch (c.kind) {
     case ConvChoice::kFew: snprintf(name, n, "few_channels_gemm_kernel"); break;
@@ -2245,35 +2255,38 @@ bool mfma_fwd_supported(const Geom &g)
 
 size_t mfma_fwd_workspace_least(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K) + pitched_x_bytes(g); }
 namespace {
-SplitPlan fwd_split_plan(const Geom &g, const Plan &pl)
+// the plan with ws_bytes of workspace; in_rounds: that of a call with the workspace it asks for, whatever the room
+SplitPlan fwd_split_plan(const Geom &g, const Plan &pl, size_t ws_bytes, bool in_rounds = false)
 {
-    const size_t least = mfma_fwd_workspace_least(g);
-    return split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, least <= NM_STATIC_SCRATCH_BYTES ? NM_STATIC_SCRATCH_BYTES - least : kNoLimit);
+    const size_t least = mfma_fwd_workspace_least(g), room = ws_bytes > least ? ws_bytes - least : 0;
+    const bool array = least <= NM_STATIC_SCRATCH_BYTES;
+    const SplitPlan sp = split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, array ? NM_STATIC_SCRATCH_BYTES - least : kNoLimit, kSplitRounds);
+    return sp.part_bytes <= room || in_rounds ? sp : split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, room);
 }
 }  // namespace
 size_t mfma_fwd_workspace(const Geom &g)
 {
-    return mfma_fwd_workspace_least(g) + fwd_split_plan(g, make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil)).part_bytes;
+    return mfma_fwd_workspace_least(g) + fwd_split_plan(g, make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil), kNoLimit).part_bytes;
 }
 
 // Whether the forward pass of this geometry runs on a kernel instance that can also write the statistics of its
 // outputs, and into how many (batch item, time tile) parts: the unrolled engine, wide tile, no lengths, 16-byte rows.
-int mfma_fwd_stats_parts(const Geom &g)
+int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes)
 {
     if (!rows16(g)) return 0;
     const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !pl.unrolled || pl.nt != 5 || g.len || !mfma_fwd_supported(g)) return 0;
     if (pl.buf_bytes < Epilogue<5>::kTileBytesWithStats) return 0;
-    if (fwd_split_plan(g, pl).nt) return 0;  // few tiles: z is small and read again instead
+    if (fwd_split_plan(g, pl, ws_bytes).nt) return 0;  // few tiles: z is small and read again instead
     return g.B * ((g.To + 159) / 160);
 }
 
 hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const float *scale, const float *shift,
-                           const void *res, void *y, bool relu, void *ws, size_t ws_bytes, hipStream_t s, double *stats)
+                           const void *res, void *y, bool relu, void *ws, size_t ws_bytes, hipStream_t s, double *stats, bool in_rounds)
 {
     const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !mfma_fwd_supported(g)) return hipErrorInvalidValue;
-    if (stats && mfma_fwd_stats_parts(g) == 0) return hipErrorInvalidValue;
+    if (stats && mfma_fwd_stats_parts(g, ws_bytes) == 0) return hipErrorInvalidValue;
     // a pointwise layer with a handful of output channels is a stream over x: no packing, no tiles
     if (skinny_fwd_supported(g) && ((uintptr_t)w % 16) == 0) return launch_skinny_fwd(g, x, w, scale, shift, res, y, relu, s);
     hipError_t e;
@@ -2300,7 +2313,7 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     p.out = (bf16_t *)y;
     p.stats = stats;
     const size_t least = mfma_fwd_workspace_least(g);
-    return launch_plan(pl, fwd_split_plan(g, pl), p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
+    return launch_plan(pl, fwd_split_plan(g, pl, ws_bytes, in_rounds), p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
 }
 
 void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n)
@@ -2316,9 +2329,8 @@ void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_
     fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad);
     p.len_in = g.len;
     p.scale = &affine;
-    if (stats && mfma_fwd_stats_parts(g) > 0) p.stats = &some_stats;
-    const size_t least = mfma_fwd_workspace_least(g);
-    name_conv(pl, fwd_split_plan(g, pl), p, ws_bytes > least ? ws_bytes - least : 0, name, n);
+    if (stats && mfma_fwd_stats_parts(g, ws_bytes) > 0) p.stats = &some_stats;
+    name_conv(pl, fwd_split_plan(g, pl, ws_bytes), p, name, n);
 }
 
 // ---- input gradient (stride 1 only; other strides use the plain kernels) ----------------
@@ -2371,20 +2383,23 @@ size_t mfma_dgrad_workspace_least(const Geom &g)
     return packed_bytes(g.Cin, g.Cout, g.K) + dz_bytes_of(g);
 }
 namespace {
-SplitPlan dgrad_split_plan(const Geom &g, const Plan &pl)
+SplitPlan dgrad_split_plan(const Geom &g, const Plan &pl, size_t ws_bytes)
 {
-    if (g.stride == 2) {
-        const Phases ph = phases_of_stride2(g);
-        return split_plan(pl, g.B, 2 * g.Cin, g.Cout, ph.Up, ph.K, 1);
-    }
-    return split_plan(pl, g.B, g.Cin, g.Cout, g.T, g.K, g.dil);
+    const size_t least = mfma_dgrad_workspace_least(g), room = ws_bytes > least ? ws_bytes - least : 0;
+    const Phases ph = g.stride == 2 ? phases_of_stride2(g) : Phases{};
+    auto plan = [&](size_t limit) {
+        return g.stride == 2 ? split_plan(pl, g.B, 2 * g.Cin, g.Cout, ph.Up, ph.K, 1, limit)
+                             : split_plan(pl, g.B, g.Cin, g.Cout, g.T, g.K, g.dil, limit);
+    };
+    const SplitPlan sp = plan(kNoLimit);
+    return sp.part_bytes <= room ? sp : plan(room);
 }
 }  // namespace
 size_t mfma_dgrad_workspace(const Geom &g)
 {
     const Phases ph = g.stride == 2 ? phases_of_stride2(g) : Phases{};
     const Plan pl = g.stride == 2 ? make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1) : make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
-    return mfma_dgrad_workspace_least(g) + dgrad_split_plan(g, pl).part_bytes;
+    return mfma_dgrad_workspace_least(g) + dgrad_split_plan(g, pl, kNoLimit).part_bytes;
 }
 
 namespace {
@@ -2454,7 +2469,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
     p.out = phase_out;
     p.len_out = g.len;  // both parities are padding from 2u >= len on (the merging pass clears an odd length's last one)
     p.len_out_div = 2;
-    e = launch_plan(pl, dgrad_split_plan(g, pl), p, s, part, part_room);
+    e = launch_plan(pl, dgrad_split_plan(g, pl, mfma_dgrad_workspace_least(g) + part_room), p, s, part, part_room);
     if (e != hipSuccess) return e;
     const unsigned n = (unsigned)g.B * g.Cin * ((g.T + 7) / 8);
     hipLaunchKernelGGL(interleave_phases_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const bf16_t *)phase_out, (bf16_t *)dx,
@@ -2490,8 +2505,7 @@ void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name
         pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
         fill_dgrad(p, pl, g, nullptr, nullptr, &dx, accumulate);
     }
-    const size_t least = mfma_dgrad_workspace_least(g);
-    name_conv(pl, dgrad_split_plan(g, pl), p, ws_bytes > least ? ws_bytes - least : 0, name, n);
+    name_conv(pl, dgrad_split_plan(g, pl, ws_bytes), p, name, n);
 }
 
 // accumulate (stride 1 only): dx = bf16(dx + gradient), one rounding.
@@ -2542,7 +2556,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
     if (g_used) *g_used = gin;
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, gin, ws, dx, accumulate);
-    return launch_plan(pl, dgrad_split_plan(g, pl), p, s, part, part_room);
+    return launch_plan(pl, dgrad_split_plan(g, pl, ws_bytes), p, s, part, part_room);
 }
 
 // ---- fused backward -------------------------------------------------------------------------
@@ -2597,7 +2611,7 @@ hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, g_plain, ws, dx, accumulate);
     const size_t least = mfma_dgrad_workspace_least(g);
-    return launch_plan(pl, dgrad_split_plan(g, pl), p, s, (unsigned char *)ws + least, ws_bytes - least);
+    return launch_plan(pl, dgrad_split_plan(g, pl, ws_bytes), p, s, (unsigned char *)ws + least, ws_bytes - least);
 }
 
 }  // namespace nm

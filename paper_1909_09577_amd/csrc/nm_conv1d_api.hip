@@ -153,7 +153,7 @@ bool tiny(int op, const Geom &g, int dtype)
     const long chain = (long)(op == NM_OP_FWD ? g.Cin : g.Cout) * g.K;
     const int rows = op == NM_OP_FWD ? g.Cout : g.Cin;
     if (g.K == 1 && g.stride == 1 && g.pad == 0 && rows > 64 && g.To > 64) return chain <= (op == NM_OP_FWD ? 40 : 24);  // the GEMM kernel
-    if (op == NM_OP_FWD) return chain <= 16;
+    if (op == NM_OP_FWD) return 5.0 + 0.3 * chain + 0.4e-6 * products < 9.3;
     return chain <= (g.stride == 2 ? 22 : g.K == 1 ? 12 : g.K >= 11 ? 16 : 10);
 }
 
@@ -224,8 +224,7 @@ size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool le
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
 // without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels, so are stride-2 input gradients;
-// calls of few tiles without room for the split engine's partial sums by the other engines (or, from a quarter of that
-// room on, by the split engine in rounds).
+// calls of few tiles without room for the split engine's partial sums with fewer parts or by the other engines.
 size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
     const bool strided = op == NM_OP_BWD_DATA && g.stride == 2;
@@ -372,7 +371,8 @@ const char *nm_strerror(int status)
 static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const int *lengths,
                           const void *x, const void *w, const float *scale, const float *shift,
                           const void *residual, void *y, unsigned flags, int dtype, void *workspace,
-                          size_t workspace_bytes, void *hip_stream, double *stats = nullptr, int *stats_parts = nullptr)
+                          size_t workspace_bytes, void *hip_stream, double *stats = nullptr, int *stats_parts = nullptr,
+                          bool in_rounds = false)
 {
     // stats / stats_parts (the BatchNorm entry point): where the kernel that runs can write the partial statistics of
     // its outputs it does, and *stats_parts says into how many parts per channel (0: it did not)
@@ -396,8 +396,8 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
     const bool relu = (flags & NM_RELU) != 0;
     t_current_op = NM_OP_FWD;
     if (r.mfma) {
-        const int parts = (stats && stats_parts) ? mfma_fwd_stats_parts(g) : 0;
-        const hipError_t err = launch_mfma_fwd(g, x, w, scale, shift, residual, y, relu, workspace, workspace_bytes, s, parts > 0 ? stats : nullptr);
+        const int parts = (stats && stats_parts) ? mfma_fwd_stats_parts(g, workspace_bytes) : 0;
+        const hipError_t err = launch_mfma_fwd(g, x, w, scale, shift, residual, y, relu, workspace, workspace_bytes, s, parts > 0 ? stats : nullptr, in_rounds);
         if (err == hipSuccess && parts > 0) *stats_parts = parts;
         return dev(err);
     }
@@ -527,7 +527,7 @@ int nm_conv1d_block_fwd_static(int B, int Cin, int Cout, int T, int K, int strid
         }
     }
     return block_fwd_impl(B, Cin, Cout, T, K, stride, dilation, pad, nullptr, x, w, scale, shift, residual, y, flags, dtype,
-                          ptr, ptr ? (size_t)NM_STATIC_SCRATCH_BYTES : 0, hip_stream);
+                          ptr, ptr ? (size_t)NM_STATIC_SCRATCH_BYTES : 0, hip_stream, nullptr, nullptr, true);
 }
 
 int nm_conv1d_bwd_data(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const void *dy,
