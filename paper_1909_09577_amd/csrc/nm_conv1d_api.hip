@@ -603,21 +603,26 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     const size_t e = elt(dtype);
     const size_t ndy = (size_t)g.B * g.Cout * g.To * e, nx = (size_t)g.B * g.Cin * g.T * e;
     const size_t nw = (size_t)g.Cout * g.Cin * g.K * e, ndw = (size_t)g.Cout * g.Cin * g.K * sizeof(float);
+    const size_t used = need < workspace_bytes ? need : workspace_bytes;
     const bool clash = overlap(dx, nx, dy, ndy) || overlap(dx, nx, y, ndy) || overlap(dx, nx, w, nw) || overlap(dx, nx, x, nx) ||
                        overlap(dres, ndy, dy, ndy) || overlap(dres, ndy, y, ndy) || overlap(dres, ndy, dx, nx) ||
                        overlap(dw, ndw, dy, ndy) || overlap(dw, ndw, y, ndy) || overlap(dw, ndw, x, nx) || overlap(dw, ndw, dx, nx) ||
-                       overlap(dw, ndw, dres, ndy) || overlap(dx, nx, workspace, need) || overlap(dres, ndy, workspace, need) ||
-                       overlap(dw, ndw, workspace, need);
+                       overlap(dw, ndw, dres, ndy) || overlap(dx, nx, workspace, used) || overlap(dres, ndy, workspace, used) ||
+                       overlap(dw, ndw, workspace, used);
     // the geometries that once were two calls keep those calls' own checks where tensors overlap
-    whole = whole && !(clash && (dtype == NM_F32 || !rows16(g)));
-    const bool fused = whole && !(lengths && (flags & NM_ACCUM_DX)) &&
-                       use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) &&
-                       g.stride == 1 && mfma_wgrad_fast_supported(g) && !wgrad_k1_supported(pitched(g)) && aligned16(x) && aligned16(dy) &&
-                       aligned16(dx) && (!relu || aligned16(y)) && (!dres || aligned16(dres));
-    const size_t ws_data = mfma_dgrad_workspace(g);  // only meaningful when fused
+    const bool own_checks = clash && (dtype == NM_F32 || !rows16(g));
+    whole = whole && !own_checks;
+    // the matrix-core kernels of both gradients, and the workspace they can do with: what is more goes to the input gradient
+    const bool both_mfma = use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags);
+    const size_t wgrad_least = both_mfma ? mfma_wgrad_workspace(g, true, false) : 0;
+    const bool fits = whole || (both_mfma && !own_checks && workspace_bytes >= mfma_dgrad_workspace_least(g) + wgrad_least);
+    const bool fused = fits && both_mfma && !(lengths && (flags & NM_ACCUM_DX)) && g.stride == 1 && mfma_wgrad_fast_supported(g) &&
+                       !wgrad_k1_supported(pitched(g)) && aligned16(x) && aligned16(dy) && aligned16(dx) && (!relu || aligned16(y)) &&
+                       (!dres || aligned16(dres));
+    // only meaningful when fused
+    const size_t ws_data = whole ? mfma_dgrad_workspace(g) : fits ? (workspace_bytes - wgrad_least) / kWsAlign * kWsAlign : 0;
     // pointwise layers: the input gradient's masked g = dy*[y>0] also feeds the K=1 weight-gradient GEMM
-    const bool fused_k1 = whole && !lengths && g.stride == 1 && use_mfma(NM_OP_BWD_DATA, g, dtype, flags) &&
-                          use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && wgrad_k1_supported(pitched(g)) && aligned16(x) &&
+    const bool fused_k1 = fits && both_mfma && !lengths && g.stride == 1 && wgrad_k1_supported(pitched(g)) && aligned16(x) &&
                           aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
     if (fused_k1) {
         DisarmOnExit disarm;
@@ -644,8 +649,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s));
     }
     // stride 2: the input gradient's g is plain too, and what the general weight-gradient kernel reads
-    const bool fused_s2 = whole && !clash && g.stride == 2 && rows16(g) && !(flags & NM_ACCUM_DX) && use_mfma(NM_OP_BWD_DATA, g, dtype, flags) &&
-                          use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags) && masked_on_mfma(g, NM_OP_BWD_WEIGHT) && aligned16(x) &&
+    const bool fused_s2 = fits && both_mfma && !clash && g.stride == 2 && rows16(g) && !(flags & NM_ACCUM_DX) && masked_on_mfma(g, NM_OP_BWD_WEIGHT) && aligned16(x) &&
                           aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
     if (fused_s2) {
         DisarmOnExit disarm;

@@ -64,6 +64,16 @@ def test_few_tiles(cfg, masked):
     U.assert_close(U.to_host_f64(dx), dx_ref, "bf16", f"{cfg.name} dx")
     dx1, _, dw1 = nm.nm_conv1d_bwd(x, dy, w, y=ysv, scale=scale, relu=cfg.relu, lengths=ld, **kw)
     assert torch.equal(dx1, dx)
+    U.assert_close(U.to_host_f64(dw1), orc.bwd_weight_masked(inp["x"], dz, cfg.K, lens, **kw), "bf16", f"{cfg.name} dw",
+                   rms_bound=U.RMS_DW_BF16)
+    if cfg.stride == 1:  # one call without room for the input gradient's partial sums: both gradients still from one pass over dy
+        part = nm.nm_conv1d_workspace_bytes(nm.NM_OP_BWD_DATA, *cfg.dims(), nm.NM_BF16, nm.NM_RELU) - _least(cfg, cfg.Cin, cfg.Cout)
+        part -= (2 * cfg.B * cfg.Cout * ((cfg.T_out + 7) // 8 * 8) + 255) // 256 * 256
+        n = nm.nm_conv1d_workspace_bytes(nm.NM_OP_BWD, *cfg.dims(), nm.NM_BF16, nm.NM_RELU) - part
+        guard = torch.full((n + 256,), 255, dtype=torch.uint8, device="cuda")
+        dx2, _, dw2 = nm.nm_conv1d_bwd(x, dy, w, y=ysv, scale=scale, relu=cfg.relu, lengths=ld, workspace=guard[:n], **kw)
+        U.assert_close(U.to_host_f64(dx2), dx_ref, "bf16", f"{cfg.name} dx, less room")
+        assert torch.equal(dw2, dw1) and bool((guard[n:] == 255).all())
     if not masked and cfg.stride == 1:  # accumulation into dx, in the second pass too
         old = torch.randn(cfg.B, cfg.Cin, cfg.T, device="cuda").bfloat16()
         acc = old.clone()
