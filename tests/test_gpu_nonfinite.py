@@ -9,21 +9,21 @@ from paper_1909_09577_amd import binding as nm
 
 pytestmark = pytest.mark.gpu
 
-# (dtype, B, Cin, Cout, T, K, stride, dilation, pad)
-CASES = [
-    ("f32", 2, 40, 72, 130, 11, 1, 1, 5),
-    ("f32", 2, 24, 40, 201, 5, 2, 1, 2),
-    ("f32", 1, 24, 80, 100, 32, 1, 1, 16),
-    ("bf16", 2, 64, 96, 133, 11, 1, 1, 5),       # the engine for few tiles
-    ("bf16", 1, 256, 64, 133, 5, 1, 2, 4),       # the same in parts, a dilated filter
-    ("bf16", 20, 128, 512, 1277, 11, 1, 1, 5),   # the unrolled kernel
-    ("bf16", 16, 72, 256, 1277, 7, 1, 1, 3),     # the tap-pair loop, with its absent eighth tap
-    ("bf16", 16, 48, 256, 1277, 5, 1, 1, 2),     # the same with a pad pair
-    ("bf16", 8, 256, 1024, 1277, 1, 1, 1, 0),    # the GEMM kernel
-    ("bf16", 3, 64, 128, 175, 4, 1, 1, 2),       # only the input rows are odd
-    ("bf16", 3, 40, 72, 123, 11, 2, 1, 5),       # both parities of a stride-2 gradient: filters of five and six taps
-    ("bf16", 3, 40, 72, 160, 11, 2, 1, 5),       # the same on 16-byte rows (its gradient only)
-]
+# (dtype, B, Cin, Cout, T, K, stride, dilation, pad), kernel of the forward pass
+CASES = {
+    ("f32", 2, 40, 72, 130, 11, 1, 1, 5): "f32_conv",
+    ("f32", 2, 24, 40, 201, 5, 2, 1, 2): "f32_conv",
+    ("f32", 1, 24, 80, 100, 32, 1, 1, 16): "f32_conv",
+    ("bf16", 2, 64, 96, 133, 11, 1, 1, 5): "conv_split_kernel<2, 1> in 1 parts",
+    ("bf16", 1, 512, 64, 133, 11, 1, 2, 10): "conv_split_kernel<2, 1> in ",
+    ("bf16", 20, 128, 512, 1277, 11, 1, 1, 5): "conv_gemm_kernel<5, 1, 11, true, false, true",        # the unrolled kernel
+    ("bf16", 8, 256, 200, 801, 7, 1, 1, 3): "conv_gemm_kernel<5, 1, 0, false, false, true, false>",    # tap pairs, an absent eighth tap
+    ("bf16", 8, 480, 250, 801, 5, 1, 1, 2): "conv_gemm_kernel<5, 1, 0, false, false, true, true>",     # the same with a pad pair
+    ("bf16", 8, 256, 1024, 1277, 1, 1, 1, 0): "pointwise_gemm_kernel<true",
+    ("bf16", 3, 64, 128, 175, 4, 1, 1, 2): "conv_split_kernel<2, 1>",                                 # only the input rows are odd
+    ("bf16", 3, 40, 72, 123, 11, 2, 1, 5): "conv_split_kernel<2, 2>",  # parities of a stride-2 gradient: filters of five and six taps
+    ("bf16", 3, 40, 72, 160, 11, 2, 1, 5): "conv_split_kernel<2, 2>",  # the same on 16-byte rows (its gradient only)
+}
 
 
 def _same(got, ref, dtype, what):
@@ -42,6 +42,8 @@ def _same(got, ref, dtype, what):
 def test_one_infinite_element(case, masked):
     import torch
     dtype, B, Cin, Cout, T, K, stride, dil, pad = case
+    name = nm.nm_conv1d_kernel_name(nm.NM_OP_FWD, *case[1:], dtype=nm.NM_F32 if dtype == "f32" else nm.NM_BF16, masked=masked)
+    assert name.startswith(CASES[case]), name
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     To = orc.out_len(T, K, stride, dil, pad)
     kw = dict(stride=stride, dilation=dil, pad=pad)
