@@ -80,6 +80,7 @@ struct ConvGemmParams {
     int nsplit;             // conv_split_kernel: parts the reduction channels are split into
     f32x4 *part;            // their partial sums (nsplit > 1)
     int col0, ncols;        // the columns (time tiles of all batch items) of this launch
+    int odd_rows;           // rows of in or out are no multiple of 16 bytes long (host: which instances serve the call)
     double *stats;          // optional [B*ntt][M][3]: count, mean and centred second moment of the stored outputs of
                             // every (batch item, time tile, channel) -- the partial statistics of a BatchNorm over out
 };
@@ -324,7 +325,7 @@ struct TileCoords {
 // LEN: the instance for ragged calls (per-sample lengths); of the unrolled kernels it
 // alone carries the test for tiles in the padding.
 // STATS: the instance that also writes the per-tile statistics of its stored outputs (ConvGemmParams::stats).
-// ANYROW: output rows of any length (the test for them costs the other calls of few tiles about 1 %).
+// ANYROW: rows of any length (the test for output rows of that kind costs the other calls of few tiles about 1 %).
 // PADPAIR: of the tap-pair kernels' ANYROW instances, the one where a wavefront may have an odd number of tap pairs (see do_pair).
 template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false, bool PADPAIR = false>
 __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParams p)
@@ -2040,7 +2041,7 @@ struct ConvChoice {
 ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p)
 {
     ConvChoice c = {};
-    c.any = p.Tout % 8 != 0;
+    c.any = p.odd_rows != 0;
     // one tap, at most one chunk of reduction channels, nothing to do after the sums: the store-bound kernel
     if (p.K == 1 && p.R <= kChunk && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout && p.Tout % 8 == 0 && !p.res &&
         !p.scale && !p.shift && !p.relu && !p.len_in && !p.len_out) {
@@ -2229,8 +2230,9 @@ hipError_t launch_prepare_rows(const Geom &g, const RowPrep &r, hipStream_t s)
 }
 namespace {
 
-void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin, int Tout, int K, int dil, int padL)
+void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin, int Tout, int K, int dil, int padL, bool odd_rows)
 {
+    p.odd_rows = odd_rows ? 1 : 0;
     p.B = B; p.M = M; p.R = R; p.Tin = Tin; p.Tout = Tout; p.K = K; p.Kp = (K + 1) & ~1; p.dil = dil; p.padL = padL;
     p.nmt = (M + kTileM - 1) / kTileM;
     p.nch = (R + kChunk - 1) / kChunk;
@@ -2304,7 +2306,7 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     }
     if (e != hipSuccess) return e;
     ConvGemmParams p = {};
-    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad);
+    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad, !rows16(g));
     p.relu = relu ? 1 : 0;
     p.in = (const bf16_t *)in;
     p.len_in = g.len;
@@ -2326,7 +2328,7 @@ void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_
     static double some_stats;
     const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
     ConvGemmParams p = {};
-    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad);
+    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad, !rows16(g));
     p.len_in = g.len;
     p.scale = &affine;
     if (stats && mfma_fwd_stats_parts(g, ws_bytes) > 0) p.stats = &some_stats;
@@ -2463,7 +2465,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
     if (e != hipSuccess) return e;
     const Plan pl = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1);
     ConvGemmParams p = {};
-    fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL);
+    fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL, false);
     p.in = (const bf16_t *)gin;
     p.wp = (const bf16x8 *)packed;
     p.out = phase_out;
@@ -2480,7 +2482,7 @@ hipError_t launch_mfma_dgrad_stride2(const Geom &g, const void *dy, const void *
 // parameters of the stride-1 input gradient as a run of the forward engine
 void fill_dgrad(ConvGemmParams &p, const Plan &pl, const Geom &g, const void *gin, const void *packed, void *dx, bool accumulate)
 {
-    fill_common(p, pl, g.B, g.Cin, g.Cout, row_pitch(g.To), g.T, g.K, g.dil, g.dil * (g.K - 1) - g.pad);
+    fill_common(p, pl, g.B, g.Cin, g.Cout, row_pitch(g.To), g.T, g.K, g.dil, g.dil * (g.K - 1) - g.pad, !rows16(g));
     p.relu = 0;
     p.in = (const bf16_t *)gin;
     p.wp = (const bf16x8 *)packed;
@@ -2499,7 +2501,7 @@ void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name
     if (g.stride == 2) {
         const Phases ph = phases_of_stride2(g);
         pl = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1);
-        fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL);
+        fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL, false);
         p.len_out = g.len;
     } else {
         pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);

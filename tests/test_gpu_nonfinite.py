@@ -18,6 +18,7 @@ CASES = {
     ("bf16", 1, 512, 64, 133, 11, 1, 2, 10): "conv_split_kernel<2, 1> in ",
     ("bf16", 20, 128, 512, 1277, 11, 1, 1, 5): "conv_gemm_kernel<5, 1, 11, true, false, true",        # the unrolled kernel
     ("bf16", 8, 256, 200, 801, 7, 1, 1, 3): "conv_gemm_kernel<5, 1, 0, false, false, true, false>",    # tap pairs, an absent eighth tap
+    ("bf16", 8, 256, 200, 798, 7, 1, 1, 4): "conv_gemm_kernel<5, 1, 0, false, false, true, false>",    # the same, only the input rows odd
     ("bf16", 8, 480, 250, 801, 5, 1, 1, 2): "conv_gemm_kernel<5, 1, 0, false, false, true, true>",     # the same with a pad pair
     ("bf16", 8, 256, 1024, 1277, 1, 1, 1, 0): "pointwise_gemm_kernel<true",
     ("bf16", 3, 64, 128, 175, 4, 1, 1, 2): "conv_split_kernel<2, 1>",                                 # only the input rows are odd
