@@ -69,7 +69,7 @@ struct ConvGemmParams {
     const bf16_t *in;       // [B][R][Tin]
     const int *len_in;      // [B] valid input lengths (samples beyond read as zero) or NULL
     const int *len_out;     // [B] lengths beyond which the output is written as zero, or NULL; the limit of
-    int len_out_sub, len_out_div;  // batch item b is ceil((len_out[b] - sub) / div) (phases of a strided gradient)
+    int len_out_div;        // batch item b is ceil(len_out[b] / div) (2: both parities of a strided gradient)
     const bf16x8 *wp;       // packed weights
     size_t wp_bytes;        // size of the packed weights including the zero pair (< 2 GiB)
     size_t wp_zero;         // offset (in fragments of 16 bytes) of one tap pair of zero weights
@@ -135,8 +135,8 @@ struct Epilogue {
     bool has_scale, relu, anyrow;
     bf16_t *out_p;        // (anyrow) the tensors themselves
     const bf16_t *res_p;
-    const int *len_out;  // optional [B]: outputs at t >= ceil((len_out[b] - sub) / div) are written as zero
-    int len_sub, len_div;
+    const int *len_out;  // optional [B]: outputs at t >= ceil(len_out[b] / div) are written as zero
+    int len_div;
     double *stats;       // see ConvGemmParams::stats (used by the STATS instances only)
     static constexpr int kStatsOffset = 16 * TN;  // float2 [16 rows][TN/8] behind the tile (in floats)
     static constexpr int kTileBytesWithStats = 16 * TN * (int)sizeof(float) + 16 * (TN / 8) * 2 * (int)sizeof(float);
@@ -152,17 +152,16 @@ struct Epilogue {
     __device__ __forceinline__ int out_limit(int b) const
     {
         if (!len_out) return Tout;
-        const int n = (len_out[b] - len_sub + len_div - 1) / len_div;
+        const int n = (len_out[b] + len_div - 1) / len_div;
         return n < 0 ? 0 : (n > Tout ? Tout : n);
     }
 
     __device__ __forceinline__ void init(const bf16_t *out, const bf16_t *res, const float *scale, const float *shift, int B,
-                                         int M_, int Tout_, int relu_, const int *len_out_ = nullptr, int sub = 0, int div = 1,
+                                         int M_, int Tout_, int relu_, const int *len_out_ = nullptr, int div = 1,
                                          double *stats_ = nullptr)
     {
         stats = stats_;
         len_out = len_out_;
-        len_sub = sub;
         len_div = div < 1 ? 1 : div;
         const int out_bytes = (int)((size_t)B * M_ * Tout_ * 2);
         M = M_;
@@ -509,7 +508,7 @@ __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParam
     uint32_t w_cur = 0;
 
     Epilogue<NT> epi;
-    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div, p.stats);
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div, p.stats);
 
     int cc = 0;  // chunks this wavefront has consumed so far: chunk number cc uses buffer cc & 1
     // accumulators: zero here, and again in the epilogue as soon as a tile's values have been handed over
@@ -883,7 +882,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const ConvGemmP
     const int c0 = (int)((long)split * p.nch / p.nsplit), c1 = (int)((long)(split + 1) * p.nch / p.nsplit);
 
     Epilogue<NT> epi;
-    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div);
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div);
     const __amdgpu_buffer_rsrc_t rs_in =
         __builtin_amdgcn_make_buffer_rsrc((void *)p.in, 0, (int)((size_t)p.B * p.R * p.Tin * 2), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)p.wp, 0, (int)p.wp_bytes, 0x00020000);
@@ -1060,7 +1059,7 @@ __global__ __launch_bounds__(64) void split_reduce_kernel(const ConvGemmParams p
     const int col = tile / p.nmt, mt = tile - col * p.nmt;
     const int b = (p.col0 + col) / p.ntt, t0 = ((p.col0 + col - b * p.ntt) * nt + ni) * 32;
     Epilogue<1> epi;
-    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div);
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div);
     const auto ld = epi.template request_rows<true>(lane, b, t0, mt * kTileM + 8 * wave, true);
     const size_t pitch = (size_t)p.nmt * p.ncols * kWaves * 2 * nt * 64;
     const f32x4 *src = p.part + ((size_t)quarter * 2 * nt + ni) * 64 + lane;
@@ -1142,7 +1141,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
         __builtin_amdgcn_make_buffer_rsrc((void *)p.in, 0, (int)((size_t)p.B * p.R * T * 2), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)p.wp, 0, (int)p.wp_bytes, 0x00020000);
     Epilogue<NT> epi;
-    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_sub, p.len_out_div);
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div);
 
     // position in the stream: tile coordinates and stage; advanced without divisions except at a tile change
     struct Pos {
@@ -1766,7 +1765,7 @@ Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
     for (int ci = 0; ci < 3; ++ci) {
         const bool unrolled = ci == 0;
         const int nt = ci == 2 ? 2 : 5;
-        if (nt == 5 && Tout <= 64) continue;  // short sequences: the narrow tile wastes less
+        if (nt == 5 && (Tout <= 64 || stride == 2)) continue;  // short sequences: the narrow tile wastes less; stride 2: its window fits no LDS
         if (unrolled && !(stride == 1 && unrolled_slots(K) > 0 && nch % kWaves == 0)) continue;
         const long taps = unrolled ? K : (K + 1) & ~1;  // the tap-pair loop also reads the zero tap of an odd K
         const long rows = (long)(nt * 32 - 1) * stride + (taps - 1) * dil + 1 + 7;
@@ -2089,7 +2088,6 @@ hipError_t launch_tap_pairs(const ConvChoice &c, const ConvGemmParams &p, size_t
 {
     if (c.nt == 5 && c.stride == 1) return launch_t<5, 1, 0, false, false, ANY, PAD>(p, lds, s);
     if (c.nt == 2 && c.stride == 1) return launch_t<2, 1, 0, false, false, ANY, PAD>(p, lds, s);
-    if (c.nt == 5 && c.stride == 2) return launch_t<5, 2, 0, false, false, ANY, PAD>(p, lds, s);
     if (c.nt == 2 && c.stride == 2) return launch_t<2, 2, 0, false, false, ANY, PAD>(p, lds, s);
     return hipErrorInvalidValue;
 }
