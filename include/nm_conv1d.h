@@ -70,7 +70,7 @@ enum {
     NM_ACCUM_DW = 2u,    /* bwd_weight: dw += result instead of dw = result (gradient
                             accumulation over several batches, paper Section 3.3) */
     NM_FORCE_DIRECT = 4u, /* use the plain one-thread-per-output kernels instead of the
-                            matrix-core kernels (always used for NM_F32) */
+                            matrix-core kernels */
     NM_ACCUM_DX = 8u     /* bwd_data / bwd: dx = round(dx + gradient), one rounding, instead of dx = gradient:
                             sums the two gradients that meet at the input of a residual block (the first
                             sub-block's and the residual projection's) without a pass of its own */
@@ -113,8 +113,10 @@ int nm_conv1d_block_fwd(int B, int Cin, int Cout, int T, int K, int stride, int 
  *   dres  [B][Cout][T_out]  out, dtype, or NULL: gradient with respect to the residual
  * In NM_BF16 mode the matrix-core kernels contract g = dy*m (exact in bfloat16) with the weights
  * bf16(w[co,ci,k]*scale[co]): the affine factor is folded into the weight operand, rounded once per weight.
- * The weight gradient contracts the same g and multiplies its float32 sums by scale[co].  The plain
- * kernels (NM_FORCE_DIRECT, NM_F32) form dz = g*scale in the storage type instead.
+ * The weight gradient contracts the same g and multiplies its float32 sums by scale[co].  The matrix-core
+ * kernels of NM_F32 mode fold scale in the same places.  The plain kernels (NM_FORCE_DIRECT, and what the
+ * others do not serve: strides from 3 on, misaligned tensors, the smallest calls) form dz = g*scale in the
+ * storage type instead.
  * With lengths and NM_ACCUM_DX, positions at or beyond a sample's length keep their old value.
  */
 int nm_conv1d_bwd_data(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad,
@@ -232,7 +234,8 @@ int nm_conv1d_block_fwd_static(int B, int Cin, int Cout, int T, int K, int strid
  * it is per thread).  Arms a one-shot timer for the calling thread: the next entry-point call made by this
  * thread records `start_event` immediately before and `stop_event` immediately after a main convolution
  * kernel of that call, on the call's stream (helper kernels -- weight packing, the mask pass, the final dw
- * reduction -- stay outside the pair).  Which kernel: the first main kernel the call launches
+ * reduction -- stay outside the pair; the pass that adds up and finishes the parts of a convolution of few
+ * tiles counts with it).  Which kernel: the first main kernel the call launches
  * (nm_conv1d_time_next_main_kernel: the input-gradient kernel of an nm_conv1d_bwd call), or the main
  * kernel of pass `op` (nm_conv1d_time_next_kernel_of: NM_OP_FWD, NM_OP_BWD_DATA or NM_OP_BWD_WEIGHT; other
  * values return NM_ERR_BAD_ARG), which reaches the weight-gradient kernel inside nm_conv1d_bwd.  Both

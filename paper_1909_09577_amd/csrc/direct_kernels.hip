@@ -1,6 +1,9 @@
 // Plain one-thread-per-output kernels for the conv1d sub-block (any stride, dilation,
-// padding; float or bfloat16 storage; float32 arithmetic).  They serve the float32
-// mode where NM_FORCE_DIRECT asks for them or a layer is too small, too wide or strided, and every geometry the matrix-core kernels do not cover.  The sums are taken
+// padding; float or bfloat16 storage; float32 arithmetic).  They serve NM_FORCE_DIRECT and
+// every call that the matrix-core kernels do not cover: in float32 layers that are too
+// small or too wide and strided input gradients, in bfloat16 misaligned tensors, strides
+// from 3 on (input gradients: 16-byte rows of T = 16n + 8 at stride 2), the smallest calls
+// on rows of other lengths and such rows without a workspace for their copies.  The sums are taken
 // in short float32 blocks that are then added together, which keeps the rounding
 // error of an n-term sum near sqrt(n)^(1/2) ulp instead of sqrt(n) ulp.
 #include "nm_common.h"

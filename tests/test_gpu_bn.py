@@ -28,7 +28,7 @@ def L(name, B, Cin, Cout, T, K, stride=1, dilation=1, pad=0, relu=True, residual
 
 CASES = [
     L("bn_small", 2, 8, 8, 40, 3, pad=1, residual=True),
-    L("bn_odd_len", 3, 12, 20, 37, 5, pad=2),                      # T % 8 != 0: element-wise passes, plain kernels
+    L("bn_odd_len", 3, 12, 20, 37, 5, pad=2),                      # T % 8 != 0: element-wise passes
     L("bn_ragged", 3, 72, 100, 336, 11, pad=5, residual=True),
     L("bn_k17", 4, 128, 192, 320, 17, pad=8, residual=True),
     L("bn_k1_proj", 2, 256, 384, 320, 1, relu=False),

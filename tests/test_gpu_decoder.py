@@ -37,7 +37,7 @@ def run(x, w, bias, dtype, force_direct):
 CASES = [  # B, Cin, Ncls, T
     (2, 64, 29, 96), (3, 1024, 29, 200), (1, 48, 5, 40), (2, 32, 32, 264), (1, 16, 1, 8),
     (2, 40, 29, 64),      # Cin % 16 != 0: plain kernel
-    (2, 64, 29, 50),      # T % 8 != 0: plain kernel
+    (2, 64, 29, 50),      # T % 8 != 0: rows of any length
     (1, 64, 70, 64),      # more than 32 classes: plain kernel
 ]
 

@@ -66,7 +66,7 @@ SMALL = [
 # Medium: several 64x160 tiles with ragged tails in every dimension (oracle: a few seconds each).
 MEDIUM = [
     L("m_ragged", 3, 72, 100, 336, 11, pad=5, residual=True),
-    L("m_odd_len", 2, 40, 48, 333, 7, pad=3, residual=True),      # T % 8 != 0: plain kernels
+    L("m_odd_len", 2, 40, 48, 333, 7, pad=3, residual=True),      # T % 8 != 0: copies in 16-byte rows
     L("m_two_tiles", 2, 128, 192, 320, 17, pad=8, residual=True),
     L("m_dil2", 2, 96, 80, 248, 9, dilation=2, pad=8),
     L("m_pad_not_same", 2, 64, 64, 176, 5, pad=6),               # T_out = T + 8
@@ -127,8 +127,6 @@ def check_layer(cfg, dtype, force_direct):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("cfg", SMALL, ids=lambda c: c.name)
 def test_small_shapes_full_tensor(cfg, dtype, force_direct):
-    if dtype == "f32" and not force_direct:
-        pytest.skip("float32 storage always takes the plain kernels")
     check_layer(cfg, dtype, force_direct)
 
 
@@ -136,8 +134,6 @@ def test_small_shapes_full_tensor(cfg, dtype, force_direct):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("cfg", MEDIUM + [syn.TINY], ids=lambda c: c.name)
 def test_medium_shapes_full_tensor(cfg, dtype, force_direct):
-    if dtype == "f32" and not force_direct:
-        pytest.skip("float32 storage always takes the plain kernels")
     check_layer(cfg, dtype, force_direct)
 
 
@@ -288,7 +284,7 @@ def test_full_size_f32_mode_sampled():
 
 
 def check_f32_sampled(cfg, n_act, n_w, seed):
-    """float32 storage (plain kernels), sampled outputs against the oracle at the 1e-5 gate."""
+    """float32 storage on the plain kernels, sampled outputs against the oracle at the 1e-5 gate."""
     dtype = "f32"
     rng = np.random.default_rng(seed)
     inp = syn.make_inputs(cfg, dtype)
@@ -339,9 +335,9 @@ def test_pure_gradients_without_epilogue_and_accumulate():
 @pytest.mark.parametrize("cfg", [
     L("acc_k1_proj", 2, 256, 384, 320, 1, relu=False),                   # a residual projection: the K=1 kernel
     L("acc_k1_few_outputs", 2, 200, 29, 328, 1, affine=False, relu=False),  # the store-bound kernel does not accumulate: the GEMM kernel takes it
-    L("acc_k11", 2, 72, 100, 336, 11, pad=5, residual=True),             # unrolled engine, ragged channel tiles
-    L("acc_k5", 2, 64, 64, 176, 5, pad=2),                               # tap-pair engine
-    L("acc_odd_len", 2, 40, 48, 333, 7, pad=3),                          # plain kernels
+    L("acc_k11", 2, 72, 100, 336, 11, pad=5, residual=True),             # engine for few tiles, ragged channel tiles
+    L("acc_k5", 2, 64, 64, 176, 5, pad=2),                               # the same, one column of tiles
+    L("acc_odd_len", 2, 40, 48, 333, 7, pad=3),                          # copies in 16-byte rows
     L("acc_stride2", 2, 64, 96, 400, 11, stride=2, pad=5),               # stride 2: accumulation on the plain kernel
 ], ids=lambda c: c.name)
 def test_input_gradient_accumulation(cfg):
@@ -427,7 +423,7 @@ FUSED = [
     L("f_two_tiles", 2, 128, 192, 320, 17, pad=8, residual=True),
     L("f_dil2", 2, 96, 80, 248, 9, dilation=2, pad=8),
     L("f_no_epilogue", 2, 64, 64, 176, 5, pad=6, affine=False, relu=False),  # dz = dy: two calls inside
-    L("f_odd_len", 2, 40, 48, 333, 7, pad=3, residual=True),         # plain kernels: two calls inside
+    L("f_odd_len", 2, 40, 48, 333, 7, pad=3, residual=True),         # copies in 16-byte rows: one pass over dy
     L("f_stride2", 2, 64, 96, 400, 11, stride=2, pad=5),
     L("f_k1", 3, 136, 200, 336, 1, residual=True),                   # K=1: the input gradient's g feeds the weight-gradient GEMM
     L("f_k1_no_relu", 2, 320, 264, 88, 1, relu=False),               # K=1 without a mask pass: g is dy

@@ -25,7 +25,7 @@ CASES = [
     L("s_dil2", 1, 256, 136, 144, 29, dilation=2, pad=28),               # the longest window
     L("s_k1", 2, 384, 512, 192, 1, relu=False),                          # half of the wavefronts idle
     L("s_k2", 1, 160, 192, 64, 2, pad=1),
-    L("s_short", 2, 256, 256, 16, 11, pad=5, residual=True),             # shorter than a tile
+    L("s_short", 2, 1024, 64, 16, 11, pad=5, residual=True),             # shorter than a tile; many parts
 ]
 
 

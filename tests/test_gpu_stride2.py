@@ -12,6 +12,11 @@ from paper_1909_09577_amd.inputs import LayerCfg
 CASES = [(3, 64, 256, T, K, pad) for T, K, pad in [
     (123, 11, 5), (122, 11, 4), (121, 10, 5), (160, 12, 0), (336, 11, 5), (9, 2, 1), (65, 3, 0), (64, 5, 7), (331, 7, 12)]]
 CASES += [(2, 40, 72, 97, 11, 5), (20, 64, 256, 1002, 11, 5)]
+# the engine for few tiles on the parities' contraction, in one part and in several, rows of any length (sums of 700 terms or
+# more: of 95, weights rounded to bfloat16 put the largest of 2.5 million elements past the gate, 1.01e-2)
+IN_SPLIT = {(27, 33, 129, 1229, 11, 5): "conv_split_kernel<3, 1> in 1 parts", (6, 33, 890, 199, 11, 5): "conv_split_kernel<4, 1> in 16 parts",
+            (2, 24, 652, 163, 11, 5): "conv_split_kernel<2, 1> in "}
+CASES += list(IN_SPLIT)
 
 
 @pytest.mark.gpu
@@ -20,6 +25,9 @@ CASES += [(2, 40, 72, 97, 11, 5), (20, 64, 256, 1002, 11, 5)]
 def test_stride2_gradients(case, masked):
     import torch
     B, Cin, Cout, T, K, pad = case
+    if case in IN_SPLIT:
+        name = nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_DATA, B, Cin, Cout, T, K, 2, 1, pad, flags=nm.NM_RELU, masked=masked)
+        assert name.startswith(IN_SPLIT[case]), name
     cfg = LayerCfg("stride2", B, Cin, Cout, T, K, 2, 1, pad, True, True, True, 47, T_out=orc.out_len(T, K, 2, 1, pad))
     inp = syn.make_inputs(cfg, "bf16")
     kw = U.geom_kw(cfg)
@@ -43,6 +51,7 @@ def test_stride2_gradients(case, masked):
     dw = nm.nm_conv1d_bwd_weight(x, dy, K, y=ysv, scale=scale, relu=True, lengths=ld, **kw)
     dx2, dres2, dw2 = nm.nm_conv1d_bwd(x, dy, w, y=ysv, scale=scale, want_dres=True, relu=True, lengths=ld, **kw)
     assert torch.equal(dx2, dx) and torch.equal(dres2, dres1) and torch.equal(dw2, dw)
+    U.assert_close(U.to_host_f64(dw), orc.bwd_weight_masked(inp["x"], dz, K, lens, **kw), "bf16", "dw", rms_bound=U.RMS_DW_BF16)
     if B * T < 2000:
         small = torch.empty((2 * dy.numel() + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
         dx3, _ = nm.nm_conv1d_bwd_data(dy, w, T, y=ysv, scale=scale, relu=True, lengths=ld, workspace=small, **kw)

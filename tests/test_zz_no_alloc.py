@@ -20,11 +20,11 @@ def L(name, B, Cin, Cout, T, K, stride=1, dilation=1, pad=0, affine=True, relu=T
 
 
 # first a layer that fills several tiles (packed weights: 2.4 MB of the 32 MiB array), then a smaller one
-# with another tap count, then one on the plain kernels (odd length: no scratch at all)
+# with another tap count, then one of odd length (weights and a copy of x)
 CASES = [
     L("na_big", 4, 256, 256, 480, 17, pad=8, residual=True),
     L("na_small", 2, 72, 100, 176, 11, pad=5, residual=True),
-    L("na_plain", 2, 40, 48, 333, 7, pad=3),
+    L("na_odd", 2, 40, 48, 333, 7, pad=3),
 ]
 
 
