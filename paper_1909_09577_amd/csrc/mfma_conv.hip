@@ -79,10 +79,10 @@ struct ConvGemmParams {
     bf16_t *out;            // [B][M][Tout]
     int nsplit;             // conv_split_kernel: parts the reduction channels are split into
     f32x4 *part;            // their partial sums (nsplit > 1)
-    int col0, ncols;        // the columns (time tiles of all batch items) of this launch
-    int odd_rows;           // rows of in or out are no multiple of 16 bytes long (host: which instances serve the call)
     double *stats;          // optional [B*ntt][M][3]: count, mean and centred second moment of the stored outputs of
                             // every (batch item, time tile, channel) -- the partial statistics of a BatchNorm over out
+    int col0, ncols;        // conv_split_kernel: the columns (time tiles of all batch items) of this launch
+    int odd_rows;           // rows of in or out are no multiple of 16 bytes long (host: which instances serve the call)
 };
 
 __device__ __forceinline__ void wave_lds_fence()
