@@ -324,7 +324,8 @@ struct TileCoords {
 // LEN: the instance for ragged calls (per-sample lengths); of the unrolled kernels it
 // alone carries the test for tiles in the padding.
 // STATS: the instance that also writes the per-tile statistics of its stored outputs (ConvGemmParams::stats).
-// ANYROW: rows of any length (the test for output rows of that kind costs the other calls of few tiles about 1 %).
+// ANYROW: rows of any length (the test for output rows of that kind costs the other calls of few tiles about 1 %;
+// conv_split_kernel and the K=1 kernel's instance for lengths make it at run time).
 // PADPAIR: of the tap-pair kernels' ANYROW instances, the one where a wavefront may have an odd number of tap pairs (see do_pair).
 template <int NT, int STRIDE, int KT, bool LEN = false, bool STATS = false, bool ANYROW = false, bool PADPAIR = false>
 __global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParams p)
