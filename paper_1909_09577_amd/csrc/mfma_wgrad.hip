@@ -1031,9 +1031,10 @@ __device__ __forceinline__ float defined_dw(const Geom &g, const DefinedDw &q, i
 }
 
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci]; one block per (co, 64 ci).
-// MEND: the instance that makes NaN sums again from the tensors of DefinedDw.  Eight parts are requested at a time: one
-// after the other, 16 parts of 64 -> 256 channels, K=11, took 15 us.
-template <bool MEND>
+// MEND: the instance that makes NaN sums again from the tensors of DefinedDw.  MANY: the instance for eight parts and more,
+// which requests eight at a time (one after the other, 16 parts of 64 -> 256 channels, K=11, took 15 us, 6 so); for fewer it
+// only costs registers (one part of 1024 -> 512 channels, K=17: 55.6 us for the gradient, 60.5 with it).
+template <bool MEND, bool MANY>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                            const float *__restrict__ scale, int S, int K, int Cout,
                                                            int Cin, int accumulate, const Geom own, const DefinedDw defined)
@@ -1049,7 +1050,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
         float s = 0.f;
         if (ci < Cin) {
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
-#pragma unroll 8
+#pragma unroll MANY ? 8 : 1
             for (int sp = 0; sp < S; ++sp) s += src[(size_t)sp * K * plane];
             if (MEND && __builtin_expect(s != s, 0)) s = defined_dw(own, defined, co, ci, k);
         }
@@ -1069,7 +1070,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
 // The same for Cin % 4 == 0 and 16-byte aligned dw: one block per (co, 256 ci), 16-byte loads along ci
 // (a wavefront reads 1 KiB contiguous per partial row) and 16-byte stores of the transposed tile.
 constexpr int kReduce4Ci = 256;
-template <bool MEND>
+template <bool MEND, bool MANY>
 __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                             const float *__restrict__ scale, int S, int K, int Cout,
                                                             int Cin, int accumulate, const Geom own, const DefinedDw defined)
@@ -1085,7 +1086,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restr
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
         if (ci < Cin) {
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
-#pragma unroll 8
+#pragma unroll MANY ? 8 : 1
             for (int sp = 0; sp < S; ++sp) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)sp * K * plane);
             if constexpr (MEND) {
                 const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);  // a NaN if one of them is
@@ -1317,13 +1318,15 @@ hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, cons
     const DefinedDw d = mend ? *defined : DefinedDw{};
     if (g.Cin % 4 == 0 && ((uintptr_t)dw % 16) == 0 && (size_t)kReduce4Ci * (g.K + 1) * sizeof(float) <= 64 * 1024) {
         dim3 grid4((g.Cin + kReduce4Ci - 1) / kReduce4Ci, g.Cout);
-        hipLaunchKernelGGL(mend ? wgrad_reduce4_kernel<true> : wgrad_reduce4_kernel<false>, grid4, dim3(256),
-                           kReduce4Ci * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
+        auto kern = S >= 8 ? (mend ? wgrad_reduce4_kernel<true, true> : wgrad_reduce4_kernel<false, true>)
+                           : (mend ? wgrad_reduce4_kernel<true, false> : wgrad_reduce4_kernel<false, false>);
+        hipLaunchKernelGGL(kern, grid4, dim3(256), kReduce4Ci * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
         return hipGetLastError();
     }
     dim3 rgrid((g.Cin + 63) / 64, g.Cout);
-    hipLaunchKernelGGL(mend ? wgrad_reduce_kernel<true> : wgrad_reduce_kernel<false>, rgrid, dim3(256),
-                       64 * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
+    auto kern = S >= 8 ? (mend ? wgrad_reduce_kernel<true, true> : wgrad_reduce_kernel<false, true>)
+                       : (mend ? wgrad_reduce_kernel<true, false> : wgrad_reduce_kernel<false, false>);
+    hipLaunchKernelGGL(kern, rgrid, dim3(256), 64 * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
     return hipGetLastError();
 }
 
