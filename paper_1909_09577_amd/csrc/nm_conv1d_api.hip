@@ -148,12 +148,13 @@ bool tiny(int op, const Geom &g, int dtype)
         const double plain = 7.0 + 0.08 * g.B * g.To + 0.6e-6 * products;
         const bool gemm = g.K == 1 && g.stride == 1 && g.Cin >= 64 && g.Cout >= 64;
         const double base = dtype == NM_F32 ? 10.5 : gemm ? 17.0 : g.stride == 1 ? 13.0 : 12.0;
-        return plain < base + 0.7 * (g.K < 14 ? g.K : 14);
+        const int most_taps = dtype == NM_F32 ? 24 : 14;  // what a tap adds to the matrix-core kernels' time, up to here
+        return plain < base + 0.7 * (g.K < most_taps ? g.K : most_taps);
     }
     const long chain = (long)(op == NM_OP_FWD ? g.Cin : g.Cout) * g.K;
     const int rows = op == NM_OP_FWD ? g.Cout : g.Cin;
     if (g.K == 1 && g.stride == 1 && g.pad == 0 && rows > 64 && g.To > 64) return chain <= (op == NM_OP_FWD ? 40 : 24);  // the GEMM kernel
-    if (op == NM_OP_FWD) return 5.0 + 0.3 * chain + 0.4e-6 * products < 9.3;
+    if (op == NM_OP_FWD) return 5.0 + 0.3 * chain + 0.4e-6 * products < (g.K == 1 && g.stride == 1 && g.To > 64 ? 12.5 : 9.3);
     return chain <= (g.stride == 2 ? 22 : g.K == 1 ? 12 : g.K >= 11 ? 16 : 10);
 }
 
