@@ -1812,6 +1812,7 @@ Plan make_plan(int Tin, int Tout, int R, int K, int stride, int dil)
 constexpr int kSplitRounds = 4;
 struct SplitPlan {
     int nt, nsplit, ngroups;  // nt = 0: another engine
+    double gain;              // estimated, against that
     size_t lds, part_bytes, col_bytes;  // parts of all columns, of one
 };
 
@@ -1829,7 +1830,7 @@ double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
     if (K == 1 && nmt >= 2 && pl.nt == 5 && pl.stride == 1) {  // pointwise_gemm_kernel, its two tiles
         const long tiles = (long)((nmt + 3) / 4) * ((Tout + 159) / 160) * B;
         const long tiles_big = (long)((nmt + 7) / 8) * ((Tout + 127) / 128) * B;
-        const double a = (double)((tiles + cus - 1) / cus) * (5.6 * ((R + 127) / 128) + 2.9);
+        const double a = (double)((tiles + cus - 1) / cus) * (3.0 * ((R + 127) / 128) + 4.0);
         const double c = (double)((tiles_big + cus - 1) / cus) * (1.7 * ((R + 63) / 64) + 2.5);
         return a < c ? a : c;
     }
@@ -1873,6 +1874,7 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
             if (col_bytes > 0 && split_rounds(wgs / (unsigned)(nmt * ns), col_bytes, part_limit) > most_rounds) continue;
             best_cost = cost;
             best_on_device = on_device;
+            best.gain = engine_cost(pl, B, M, R, Tout, K) - cost;
             best.nt = nt;
             best.nsplit = ns;
             best.ngroups = (int)((rows + 7) / 8);
@@ -2256,13 +2258,16 @@ bool mfma_fwd_supported(const Geom &g)
 
 size_t mfma_fwd_workspace_least(const Geom &g) { return packed_bytes(g.Cout, g.Cin, g.K) + pitched_x_bytes(g); }
 namespace {
+// Where the best plan's parts do not fit: a plan in fewer, else another engine (a plan in one part is close to that, and the
+// estimates are not close enough to tell: 896 -> 16 channels, K=29, B=2, T=304 83 us in one part, 75 there).
+SplitPlan in_parts(const SplitPlan &sp) { return sp.nsplit > 1 ? sp : SplitPlan{}; }
 // the plan with ws_bytes of workspace; in_rounds: that of a call with the workspace it asks for, whatever the room
 SplitPlan fwd_split_plan(const Geom &g, const Plan &pl, size_t ws_bytes, bool in_rounds = false)
 {
     const size_t least = mfma_fwd_workspace_least(g), room = ws_bytes > least ? ws_bytes - least : 0;
     const bool array = least <= NM_STATIC_SCRATCH_BYTES;
     const SplitPlan sp = split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, array ? NM_STATIC_SCRATCH_BYTES - least : kNoLimit, kSplitRounds);
-    return sp.part_bytes <= room || in_rounds ? sp : split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, room);
+    return sp.part_bytes <= room || in_rounds ? sp : in_parts(split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, room));
 }
 }  // namespace
 size_t mfma_fwd_workspace(const Geom &g)
@@ -2278,7 +2283,9 @@ int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes)
     const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !pl.unrolled || pl.nt != 5 || g.len || !mfma_fwd_supported(g)) return 0;
     if (pl.buf_bytes < Epilogue<5>::kTileBytesWithStats) return 0;
-    if (fwd_split_plan(g, pl, ws_bytes).nt) return 0;  // few tiles: z is small and read again instead
+    // few tiles: z is small and read again instead, where the engine for those saves more than that takes
+    const SplitPlan sp = fwd_split_plan(g, pl, ws_bytes);
+    if (sp.nt && sp.gain > 3.0) return 0;
     return g.B * ((g.To + 159) / 160);
 }
 
@@ -2393,7 +2400,7 @@ SplitPlan dgrad_split_plan(const Geom &g, const Plan &pl, size_t ws_bytes)
                              : split_plan(pl, g.B, g.Cin, g.Cout, g.T, g.K, g.dil, limit);
     };
     const SplitPlan sp = plan(kNoLimit);
-    return sp.part_bytes <= room ? sp : plan(room);
+    return sp.part_bytes <= room ? sp : in_parts(plan(room));
 }
 }  // namespace
 size_t mfma_dgrad_workspace(const Geom &g)
