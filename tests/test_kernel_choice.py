@@ -111,3 +111,18 @@ def test_plans_in_parts_are_ranked_by_their_estimate():
     And a K=1 call whose other engine was estimated too high: 44 us there, 58 in the engine for few tiles."""
     assert nm.nm_conv1d_kernel_name(FWD, 1, 384, 384, 600, 13, 1, 1, 6).startswith("conv_split_kernel<2, 1>")
     assert nm.nm_conv1d_kernel_name(DGRAD, 23, 896, 64, 1496, 1) .startswith("pointwise_gemm_kernel<false")
+
+
+def test_a_plan_in_one_part_is_no_way_out_of_a_small_workspace():
+    """896 -> 16 channels, K=29: with the room of the weights alone the call goes to the other engine."""
+    dims = (2, 896, 16, 304, 29, 1, 1, 14)
+    least = (1 * 28 * 30 * 256 + 512) * 16
+    assert least < nm.nm_conv1d_workspace_bytes(FWD, *dims)
+    assert nm.nm_conv1d_kernel_name(FWD, *dims, workspace_bytes=least).startswith("conv_gemm_kernel<")
+    assert nm.nm_conv1d_kernel_name(FWD, *dims).startswith("conv_split_kernel<")
+
+
+def test_smallest_calls_run_on_the_plain_kernels():
+    assert nm.nm_conv1d_kernel_name(FWD, 9, 16, 64, 68, 1) == "direct_fwd_kernel"
+    assert nm.nm_conv1d_kernel_name(WGRAD, 7, 256, 16, 47, 21, 3, 1, 10, dtype=nm.NM_F32) == "direct_wgrad_kernel"
+    assert nm.nm_conv1d_kernel_name(FWD, 4, 256, 256, 400, 11, 1, 1, 5) != "direct_fwd_kernel"
