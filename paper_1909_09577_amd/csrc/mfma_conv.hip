@@ -31,7 +31,7 @@
 // straight-line block of 4*NT*KT MFMAs with every load, LDS write and wait placed between them;
 // for any other K (KT == 0) tap pairs run in a loop with staging in out-of-line blocks.
 #include "../../include/nm_conv1d.h"
-#include "nm_common.h"
+#include "conv_tile.h"
 
 #include <stdio.h>
 #include <string.h>
@@ -42,278 +42,6 @@
 
 namespace nm {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kWaves = 4;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kTileM = 64;       // output channels per tile
-constexpr int kChunk = 32;       // reduction channels per staged chunk
-constexpr int kRowBytes = 80;    // LDS row: 32 channels * 2 B + 16 B pad (bank-conflict-free 16 B reads)
-constexpr int kRowDwords = kRowBytes / 4;
-constexpr int kDumpRows = 8;     // rows at the end of a staging buffer that absorb idle staging writes
-constexpr int kMaxLds = 160 * 1024;
-
-struct ConvGemmParams {
-    int B, M, R, Tin, Tout, K, Kp, dil, padL;  // Kp: K rounded up to even (packed weights)
-    int nmt, nch, ntt, num_tiles;
-    int nitems;      // staging items per lane and chunk = ceil(rows/8 * 16 / 64)
-    int buf_bytes;   // bytes of one staging buffer: (nitems*32 + kDumpRows) rows of kRowBytes
-    int overlap;     // the next tile's first chunk is staged during the current tile
-    int full;        // tiles every wavefront computes on its own, over the whole reduction, before the shared ones
-    int relu;
-    const bf16_t *in;       // [B][R][Tin]
-    const int *len_in;      // [B] valid input lengths (samples beyond read as zero) or NULL
-    const int *len_out;     // [B] lengths beyond which the output is written as zero, or NULL; the limit of
-    int len_out_div;        // batch item b is ceil(len_out[b] / div) (2: both parities of a strided gradient)
-    const bf16x8 *wp;       // packed weights
-    size_t wp_bytes;        // size of the packed weights including the zero pair (< 2 GiB)
-    size_t wp_zero;         // offset (in fragments of 16 bytes) of one tap pair of zero weights
-    const float *scale;     // epilogue (may be NULL)
-    const float *shift;     // epilogue (may be NULL)
-    const bf16_t *res;      // epilogue (may be NULL)
-    bf16_t *out;            // [B][M][Tout]
-    int nsplit;             // conv_split_kernel: parts the reduction channels are split into
-    f32x4 *part;            // their partial sums (nsplit > 1)
-    double *stats;          // optional [B*ntt][M][3]: count, mean and centred second moment of the stored outputs of
-                            // every (batch item, time tile, channel) -- the partial statistics of a BatchNorm over out
-    int col0, ncols;        // conv_split_kernel: the columns (time tiles of all batch items) of this launch
-    int odd_rows;           // rows of in or out are no multiple of 16 bytes long (host: which instances serve the call)
-};
-
-__device__ __forceinline__ void wave_lds_fence()
-{
-    // LDS operations of one wavefront execute in order; this only stops the compiler from
-    // moving LDS accesses across the point where other lanes' data must be visible.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Buffer offset beyond any tensor this engine accepts (the host limits them to 1 GiB): the load
-// returns zeros.  Small additions to it neither wrap nor come back into range.
-constexpr uint32_t kOutOfRange = 0x80000000u;
-
-// The lane number, recomputed where it is needed.  The staging code runs once per chunk inside a
-// loop whose registers are all taken; values derived from a long-lived lane id would be spilled
-// and their reload would wait for every load in flight.  Two ALU operations avoid that.
-__device__ __forceinline__ int fresh_lane()
-{
-    int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    asm volatile("" : "+v"(l));
-    return l;
-}
-
-// f(integral_constant<0>), f(integral_constant<1>), ... in order
-template <class F, int... Is>
-__device__ __forceinline__ void for_each_index(F &&f, std::integer_sequence<int, Is...>)
-{
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-
-// Staging items the unrolled kernel built for K taps keeps in registers; 0: no such kernel.
-__host__ __device__ constexpr int unrolled_slots(int K) { return K == 29 ? 7 : (K == 11 || K == 13 || K == 17 || K == 21 || K == 25) ? 6 : 0; }
-
-// ---- epilogue shared by the engines of this file ------------------------------------------------
-// The sums leave the accumulators through a wave-private LDS tile [16 rows][NT*32] (float32) so that
-// each lane finishes 8 consecutive time steps of one channel: one 16-byte residual load, one scale,
-// one shift, one 16-byte store per item.  All of these are buffer accesses without branches: absent
-// operands have empty descriptors and read zeros, masked lanes go out of range.  That needs 16-byte
-// aligned rows of out and res; the ANYROW instances also serve rows of any length (`anyrow`): the same
-// items through 16-byte global accesses at 2-byte aligned addresses, element by element for the group
-// that holds the end of a row.
-template <int NT>
-struct Epilogue {
-    static constexpr int TN = NT * 32;
-    static constexpr int kItems = NT;  // 16 rows * (TN/8) groups / 64 lanes
-    __amdgpu_buffer_rsrc_t rs_out, rs_res, rs_scale, rs_shift;
-    int M, Tout;
-    bool has_scale, relu, anyrow;
-    bf16_t *out_p;        // (anyrow) the tensors themselves
-    const bf16_t *res_p;
-    const int *len_out;  // optional [B]: outputs at t >= ceil(len_out[b] / div) are written as zero
-    int len_div;
-    double *stats;       // see ConvGemmParams::stats (used by the STATS instances only)
-    static constexpr int kStatsOffset = 16 * TN;  // float2 [16 rows][TN/8] behind the tile (in floats)
-    static constexpr int kTileBytesWithStats = 16 * TN * (int)sizeof(float) + 16 * (TN / 8) * 2 * (int)sizeof(float);
-
-    struct RowLoads {
-        u32x4 rvec[kItems];
-        float scv[kItems], shv[kItems];
-        uint32_t ooff[kItems];
-        int tlim_rel;  // output limit of the batch item relative to the tile's first time step (wave-uniform)
-        int tout_rel;  // the same of the row's end
-    };
-    // first time step of batch item b that is written as zero (Tout without lengths)
-    __device__ __forceinline__ int out_limit(int b) const
-    {
-        if (!len_out) return Tout;
-        const int n = (len_out[b] + len_div - 1) / len_div;
-        return n < 0 ? 0 : (n > Tout ? Tout : n);
-    }
-
-    __device__ __forceinline__ void init(const bf16_t *out, const bf16_t *res, const float *scale, const float *shift, int B,
-                                         int M_, int Tout_, int relu_, const int *len_out_ = nullptr, int div = 1,
-                                         double *stats_ = nullptr)
-    {
-        stats = stats_;
-        len_out = len_out_;
-        len_div = div < 1 ? 1 : div;
-        const int out_bytes = (int)((size_t)B * M_ * Tout_ * 2);
-        M = M_;
-        Tout = Tout_;
-        has_scale = scale != nullptr;
-        relu = relu_ != 0;
-        anyrow = Tout_ % 8 != 0;
-        out_p = const_cast<bf16_t *>(out);
-        res_p = res;
-        rs_out = __builtin_amdgcn_make_buffer_rsrc((void *)out, 0, out_bytes, 0x00020000);
-        rs_res = __builtin_amdgcn_make_buffer_rsrc((void *)res, 0, res ? out_bytes : 0, 0x00020000);
-        rs_scale = __builtin_amdgcn_make_buffer_rsrc((void *)scale, 0, scale ? M_ * 4 : 0, 0x00020000);
-        rs_shift = __builtin_amdgcn_make_buffer_rsrc((void *)shift, 0, shift ? M_ * 4 : 0, 0x00020000);
-    }
-    // operands of the 16 tile rows whose first channel is m0 (tile row r is channel m0 + r, or
-    // m0 + 32*(r/8) + r%8 when `split`: eight rows from each row of blocks); el: the lane number
-    template <bool ANYROW = false>
-    __device__ __forceinline__ RowLoads request_rows(int el, int b, int t0, int m0, bool split) const
-    {
-        RowLoads ld;
-        ld.tlim_rel = out_limit(b) - t0;
-        ld.tout_rel = Tout - t0;
-#pragma unroll
-        for (int q = 0; q < kItems; ++q) {
-            const int idx = el + 64 * q;
-            const int r = idx / (TN / 8), c8 = idx - r * (TN / 8);
-            const int m = m0 + (split ? (r >> 3) * 32 + (r & 7) : r);
-            const int t = t0 + c8 * 8;
-            const bool ok = m < M && t < Tout;
-            ld.ooff[q] = ok ? (uint32_t)((((size_t)b * M + m) * Tout + t) * 2) : kOutOfRange;
-            const uint32_t moff = ok ? (uint32_t)m * 4u : kOutOfRange;
-            if (ANYROW && anyrow)
-                ld.rvec[q] = load8_any(res_p + ld.ooff[q] / 2, ok && res_p ? Tout - t : 0);
-            else
-                ld.rvec[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_res, ld.ooff[q], 0, 0);
-            ld.scv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_scale, moff, 0, 0));
-            ld.shv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_shift, moff, 0, 0));
-        }
-        return ld;
-    }
-    // affine, residual, ReLU, rounding and the stores of the 16 rows that sit in the LDS tile tp
-    template <bool STATS = false, bool ANYROW = false>
-    __device__ __forceinline__ void finish_rows(int el, float *tp, const RowLoads &ld) const
-    {
-#pragma unroll
-        for (int q = 0; q < kItems; ++q) {
-            const int idx = el + 64 * q;
-            const int r = idx / (TN / 8), c8 = idx - r * (TN / 8);
-            const f32x4 lo = *reinterpret_cast<const f32x4 *>(tp + r * TN + c8 * 8);
-            const f32x4 hi = *reinterpret_cast<const f32x4 *>(tp + r * TN + c8 * 8 + 4);
-            const float sc = has_scale ? ld.scv[q] : 1.f;
-            u32x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float a0 = (e < 2 ? lo[2 * e] : hi[2 * e - 4]), a1 = (e < 2 ? lo[2 * e + 1] : hi[2 * e - 3]);
-                float v0 = a0 * sc + ld.shv[q] + __uint_as_float(ld.rvec[q][e] << 16);
-                float v1 = a1 * sc + ld.shv[q] + __uint_as_float(ld.rvec[q][e] & 0xffff0000u);
-                if (relu) {
-                    v0 = v0 > 0.f ? v0 : 0.f;
-                    v1 = v1 > 0.f ? v1 : 0.f;
-                }
-                o[e] = pack_bf16x2(v0, v1);
-            }
-            if (len_out) {  // zeros from the output limit on (a uniform branch: nothing to do without lengths)
-                const int nvalid = ld.tlim_rel - c8 * 8;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] &= nvalid >= 2 * e + 2 ? 0xffffffffu : (nvalid == 2 * e + 1 ? 0x0000ffffu : 0u);
-            }
-            if (ANYROW && anyrow)
-                store8_any(out_p + ld.ooff[q] / 2, o, ld.ooff[q] != kOutOfRange ? ld.tout_rel - c8 * 8 : 0);
-            else
-                __builtin_amdgcn_raw_buffer_store_b128(o, rs_out, ld.ooff[q], 0, 0);
-            if constexpr (STATS) {  // sums of the eight stored (rounded) values; an item outside the tensor adds nothing
-                float s1 = 0.f, s2 = 0.f;
-                if (ld.ooff[q] != kOutOfRange) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float v0 = __uint_as_float(o[e] << 16), v1 = __uint_as_float(o[e] & 0xffff0000u);
-                        s1 += v0 + v1;
-                        s2 = fmaf(v0, v0, fmaf(v1, v1, s2));
-                    }
-                }
-                reinterpret_cast<f32x2 *>(tp + kStatsOffset)[idx] = f32x2{s1, s2};
-            }
-        }
-    }
-    // (STATS instances) after finish_rows<true> and a fence: lane r < 16 adds the TN/8 partial sums of tile row r in
-    // order and writes count, mean and centred second moment of that row's part of channel m_of_row
-    __device__ __forceinline__ void emit_row_stats(int el, const float *tp, int m_of_row, int part, int t0) const
-    {
-        if (el >= 16 || m_of_row >= M) return;
-        const f32x2 *sp = reinterpret_cast<const f32x2 *>(tp + kStatsOffset) + el * (TN / 8);
-        double a = 0.0, b2 = 0.0;
-#pragma unroll
-        for (int i = 0; i < TN / 8; ++i) {
-            const f32x2 v = sp[i];
-            a += (double)v[0];
-            b2 += (double)v[1];
-        }
-        const int left = Tout - t0;
-        const double n = (double)(left < TN ? (left > 0 ? left : 0) : TN);
-        double *o = stats + ((size_t)part * M + m_of_row) * 3;
-        o[0] = n;
-        o[1] = n > 0 ? a / n : 0.0;
-        o[2] = n > 0 ? b2 - a * a / n : 0.0;
-    }
-    // the 16 rows of a wavefront's quarter of a tile (eight from each row of blocks) to the LDS tile
-    __device__ __forceinline__ void put_quarter(float *tp, int el, const f32x4 (&own)[2][NT]) const
-    {
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int ni = 0; ni < NT; ++ni) tp[(mi * 8 + 4 * (el >> 5) + j) * TN + ni * 32 + (el & 31)] = own[mi][ni][j];
-    }
-    // A whole 64-row tile held by one wavefront (rows m_first .. m_first+63): four rounds of 16 rows
-    // (row of blocks mi, accumulator registers 8*gp .. 8*gp+7) through tp; the operands of a round
-    // are requested two rounds ahead.
-    template <bool STATS = false, bool ANYROW = false>
-    __device__ __forceinline__ void store_private_tile(const f32x16 (&acc)[2][NT], float *tp, int el, int b, int t0,
-                                                       int m_first, int part = 0) const
-    {
-        const int tcol = el & 31, thalf = el >> 5;
-        RowLoads ld[2] = {request_rows<ANYROW>(el, b, t0, m_first, false), request_rows<ANYROW>(el, b, t0, m_first + 16, false)};
-#pragma unroll
-        for (int rd = 0; rd < 4; ++rd) {
-            const int mi = rd >> 1, gp = rd & 1;
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = g * 8 + 4 * thalf + j;
-#pragma unroll
-                    for (int ni = 0; ni < NT; ++ni) tp[r * TN + ni * 32 + tcol] = acc[mi][ni][4 * (2 * gp + g) + j];
-                }
-            wave_lds_fence();
-            finish_rows<STATS, ANYROW>(el, tp, ld[rd & 1]);
-            if (rd + 2 < 4) ld[rd & 1] = request_rows<ANYROW>(el, b, t0, m_first + (rd + 2) * 16, false);
-            wave_lds_fence();
-            if constexpr (STATS) emit_row_stats(el, tp, m_first + rd * 16 + el, part, t0);
-        }
-    }
-};
-
-// valid length of batch item b from an optional device array, clipped to [0, T]
-__device__ __forceinline__ int clipped_len(const int *len, int b, int T)
-{
-    if (!len) return T;
-    const int n = len[b];
-    return n < 0 ? 0 : (n > T ? T : n);
-}
 
 struct TileCoords {
     int mt, b, t0, ws_al, off0;
@@ -1813,6 +1541,7 @@ constexpr int kSplitRounds = 4;
 struct SplitPlan {
     int nt, nsplit, ngroups;  // nt = 0: another engine
     double gain;              // estimated, against that
+    double device;            // estimated time on the device
     size_t lds, part_bytes, col_bytes;  // parts of all columns, of one
 };
 
@@ -1874,6 +1603,7 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
             if (col_bytes > 0 && split_rounds(wgs / (unsigned)(nmt * ns), col_bytes, part_limit) > most_rounds) continue;
             best_cost = cost;
             best_on_device = on_device;
+            best.device = on_device;
             best.gain = engine_cost(pl, B, M, R, Tout, K) - cost;
             best.nt = nt;
             best.nsplit = ns;
@@ -1907,6 +1637,28 @@ SplitPlan split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, int d
         memcpy(t.key, key, sizeof key);
     }
     return t.plan;
+}
+
+// What a call on packed weights takes on the device, packing included (fitted to the 345 geometries of unpacked_plan; rms 7 %):
+// the engines' own estimates above, corrected, a launch of the packing (an input gradient's has a pass over dy in it that
+// stays), its bytes and, forward, a copy of rows that are no multiple of eight long.
+double packed_cost(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int Tin, int Tout, int K, bool flip)
+{
+    const double w = 2e-6 * M * R * K;
+    const double run = sp.nt ? 5.8 + 0.73 * sp.device : 3.7 + 0.99 * engine_cost(pl, B, M, R, Tout, K);
+    if (flip) return run + 4.0 + 0.73 * w;
+    return run + 4.9 + 0.43 * w + (Tin % 8 != 0 ? 1.0 + 2.4e-6 * B * R * Tin : 0.0);
+}
+// The plan on unpacked weights where it is the better one by more than the estimates err.  Chosen over those 345 (fewer than
+// one in a hundred of them slower, 14 % at most): 1.25 times as fast on average.
+UnpackedPlan better_unpacked(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int Tin, int Tout, int K, int dil, bool flip, size_t part_limit)
+{
+    if (!pl.ok || !unpacked_supported(M, R, K, pl.stride, flip)) return UnpackedPlan{};
+    const double most = 0.9 * packed_cost(pl, sp, B, M, R, Tin, Tout, K, flip);
+    // (whatever the plan, its multiplications spread evenly: most large calls need not be looked at any further)
+    if (10.7 + 0.69 * 0.0444 / 4 / 256 * ((M + kTileM - 1) / kTileM) * (R / 16) * (double)B * ((Tout + 31) / 32) * K > most) return UnpackedPlan{};
+    const UnpackedPlan up = unpacked_plan(B, M, R, Tout, K, dil, flip, part_limit);
+    return up.nt && up.cost < most ? up : UnpackedPlan{};
 }
 
 size_t packed_bytes(int M, int R, int K)
@@ -2006,7 +1758,7 @@ hipError_t launch_split_t(ConvGemmParams p, int cols_at_once, size_t lds, hipStr
     for (p.col0 = 0; p.col0 < cols; p.col0 += cols_at_once) {
         p.ncols = std::min(cols_at_once, cols - p.col0);
         hipLaunchKernelGGL((conv_split_kernel<NT, STRIDE>), dim3(p.nmt * p.ncols * p.nsplit), dim3(kThreads), lds, s, p);
-        if (p.nsplit > 1) hipLaunchKernelGGL(split_reduce_kernel, dim3(p.nmt * p.ncols * kWaves * NT), dim3(64), 0, s, p, NT);
+        if (p.nsplit > 1) (void)launch_split_reduce(p, NT, s);
     }
     return hipGetLastError();
 }
@@ -2248,6 +2000,12 @@ void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin
 
 }  // namespace
 
+hipError_t launch_split_reduce(const ConvGemmParams &p, int nt, hipStream_t s)
+{
+    hipLaunchKernelGGL(split_reduce_kernel, dim3(p.nmt * p.ncols * kWaves * nt), dim3(64), 0, s, p, nt);
+    return hipGetLastError();
+}
+
 // ---- forward ---------------------------------------------------------------------------
 bool mfma_fwd_supported(const Geom &g)
 {
@@ -2269,10 +2027,21 @@ SplitPlan fwd_split_plan(const Geom &g, const Plan &pl, size_t ws_bytes, bool in
     const SplitPlan sp = split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, array ? NM_STATIC_SCRATCH_BYTES - least : kNoLimit, kSplitRounds);
     return sp.part_bytes <= room || in_rounds ? sp : in_parts(split_plan(pl, g.B, g.Cout, g.Cin, g.To, g.K, g.dil, room));
 }
+// The same on unpacked weights.  The parts lie behind the room of a call on packed ones; nm_conv1d_block_fwd_static, whose
+// array has that room free, keeps them there, so the plan of a call it serves has parts of that size at most.
+UnpackedPlan fwd_unpacked_plan(const Geom &g, const Plan &pl, size_t ws_bytes, bool in_rounds = false)
+{
+    const size_t least = mfma_fwd_workspace_least(g), room = ws_bytes > least ? ws_bytes - least : 0;
+    const SplitPlan sp = fwd_split_plan(g, pl, ws_bytes, in_rounds);
+    auto plan = [&](size_t limit) { return better_unpacked(pl, sp, g.B, g.Cout, g.Cin, g.T, g.To, g.K, g.dil, false, limit); };
+    const UnpackedPlan up = plan(least <= NM_STATIC_SCRATCH_BYTES ? NM_STATIC_SCRATCH_BYTES : kNoLimit);
+    return up.part_bytes <= room || in_rounds ? up : plan(room);
+}
 }  // namespace
 size_t mfma_fwd_workspace(const Geom &g)
 {
-    return mfma_fwd_workspace_least(g) + fwd_split_plan(g, make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil), kNoLimit).part_bytes;
+    const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
+    return mfma_fwd_workspace_least(g) + std::max(fwd_split_plan(g, pl, kNoLimit).part_bytes, fwd_unpacked_plan(g, pl, kNoLimit).part_bytes);
 }
 
 // Whether the forward pass of this geometry runs on a kernel instance that can also write the statistics of its
@@ -2286,6 +2055,8 @@ int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes)
     // few tiles: z is small and read again instead, where the engine for those saves more than that takes
     const SplitPlan sp = fwd_split_plan(g, pl, ws_bytes);
     if (sp.nt && sp.gain > 3.0) return 0;
+    const UnpackedPlan up = fwd_unpacked_plan(g, pl, ws_bytes);
+    if (up.nt && packed_cost(pl, SplitPlan{}, g.B, g.Cout, g.Cin, g.T, g.To, g.K, false) - up.cost > 5.0) return 0;
     return g.B * ((g.To + 159) / 160);
 }
 
@@ -2299,6 +2070,25 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     if (skinny_fwd_supported(g) && ((uintptr_t)w % 16) == 0) return launch_skinny_fwd(g, x, w, scale, shift, res, y, relu, s);
     hipError_t e;
     const void *in = x;
+    const size_t least = mfma_fwd_workspace_least(g);
+    auto fill = [&](ConvGemmParams &p, int Tin) {
+        fill_common(p, pl, g.B, g.Cout, g.Cin, Tin, g.To, g.K, g.dil, g.pad, !rows16(g));
+        p.relu = relu ? 1 : 0;
+        p.in = (const bf16_t *)in;
+        p.len_in = g.len;
+        p.wp = (const bf16x8 *)ws;
+        p.scale = scale; p.shift = shift; p.res = (const bf16_t *)res;
+        p.out = (bf16_t *)y;
+        p.stats = stats;
+    };
+    if (!stats && ((uintptr_t)w % 16) == 0) {
+        const UnpackedPlan up = fwd_unpacked_plan(g, pl, ws_bytes, in_rounds);
+        if (up.nt) {
+            ConvGemmParams p = {};
+            fill(p, g.T);
+            return launch_unpacked_conv(up, p, w, false, nullptr, (unsigned char *)ws + (in_rounds ? 0 : least), s);
+        }
+    }
     if (g.T % 8 == 0) {
         e = run_prepack(w, ws, g.Cout, g.Cin, g.K, false, nullptr, s);
     } else {
@@ -2312,18 +2102,17 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
     }
     if (e != hipSuccess) return e;
     ConvGemmParams p = {};
-    fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad, !rows16(g));
-    p.relu = relu ? 1 : 0;
-    p.in = (const bf16_t *)in;
-    p.len_in = g.len;
-    p.wp = (const bf16x8 *)ws;
-    p.scale = scale; p.shift = shift; p.res = (const bf16_t *)res;
-    p.out = (bf16_t *)y;
-    p.stats = stats;
-    const size_t least = mfma_fwd_workspace_least(g);
+    fill(p, row_pitch(g.T));
     return launch_plan(pl, fwd_split_plan(g, pl, ws_bytes, in_rounds), p, s, (unsigned char *)ws + least, ws_bytes > least ? ws_bytes - least : 0);
 }
 
+namespace {
+void name_unpacked(const UnpackedPlan &up, int K, bool flip, char *name, size_t n)
+{
+    snprintf(name, n, "conv_split_kernel<%d, 1> in %d parts of unpacked weights: conv_unpacked_kernel<%d, %d, %s>", up.nt, up.nsplit, up.nt, K,
+             flip ? "true" : "false");
+}
+}  // namespace
 void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n)
 {
     if (skinny_fwd_supported(g)) {
@@ -2338,6 +2127,8 @@ void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_
     p.len_in = g.len;
     p.scale = &affine;
     if (stats && mfma_fwd_stats_parts(g, ws_bytes) > 0) p.stats = &some_stats;
+    const UnpackedPlan up = p.stats ? UnpackedPlan{} : fwd_unpacked_plan(g, pl, ws_bytes);
+    if (up.nt) return name_unpacked(up, g.K, false, name, n);
     name_conv(pl, fwd_split_plan(g, pl, ws_bytes), p, name, n);
 }
 
@@ -2402,12 +2193,26 @@ SplitPlan dgrad_split_plan(const Geom &g, const Plan &pl, size_t ws_bytes)
     const SplitPlan sp = plan(kNoLimit);
     return sp.part_bytes <= room ? sp : in_parts(plan(room));
 }
+UnpackedPlan dgrad_unpacked_plan(const Geom &g, const Plan &pl, size_t ws_bytes)
+{
+    if (g.stride != 1) return UnpackedPlan{};
+    const size_t least = mfma_dgrad_workspace_least(g), room = ws_bytes > least ? ws_bytes - least : 0;
+    const SplitPlan sp = dgrad_split_plan(g, pl, ws_bytes);
+    auto plan = [&](size_t limit) { return better_unpacked(pl, sp, g.B, g.Cin, g.Cout, row_pitch(g.To), g.T, g.K, g.dil, true, limit); };
+    const UnpackedPlan up = plan(kNoLimit);
+    return up.part_bytes <= room ? up : plan(room);
+}
 }  // namespace
+bool mfma_dgrad_unpacked(const Geom &g, const void *w, size_t ws_bytes)
+{
+    return g.stride == 1 && ((uintptr_t)w % 16) == 0 &&
+           dgrad_unpacked_plan(g, make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil), ws_bytes).nt != 0;
+}
 size_t mfma_dgrad_workspace(const Geom &g)
 {
     const Phases ph = g.stride == 2 ? phases_of_stride2(g) : Phases{};
     const Plan pl = g.stride == 2 ? make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1) : make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
-    return mfma_dgrad_workspace_least(g) + dgrad_split_plan(g, pl, kNoLimit).part_bytes;
+    return mfma_dgrad_workspace_least(g) + std::max(dgrad_split_plan(g, pl, kNoLimit).part_bytes, dgrad_unpacked_plan(g, pl, kNoLimit).part_bytes);
 }
 
 namespace {
@@ -2512,6 +2317,8 @@ void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name
     } else {
         pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
         fill_dgrad(p, pl, g, nullptr, nullptr, &dx, accumulate);
+        const UnpackedPlan up = dgrad_unpacked_plan(g, pl, ws_bytes);
+        if (up.nt) return name_unpacked(up, g.K, true, name, n);
     }
     name_conv(pl, dgrad_split_plan(g, pl, ws_bytes), p, name, n);
 }
@@ -2534,37 +2341,39 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
     // g = dy*[y>0] (exact in bf16) comes from one elementwise pass, which shares a launch with the weight
     // packing when it can use 16-byte accesses (To % 8 == 0 on this path; dres aligned); the affine
     // factor scale[co] is folded into the packed weights.
-    hipError_t e;
+    hipError_t e = hipSuccess;
     const void *gin = dy;
     void *gbuf = (unsigned char *)ws + packed_bytes(g.Cin, g.Cout, g.K);
+    const bool pack = !mfma_dgrad_unpacked(g, w, ws_bytes);
     if (g.To % 8 != 0) {
         const DzfLayout none = {};
-        e = launch_bwd_prepare(g, dy, y, scale, w, relu, ws, nullptr, none, dres, &gin, s);
+        e = launch_bwd_prepare(g, dy, y, scale, w, pack, relu, ws, nullptr, none, dres, &gin, s);
         if (e != hipSuccess) return e;
     } else if (!dres || ((uintptr_t)dres % 16) == 0) {
         const int M = g.Cin, R = g.Cout;  // the engine's roles for this pass
-        const PackGeom q = pack_geom(w, M, R, g.K, true);
+        PackGeom q = pack_geom(w, M, R, g.K, true);
+        if (!pack) q.blocks = 0, q.lds = 0;
         void *gout = dres ? dres : (relu ? gbuf : nullptr);
         const size_t n8 = gout ? (size_t)g.B * g.Cout * g.To / 8 : 0;
+        const unsigned blocks = q.blocks + (unsigned)((n8 + 255) / 256);
         static LdsOptIn opt_in;
         e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(dgrad_prepare_kernel), kMaxLds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(dgrad_prepare_kernel, dim3(q.blocks + (unsigned)((n8 + 255) / 256)), dim3(256), q.lds, s, q.blocks,
-                           (const bf16_t *)w, (u32x4 *)ws, M, R, g.K, q.nch, M * g.K, q.zero_off, q.vec, scale, n8,
-                           (const u32x4 *)dy, (const u32x4 *)y, relu ? 1 : 0, (u32x4 *)gout);
+        if (blocks)
+            hipLaunchKernelGGL(dgrad_prepare_kernel, dim3(blocks), dim3(256), q.lds, s, q.blocks,
+                               (const bf16_t *)w, (u32x4 *)ws, M, R, g.K, q.nch, M * g.K, q.zero_off, q.vec, scale, n8,
+                               (const u32x4 *)dy, (const u32x4 *)y, relu ? 1 : 0, (u32x4 *)gout);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (relu) gin = gout;
     } else {
-        e = run_prepack(w, ws, g.Cin, g.Cout, g.K, true, scale, s);
+        if (pack) e = run_prepack(w, ws, g.Cin, g.Cout, g.K, true, scale, s);
         if (e != hipSuccess) return e;
         e = mask_pass(g, dy, y, relu, gbuf, dres, &gin, s);
         if (e != hipSuccess) return e;
     }
     if (g_used) *g_used = gin;
-    ConvGemmParams p = {};
-    fill_dgrad(p, pl, g, gin, ws, dx, accumulate);
-    return launch_plan(pl, dgrad_split_plan(g, pl, ws_bytes), p, s, part, part_room);
+    return launch_mfma_dgrad_prepared(g, gin, scale, w, dx, accumulate, ws, ws_bytes, s);
 }
 
 // ---- fused backward -------------------------------------------------------------------------
@@ -2574,12 +2383,12 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
 // order (gf).  *g_plain receives the tensor the input-gradient engine has to contract.  Rows of any length: g is
 // always formed, pitched, in the workspace; gf is optional; x (optional) is copied to xp in the same launch.
 hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
-                              bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
+                              bool pack, bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
                               hipStream_t s, const void *x, void *xp)
 {
     if (!rows16(g)) {
         RowPrep a = {};
-        a.w = w;
+        a.w = pack ? w : nullptr;
         a.wp = ws;
         a.flip = true;
         a.rscale = scale;
@@ -2597,7 +2406,8 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
         return launch_prepare_rows(g, a, s);
     }
     const int M = g.Cin, R = g.Cout;  // the engine's roles for the input gradient
-    const PackGeom q = pack_geom(w, M, R, g.K, true);
+    PackGeom q = pack_geom(w, M, R, g.K, true);
+    if (!pack) q.blocks = 0, q.lds = 0;
     const size_t nfrag = (size_t)g.B * layout.ncm * ((layout.nst + 3) / 4);  // items of four fragments, one per wavefront
     void *gbuf = (unsigned char *)ws + packed_bytes(g.Cin, g.Cout, g.K);
     void *gout = dres ? dres : (relu ? gbuf : nullptr);
@@ -2611,14 +2421,16 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws, size_t ws_bytes,
-                                      hipStream_t s)
+hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, const float *scale, const void *w, void *dx, bool accumulate,
+                                      void *ws, size_t ws_bytes, hipStream_t s)
 {
     const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;
     ConvGemmParams p = {};
     fill_dgrad(p, pl, g, g_plain, ws, dx, accumulate);
     const size_t least = mfma_dgrad_workspace_least(g);
+    if (mfma_dgrad_unpacked(g, w, ws_bytes))
+        return launch_unpacked_conv(dgrad_unpacked_plan(g, pl, ws_bytes), p, w, true, scale, (unsigned char *)ws + least, s);
     return launch_plan(pl, dgrad_split_plan(g, pl, ws_bytes), p, s, (unsigned char *)ws + least, ws_bytes - least);
 }
 

@@ -373,15 +373,17 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g);
 // multiplies the float32 sums; defined: for rows of any length
 hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float *scale, float *dw, bool accumulate,
                                       void *ws, hipStream_t s, const DefinedDw *defined = nullptr);
-// packs the flipped weights times scale into ws (as launch_mfma_dgrad does) and, in the same launch, forms
+// packs the flipped weights times scale into ws (as launch_mfma_dgrad does; where `pack`) and, in the same launch, forms
 // g plain (into dres, else behind the packed weights in ws, else nowhere) and in fragment order (gf);
 // *g_plain: the tensor the input gradient contracts
 hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
-                              bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
+                              bool pack, bool relu, void *ws, void *gf, const DzfLayout &layout, void *dres, const void **g_plain,
                               hipStream_t s, const void *x = nullptr, void *xp = nullptr);
+// whether the input gradient of a call takes w as it lies in memory (ws_bytes: of its workspace): then nothing is packed
+bool mfma_dgrad_unpacked(const Geom &g, const void *w, size_t ws_bytes);
 // input gradient from a workspace prepared by launch_bwd_prepare
-hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, void *dx, bool accumulate, void *ws, size_t ws_bytes,
-                                      hipStream_t s);
+hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, const float *scale, const void *w, void *dx, bool accumulate,
+                                      void *ws, size_t ws_bytes, hipStream_t s);
 
 // ---- training-mode BatchNorm passes (bn_train.hip) ---------------------------------------------
 size_t bn_fwd_scratch_bytes(int B, int C, int T);

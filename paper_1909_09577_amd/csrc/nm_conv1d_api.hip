@@ -635,10 +635,10 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
             unsigned char *ws_w = (unsigned char *)workspace + ws_data;
             void *xp = ws_w + mfma_wgrad_x_offset(g);
             const DzfLayout none = {};
-            err = launch_bwd_prepare(g, dy, y, scale, w, relu, workspace, nullptr, none, dres, &g_plain, s, x, xp);
+            err = launch_bwd_prepare(g, dy, y, scale, w, true, relu, workspace, nullptr, none, dres, &g_plain, s, x, xp);
             if (err != hipSuccess) return NM_ERR_DEVICE;
             t_current_op = NM_OP_BWD_DATA;
-            err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
+            err = launch_mfma_dgrad_prepared(g, g_plain, scale, w, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
             if (err != hipSuccess) return NM_ERR_DEVICE;
             t_current_op = NM_OP_BWD_WEIGHT;
             return dev(launch_wgrad_k1(pitched(g), xp, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
@@ -702,11 +702,11 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     const DzfLayout layout = mfma_wgrad_dzf_layout(g);
     const void *g_plain = nullptr;
     void *xp = g.T % 8 == 0 ? nullptr : (unsigned char *)ws_w + mfma_wgrad_x_offset(g);  // pitched copy of x
-    hipError_t err = launch_bwd_prepare(g, dy, y, scale, w, relu, workspace, (unsigned char *)ws_w + layout.offset, layout,
+    hipError_t err = launch_bwd_prepare(g, dy, y, scale, w, !mfma_dgrad_unpacked(g, w, ws_data), relu, workspace, (unsigned char *)ws_w + layout.offset, layout,
                                         dres, &g_plain, s, x, xp);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_DATA;
-    err = launch_mfma_dgrad_prepared(g, g_plain, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
+    err = launch_mfma_dgrad_prepared(g, g_plain, scale, w, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
     const DefinedDw defined = {false, x, dy, relu ? y : nullptr};
