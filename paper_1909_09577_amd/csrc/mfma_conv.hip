@@ -1654,7 +1654,7 @@ double packed_cost(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int
 UnpackedPlan better_unpacked(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int Tin, int Tout, int K, int dil, bool flip, size_t part_limit)
 {
     if (!pl.ok || !unpacked_supported(M, R, K, pl.stride, flip)) return UnpackedPlan{};
-    const double most = 0.9 * packed_cost(pl, sp, B, M, R, Tin, Tout, K, flip);
+    const double most = 0.92 * packed_cost(pl, sp, B, M, R, Tin, Tout, K, flip);
     // (whatever the plan, its multiplications spread evenly: most large calls need not be looked at any further)
     if (10.7 + 0.69 * 0.0444 / 4 / 256 * ((M + kTileM - 1) / kTileM) * (R / 16) * (double)B * ((Tout + 31) / 32) * K > most) return UnpackedPlan{};
     const UnpackedPlan up = unpacked_plan(B, M, R, Tout, K, dil, flip, part_limit);
