@@ -69,7 +69,7 @@ def kernel_names_for(cfg):
             return ("pointwise_gemm_kernel<false, 4, 4, 64>" if waste(512, 128) <= 1.12 * waste(256, 160)
                     else "pointwise_gemm_kernel<false, 2, 5, 128>")
         if cfg.Cout <= 32 and cfg.Cin % 16 == 0 and cfg.T % 8 == 0:
-            conv = "decoder_mfma_kernel<true, false>"
+            conv = "decoder_mfma_kernel<true, false, 1>"
         else:
             conv = pointwise(cfg.Cout) if cfg.Cout > 64 else "conv_gemm_kernel<5, 1, 0, false, false, false, false>"
         if cfg.Cout <= 32 and cfg.T % 8 == 0:

@@ -22,6 +22,8 @@
 //   * rows that do not start at 16-byte boundaries (the ANYROW instance: T no multiple of eight, or x at an odd
 //     address) are read with 16-byte global loads at 2-byte aligned addresses; the group that holds the end of a
 //     row is loaded as the row's last eight frames and moved down when it is written to LDS.
+//   * calls of few frames leave most of the chip idle and wait for one load after the other: there SPLIT of a workgroup's
+//     wavefronts share the channels of the same frames and add their sums through LDS (decoder_split()).
 // Shapes the matrix-core kernel does not take (Ncls > 32, Cin % 16 != 0, T < 8, float32
 // storage, misaligned weights) use a plain kernel: one thread per frame, two passes over the classes.
 #include "../../include/nm_conv1d.h"
@@ -33,6 +35,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -51,7 +54,7 @@ __device__ __forceinline__ void wave_lds_fence()
 // BLOCK == false: the decoder tail (bias, log-softmax, float32 out).  BLOCK == true: the same load stream as the
 // forward pass of a pointwise conv1d sub-block with at most 32 output channels (the 1024 -> 29 projection in
 // front of the decoder): `bias` is the shift, and the epilogue is scale, shift, residual, ReLU, bf16 out.
-template <bool BLOCK, bool ANYROW = false>
+template <bool BLOCK, bool ANYROW = false, int SPLIT = 1>
 __global__ __launch_bounds__(256) void decoder_mfma_kernel(int B, int Cin, int Ncls, int T, const bf16_t *__restrict__ x,
                                                            const bf16_t *__restrict__ w, const float *__restrict__ bias,
                                                            float *__restrict__ logp, const float *__restrict__ scale,
@@ -62,12 +65,15 @@ __global__ __launch_bounds__(256) void decoder_mfma_kernel(int B, int Cin, int N
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b = blockIdx.y;
-    const int t0 = (blockIdx.x * 4 + wave) * kFramesPerWave;
-    if (t0 >= T) return;
+    constexpr int kSide = 4 / SPLIT;  // wavefronts side by side
+    const int share = wave / kSide;   // which of the SPLIT shares of the channels
+    const int t0 = (blockIdx.x * kSide + wave - share * kSide) * kFramesPerWave;
+    if (SPLIT == 1 && t0 >= T) return;
     unsigned char *buf = smem + wave * 2 * kStepBytes;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, (int)((size_t)B * Cin * T * 2), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)w, 0, (int)((size_t)Ncls * Cin * 2), 0x00020000);
-    const int first = 0, last = Cin / 16, per_wave = last;  // steps of 16 channels
+    const int steps = Cin / 16, per_wave = (steps + SPLIT - 1) / SPLIT;  // steps of 16 channels
+    const int first = min(share * per_wave, steps), last = min((share + 1) * per_wave, steps);
 
     // x: lane = (channel lane/4 of the step, frames 8*(lane%4) .. +7); frames beyond T read zeros
     const int xt = t0 + 8 * (lane & 3);
@@ -155,6 +161,23 @@ __global__ __launch_bounds__(256) void decoder_mfma_kernel(int B, int Cin, int N
         }
     }
 
+    if constexpr (SPLIT > 1) {  // the shares are added in order by the wavefronts of the first
+        __shared__ f32x4 sums[(4 - kSide) * 4 * 64];
+        if (share > 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sums[((wave - kSide) * 4 + r) * 64 + lane] = f32x4{acc[4 * r], acc[4 * r + 1], acc[4 * r + 2], acc[4 * r + 3]};
+        }
+        __syncthreads();
+        if (share > 0 || t0 >= T) return;
+#pragma unroll
+        for (int o = 1; o < SPLIT; ++o)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const f32x4 v = sums[((wave + (o - 1) * kSide) * 4 + r) * 64 + lane];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[4 * r + j] += v[j];
+            }
+    }
     // Register r of the accumulator is class 8*(r/4) + 4*(lane/32) + r%4, frame lane%32.
     const int t = t0 + (lane & 31);
     if constexpr (BLOCK) {
@@ -234,6 +257,16 @@ __global__ __launch_bounds__(256) void decoder_plain_kernel(int B, int Cin, int 
 
 }  // namespace
 
+// Wavefronts that share the channels of the same 32 frames.  A workgroup's row segments get shorter with them (256 / 128 /
+// 64 bytes), which costs more than it gains once there are wavefronts enough.  1024 channels, 29 classes, 1 / 2 / 4
+// (us, replayed in a graph, cold x): B=1, T=88 11.4 / 9.7 / 7.8; B=1, T=600 13.9 / 10.2 / 8.7; B=8, T=800 14.5 / 11.1 / 10.0;
+// B=16, T=800 15.1 / 12.4 / 14.4; B=32, T=800 19.5 / 22.3 / 28.0; odd rows B=2, T=265 17.3 / 12.6 / 10.7.
+int decoder_split(int B, int T)
+{
+    const long waves = (long)B * ((T + kFramesPerWave - 1) / kFramesPerWave);
+    return waves <= 256 ? 4 : waves <= 512 ? 2 : 1;
+}
+
 // Forward of a pointwise sub-block with few output channels on the decoder's load stream.
 bool skinny_fwd_supported(const Geom &g)
 {
@@ -244,9 +277,11 @@ bool skinny_fwd_supported(const Geom &g)
 hipError_t launch_skinny_fwd(const Geom &g, const void *x, const void *w, const float *scale, const float *shift,
                              const void *res, void *y, bool relu, hipStream_t s)
 {
-    dim3 grid((g.T + 4 * kFramesPerWave - 1) / (4 * kFramesPerWave), g.B);
+    const int split = decoder_split(g.B, g.T), frames = 4 / split * kFramesPerWave;
+    dim3 grid((g.T + frames - 1) / frames, g.B);
     MainKernelTimer timer(s);
-    hipLaunchKernelGGL(decoder_mfma_kernel<true>, grid, dim3(256), 0, s, g.B, g.Cin, g.Cout, g.T, (const bf16_t *)x,
+    auto kern = split == 4 ? decoder_mfma_kernel<true, false, 4> : split == 2 ? decoder_mfma_kernel<true, false, 2> : decoder_mfma_kernel<true>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, g.B, g.Cin, g.Cout, g.T, (const bf16_t *)x,
                        (const bf16_t *)w, shift, (float *)nullptr, scale, (const bf16_t *)res, relu ? 1 : 0, (bf16_t *)y);
     return hipGetLastError();
 }
@@ -270,10 +305,13 @@ extern "C" int nm_decoder_logsoftmax_fwd(int B, int Cin, int Ncls, int T, const 
                       ((uintptr_t)w % 16) == 0 && ((uintptr_t)x % 2) == 0 &&
                       (size_t)B * Cin * T * 2 <= ((size_t)1 << 30);
     if (fast) {
-        dim3 grid((T + 4 * kFramesPerWave - 1) / (4 * kFramesPerWave), B);
+        const int split = decoder_split(B, T), frames = 4 / split * kFramesPerWave;
+        dim3 grid((T + frames - 1) / frames, B);
         // 1024 channels, 29 classes: B=2, T=265 6034 us on the plain kernel, 17.4 here; B=32, T=777 19.9 (T=776 18.4)
         const bool rows16 = T % 8 == 0 && ((uintptr_t)x % 16) == 0;
-        auto kern = rows16 ? decoder_mfma_kernel<false> : decoder_mfma_kernel<false, true>;
+        auto kern = split == 4   ? (rows16 ? decoder_mfma_kernel<false, false, 4> : decoder_mfma_kernel<false, true, 4>)
+                    : split == 2 ? (rows16 ? decoder_mfma_kernel<false, false, 2> : decoder_mfma_kernel<false, true, 2>)
+                                 : (rows16 ? decoder_mfma_kernel<false> : decoder_mfma_kernel<false, true>);
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, B, Cin, Ncls, T, (const bf16_t *)x, (const bf16_t *)w, bias, logp,
                            (const float *)nullptr, (const bf16_t *)nullptr, 0, (bf16_t *)nullptr);
     } else {
