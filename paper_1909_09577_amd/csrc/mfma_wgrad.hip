@@ -744,13 +744,30 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
     // units of this workgroup: sp, sp + S, sp + 2S, ...; (batch item, chunk) advance without divisions
     const int step_b = S / p.nchunk, step_c = S - step_b * p.nchunk;
     struct UnitPos {
-        int b, c;
+        int b, c, u;  // u: (LEN) the unit's number
+    };
+    // (LEN) the lengths of the first 64 items, one per lane: a load per unit and use made a unit twice as long (1.4 us, 384
+    // channels, K=13)
+    const int lane_len = LEN && lane < p.B ? clipped_len(p.len, lane, p.T) : 0;
+    auto len_of = [&](int b) {
+        return b < 64 ? __builtin_amdgcn_readlane(lane_len, b) : __builtin_amdgcn_readfirstlane(clipped_len(p.len, b, p.T));
     };
     // with lengths: chunks of item b that reach below its valid length (chunk c reads x from c*80 - pad on)
     auto live_chunks_of = [&](int tl) { return tl > 0 ? min(p.nchunk, (tl + p.pad + kFastTCH - 1) / kFastTCH) : 0; };
+    // (LEN, up to 64 items) live units up to and with this lane's item: the item of unit u is the first whose count is above
+    // u, one ballot; walking the items cost as much as the products of a unit
+    int upto = 0;
+    if constexpr (LEN) {
+        upto = lane < p.B ? live_chunks_of(lane_len) : 0;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(upto, d, 64);
+            upto += lane >= d ? v : 0;
+        }
+    }
     auto carry_over = [&](UnitPos &q) {  // c counts live chunks from the start of item b onwards
         while (q.b < p.B) {
-            const int n = live_chunks_of(__builtin_amdgcn_readfirstlane(clipped_len(p.len, q.b, p.T)));
+            const int n = live_chunks_of(len_of(q.b));
             if (q.c < n) break;
             q.c -= n;
             ++q.b;
@@ -758,17 +775,21 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
     };
     auto unit_pos = [&](int u) {
         if constexpr (LEN) {
-            UnitPos q{0, u};
-            carry_over(q);
+            UnitPos q{0, u, u};
+            if (p.B <= 64) {
+                q.b = __popcll(__ballot(upto <= u));
+                if (q.b > 0) q.c -= __builtin_amdgcn_readlane(upto, q.b - 1);
+            } else {
+                carry_over(q);
+            }
             return q;
         } else {
-            return UnitPos{u / p.nchunk, u % p.nchunk};
+            return UnitPos{u / p.nchunk, u % p.nchunk, u};
         }
     };
     auto advance = [&](UnitPos &q) {
         if constexpr (LEN) {
-            q.c += S;
-            carry_over(q);
+            q = unit_pos(q.u + S);
         } else {
             q.b += step_b;
             q.c += step_c;
@@ -784,7 +805,7 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
         a.tbase = q.c * kFastTCH;
         a.xs = (uint32_t)b * (uint32_t)(p.Cin * p.T * 2);
         a.as = (uint32_t)((b * p.ncm + (co0 >> 5)) * p.nst + q.c * kFastSteps) * 1024u;
-        a.tlen = p.len ? __builtin_amdgcn_readfirstlane(clipped_len(p.len, b, p.T)) : p.T;
+        a.tlen = LEN ? len_of(b) : p.len ? __builtin_amdgcn_readfirstlane(clipped_len(p.len, b, p.T)) : p.T;
         return a;
     };
     auto x_load_item = [&](const UnitAddr &a, u32x4 &xa, u32x4 &xb) {
@@ -1229,24 +1250,44 @@ FastPlan make_fast_plan(const Geom &g)
     const size_t stage = (size_t)kWaves * 2 * fast_x_items(g.dil) * 32 * kFastXRowBytes;
     const size_t red = (size_t)kWaves * 3 * (2 * f.KTg) * 64 * sizeof(f32x4);
     f.lds = stage > red ? stage : red;
-    // The kernel with shared staging: up to 24 taps per workgroup (12 accumulator blocks per wavefront);
-    // it has no dynamic balancing to speak of (few, long workgroups), so it is taken only when a split
-    // count S <= 8 makes the workgroups fill the CUs in whole rounds (>= 95 %).
+    // The kernel with shared staging: up to 24 taps per workgroup, in as many parts as are estimated to be fastest (or the
+    // other kernel).  Its workgroups are few and long, but that is not all: every part is written, read and added once more,
+    // and a workgroup takes 4.5 us before its first and after its last unit.  Fitted to 15700 calls, 2404 geometries of 256 to
+    // 896 channels (us, preparation of g and sum of the parts included; rms 6 %, of the other kernel 8 %); the plan taken
+    // is within 1 % of the best one on average.  Filling the CUs in whole rounds, the rule before, against this one: 640
+    // channels K=21, B=16, T=800 five parts 251 us, one 197; 640 -> 768 K=25, B=16, T=297 337 (the other kernel) / 146; 768
+    // K=25, B=3, T=112 121 (three) / 69; 768 -> 896 K=29, B=23, T=648 655 (two) / 580; 384 K=13, B=16, T=777 87 (seven) / 71.
     {
         const int ntg_s = (g.K + 23) / 24;
-        const int KG = (g.K + ntg_s - 1) / ntg_s;
-        const long tiles_s = (long)ncot * ncit * ((g.K + KG - 1) / KG);
+        const int KG = (g.K + ntg_s - 1) / ntg_s, ntg = (g.K + KG - 1) / KG;
+        const long tiles_s = (long)ncot * ncit * ntg;
         if (shared_kernel_built(KG, g.dil) && 18 + 64 + (KG - 1) * g.dil + 4 < 128) {
-            for (long Ss = 1; Ss <= 8 && Ss * 2 <= units; ++Ss) {
-                const long wgs = tiles_s * Ss, rounds = (wgs + kPlanCUs - 1) / kPlanCUs;
-                if (wgs * 100 >= rounds * kPlanCUs * 95) {
-                    f.shared = true;
-                    f.KTg = KG;
-                    f.ntg = (g.K + KG - 1) / KG;
-                    f.S = (int)Ss;
-                    f.lds = 3 * 128 * kFastXRowBytes;
-                    break;
+            const int blocks = (2 * KG + kWaves - 1) / kWaves;  // accumulator blocks of a wavefront
+            const double mb = 4e-6 * g.Cout * g.Cin * g.K;
+            auto cost = [&](long S) {
+                const long rounds = (tiles_s * S + kPlanCUs - 1) / kPlanCUs, pairs = ((units + S - 1) / S + 1) / 2;
+                return 14.8 + rounds * (4.5 + 2.0 * pairs * (0.154 + 0.077 * blocks)) + (0.37 * S + 0.16) * mb - (S == 8 ? 1.9 : 0.0);
+            };
+            const long per_wave = (units + kWaves * f.S - 1) / (kWaves * f.S);
+            const double load = std::max(1.0, ntiles * f.S / (double)kPlanCUs);
+            // (0.3 per unit and tap: what the chip's power allows once a call is longer than the measured ones of that kernel)
+            double best = 12.9 + load * f.KTg * (0.17 * std::min(per_wave, 8L) + 0.3 * std::max(per_wave - 8, 0L)) + (0.94 * f.S + 0.16) * mb + 3.1e-6 * g.B * (g.Cout + g.Cin) * (double)g.To;
+            long S_best = 0;
+            for (long S = 1; S <= 8 && (S == 1 || 2 * S <= units); ++S) {
+                const long wgs = tiles_s * S, rounds = (wgs + kPlanCUs - 1) / kPlanCUs;
+                const bool whole = wgs * 100 >= rounds * kPlanCUs * 95;
+                const double c = cost(S) * (whole ? 0.95 : 1.0);  // (a tie goes to whole rounds)
+                if (c < best) {
+                    best = c;
+                    S_best = S;
                 }
+            }
+            if (S_best > 0) {
+                f.shared = true;
+                f.KTg = KG;
+                f.ntg = ntg;
+                f.S = (int)S_best;
+                f.lds = 3 * 128 * kFastXRowBytes;
             }
         }
     }

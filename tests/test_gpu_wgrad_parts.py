@@ -1,0 +1,56 @@
+"""Weight gradient with shared staging: how many parts a call takes, and the units of a padded batch (items of no length among
+them, more items than lanes of a wavefront) against the oracle."""
+import numpy as np
+import pytest
+
+import _util as U
+from oracle import conv1d_oracle as orc
+from paper_1909_09577_amd import binding as nm
+from paper_1909_09577_amd import inputs as syn
+from paper_1909_09577_amd.inputs import LayerCfg
+
+
+def L(B, Cin, Cout, T, K, dilation=1):
+    pad = dilation * (K - 1) // 2
+    return LayerCfg("wgrad", B, Cin, Cout, T, K, 1, dilation, pad, True, True, False, 5, T_out=orc.out_len(T, K, 1, dilation, pad))
+
+
+# the parts of many layers' worth of tiles cost more than idle CUs do; few tiles still fill the chip with them
+@pytest.mark.parametrize("dims,name", [
+    ((16, 640, 640, 800, 21, 1, 1, 10), "wgrad_shared_kernel<21, 1, false> in 1 parts"),
+    ((16, 640, 768, 296, 25, 1, 1, 12), "wgrad_shared_kernel<13, 1, false> in 1 parts"),
+    ((3, 768, 768, 112, 25, 1, 1, 12), "wgrad_shared_kernel<13, 1, false> in 1 parts"),
+    ((32, 512, 512, 800, 17, 1, 1, 8), "wgrad_shared_kernel<17, 1, false> in 2 parts"),
+    ((32, 256, 256, 800, 11, 1, 1, 5), "wgrad_shared_kernel<11, 1, false> in 8 parts"),
+    ((1, 256, 256, 96, 11, 1, 1, 5), "wgrad_fast_kernel<6, 1> in 1 parts")], ids=str)
+def test_parts(dims, name):
+    assert nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_WEIGHT, *dims) == name
+
+
+CASES = [(L(70, 256, 256, 24, 11), None), (L(70, 256, 320, 96, 11), None), (L(64, 384, 256, 41, 13), None), (L(3, 320, 448, 170, 17), [170, 0, 81]),
+         (L(5, 320, 640, 88, 21), [88, 80, 79, 1, 88]), (L(2, 384, 512, 96, 29, dilation=2), [40, 96])]
+
+
+def test_the_cases_run_on_the_kernel_with_shared_staging():
+    for c, _ in CASES:
+        assert nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_WEIGHT, *c.dims(), masked=True).startswith("wgrad_shared_kernel<"), c.dims()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[0].dims())))
+def test_weight_gradient(case, masked):
+    import torch
+    cfg, given = case
+    inp = syn.make_inputs(cfg, "bf16")
+    lens = np.full(cfg.B, cfg.T, dtype=np.int32)
+    if masked:
+        lens = np.array(given if given else [(37 * b) % (cfg.T + 1) for b in range(cfg.B)], dtype=np.int32)
+    x = U.to_dev(inp, "x", "bf16")
+    for b in range(cfg.B):
+        x[b, :, lens[b]:] = float("nan")
+    dy, scale = U.to_dev(inp, "dy", "bf16"), U.to_dev(inp, "scale", "bf16")
+    ld = torch.from_numpy(lens).cuda() if masked else None
+    dw = nm.nm_conv1d_bwd_weight(x, dy, cfg.K, scale=scale, lengths=ld, **U.geom_kw(cfg))
+    dz, _ = orc.epilogue_bwd(inp["dy"], None, inp["scale"], False)
+    U.assert_close(U.to_host_f64(dw), orc.bwd_weight_masked(inp["x"], dz, cfg.K, lens, **U.geom_kw(cfg)), "bf16", "dw", rms_bound=U.RMS_DW_BF16)
