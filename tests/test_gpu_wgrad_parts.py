@@ -54,3 +54,14 @@ def test_weight_gradient(case, masked):
     dw = nm.nm_conv1d_bwd_weight(x, dy, cfg.K, scale=scale, lengths=ld, **U.geom_kw(cfg))
     dz, _ = orc.epilogue_bwd(inp["dy"], None, inp["scale"], False)
     U.assert_close(U.to_host_f64(dw), orc.bwd_weight_masked(inp["x"], dz, cfg.K, lens, **U.geom_kw(cfg)), "bf16", "dw", rms_bound=U.RMS_DW_BF16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", [L(1, 512, 512, 70, 17), L(5, 512, 640, 193, 21), L(1, 768, 768, 64, 25), L(4, 512, 512, 321, 17)],
+                         ids=lambda c: "x".join(map(str, c.dims())))
+def test_fp8_weight_gradient_in_any_number_of_parts(cfg):
+    """One part up to several (the fewest where a part costs more than idle CUs), the gate of the other 8-bit weight gradients."""
+    import test_gpu_fp8 as T8
+    got, ref = T8.run_wgrad_case(cfg, accumulate=True)
+    mx, rr = U.err_metrics(got, ref)
+    assert mx <= T8.WGRAD_TOL and rr <= T8.WGRAD_RMS, (mx, rr)
