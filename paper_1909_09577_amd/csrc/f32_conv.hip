@@ -15,6 +15,8 @@
 // take 28 (19 at the full clock), the LDS reads 5 and the staging 9.
 #include "nm_common.h"
 
+#include <algorithm>
+
 namespace nm {
 namespace {
 
@@ -58,6 +60,8 @@ struct F32ConvParams {
     const float *res;              // optional, layout of out
     float *out;                    // [B][M][Tout]
     const int *len_in, *len_out;   // optional [B]
+    int nsplit;                    // workgroups that share a tile's reduction channels
+    float *part;                   // their sums [nsplit][B][M][Tout] (nsplit > 1)
 };
 
 // One output as the definition has it, the sums as the plain kernels take them.  The kernel below also multiplies zeros for
@@ -84,6 +88,19 @@ __device__ __forceinline__ float defined_sum(const F32ConvParams &p, const float
     return z;
 }
 
+// lim: outputs from there on are zero
+template <bool FLIP>
+__device__ __forceinline__ void finish_output(const F32ConvParams &p, float v, const float *in, int len, int lim, int m, int t, size_t o)
+{
+    if (v != v && t < lim) v = defined_sum<FLIP>(p, in, len, m, t);
+    if (p.scale) v *= p.scale[m];
+    if (p.shift) v += p.shift[m];
+    if (t >= lim) v = 0.f;
+    if (p.res) v += p.res[o];
+    if (p.relu) v = v > 0.f ? v : 0.f;
+    p.out[o] = v;
+}
+
 // A workgroup owns 64 output channels x 32*NT time steps of one batch item.  The reduction channels are staged in chunks
 // of CC (16 up to 16 taps, 8 up to 32) and split over the eight wavefronts in pairs (lane half h takes the pair's channel
 // h, so that both operands of a tap are one LDS word at a fixed offset), with CC = 8 also by halves of the taps; their
@@ -103,7 +120,10 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
     constexpr int kXRows = CC / kConvWaves;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int mt = (int)blockIdx.x % p.nmt, col = (int)blockIdx.x / p.nmt;
+    const int tile = (int)blockIdx.x / p.nsplit, split = (int)blockIdx.x - tile * p.nsplit;
+    const int mt = tile % p.nmt, col = tile / p.nmt;
+    const int chunks = (p.R + CC - 1) / CC;
+    const int r_first = split * chunks / p.nsplit * CC, r_end = min(p.R, (split + 1) * chunks / p.nsplit * CC);
     const int b = col / p.ntt, t0 = (col - b * p.ntt) * TN;
     const int m0 = mt * kTileM;
     const int K = p.K;
@@ -132,7 +152,7 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
             xoff[i][j] = c < p.W && tau >= 0 && tau < len ? (uint32_t)((wave * kXRows + i) * p.Tin + tau) * 4u : kFar;
         }
     auto load_chunk = [&](int r0) {
-        if (r0 >= p.R) return;
+        if (r0 >= r_end) return;
         const int nr = min(CC, p.R - r0);
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i)
@@ -260,14 +280,14 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
                     acc[mi][ni][r] = 0.f;
                 }
     };
-    load_chunk(0);
-    store_chunk(0, lds);
-    load_chunk(CC);
-    for (int r0 = 0, par = 0; r0 < p.R; r0 += CC, par ^= 1) {
+    load_chunk(r_first);
+    store_chunk(r_first, lds);
+    load_chunk(r_first + CC);
+    for (int r0 = r_first, par = 0; r0 < r_end; r0 += CC, par ^= 1) {
         __syncthreads();  // this chunk is in its buffer, the other buffer has been read
         const float *cur = lds + par * buf_floats;
         float *nxt = lds + (par ^ 1) * buf_floats;
-        const bool more = r0 + CC < p.R;
+        const bool more = r0 + CC < r_end;
         if (wave < 4 && more) {
             store_chunk(r0 + CC, nxt);
             load_chunk(r0 + 2 * CC);
@@ -300,15 +320,29 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
         float v = 0.f;
 #pragma unroll
         for (int q = 0; q < kConvWaves; ++q) v += lds[(size_t)q * kTileM * TN + e];
-        if (v != v && t < lim) v = defined_sum<FLIP>(p, xb, len, m, t);
-        if (p.scale) v *= p.scale[m];
-        if (p.shift) v += p.shift[m];
-        if (t >= lim) v = 0.f;
         const size_t o = ((size_t)b * p.M + m) * p.Tout + t;
-        if (p.res) v += p.res[o];
-        if (p.relu) v = v > 0.f ? v : 0.f;
-        p.out[o] = v;
+        if (p.nsplit > 1)
+            p.part[(size_t)split * p.B * p.M * p.Tout + o] = v;
+        else
+            finish_output<FLIP>(p, v, xb, len, lim, m, t, o);
     }
+}
+
+// Adds the parts of an output in order and finishes it: a thread each.
+template <bool FLIP>
+__global__ __launch_bounds__(256) void f32_split_finish_kernel(const F32ConvParams p)
+{
+    const size_t n = (size_t)p.B * p.M * p.Tout, o = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (o >= n) return;
+    const int row = (int)(o / p.Tout), t = (int)(o - (size_t)row * p.Tout), b = row / p.M, m = row - b * p.M;
+    float v = 0.f;
+#pragma unroll 8
+    for (int s = 0; s < p.nsplit; ++s) v += p.part[(size_t)s * n + o];
+    auto limit = [&](const int *len_of, int most) {
+        const int l = len_of ? len_of[b] : most;
+        return l < 0 ? 0 : (l < most ? l : most);
+    };
+    finish_output<FLIP>(p, v, p.in + (size_t)b * p.R * p.Tin, limit(p.len_in, p.Tin), limit(p.len_out, p.Tout), m, t, o);
 }
 
 struct F32ConvPlan {
@@ -348,8 +382,12 @@ hipError_t launch_f32_conv_t(F32ConvParams p, const F32ConvPlan &q, hipStream_t 
     static LdsOptIn opt_in;
     hipError_t e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), kMaxLds);
     if (e != hipSuccess) return e;
-    MainKernelTimer timer(s);
-    hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B)), dim3(64 * kConvWaves), q.lds, s, p);
+    {
+        MainKernelTimer timer(s);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B * p.nsplit)), dim3(64 * kConvWaves), q.lds, s, p);
+    }
+    if (p.nsplit > 1)
+        hipLaunchKernelGGL(f32_split_finish_kernel<FLIP>, dim3((unsigned)(((size_t)p.B * p.M * p.Tout + 255) / 256)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 template <int NT, bool FLIP>
@@ -359,9 +397,28 @@ hipError_t launch_f32_conv_nt(const F32ConvParams &p, const F32ConvPlan &q, hipS
         return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 16, 2>(p, q, s) : launch_f32_conv_t<NT, FLIP, 16, kXIter>(p, q, s);
     return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 8, 2>(p, q, s) : launch_f32_conv_t<NT, FLIP, 8, kXIter>(p, q, s);
 }
-template <bool FLIP>
-hipError_t launch_f32_conv(const F32ConvParams &p, hipStream_t s)
+// Workgroups that share a tile's reduction channels where the tiles are too few to fill the chip (NT = 1 there): a
+// workgroup takes 3 us per chunk of channels, 16 chunks at 256 channels, K=11, and the second launch 4.
+// Channels, K, B, T: 256 -> 384, 13, 1, 260 50.9 -> 20.7 us; 256, 11, 1, 60 46.5 -> 12.2; 256, 11, 4, 250 47.1 -> 29.7; from half of
+// the chip on there is nothing to share out.
+int f32_splits(int B, int M, int R, int Tout, int K)
 {
+    const size_t tiles = (size_t)((M + kTileM - 1) / kTileM) * ((Tout + 31) / 32) * B;
+    const int cc = 16 * K <= kRun ? 16 : 8, chunks = (R + cc - 1) / cc;
+    return tiles > 128 ? 1 : std::max(1, std::min({(int)(256 / tiles), chunks, 8}));
+}
+size_t f32_split_bytes(int B, int M, int R, int Tout, int K)
+{
+    const int n = f32_splits(B, M, R, Tout, K);
+    return n > 1 ? align_up((size_t)n * B * M * Tout * sizeof(float), 256) : 0;
+}
+
+template <bool FLIP>
+hipError_t launch_f32_conv(F32ConvParams p, void *part, size_t room, hipStream_t s)
+{
+    const size_t bytes = f32_split_bytes(p.B, p.M, p.R, p.Tout, p.K);
+    p.nsplit = bytes > 0 && part && bytes <= room ? f32_splits(p.B, p.M, p.R, p.Tout, p.K) : 1;
+    p.part = (float *)part;
     // the wide tile from two workgroups per CU on (and where its window fits)
     const size_t wide = (size_t)((p.M + kTileM - 1) / kTileM) * ((p.Tout + 63) / 64) * p.B;
     const F32ConvPlan q2 = f32_conv_plan(p.K, p.stride, p.dil, 2, FLIP), q1 = f32_conv_plan(p.K, p.stride, p.dil, 1, FLIP);
@@ -545,8 +602,11 @@ bool f32_fwd_supported(const Geom &g) { return worth_it(g) && f32_conv_plan(g.K,
 bool f32_dgrad_supported(const Geom &g) { return worth_it(g) && g.stride == 1 && f32_conv_plan(g.K, 1, g.dil, 1, true).ok; }
 bool f32_wgrad_supported(const Geom &g) { return worth_it(g) && f32_wgrad_plan(g).ok; }
 
+size_t f32_fwd_part_bytes(const Geom &g) { return f32_split_bytes(g.B, g.Cout, g.Cin, g.To, g.K); }
+size_t f32_dgrad_part_bytes(const Geom &g) { return f32_split_bytes(g.B, g.Cin, g.Cout, g.T, g.K); }
+
 hipError_t launch_f32_fwd(const Geom &g, const float *x, const float *w, const float *scale, const float *shift,
-                          const float *res, float *y, bool relu, hipStream_t s)
+                          const float *res, float *y, bool relu, void *part, size_t room, hipStream_t s)
 {
     F32ConvParams p = {};
     p.B = g.B; p.M = g.Cout; p.R = g.Cin; p.Tin = g.T; p.Tout = g.To;
@@ -554,11 +614,11 @@ hipError_t launch_f32_fwd(const Geom &g, const float *x, const float *w, const f
     p.relu = relu ? 1 : 0;
     p.in = x; p.w = w; p.scale = scale; p.shift = shift; p.res = res; p.out = y;
     p.len_in = g.len;
-    return launch_f32_conv<false>(p, s);
+    return launch_f32_conv<false>(p, part, room, s);
 }
 
 hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, const float *w, float *dx, bool accumulate,
-                            hipStream_t s)
+                            void *part, size_t room, hipStream_t s)
 {
     F32ConvParams p = {};
     p.B = g.B; p.M = g.Cin; p.R = g.Cout; p.Tin = g.To; p.Tout = g.T;
@@ -566,7 +626,7 @@ hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, 
     p.in = gy; p.w = w; p.rscale = scale; p.out = dx;
     p.res = accumulate ? dx : nullptr;  // every thread reads the element it then writes
     p.len_out = g.len;
-    return launch_f32_conv<true>(p, s);
+    return launch_f32_conv<true>(p, part, room, s);
 }
 
 size_t f32_wgrad_part_bytes(const Geom &g)

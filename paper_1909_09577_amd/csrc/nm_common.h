@@ -265,11 +265,14 @@ bool f32_fwd_supported(const Geom &g);
 bool f32_dgrad_supported(const Geom &g);
 bool f32_wgrad_supported(const Geom &g);
 hipError_t launch_f32_fwd(const Geom &g, const float *x, const float *w, const float *scale, const float *shift,
-                          const float *res, float *y, bool relu, hipStream_t s);
+                          const float *res, float *y, bool relu, void *part, size_t room, hipStream_t s);
+// part, room: optional scratch for the sums of workgroups that share a tile, *_part_bytes(g) where it is used
+size_t f32_fwd_part_bytes(const Geom &g);
+size_t f32_dgrad_part_bytes(const Geom &g);
 // gy = dy*[y>0] for both gradients (scale[co] is folded into the weights, resp. multiplies the sums);
 // part: f32_wgrad_part_bytes(g) bytes
 hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, const float *w, float *dx, bool accumulate,
-                            hipStream_t s);
+                            void *part, size_t room, hipStream_t s);
 size_t f32_wgrad_part_bytes(const Geom &g);
 hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *gy, const float *scale, float *dw, bool accumulate,
                             void *part, hipStream_t s);

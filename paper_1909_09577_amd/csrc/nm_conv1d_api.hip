@@ -7,6 +7,8 @@
 
 #include <stdio.h>
 
+#include <initializer_list>
+
 #include <mutex>
 
 using namespace nm;
@@ -214,13 +216,36 @@ size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_
     return scale_or_relu ? align_up((size_t)g.B * g.Cout * g.To * elt(dtype), kWsAlign) : 0;
 }
 
+// Room that a float32 forward pass or input gradient of few tiles asks for and does without (parts of
+// nm_conv1d_block_fwd_static, which gives the bits of the ordinary call, fit its array).
+size_t f32_conv_room(int op, const Geom &g)
+{
+    const size_t n = op == NM_OP_FWD ? f32_fwd_part_bytes(g) : f32_dgrad_part_bytes(g);
+    return n <= NM_STATIC_SCRATCH_BYTES ? n : 0;
+}
+// That room inside a workspace, behind the `used` bytes: none where it is not there, or where a tensor of the call lies in it.
+struct Tensor {
+    const void *p;
+    size_t bytes;
+};
+void *f32_conv_part(int op, const Geom &g, void *ws, size_t have, size_t used, std::initializer_list<Tensor> tensors)
+{
+    const size_t n = f32_conv_room(op, g);
+    if (n == 0 || !ws || ((uintptr_t)ws % kWsAlign) != 0 || have < used + n) return nullptr;
+    unsigned char *at = (unsigned char *)ws + used;
+    for (const Tensor &t : tensors)
+        if (overlap(at, n, t.p, t.bytes)) return nullptr;
+    return at;
+}
+
 // What nm_conv1d_workspace_bytes answers for one pass.  The query sees neither the scale pointer nor the
 // alignment of the tensors (misaligned tensors take the plain kernels); it sizes for the larger of the cases.
 size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool least = false)
 {
     const size_t plain = workspace_for(op, g, dtype, false, true);
     const size_t fast = use_mfma(op, g, dtype, flags) ? workspace_for(op, g, dtype, true, true, least) : 0;
-    if (op == NM_OP_BWD_WEIGHT && use_f32(op, g, dtype, flags)) return plain + f32_wgrad_part_bytes(g);
+    if (use_f32(op, g, dtype, flags))
+        return plain + (op == NM_OP_BWD_WEIGHT ? f32_wgrad_part_bytes(g) : f32_conv_room(op, g));
     return plain > fast ? plain : fast;
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
@@ -402,8 +427,14 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
         if (err == hipSuccess && parts > 0) *stats_parts = parts;
         return dev(err);
     }
-    if (r.f32)
-        return dev(launch_f32_fwd(g, (const float *)x, (const float *)w, scale, shift, (const float *)residual, (float *)y, relu, s));
+    if (r.f32) {
+        const size_t nc = (size_t)g.Cout * sizeof(float);
+        void *part = f32_conv_part(NM_OP_FWD, g, workspace, workspace_bytes, 0,
+                                   {{x, (size_t)g.B * g.Cin * g.T * e}, {w, (size_t)g.Cout * g.Cin * g.K * e}, {residual, ny}, {y, ny},
+                                    {scale, nc}, {shift, nc}, {lengths, (size_t)g.B * sizeof(int)}});
+        return dev(launch_f32_fwd(g, (const float *)x, (const float *)w, scale, shift, (const float *)residual, (float *)y, relu, part,
+                                  part ? f32_conv_room(NM_OP_FWD, g) : 0, s));
+    }
     MainKernelTimer timer(s);
     return dev(launch_direct_fwd(g, dtype == NM_BF16, x, w, scale, shift, residual, y, relu, s));
 }
@@ -443,7 +474,11 @@ static int bwd_data_impl(int B, int Cin, int Cout, int T, int K, int stride, int
         const void *gy = dy;
         hipError_t err = f32_mask_pass(g, dy, y, relu, workspace, dres, &gy, s);
         if (err != hipSuccess) return NM_ERR_DEVICE;
-        return dev(launch_f32_dgrad(g, (const float *)gy, scale, (const float *)w, (float *)dx, accum, s));
+        void *part = f32_conv_part(NM_OP_BWD_DATA, g, workspace, workspace_bytes, align_up(need, kWsAlign),
+                                   {{dy, ndy}, {y, ndy}, {w, (size_t)g.Cout * g.Cin * g.K * e}, {dx, ndx}, {dres, ndy},
+                                    {scale, (size_t)g.Cout * sizeof(float)}, {lengths, (size_t)g.B * sizeof(int)}});
+        return dev(launch_f32_dgrad(g, (const float *)gy, scale, (const float *)w, (float *)dx, accum, part,
+                                    part ? f32_conv_room(NM_OP_BWD_DATA, g) : 0, s));
     }
     const bool bf = dtype == NM_BF16;
     const void *dz = dy;
@@ -664,7 +699,11 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
                                      (unsigned char *)workspace + ws_data, workspace_bytes - ws_data, s));
     }
     // float32 on the matrix cores: the masked gradient is formed once for both
-    const bool fused_f32 = whole && use_f32(NM_OP_BWD_DATA, g, dtype, flags) && use_f32(NM_OP_BWD_WEIGHT, g, dtype, flags);
+    // (a workspace without room for the input gradient's parts serves it too)
+    const bool f32_room = whole || (!own_checks && dtype == NM_F32 &&
+                                    check_workspace(workspace, workspace_bytes, workspace_for(NM_OP_BWD_DATA, g, dtype, false, true) +
+                                                                                    asked_workspace(NM_OP_BWD_WEIGHT, g, dtype, flags)) == NM_OK);
+    const bool fused_f32 = f32_room && use_f32(NM_OP_BWD_DATA, g, dtype, flags) && use_f32(NM_OP_BWD_WEIGHT, g, dtype, flags);
     if (fused_f32) {
         DisarmOnExit disarm;
         hipStream_t s = (hipStream_t)hip_stream;
@@ -672,7 +711,13 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         hipError_t err = f32_mask_pass(g, dy, y, relu, workspace, dres, &gy, s);
         if (err != hipSuccess) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_DATA;
-        err = launch_f32_dgrad(g, (const float *)gy, scale, (const float *)w, (float *)dx, (flags & NM_ACCUM_DX) != 0, s);
+        // (the weight gradient's parts come to lie where the input gradient's were)
+        const size_t behind = workspace_for(NM_OP_BWD_DATA, g, dtype, false, true);
+        void *part = f32_conv_part(NM_OP_BWD_DATA, g, workspace, workspace_bytes, behind,
+                                   {{x, nx}, {dy, ndy}, {y, ndy}, {w, nw}, {dx, nx}, {dres, ndy}, {dw, ndw},
+                                    {scale, (size_t)g.Cout * sizeof(float)}, {lengths, (size_t)g.B * sizeof(int)}});
+        err = launch_f32_dgrad(g, (const float *)gy, scale, (const float *)w, (float *)dx, (flags & NM_ACCUM_DX) != 0, part,
+                               part ? f32_conv_room(NM_OP_BWD_DATA, g) : 0, s);
         if (err != hipSuccess) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_f32_wgrad(g, (const float *)x, (const float *)gy, scale, dw, (flags & NM_ACCUM_DW) != 0,

@@ -1,0 +1,71 @@
+"""Float32 calls of few tiles, whose reduction channels are shared by several workgroups: with the room for their sums, without it,
+with a tensor of the call inside it, and sums that a zero of the padding must not turn into NaN."""
+import numpy as np
+import pytest
+
+import _util as U
+from oracle import conv1d_oracle as orc
+from paper_1909_09577_amd import binding as nm
+from paper_1909_09577_amd import inputs as syn
+from paper_1909_09577_amd.inputs import LayerCfg
+
+
+def L(B, Cin, Cout, T, K):
+    pad = (K - 1) // 2
+    return LayerCfg("f32split", B, Cin, Cout, T, K, 1, 1, pad, True, True, True, 9, T_out=orc.out_len(T, K, 1, 1, pad))
+
+
+# sums of the forward pass, of the input gradient
+CASES = [(L(1, 256, 256, 32, 11), 8, 8), (L(2, 200, 72, 77, 13), 8, 5), (L(1, 24, 640, 129, 21), 3, 8), (L(3, 130, 256, 320, 5), 2, 2), (L(4, 256, 256, 400, 11), 1, 1)]
+
+
+def _room(op, c):
+    g = 4 * c.B * (c.Cout if op == nm.NM_OP_FWD else c.Cin) * c.T
+    return (g + 255) // 256 * 256 if op == nm.NM_OP_BWD_DATA else 0
+
+
+@pytest.mark.parametrize("cfg,f,d", CASES, ids=lambda v: "x".join(map(str, v.dims())) if isinstance(v, LayerCfg) else str(v))
+def test_room_asked_for(cfg, f, d):
+    for op, n, rows in ((nm.NM_OP_FWD, f, cfg.Cout), (nm.NM_OP_BWD_DATA, d, cfg.Cin)):
+        part = (n * 4 * cfg.B * rows * cfg.T + 255) // 256 * 256 if n > 1 else 0
+        g = (4 * cfg.B * cfg.Cout * cfg.T + 255) // 256 * 256 if op == nm.NM_OP_BWD_DATA else 0
+        assert nm.nm_conv1d_workspace_bytes(op, *cfg.dims(), nm.NM_F32, nm.NM_RELU) == part + g
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", [c for c, _, _ in CASES], ids=lambda c: "x".join(map(str, c.dims())))
+def test_shared_reduction(cfg):
+    """The gate of the other float32 tests (1e-5 of the result): the sums only get shorter."""
+    import torch
+    inp = syn.make_inputs(cfg, "f32")
+    kw = U.geom_kw(cfg)
+    x, w, dy, scale, shift, res = (U.to_dev(inp, n, "f32") for n in ("x", "w", "dy", "scale", "shift", "residual"))
+    y_ref = orc.block_fwd(inp["x"], inp["w"], inp["scale"], inp["shift"], inp["residual"], True, **kw)
+    ysv = U.arr_to_dev(U.round_to_storage(y_ref, "f32"), "f32")
+    dz, _ = orc.epilogue_bwd(inp["dy"], U.round_to_storage(y_ref, "f32").astype(np.float64), inp["scale"], True)
+    dx_ref = orc.bwd_data(dz, inp["w"], cfg.T, **kw)
+    for op in (nm.NM_OP_FWD, nm.NM_OP_BWD_DATA):
+        full = nm.nm_conv1d_workspace_bytes(op, *cfg.dims(), nm.NM_F32, nm.NM_RELU)
+        least = (4 * cfg.B * cfg.Cout * cfg.T + 255) // 256 * 256 if op == nm.NM_OP_BWD_DATA else 0
+        for n in {full, least}:
+            guard = torch.full((n + 512,), 255, dtype=torch.uint8, device="cuda")
+            ws = guard[:n]
+            if op == nm.NM_OP_FWD:
+                got = nm.nm_conv1d_block_fwd(x, w, scale, shift, res, relu=True, workspace=ws, **kw)
+            else:
+                got = nm.nm_conv1d_bwd_data(dy, w, cfg.T, y=ysv, scale=scale, relu=True, workspace=ws, **kw)[0]
+            U.assert_close(U.to_host_f64(got), y_ref if op == nm.NM_OP_FWD else dx_ref, "f32", f"pass {op}, workspace {n}")
+            assert bool((guard[n:] == 255).all())
+    # the input lies inside the workspace: read before anything is written there
+    n = max(nm.nm_conv1d_workspace_bytes(nm.NM_OP_FWD, *cfg.dims(), nm.NM_F32, 0), 4 * x.numel())
+    buf = torch.zeros(n // 4 + 64, device="cuda")
+    xin = buf[:x.numel()].view(x.shape)
+    xin.copy_(x)
+    y = nm.nm_conv1d_block_fwd(xin, w, scale, shift, res, relu=True, workspace=buf.view(torch.uint8), **kw)
+    U.assert_close(U.to_host_f64(y), y_ref, "f32", "x inside the workspace")
+    # an infinite weight of the first tap meets only padding at the first output
+    w[:, :, 0] = float("inf")
+    y = nm.nm_conv1d_block_fwd(x, w, scale, shift, res, relu=False, **kw)
+    want = nm.nm_conv1d_block_fwd(x, w, scale, shift, res, relu=False, force_direct=True, **kw)
+    fin = torch.isfinite(want)
+    assert bool(fin[:, :, 0].all()) and torch.equal(torch.isfinite(y), fin)
