@@ -1231,7 +1231,8 @@ struct FastPlan {
 };
 // tap-group sizes wgrad_shared_kernel is built for
 constexpr bool shared_kernel_built(int KG, int dil) { return dil == 1 ? (KG == 11 || KG == 13 || KG == 17 || KG == 21) : (dil == 2 && KG == 15); }
-FastPlan make_fast_plan(const Geom &g)
+// wide: as for make_wplan; without it no more parts than whole rounds over the CUs, or the other kernel, take.
+FastPlan make_fast_plan(const Geom &g, bool wide = true)
 {
     FastPlan f = {};
     const int ntg = (g.K + kMaxKT - 1) / kMaxKT;
@@ -1271,12 +1272,21 @@ FastPlan make_fast_plan(const Geom &g)
             const long per_wave = (units + kWaves * f.S - 1) / (kWaves * f.S);
             const double load = std::max(1.0, ntiles * f.S / (double)kPlanCUs);
             // (0.3 per unit and tap: what the chip's power allows once a call is longer than the measured ones of that kernel)
+            auto whole = [&](long S) {
+                const long rounds = (tiles_s * S + kPlanCUs - 1) / kPlanCUs;
+                return tiles_s * S * 100 >= rounds * kPlanCUs * 95;
+            };
+            long most = std::min(8L, std::max(1L, units / 2));
+            if (!wide) {
+                long rounds_at = 1;
+                while (rounds_at <= most && (2 * rounds_at > units || !whole(rounds_at))) ++rounds_at;
+                most = std::min(most, rounds_at <= most ? rounds_at : (long)f.S);
+            }
             double best = 12.9 + load * f.KTg * (0.17 * std::min(per_wave, 8L) + 0.3 * std::max(per_wave - 8, 0L)) + (0.94 * f.S + 0.16) * mb + 3.1e-6 * g.B * (g.Cout + g.Cin) * (double)g.To;
+            if (f.S > most) best = 1e30;
             long S_best = 0;
-            for (long S = 1; S <= 8 && (S == 1 || 2 * S <= units); ++S) {
-                const long wgs = tiles_s * S, rounds = (wgs + kPlanCUs - 1) / kPlanCUs;
-                const bool whole = wgs * 100 >= rounds * kPlanCUs * 95;
-                const double c = cost(S) * (whole ? 0.95 : 1.0);  // (a tie goes to whole rounds)
+            for (long S = 1; S <= most; ++S) {
+                const double c = cost(S) * (whole(S) ? 0.95 : 1.0);  // (a tie goes to whole rounds)
                 if (c < best) {
                     best = c;
                     S_best = S;
@@ -1395,13 +1405,13 @@ size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide)
     Geom g0 = g;
     g0.len = nullptr;
     if (wgrad_k1_supported(g0)) {
-        const FastPlan f = make_fast_plan(g);
+        const FastPlan f = make_fast_plan(g, wide);
         const size_t fast = part_bytes(g, f.S) + dzf_bytes(g, f);
         const size_t k1 = wgrad_k1_part_bytes(g0) + dz_buf_bytes(g);
         return fast > k1 ? fast : k1;
     }
     if (fast_ok(g)) {
-        const FastPlan f = make_fast_plan(g);
+        const FastPlan f = make_fast_plan(g, wide);
         return part_bytes(g, f.S) + dzf_bytes(g, f);
     }
     const WPlan w = make_wplan(g, wide);
@@ -1413,10 +1423,10 @@ size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide)
 // ---- stride-1 kernel with dz already in fragment order (dz_pack_kernel's layout) ----------------
 bool mfma_wgrad_fast_supported(const Geom &g) { return fast_ok(pitched(g)); }
 
-DzfLayout mfma_wgrad_dzf_layout(const Geom &g0)
+DzfLayout mfma_wgrad_dzf_layout(const Geom &g0, bool wide)
 {
     const Geom g = pitched(g0);
-    const FastPlan f = make_fast_plan(g);
+    const FastPlan f = make_fast_plan(g, wide);
     DzfLayout l;
     l.ncm = f.ncm;
     l.nst = f.nst;
@@ -1426,10 +1436,10 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g0)
 }
 
 hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float *scale, float *dw, bool accumulate, void *ws,
-                                      hipStream_t s, const DefinedDw *defined)
+                                      hipStream_t s, bool wide, const DefinedDw *defined)
 {
     const Geom g = pitched(g0);
-    const FastPlan f = make_fast_plan(g);
+    const FastPlan f = make_fast_plan(g, wide);
     float *part = (float *)ws;
     const u32x4 *dzf = (const u32x4 *)((unsigned char *)ws + part_bytes(g, f.S));
     WgradParams p = {};
@@ -1513,7 +1523,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
         return launch_wgrad_k1(g, x, gplain, scale, dw, accumulate, ws, s);
     }
     if (fast_ok(g)) {
-        const FastPlan f = make_fast_plan(g);
+        const FastPlan f = make_fast_plan(g, wide);
         u32x4 *dzf = (u32x4 *)((unsigned char *)ws + part_bytes(g, f.S));
         hipError_t e;
         if (copies) {
@@ -1527,7 +1537,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
             e = hipGetLastError();
         }
         if (e != hipSuccess) return e;
-        return launch_mfma_wgrad_prepared(g0, x, scale, dw, accumulate, ws, s, defined);
+        return launch_mfma_wgrad_prepared(g0, x, scale, dw, accumulate, ws, s, wide, defined);
     }
     const WPlan w = make_wplan(g, wide);
     if (!w.ok) return hipErrorInvalidValue;
@@ -1574,16 +1584,17 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
 void name_mfma_wgrad(const Geom &g0, bool relu, size_t ws_bytes, char *name, size_t n)
 {
     const Geom g = pitched(g0);
+    const bool wide = ws_bytes >= mfma_wgrad_workspace(g0, relu || !rows16(g0), true);
     if (wgrad_k1_supported(g)) {
         snprintf(name, n, "wgrad_k1_kernel");
     } else if (fast_ok(g)) {
-        const FastPlan f = make_fast_plan(g);
+        const FastPlan f = make_fast_plan(g, wide);
         if (f.shared)
             snprintf(name, n, "wgrad_shared_kernel<%d, %d, %s> in %d parts", f.KTg, g.dil, g.len ? "true" : "false", f.S);
         else
             snprintf(name, n, "wgrad_fast_kernel<%d, %d> in %d parts", f.KTg, g.dil, f.S);
     } else {
-        const WPlan w = make_wplan(g, ws_bytes >= mfma_wgrad_workspace(g0, relu || !rows16(g0), true));
+        const WPlan w = make_wplan(g, wide);
         snprintf(name, n, "wgrad_kernel<%d> in %d parts", w.KTg, w.S);
     }
 }

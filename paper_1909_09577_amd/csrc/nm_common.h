@@ -308,7 +308,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
                              size_t ws_bytes, hipStream_t s, const void **g_used = nullptr);
 
 bool mfma_wgrad_supported(const Geom &g);
-// wide: with room for the parts that let few tiles fill the chip (general kernel); less serves too
+// wide: with room for as many parts as are fastest; less serves too
 size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, bool wide = true);
 size_t mfma_wgrad_x_offset(const Geom &g, bool wide = true);  // where the pitched copy of x lies in a workspace sized with need_dz
 hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const void *y,
@@ -372,11 +372,11 @@ struct DzfLayout {
     size_t offset, bytes;
 };
 bool mfma_wgrad_fast_supported(const Geom &g);
-DzfLayout mfma_wgrad_dzf_layout(const Geom &g);
+DzfLayout mfma_wgrad_dzf_layout(const Geom &g, bool wide);
 // weight gradient from a workspace whose fragment-order g has been written already; scale[co] (or NULL)
 // multiplies the float32 sums; defined: for rows of any length
 hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float *scale, float *dw, bool accumulate,
-                                      void *ws, hipStream_t s, const DefinedDw *defined = nullptr);
+                                      void *ws, hipStream_t s, bool wide, const DefinedDw *defined = nullptr);
 // packs the flipped weights times scale into ws (as launch_mfma_dgrad does; where `pack`) and, in the same launch, forms
 // g plain (into dres, else behind the packed weights in ws, else nowhere) and in fragment order (gf);
 // *g_plain: the tensor the input gradient contracts

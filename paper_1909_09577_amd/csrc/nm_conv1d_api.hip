@@ -204,7 +204,7 @@ bool masked_on_mfma(const Geom &g, int op = NM_OP_FWD)
 }
 
 // Scratch need of one operation on one path (mfma: matrix-core kernels, else plain kernels).
-// least: without room for the partial sums of the split engine and for more than eight parts of a weight gradient.
+// least: without room for the partial sums of the split engine and for as many parts of a weight gradient as are fastest.
 size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_relu, bool least = false)
 {
     if (mfma) {
@@ -250,7 +250,7 @@ size_t asked_workspace(int op, const Geom &g, int dtype, unsigned flags, bool le
 }
 // The smallest workspace a pass of this geometry is served with: rows that are no multiple of eight long are served
 // without room for their copies too, and float32 weight gradients without room for partial sums, by the plain kernels, so are stride-2 input gradients;
-// calls of few tiles without room for the split engine's partial sums with fewer parts or by the other engines.
+// calls of few tiles without room for the split engine's partial sums with fewer parts or by the other engines, weight gradients with fewer parts.
 size_t least_workspace(int op, const Geom &g, int dtype, unsigned flags)
 {
     const bool strided = op == NM_OP_BWD_DATA && g.stride == 2;
@@ -744,9 +744,10 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     if (clash) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     void *ws_w = (unsigned char *)workspace + ws_data;  // the weight gradient's workspace: partials, then dz fragments
-    const DzfLayout layout = mfma_wgrad_dzf_layout(g);
+    const bool wide = workspace_bytes - ws_data >= mfma_wgrad_workspace(g, true);
+    const DzfLayout layout = mfma_wgrad_dzf_layout(g, wide);
     const void *g_plain = nullptr;
-    void *xp = g.T % 8 == 0 ? nullptr : (unsigned char *)ws_w + mfma_wgrad_x_offset(g);  // pitched copy of x
+    void *xp = g.T % 8 == 0 ? nullptr : (unsigned char *)ws_w + mfma_wgrad_x_offset(g, wide);  // pitched copy of x
     hipError_t err = launch_bwd_prepare(g, dy, y, scale, w, !mfma_dgrad_unpacked(g, w, ws_data), relu, workspace, (unsigned char *)ws_w + layout.offset, layout,
                                         dres, &g_plain, s, x, xp);
     if (err != hipSuccess) return NM_ERR_DEVICE;
@@ -755,7 +756,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
     const DefinedDw defined = {false, x, dy, relu ? y : nullptr};
-    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, rows16(g) ? nullptr : &defined));
+    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, wide, rows16(g) ? nullptr : &defined));
 }
 
 int nm_conv1d_bwd(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const void *x,

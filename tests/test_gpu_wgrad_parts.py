@@ -65,3 +65,35 @@ def test_fp8_weight_gradient_in_any_number_of_parts(cfg):
     got, ref = T8.run_wgrad_case(cfg, accumulate=True)
     mx, rr = U.err_metrics(got, ref)
     assert mx <= T8.WGRAD_TOL and rr <= T8.WGRAD_RMS, (mx, rr)
+
+
+# a workspace with room for the parts of whole rounds only (what these calls once asked for: weight gradient, both gradients)
+SMALLER = [(L(3, 192, 160, 648, 11), 8939520, 10307072, "wgrad_fast_kernel<6, 1> in 6 parts"),
+           (L(7, 640, 80, 648, 13), 14602240, 17056512, "wgrad_shared_kernel<13, 1, false> in 5 parts"),
+           (L(16, 80, 640, 297, 21), 28835840, 46538752, "wgrad_shared_kernel<21, 1, false> in 5 parts")]
+
+
+@pytest.mark.parametrize("cfg,ws_w,ws_both,name", SMALLER, ids=lambda c: "x".join(map(str, c.dims())) if isinstance(c, LayerCfg) else "")
+def test_less_room_takes_fewer_parts(cfg, ws_w, ws_both, name):
+    assert nm.nm_conv1d_workspace_bytes(nm.NM_OP_BWD_WEIGHT, *cfg.dims(), nm.NM_BF16, nm.NM_RELU) > ws_w
+    assert nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_WEIGHT, *cfg.dims(), workspace_bytes=ws_w) == name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("both", [False, True], ids=["weight", "both"])
+@pytest.mark.parametrize("cfg,ws_w,ws_both,name", SMALLER, ids=lambda c: "x".join(map(str, c.dims())) if isinstance(c, LayerCfg) else "")
+def test_weight_gradient_in_less_room(cfg, ws_w, ws_both, name, both):
+    import torch
+    inp = syn.make_inputs(cfg, "bf16")
+    x, dy, scale, w = (U.to_dev(inp, k, "bf16") for k in ("x", "dy", "scale", "w"))
+    n = ws_both if both else ws_w
+    buf = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    kw = dict(scale=scale, workspace=buf[:n], **U.geom_kw(cfg))
+    dz, _ = orc.epilogue_bwd(inp["dy"], None, inp["scale"], False)
+    if both:
+        dx, _, dw = nm.nm_conv1d_bwd(x, dy, w, **kw)
+        U.assert_close(U.to_host_f64(dx), orc.bwd_data(dz, inp["w"], cfg.T, **U.geom_kw(cfg)), "bf16", "dx")
+    else:
+        dw = nm.nm_conv1d_bwd_weight(x, dy, cfg.K, **kw)
+    assert (buf[n:] == 0xA5).all()
+    U.assert_close(U.to_host_f64(dw), orc.bwd_weight(inp["x"], dz, cfg.K, **U.geom_kw(cfg)), "bf16", "dw", rms_bound=U.RMS_DW_BF16)
