@@ -104,7 +104,7 @@ def cpu_baseline(cfg):
             "sample": f"the whole workload (all {cfg.B} batch items), fp64, fwd+dgrad+wgrad, {dt:.1f} s"}
 
 
-HEADLINE_SOURCES = ("mfma_conv.hip", "mfma_wgrad.hip", "nm_common.h", "nm_conv1d_api.hip")
+HEADLINE_SOURCES = ("conv_tile.h", "mfma_conv.hip", "mfma_wgrad.hip", "nm_common.h", "nm_conv1d_api.hip")
 
 
 def headline_sources_sha256():
