@@ -88,14 +88,12 @@ __device__ __forceinline__ float defined_sum(const F32ConvParams &p, const float
     return z;
 }
 
-// lim: outputs from there on are zero
-template <bool FLIP>
-__device__ __forceinline__ void finish_output(const F32ConvParams &p, float v, const float *in, int len, int lim, int m, int t, size_t o)
+// there: not behind the outputs' valid length, where they are zero
+__device__ __forceinline__ void finish_output(const F32ConvParams &p, float v, bool there, int m, size_t o)
 {
-    if (v != v && t < lim) v = defined_sum<FLIP>(p, in, len, m, t);
     if (p.scale) v *= p.scale[m];
     if (p.shift) v += p.shift[m];
-    if (t >= lim) v = 0.f;
+    if (!there) v = 0.f;
     if (p.res) v += p.res[o];
     if (p.relu) v = v > 0.f ? v : 0.f;
     p.out[o] = v;
@@ -109,7 +107,7 @@ __device__ __forceinline__ void finish_output(const F32ConvParams &p, float v, c
 // Two LDS buffers, one barrier per chunk; the next chunk is written while the current one is multiplied, by the wavefronts
 // 0-3 before their products and by 4-7, the others of the same SIMDs, after them, so that a SIMD's matrix pipe has work
 // while one of its two wavefronts stages (with two barriers around the writes the pipes were busy 41 % of the time).
-template <int NT, bool FLIP, int CC, int XN>
+template <int NT, bool FLIP, int CC, int XN, bool SPLIT>
 __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32ConvParams p)
 {
     extern __shared__ __align__(16) float lds[];
@@ -120,10 +118,14 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
     constexpr int kXRows = CC / kConvWaves;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = (int)blockIdx.x / p.nsplit, split = (int)blockIdx.x - tile * p.nsplit;
-    const int mt = tile % p.nmt, col = tile / p.nmt;
-    const int chunks = (p.R + CC - 1) / CC;
-    const int r_first = split * chunks / p.nsplit * CC, r_end = min(p.R, (split + 1) * chunks / p.nsplit * CC);
+    const int mt = (int)blockIdx.x % p.nmt, col = (int)blockIdx.x / p.nmt;
+    // (an instance of its own: decided at run time, this cost the calls of many tiles 0.3 to 1 %)
+    int r_first = 0, r_end = p.R;
+    if constexpr (SPLIT) {
+        const int split = (int)blockIdx.y, chunks = (p.R + CC - 1) / CC;
+        r_first = split * chunks / p.nsplit * CC;
+        r_end = min(p.R, (split + 1) * chunks / p.nsplit * CC);
+    }
     const int b = col / p.ntt, t0 = (col - b * p.ntt) * TN;
     const int m0 = mt * kTileM;
     const int K = p.K;
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
             xoff[i][j] = c < p.W && tau >= 0 && tau < len ? (uint32_t)((wave * kXRows + i) * p.Tin + tau) * 4u : kFar;
         }
     auto load_chunk = [&](int r0) {
-        if (r0 >= r_end) return;
+        if (r0 >= (SPLIT ? r_end : p.R)) return;
         const int nr = min(CC, p.R - r0);
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i)
@@ -283,11 +285,11 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
     load_chunk(r_first);
     store_chunk(r_first, lds);
     load_chunk(r_first + CC);
-    for (int r0 = r_first, par = 0; r0 < r_end; r0 += CC, par ^= 1) {
+    for (int r0 = r_first, par = 0; r0 < (SPLIT ? r_end : p.R); r0 += CC, par ^= 1) {
         __syncthreads();  // this chunk is in its buffer, the other buffer has been read
         const float *cur = lds + par * buf_floats;
         float *nxt = lds + (par ^ 1) * buf_floats;
-        const bool more = r0 + CC < r_end;
+        const bool more = r0 + CC < (SPLIT ? r_end : p.R);
         if (wave < 4 && more) {
             store_chunk(r0 + CC, nxt);
             load_chunk(r0 + 2 * CC);
@@ -320,11 +322,12 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_conv_kernel(const F32Conv
         float v = 0.f;
 #pragma unroll
         for (int q = 0; q < kConvWaves; ++q) v += lds[(size_t)q * kTileM * TN + e];
-        const size_t o = ((size_t)b * p.M + m) * p.Tout + t;
-        if (p.nsplit > 1)
-            p.part[(size_t)split * p.B * p.M * p.Tout + o] = v;
-        else
-            finish_output<FLIP>(p, v, xb, len, lim, m, t, o);
+        if constexpr (SPLIT) {
+            p.part[(size_t)blockIdx.y * p.B * p.M * p.Tout + ((size_t)b * p.M + m) * p.Tout + t] = v;
+        } else {
+            if (v != v && t < lim) v = defined_sum<FLIP>(p, xb, len, m, t);
+            finish_output(p, v, t < lim, m, ((size_t)b * p.M + m) * p.Tout + t);
+        }
     }
 }
 
@@ -342,7 +345,9 @@ __global__ __launch_bounds__(256) void f32_split_finish_kernel(const F32ConvPara
         const int l = len_of ? len_of[b] : most;
         return l < 0 ? 0 : (l < most ? l : most);
     };
-    finish_output<FLIP>(p, v, p.in + (size_t)b * p.R * p.Tin, limit(p.len_in, p.Tin), limit(p.len_out, p.Tout), m, t, o);
+    const int lim = limit(p.len_out, p.Tout);
+    if (v != v && t < lim) v = defined_sum<FLIP>(p, p.in + (size_t)b * p.R * p.Tin, limit(p.len_in, p.Tin), m, t);
+    finish_output(p, v, t < lim, m, o);
 }
 
 struct F32ConvPlan {
@@ -370,7 +375,7 @@ F32ConvPlan f32_conv_plan(int K, int stride, int dil, int nt, bool flip)
     return q;
 }
 
-template <int NT, bool FLIP, int CC, int XN>
+template <int NT, bool FLIP, int CC, int XN, bool SPLIT>
 hipError_t launch_f32_conv_t(F32ConvParams p, const F32ConvPlan &q, hipStream_t s)
 {
     p.W = q.W; p.w_stride = q.w_stride; p.x_stride = q.x_stride;
@@ -378,24 +383,24 @@ hipError_t launch_f32_conv_t(F32ConvParams p, const F32ConvPlan &q, hipStream_t 
     p.flush = 32 / taps;  // 64 products at most, two a tap and chunk
     p.nmt = (p.M + kTileM - 1) / kTileM;
     p.ntt = (p.Tout + 32 * NT - 1) / (32 * NT);
-    auto kern = f32_conv_kernel<NT, FLIP, CC, XN>;
+    auto kern = f32_conv_kernel<NT, FLIP, CC, XN, SPLIT>;
     static LdsOptIn opt_in;
     hipError_t e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), kMaxLds);
     if (e != hipSuccess) return e;
     {
         MainKernelTimer timer(s);
-        hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B * p.nsplit)), dim3(64 * kConvWaves), q.lds, s, p);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B), (unsigned)p.nsplit), dim3(64 * kConvWaves), q.lds, s, p);
     }
-    if (p.nsplit > 1)
+    if (SPLIT)
         hipLaunchKernelGGL(f32_split_finish_kernel<FLIP>, dim3((unsigned)(((size_t)p.B * p.M * p.Tout + 255) / 256)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
-template <int NT, bool FLIP>
+template <int NT, bool FLIP, bool SPLIT>
 hipError_t launch_f32_conv_nt(const F32ConvParams &p, const F32ConvPlan &q, hipStream_t s)
 {
     if (q.cc == 16)
-        return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 16, 2>(p, q, s) : launch_f32_conv_t<NT, FLIP, 16, kXIter>(p, q, s);
-    return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 8, 2>(p, q, s) : launch_f32_conv_t<NT, FLIP, 8, kXIter>(p, q, s);
+        return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 16, 2, SPLIT>(p, q, s) : launch_f32_conv_t<NT, FLIP, 16, kXIter, SPLIT>(p, q, s);
+    return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 8, 2, SPLIT>(p, q, s) : launch_f32_conv_t<NT, FLIP, 8, kXIter, SPLIT>(p, q, s);
 }
 // Workgroups that share a tile's reduction channels where the tiles are too few to fill the chip (NT = 1 there): a
 // workgroup takes 3 us per chunk of channels, 16 chunks at 256 channels, K=11, and the second launch 4.
@@ -422,8 +427,9 @@ hipError_t launch_f32_conv(F32ConvParams p, void *part, size_t room, hipStream_t
     // the wide tile from two workgroups per CU on (and where its window fits)
     const size_t wide = (size_t)((p.M + kTileM - 1) / kTileM) * ((p.Tout + 63) / 64) * p.B;
     const F32ConvPlan q2 = f32_conv_plan(p.K, p.stride, p.dil, 2, FLIP), q1 = f32_conv_plan(p.K, p.stride, p.dil, 1, FLIP);
-    if (wide >= 512 && q2.ok) return launch_f32_conv_nt<2, FLIP>(p, q2, s);
-    return q1.ok ? launch_f32_conv_nt<1, FLIP>(p, q1, s) : hipErrorInvalidValue;
+    if (wide >= 512 && q2.ok) return launch_f32_conv_nt<2, FLIP, false>(p, q2, s);
+    if (!q1.ok) return hipErrorInvalidValue;
+    return p.nsplit > 1 ? launch_f32_conv_nt<1, FLIP, true>(p, q1, s) : launch_f32_conv_nt<1, FLIP, false>(p, q1, s);
 }
 
 // ---- weight gradient -------------------------------------------------------------------------------------------
