@@ -1764,9 +1764,10 @@ hipError_t launch_split_t(ConvGemmParams p, int cols_at_once, size_t lds, hipStr
     for (p.col0 = 0; p.col0 < cols; p.col0 += cols_at_once) {
         p.ncols = std::min(cols_at_once, cols - p.col0);
         hipLaunchKernelGGL((conv_split_kernel<NT, STRIDE>), dim3(p.nmt * p.ncols * p.nsplit), dim3(kThreads), lds, s, p);
-        if (p.nsplit > 1) (void)launch_split_reduce(p, NT, s);
+        const hipError_t e = p.nsplit > 1 ? launch_split_reduce(p, NT, s) : hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // [part, part + part_room): room for the parts of one column of tiles at least
@@ -2006,6 +2007,7 @@ void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin
 
 }  // namespace
 
+// (also reports a refused launch before it: asking clears it)
 hipError_t launch_split_reduce(const ConvGemmParams &p, int nt, hipStream_t s)
 {
     hipLaunchKernelGGL(split_reduce_kernel, dim3(p.nmt * p.ncols * kWaves * nt), dim3(64), 0, s, p, nt);
