@@ -387,10 +387,8 @@ hipError_t launch_f32_conv_t(F32ConvParams p, const F32ConvPlan &q, hipStream_t 
     static LdsOptIn opt_in;
     hipError_t e = ensure_dynamic_lds(opt_in, reinterpret_cast<const void *>(kern), kMaxLds);
     if (e != hipSuccess) return e;
-    {
-        MainKernelTimer timer(s);
-        hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B), (unsigned)p.nsplit), dim3(64 * kConvWaves), q.lds, s, p);
-    }
+    MainKernelTimer timer(s);  // (the sum of the parts counts with the kernel)
+    hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B), (unsigned)p.nsplit), dim3(64 * kConvWaves), q.lds, s, p);
     if (SPLIT)
         hipLaunchKernelGGL(f32_split_finish_kernel<FLIP>, dim3((unsigned)(((size_t)p.B * p.M * p.Tout + 255) / 256)), dim3(256), 0, s, p);
     return hipGetLastError();

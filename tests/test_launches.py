@@ -49,3 +49,20 @@ def test_a_refused_launch_is_reported(name, whole):
     for (st, s), (_, kernel, _) in zip(got, seq):
         assert any(kind == "refused" and k == kernel for kind, k, _ in s)
         assert st == nm.NM_ERR_DEVICE, f"{kernel} refused, status {st}"
+
+
+def test_the_timer_counts_the_sum_of_the_parts():
+    """A convolution's pair of events encloses the pass that adds up and finishes its parts, and nothing else."""
+    pairs = [(name, op, kernels) for name, op, kernels in [
+        ("split engine, parts", nm.NM_OP_FWD, ["conv_split_kernel", "split_reduce_kernel"]),
+        ("unpacked", nm.NM_OP_FWD, ["conv_unpacked_kernel", "split_reduce_kernel"]),
+        ("unpacked gradient", nm.NM_OP_BWD_DATA, ["conv_unpacked_kernel", "split_reduce_kernel"]),
+        ("float32", nm.NM_OP_FWD, ["f32_conv_kernel"]),
+        ("float32, shared", nm.NM_OP_FWD, ["f32_conv_kernel", "f32_split_finish_kernel"]),
+        ("float32, shared, gradients", nm.NM_OP_BWD_DATA, ["f32_conv_kernel", "f32_split_finish_kernel"]),
+        ("float32, shared, gradients", nm.NM_OP_BWD_WEIGHT, ["f32_wgrad_kernel"])]]
+    for (name, op, kernels), (status, seq) in zip(pairs, la.run([dict(CALLS[n], timer=op) for n, op, _ in pairs])):
+        assert status == nm.NM_OK
+        a, b = ([i for i, (kind, what, _) in enumerate(seq) if (kind, what) == ("event", e)] for e in (la.START, la.STOP))
+        assert len(a) == len(b) == 1, (name, seq)
+        assert [k for _, k, _ in seq[a[0] + 1:b[0]]] == kernels, (name, op)
