@@ -2117,8 +2117,7 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
 namespace {
 void name_unpacked(const UnpackedPlan &up, int K, bool flip, char *name, size_t n)
 {
-    snprintf(name, n, "conv_split_kernel<%d, 1> in %d parts of unpacked weights: conv_unpacked_kernel<%d, %d, %s>", up.nt, up.nsplit, up.nt, K,
-             flip ? "true" : "false");
+    snprintf(name, n, "conv_unpacked_kernel<%d, %d, %s> in %d parts", up.nt, K, flip ? "true" : "false", up.nsplit);
 }
 }  // namespace
 void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n)

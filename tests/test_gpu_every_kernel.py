@@ -35,7 +35,7 @@ POINTWISE = [("pointwise_gemm_kernel<false, 2, 5, 128>", "pointwise_gemm_kernel<
              ("pointwise_gemm_kernel<false, 4, 4, 64>", "pointwise_gemm_kernel<true, 4, 4, 64>", L(26, 221, 1050, 168, 1)),
              ("pointwise_gemm_kernel<true, 4, 4, 64>", "pointwise_gemm_kernel<true, 4, 4, 64>", L(33, 270, 773, 172, 1))]
 SPLIT = [(f"conv_split_kernel<{nt}, {c.stride}> {n}",) * 2 + (c,) for nt, n, c in [
-    (2, "one", L(1, 64, 640, 264, 13)), (2, "parts", L(1, 512, 256, 203, 17)), (3, "one", L(29, 70, 522, 73, 3)), (3, "parts", L(1, 531, 648, 219, 1)),
+    (2, "one", L(1, 64, 640, 264, 13)), (2, "parts", L(1, 512, 256, 203, 15)), (3, "one", L(29, 70, 522, 73, 3)), (3, "parts", L(1, 531, 648, 219, 1)),
     (4, "one", L(38, 40, 492, 104, 4, dilation=2)), (4, "parts", L(9, 520, 68, 206, 1)), (2, "one", L(3, 64, 256, 400, 11, stride=2)),
     (2, "parts", L(1, 596, 44, 91, 29, stride=2)), (3, "one", L(20, 40, 866, 144, 4, stride=2)), (3, "parts", L(22, 293, 37, 144, 29, stride=2))]]
 CASES = UNROLLED + TAP_PAIRS + POINTWISE + SPLIT

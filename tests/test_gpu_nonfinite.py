@@ -15,7 +15,10 @@ CASES = {
     ("f32", 2, 24, 40, 201, 5, 2, 1, 2): "f32_conv",
     ("f32", 1, 24, 80, 100, 32, 1, 1, 16): "f32_conv",
     ("bf16", 2, 64, 96, 133, 11, 1, 1, 5): "conv_split_kernel<2, 1> in 1 parts",
-    ("bf16", 1, 512, 64, 133, 11, 1, 2, 10): "conv_split_kernel<2, 1> in ",
+    ("bf16", 1, 512, 64, 133, 9, 1, 2, 8): "conv_split_kernel<2, 1> in 16 parts",
+    ("bf16", 1, 256, 256, 133, 11, 1, 1, 5): "conv_unpacked_kernel<2, 11, false>",
+    ("bf16", 1, 512, 512, 131, 25, 1, 1, 12): "conv_unpacked_kernel<2, 25, false>",
+    ("bf16", 1, 256, 256, 133, 13, 1, 2, 12): "conv_unpacked_kernel<2, 13, false>",
     ("bf16", 20, 128, 512, 1277, 11, 1, 1, 5): "conv_gemm_kernel<5, 1, 11, true, false, true",        # the unrolled kernel
     ("bf16", 8, 256, 200, 801, 7, 1, 1, 3): "conv_gemm_kernel<5, 1, 0, false, false, true, false>",    # tap pairs, an absent eighth tap
     ("bf16", 8, 256, 200, 798, 7, 1, 1, 4): "conv_gemm_kernel<5, 1, 0, false, false, true, false>",    # the same, only the input rows odd
@@ -45,6 +48,9 @@ def test_one_infinite_element(case, masked):
     dtype, B, Cin, Cout, T, K, stride, dil, pad = case
     name = nm.nm_conv1d_kernel_name(nm.NM_OP_FWD, *case[1:], dtype=nm.NM_F32 if dtype == "f32" else nm.NM_BF16, masked=masked)
     assert name.startswith(CASES[case]), name
+    if "conv_unpacked" in name:  # the gradient's infinities go through the flipped instance
+        back = nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_DATA, *case[1:], masked=masked)
+        assert back.startswith(f"conv_unpacked_kernel<2, {case[5]}, true>"), back
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     To = orc.out_len(T, K, stride, dil, pad)
     kw = dict(stride=stride, dilation=dil, pad=pad)

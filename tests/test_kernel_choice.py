@@ -23,17 +23,18 @@ def test_full_size_layers_run_on_the_unrolled_kernels(cfg):
 
 
 def test_the_workspace_has_a_say():
-    few = (1, 768, 768, 600, 25, 1, 1, 12)
-    assert nm.nm_conv1d_kernel_name(FWD, *few).startswith("conv_split_kernel<")
-    full = nm.nm_conv1d_workspace_bytes(FWD, *few)
-    # with less room fewer parts, without any the other engine
-    least = -(-768 // 64) * (768 // 32) * 26 * 256 * 16 + 512 * 16
-    parts = [int(nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=n).split(" in ")[1].split()[0]) for n in (full, least + (full - least) // 2)]
-    assert parts[0] > parts[1] > 1
-    assert nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least) == "conv_gemm_kernel<5, 1, 25, false, false, false, false>"
-    with pytest.raises(nm.NmError) as e:
-        nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least - 1)
-    assert e.value.status == nm.NM_ERR_WORKSPACE
+    for K, engine, other in ((15, "conv_split_kernel<", 0), (25, "conv_unpacked_kernel<", 25)):
+        few = (1, 768, 768, 600, K, 1, 1, K // 2)
+        assert nm.nm_conv1d_kernel_name(FWD, *few).startswith(engine)
+        full = nm.nm_conv1d_workspace_bytes(FWD, *few)
+        # with less room fewer parts, without any the other engine
+        least = -(-768 // 64) * (768 // 32) * (K + 1) * 256 * 16 + 512 * 16
+        parts = [int(nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=n).split(" in ")[1].split()[0]) for n in (full, least + (full - least) // 2)]
+        assert parts[0] > parts[1] > 1
+        assert nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least) == f"conv_gemm_kernel<5, 1, {other}, false, false, false, false>"
+        with pytest.raises(nm.NmError) as e:
+            nm.nm_conv1d_kernel_name(FWD, *few, workspace_bytes=least - 1)
+        assert e.value.status == nm.NM_ERR_WORKSPACE
     odd = (16, 384, 384, 777, 13, 1, 1, 6)
     for op, plain in ((FWD, "direct_fwd_kernel"), (DGRAD, "direct_dgrad_kernel"), (WGRAD, "direct_wgrad_kernel")):
         assert not nm.nm_conv1d_kernel_name(op, *odd).startswith("direct")
@@ -107,9 +108,10 @@ def test_the_smallest_calls_stay_on_the_plain_kernels(dtype):
 
 def test_plans_in_parts_are_ranked_by_their_estimate():
     """Below the host's floor for a third launch all plans in parts cost the same against another engine; among themselves the
-    first one tried (128-step tiles, four parts) must not win: 17.3 us on the device with 64-step tiles, 19.1 with those.
+    first one tried (128-step tiles, four parts) must not win (K=13 on packed weights: 17.3 us on the device with 64-step tiles,
+    19.1 with those).
     And a K=1 call whose other engine was estimated too high: 44 us there, 58 in the engine for few tiles."""
-    assert nm.nm_conv1d_kernel_name(FWD, 1, 384, 384, 600, 13, 1, 1, 6).startswith("conv_split_kernel<2, 1>")
+    assert nm.nm_conv1d_kernel_name(FWD, 1, 384, 384, 600, 12, 1, 1, 6).startswith("conv_split_kernel<2, 1>")
     assert nm.nm_conv1d_kernel_name(DGRAD, 23, 896, 64, 1496, 1) .startswith("pointwise_gemm_kernel<false")
 
 
