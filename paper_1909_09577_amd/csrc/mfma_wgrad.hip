@@ -744,47 +744,38 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
     // units of this workgroup: sp, sp + S, sp + 2S, ...; (batch item, chunk) advance without divisions
     const int step_b = S / p.nchunk, step_c = S - step_b * p.nchunk;
     struct UnitPos {
-        int b, c, u;  // u: (LEN) the unit's number
-    };
-    // (LEN) the lengths of the first 64 items, one per lane: a load per unit and use made a unit twice as long (1.4 us, 384
-    // channels, K=13)
-    const int lane_len = LEN && lane < p.B ? clipped_len(p.len, lane, p.T) : 0;
-    auto len_of = [&](int b) {
-        return b < 64 ? __builtin_amdgcn_readlane(lane_len, b) : __builtin_amdgcn_readfirstlane(clipped_len(p.len, b, p.T));
+        int b, c, u, tlen;  // u, tlen: (LEN) the unit's number, its item's length
     };
     // with lengths: chunks of item b that reach below its valid length (chunk c reads x from c*80 - pad on)
     auto live_chunks_of = [&](int tl) { return tl > 0 ? min(p.nchunk, (tl + p.pad + kFastTCH - 1) / kFastTCH) : 0; };
-    // (LEN, up to 64 items) live units up to and with this lane's item: the item of unit u is the first whose count is above
-    // u, one ballot; walking the items cost as much as the products of a unit
-    int upto = 0;
-    if constexpr (LEN) {
-        upto = lane < p.B ? live_chunks_of(lane_len) : 0;
+    // (LEN) 64 items from item0 on, one per lane: their lengths (a load per unit and use made a unit twice as long, 1.4 us at
+    // 384 channels, K=13) and the live units up to and with each, counted from unit0, the first unit of item0.  The item of unit
+    // u is the first whose count is above u: one ballot, where walking the items costs as much as the products of a unit.
+    int item0 = 0, unit0 = 0, lane_len = 0, upto = 0;
+    auto look_at_items = [&]() {
+        lane_len = item0 + lane < p.B ? clipped_len(p.len, item0 + lane, p.T) : 0;
+        upto = live_chunks_of(lane_len);
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int v = __shfl_up(upto, d, 64);
             upto += lane >= d ? v : 0;
         }
-    }
-    auto carry_over = [&](UnitPos &q) {  // c counts live chunks from the start of item b onwards
-        while (q.b < p.B) {
-            const int n = live_chunks_of(len_of(q.b));
-            if (q.c < n) break;
-            q.c -= n;
-            ++q.b;
-        }
     };
+    if constexpr (LEN) look_at_items();
     auto unit_pos = [&](int u) {
-        if constexpr (LEN) {
-            UnitPos q{0, u, u};
-            if (p.B <= 64) {
-                q.b = __popcll(__ballot(upto <= u));
-                if (q.b > 0) q.c -= __builtin_amdgcn_readlane(upto, q.b - 1);
-            } else {
-                carry_over(q);
+        if constexpr (LEN) {  // (u never goes back)
+            while (item0 + 64 < p.B && u - unit0 >= __builtin_amdgcn_readlane(upto, 63)) {
+                unit0 += __builtin_amdgcn_readlane(upto, 63);
+                item0 += 64;
+                look_at_items();
             }
+            const int i = __popcll(__ballot(upto <= u - unit0));  // 64: behind the last item
+            UnitPos q{item0 + i, u - unit0, u, p.T};
+            if (i > 0) q.c -= __builtin_amdgcn_readlane(upto, i - 1);
+            if (i < 64) q.tlen = __builtin_amdgcn_readlane(lane_len, i);
             return q;
         } else {
-            return UnitPos{u / p.nchunk, u % p.nchunk, u};
+            return UnitPos{u / p.nchunk, u % p.nchunk, u, p.T};
         }
     };
     auto advance = [&](UnitPos &q) {
@@ -805,7 +796,7 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
         a.tbase = q.c * kFastTCH;
         a.xs = (uint32_t)b * (uint32_t)(p.Cin * p.T * 2);
         a.as = (uint32_t)((b * p.ncm + (co0 >> 5)) * p.nst + q.c * kFastSteps) * 1024u;
-        a.tlen = LEN ? len_of(b) : p.len ? __builtin_amdgcn_readfirstlane(clipped_len(p.len, b, p.T)) : p.T;
+        a.tlen = LEN ? q.tlen : p.len ? __builtin_amdgcn_readfirstlane(clipped_len(p.len, b, p.T)) : p.T;
         return a;
     };
     auto x_load_item = [&](const UnitAddr &a, u32x4 &xa, u32x4 &xb) {

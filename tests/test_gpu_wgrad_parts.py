@@ -28,7 +28,8 @@ def test_parts(dims, name):
 
 
 CASES = [(L(70, 256, 256, 24, 11), None), (L(70, 256, 320, 96, 11), None), (L(64, 384, 256, 41, 13), None), (L(3, 320, 448, 170, 17), [170, 0, 81]),
-         (L(5, 320, 640, 88, 21), [88, 80, 79, 1, 88]), (L(2, 384, 512, 96, 29, dilation=2), [40, 96])]
+         (L(5, 320, 640, 88, 21), [88, 80, 79, 1, 88]), (L(2, 384, 512, 96, 29, dilation=2), [40, 96]),
+         (L(200, 256, 256, 40, 11), [0] * 130 + [33] * 70), (L(129, 256, 320, 88, 13), [88, 5, 0] * 43)]
 
 
 def test_the_cases_run_on_the_kernel_with_shared_staging():
@@ -54,6 +55,33 @@ def test_weight_gradient(case, masked):
     dw = nm.nm_conv1d_bwd_weight(x, dy, cfg.K, scale=scale, lengths=ld, **U.geom_kw(cfg))
     dz, _ = orc.epilogue_bwd(inp["dy"], None, inp["scale"], False)
     U.assert_close(U.to_host_f64(dw), orc.bwd_weight_masked(inp["x"], dz, cfg.K, lens, **U.geom_kw(cfg)), "bf16", "dw", rms_bound=U.RMS_DW_BF16)
+
+
+@pytest.mark.gpu
+def test_units_of_many_items_are_not_walked():
+    """256 padded items take no longer than 256 whole ones but for what it costs to look the lengths up (1.1 times); a walk over
+    the items for every unit took 20 times as long."""
+    import torch
+    B, C, T, K = 256, 128, 160, 11
+    x, dy = torch.randn(B, C, T, device="cuda").bfloat16(), torch.randn(B, C, T, device="cuda").bfloat16()
+    assert nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_WEIGHT, B, C, C, T, K, 1, 1, 5, masked=True).startswith("wgrad_shared_kernel<11, 1, true>")
+    ws = torch.empty(nm.nm_conv1d_workspace_bytes(nm.NM_OP_BWD_WEIGHT, B, C, C, T, K, 1, 1, 5), dtype=torch.uint8, device="cuda")
+    dw = torch.empty(C, C, K, device="cuda")
+
+    def best(lengths):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        times = []
+        for _ in range(6):
+            ev[0].record()
+            for _ in range(10):
+                nm.nm_conv1d_bwd_weight(x, dy, K, dw=dw, pad=5, lengths=lengths, workspace=ws)
+            ev[1].record()
+            torch.cuda.synchronize()
+            times.append(ev[0].elapsed_time(ev[1]))
+        return min(times)
+
+    whole, padded = best(None), best(torch.full((B,), T, dtype=torch.int32, device="cuda"))
+    assert padded < 3 * whole, (padded, whole)
 
 
 @pytest.mark.gpu
