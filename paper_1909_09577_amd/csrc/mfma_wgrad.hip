@@ -64,6 +64,7 @@ struct WgradParams {
     // stride-1, dilation-1 kernel only: dz in MFMA A-fragment order [B][ncm][nst][64 lanes][8]
     const u32x4 *dzf;
     int ncm, nst;              // 32-channel blocks (2 per tile), 16-step blocks per batch row
+    int chain;                 // wgrad_shared_kernel: pairs of units after which a sum is added to a total (0: never)
 };
 
 __device__ __forceinline__ void wave_lds_fence()
@@ -706,9 +707,19 @@ constexpr TapPlan make_tap_plan()
     return q;
 }
 
+// Blocks of a wavefront whose totals lie in LDS (see CUT): eight is what fits there behind the three windows.
+constexpr int total_blocks(int KG) { return (2 * KG + kWaves - 1) / kWaves < 8 ? (2 * KG + kWaves - 1) / kWaves : 8; }
+
 // LEN: the launch carries valid lengths; the units of an item whose x window lies wholly in the padding
 // multiply zeros and are left out of the enumeration (every workgroup walks the same shortened list).
-template <int KG, int DIL, int W, bool LEN>
+// CUT: a float32 sum is a chain of one product after the other, and its error grows with the root of the chain's length.
+// Where a workgroup has more units than a part of the plan in whole rounds would (make_fast_plan), its sums are added to
+// totals and begun again every p.chain pairs of units, which keeps the chains as short as that plan's: error of dw against
+// 64 bits, 640 -> 768 channels, K=25, B=5, T=528 9.5e-8 in eight parts, 2.4e-7 in one, 9.8e-8 in one that is cut; 303 layers
+// of the encoder 0.99 times those parts' on average, 1.11 at most (5.0e-8 -> 5.6e-8: a chain has two units at least).  The
+// totals lie in LDS, the registers being taken; adding to them costs 0.17 us per block and chain (LDS atomics took 30 times
+// as long), the whole 5 % of the calls concerned.  An instance of its own: the others keep their registers.
+template <int KG, int DIL, int W, bool LEN, bool CUT>
 __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char *smem, int sp, int k0, int kt, int co0,
                                              int ci0)
 {
@@ -849,6 +860,27 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
     for (int j = 0; j < NBW; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    // (CUT) the sums of the chains before this one: of the first blocks in LDS, four registers of a block and lane at a time, of
+    // the others in registers
+    constexpr int kTotals = total_blocks(KG), kKept = CUT && NBW > kTotals ? NBW - kTotals : 1;
+    f32x4 *const totals = reinterpret_cast<f32x4 *>(smem + 3 * kBufBytes + W * kTotals * 4096) + lane;
+    f32x16 kept[kKept];
+    if constexpr (CUT) {
+#pragma unroll
+        for (int j = 0; j < NBW && j < kTotals; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) totals[(j * 4 + q) * 64] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < kKept; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) kept[j][r] = 0.f;
+    }
+    auto add_total = [&](int j, int q) __attribute__((always_inline)) {  // registers 4q .. 4q+3 of block j and their total
+        const f32x4 v = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+        if (j < kTotals) return totals[(j * 4 + q) * 64] + v;
+        const f32x16 &k = kept[j < kTotals ? 0 : j - kTotals];
+        return f32x4{k[4 * q], k[4 * q + 1], k[4 * q + 2], k[4 * q + 3]} + v;
+    };
 
     int units = p.units;
     if constexpr (LEN) {  // live units of the whole batch: one item per lane, summed over the wavefront
@@ -970,9 +1002,34 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
         __syncthreads();  // window u+2 is complete; window u may be overwritten from the next unit on
     };
     const int npairs = (my_units + 1) >> 1;
-    for (int i = 0; i < npairs; ++i) {
-        unit(std::integral_constant<int, 0>{}, afr0, xa1, xb1r, tlen1, tbase1, xa0, xb0r, tlen0, tbase0);
-        unit(std::integral_constant<int, 1>{}, afr1, xa0, xb0r, tlen0, tbase0, xa1, xb1r, tlen1, tbase1);
+    // (with lengths there are fewer units in all, and in a chain)
+    const int chain = !CUT ? npairs : max(1, LEN ? (int)((long)p.chain * units / p.units) : p.chain);
+    for (int first = 0; first < npairs; first += chain) {
+        const int end = CUT ? min(first + chain, npairs) : npairs;
+        for (int i = first; i < end; ++i) {
+            unit(std::integral_constant<int, 0>{}, afr0, xa1, xb1r, tlen1, tbase1, xa0, xb0r, tlen0, tbase0);
+            unit(std::integral_constant<int, 1>{}, afr1, xa0, xb0r, tlen0, tbase0, xa1, xb1r, tlen1, tbase1);
+        }
+        if constexpr (CUT) {
+            if (end == npairs) break;
+#pragma unroll
+            for (int j = 0; j < NBW; ++j) {
+                // one block after the other: the compiler otherwise copies all of them to vector registers first, more than there are
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" : "+a"(acc[j]));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = add_total(j, q);
+                    if (j < kTotals) totals[(j * 4 + q) * 64] = v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (j >= kTotals) kept[j < kTotals ? 0 : j - kTotals][4 * q + r] = v[r];
+                        acc[j][4 * q + r] = 0.f;
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 
     // ---- every block goes straight to the scratch: register r of a block is output channel
@@ -983,16 +1040,22 @@ __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char
         for (int j = 0; j < NBW; ++j) {
             const int tap = plan.tap[j], half = plan.half[j];
             if (tap >= kt) continue;  // a group shorter than KG
+            if constexpr (CUT) asm volatile("" : "+a"(acc[j]));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int co = co0 + 32 * half + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (co < p.Cout) p.part[(((size_t)sp * p.K + k0 + tap) * p.Cout + co) * p.Cin + ci] = acc[j][r];
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+                if constexpr (CUT) v = add_total(j, q);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int co = co0 + 32 * half + 8 * q + 4 * (lane >> 5) + r;
+                    if (co < p.Cout) p.part[(((size_t)sp * p.K + k0 + tap) * p.Cout + co) * p.Cin + ci] = v[r];
+                }
             }
         }
     }
 }
 
-template <int KG, int DIL, bool LEN = false>
+template <int KG, int DIL, bool LEN, bool CUT>
 __global__ __launch_bounds__(kThreads) void wgrad_shared_kernel(const WgradParams p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1003,10 +1066,10 @@ __global__ __launch_bounds__(kThreads) void wgrad_shared_kernel(const WgradParam
     const int kt = min(p.KTg, p.K - k0);
     const int co0 = tcd.cot * kTileCo, ci0 = tcd.cit * kTileCi;
     switch (wave) {  // one copy per wavefront number: the block lists are static
-    case 0: shared_units<KG, DIL, 0, LEN>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
-    case 1: shared_units<KG, DIL, 1, LEN>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
-    case 2: shared_units<KG, DIL, 2, LEN>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
-    default: shared_units<KG, DIL, 3, LEN>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
+    case 0: shared_units<KG, DIL, 0, LEN, CUT>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
+    case 1: shared_units<KG, DIL, 1, LEN, CUT>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
+    case 2: shared_units<KG, DIL, 2, LEN, CUT>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
+    default: shared_units<KG, DIL, 3, LEN, CUT>(p, smem, tcd.sp, k0, kt, co0, ci0); break;
     }
 }
 
@@ -1217,6 +1280,7 @@ bool fast_ok(const Geom &g)
 }
 struct FastPlan {
     int KTg, ntg, S, nchunk, ncm, nst;
+    int chain;    // see WgradParams
     size_t lds;
     bool shared;  // wgrad_shared_kernel (taps split over the wavefronts) instead of wgrad_fast_kernel
 };
@@ -1268,11 +1332,10 @@ FastPlan make_fast_plan(const Geom &g, bool wide = true)
                 return tiles_s * S * 100 >= rounds * kPlanCUs * 95;
             };
             long most = std::min(8L, std::max(1L, units / 2));
-            if (!wide) {
-                long rounds_at = 1;
-                while (rounds_at <= most && (2 * rounds_at > units || !whole(rounds_at))) ++rounds_at;
-                most = std::min(most, rounds_at <= most ? rounds_at : (long)f.S);
-            }
+            long rounds_at = 1;  // parts that fill whole rounds
+            while (rounds_at <= most && (2 * rounds_at > units || !whole(rounds_at))) ++rounds_at;
+            const long chain = rounds_at <= most ? units / rounds_at : std::max(1L, units / (kWaves * f.S));
+            if (!wide) most = std::min(most, rounds_at <= most ? rounds_at : (long)f.S);
             double best = 12.9 + load * f.KTg * (0.17 * std::min(per_wave, 8L) + 0.3 * std::max(per_wave - 8, 0L)) + (0.94 * f.S + 0.16) * mb + 3.1e-6 * g.B * (g.Cout + g.Cin) * (double)g.To;
             if (f.S > most) best = 1e30;
             long S_best = 0;
@@ -1288,6 +1351,7 @@ FastPlan make_fast_plan(const Geom &g, bool wide = true)
                 f.KTg = KG;
                 f.ntg = ntg;
                 f.S = (int)S_best;
+                f.chain = (units + S_best - 1) / S_best > std::max(2L, chain) ? (int)std::max(1L, chain / 2) : 0;
                 f.lds = 3 * 128 * kFastXRowBytes;
             }
         }
@@ -1314,11 +1378,16 @@ hipError_t launch_fast_kt(const WgradParams &p, size_t lds, int grid, hipStream_
 template <int KG, int DIL>
 hipError_t launch_shared(const WgradParams &p, size_t lds, int grid, hipStream_t s)
 {
+    auto kern = p.chain > 0 ? (p.len ? wgrad_shared_kernel<KG, DIL, true, true> : wgrad_shared_kernel<KG, DIL, false, true>)
+                            : (p.len ? wgrad_shared_kernel<KG, DIL, true, false> : wgrad_shared_kernel<KG, DIL, false, false>);
+    if (p.chain > 0) {
+        lds += (size_t)kWaves * total_blocks(KG) * 4096;
+        static LdsOptIn opt_in[2];
+        const hipError_t e = ensure_dynamic_lds(opt_in[p.len ? 1 : 0], reinterpret_cast<const void *>(kern), kMaxLds);
+        if (e != hipSuccess) return e;
+    }
     MainKernelTimer timer(s);
-    if (p.len)
-        hipLaunchKernelGGL((wgrad_shared_kernel<KG, DIL, true>), dim3(grid), dim3(kThreads), lds, s, p);
-    else
-        hipLaunchKernelGGL((wgrad_shared_kernel<KG, DIL>), dim3(grid), dim3(kThreads), lds, s, p);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, s, p);
     return hipGetLastError();
 }
 
@@ -1445,6 +1514,7 @@ hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float
     if (f.shared) p.CL = -1;
     p.x = (const bf16_t *)x; p.dzf = dzf; p.part = part;
     p.len = g.len;
+    p.chain = f.chain;
     const int grid = p.per_xcd * 8;
     hipError_t e;
     if (f.shared) {

@@ -58,6 +58,32 @@ def test_weight_gradient(case, masked):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
+@pytest.mark.parametrize("cfg,parts", [(L(4, 640, 640, 392, 21), 5), (L(5, 768, 768, 360, 25), 3), (L(3, 768, 896, 400, 29, dilation=2), 3)],
+                         ids=lambda c: "x".join(map(str, c.dims())) if isinstance(c, LayerCfg) else "")
+def test_fewer_parts_are_no_less_exact(cfg, parts, masked):
+    """One part where whole rounds over the CUs would take several: its sums are no longer chains than theirs.  A chain of n
+    roundings of growing sums, each 2^-24 / sqrt(3) of its sum, ends sqrt(n / 2) of that off (measured: 0.8 of it); a chain over
+    the whole part is sqrt(parts) as far off, 1.5 to 2.1 times here, which the gate of the other tests does not see."""
+    import torch
+    d = cfg.dims()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, dy = (torch.randn(cfg.B, c, cfg.T, device="cuda", generator=gen).bfloat16() for c in (cfg.Cin, cfg.Cout))
+    lens = torch.full((cfg.B,), cfg.T, dtype=torch.int32, device="cuda")
+    if masked:
+        lens[1:] = cfg.T - 100
+    keep = torch.arange(cfg.T, device="cuda") < lens[:, None]
+    pad = torch.nn.functional.pad((x * keep[:, None, :]).double(), (cfg.pad, cfg.pad))
+    g = dy.double().transpose(0, 1).reshape(cfg.Cout, -1)
+    ref = torch.stack([g @ pad[:, :, k * cfg.dilation:k * cfg.dilation + cfg.T].transpose(1, 2).reshape(-1, cfg.Cin)
+                       for k in range(cfg.K)], dim=2)
+    assert nm.nm_conv1d_kernel_name(nm.NM_OP_BWD_WEIGHT, *d, masked=masked).endswith(" in 1 parts")
+    dw = nm.nm_conv1d_bwd_weight(x, dy, cfg.K, lengths=lens if masked else None, **U.geom_kw(cfg))
+    steps = 5 * cfg.B * -(-cfg.T // 80) // parts
+    assert ((dw.double() - ref).norm() / ref.norm()).item() <= 2**-24 / 3**0.5 * (steps / 2) ** 0.5
+
+
+@pytest.mark.gpu
 def test_units_of_many_items_are_not_walked():
     """256 padded items take no longer than 256 whole ones but for what it costs to look the lengths up (1.1 times); a walk over
     the items for every unit took 20 times as long."""
