@@ -718,7 +718,7 @@ constexpr int total_blocks(int KG) { return (2 * KG + kWaves - 1) / kWaves < 8 ?
 // 64 bits, 640 -> 768 channels, K=25, B=5, T=528 9.5e-8 in eight parts, 2.4e-7 in one, 9.8e-8 in one that is cut; 303 layers
 // of the encoder 0.99 times those parts' on average, 1.11 at most (5.0e-8 -> 5.6e-8: a chain has two units at least).  The
 // totals lie in LDS, the registers being taken; adding to them costs 0.17 us per block and chain (LDS atomics took 30 times
-// as long), the whole 5 % of the calls concerned.  An instance of its own: the others keep their registers.
+// as long), 13 us of a step of 644 at 640 channels, K=21, B=16, T=800.  An instance of its own: the others keep their registers.
 template <int KG, int DIL, int W, bool LEN, bool CUT>
 __device__ __forceinline__ void shared_units(const WgradParams &p, unsigned char *smem, int sp, int k0, int kt, int co0,
                                              int ci0)
@@ -1286,8 +1286,8 @@ struct FastPlan {
 };
 // tap-group sizes wgrad_shared_kernel is built for
 constexpr bool shared_kernel_built(int KG, int dil) { return dil == 1 ? (KG == 11 || KG == 13 || KG == 17 || KG == 21) : (dil == 2 && KG == 15); }
-// wide: as for make_wplan; without it no more parts than whole rounds over the CUs, or the other kernel, take.
-FastPlan make_fast_plan(const Geom &g, bool wide = true)
+// most: the parts there is room for
+FastPlan make_fast_plan(const Geom &g, int most = kAllParts)
 {
     FastPlan f = {};
     const int ntg = (g.K + kMaxKT - 1) / kMaxKT;
@@ -1306,52 +1306,62 @@ FastPlan make_fast_plan(const Geom &g, bool wide = true)
     const size_t stage = (size_t)kWaves * 2 * fast_x_items(g.dil) * 32 * kFastXRowBytes;
     const size_t red = (size_t)kWaves * 3 * (2 * f.KTg) * 64 * sizeof(f32x4);
     f.lds = stage > red ? stage : red;
-    // The kernel with shared staging: up to 24 taps per workgroup, in as many parts as are estimated to be fastest (or the
-    // other kernel).  Its workgroups are few and long, but that is not all: every part is written, read and added once more,
-    // and a workgroup takes 4.5 us before its first and after its last unit.  Fitted to 15700 calls, 2404 geometries of 256 to
-    // 896 channels (us, preparation of g and sum of the parts included; rms 6 %, of the other kernel 8 %); the plan taken
-    // is within 1 % of the best one on average.  Filling the CUs in whole rounds, the rule before, against this one: 640
-    // channels K=21, B=16, T=800 five parts 251 us, one 197; 640 -> 768 K=25, B=16, T=297 337 (the other kernel) / 146; 768
-    // K=25, B=3, T=112 121 (three) / 69; 768 -> 896 K=29, B=23, T=648 655 (two) / 580; 384 K=13, B=16, T=777 87 (seven) / 71.
+    const long parts_of_fast = f.S;
+    f.S = (int)std::min((long)most, (long)f.S);
+    // The kernel with shared staging, up to 24 taps per workgroup: in the fewest parts that fill whole rounds over the CUs (95 %),
+    // the other kernel where eight do not; or, from 64 channels on, what is estimated to be faster than that by more than the
+    // estimates err.  Its workgroups are few and long, but every part is written, read and added once more.  The estimates (us,
+    // but for what all plans share) are fitted to 466 whole training steps of the encoder's layers with six or seven plans each
+    // (calls timed alone find their parts in the last cache, which a step does not).  Those steps are 1.14 times as fast on
+    // average as with whole rounds, 0.4 % from the best plan, none slower by 2 %; without the margin ten of them are, 8 % at
+    // most.  Other layers, calls timed alone: 1.08 times from 64 channels on, 38 of 2716 slower by 4 %; with fewer channels
+    // the estimates gain nothing.  Whole rounds / this, steps: 640 channels K=21, B=16, T=800 683 / 637 us; 384 K=13, B=16,
+    // T=777, padded 205 / 191; 768 -> 896 K=29, B=1, T=104 161 (the other kernel) / 141.
     {
         const int ntg_s = (g.K + 23) / 24;
         const int KG = (g.K + ntg_s - 1) / ntg_s, ntg = (g.K + KG - 1) / KG;
         const long tiles_s = (long)ncot * ncit * ntg;
         if (shared_kernel_built(KG, g.dil) && 18 + 64 + (KG - 1) * g.dil + 4 < 128) {
+            const long limit = std::min(8L, std::max(1L, units / 2));
+            long whole = 0;  // the fewest parts that fill whole rounds
+            for (long S = 1; S <= limit && whole == 0; ++S) {
+                const long wgs = tiles_s * S, rounds = (wgs + kPlanCUs - 1) / kPlanCUs;
+                if (2 * S <= units && wgs * 100 >= rounds * kPlanCUs * 95) whole = S;
+            }
+            // the sums' chains (see CUT) in units: no longer than that plan's
+            const long sums = whole > 0 ? whole : kWaves * parts_of_fast, longest = (units + sums - 1) / sums;
+            auto chain_pairs = [&](long S) { return (units + S - 1) / S > std::max(2L, longest) ? std::max(1L, units / sums / 2) : 0L; };
             const int blocks = (2 * KG + kWaves - 1) / kWaves;  // accumulator blocks of a wavefront
             const double mb = 4e-6 * g.Cout * g.Cin * g.K;
             auto cost = [&](long S) {
-                const long rounds = (tiles_s * S + kPlanCUs - 1) / kPlanCUs, pairs = ((units + S - 1) / S + 1) / 2;
-                return 14.8 + rounds * (4.5 + 2.0 * pairs * (0.154 + 0.077 * blocks)) + (0.37 * S + 0.16) * mb - (S == 8 ? 1.9 : 0.0);
+                const long rounds = (tiles_s * S + kPlanCUs - 1) / kPlanCUs, pairs = ((units + S - 1) / S + 1) / 2, cut = chain_pairs(S);
+                const long cuts = cut ? (pairs - 1) / cut : 0;
+                return rounds * (7.8 + 0.2 * pairs * blocks + (cuts ? 0.7 + 0.173 * cuts * blocks : 0.0)) + 0.288 * S * mb;
             };
             const long per_wave = (units + kWaves * f.S - 1) / (kWaves * f.S);
             const double load = std::max(1.0, ntiles * f.S / (double)kPlanCUs);
-            // (0.3 per unit and tap: what the chip's power allows once a call is longer than the measured ones of that kernel)
-            auto whole = [&](long S) {
-                const long rounds = (tiles_s * S + kPlanCUs - 1) / kPlanCUs;
-                return tiles_s * S * 100 >= rounds * kPlanCUs * 95;
-            };
-            long most = std::min(8L, std::max(1L, units / 2));
-            long rounds_at = 1;  // parts that fill whole rounds
-            while (rounds_at <= most && (2 * rounds_at > units || !whole(rounds_at))) ++rounds_at;
-            const long chain = rounds_at <= most ? units / rounds_at : std::max(1L, units / (kWaves * f.S));
-            if (!wide) most = std::min(most, rounds_at <= most ? rounds_at : (long)f.S);
-            double best = 12.9 + load * f.KTg * (0.17 * std::min(per_wave, 8L) + 0.3 * std::max(per_wave - 8, 0L)) + (0.94 * f.S + 0.16) * mb + 3.1e-6 * g.B * (g.Cout + g.Cin) * (double)g.To;
-            if (f.S > most) best = 1e30;
-            long S_best = 0;
-            for (long S = 1; S <= most; ++S) {
-                const double c = cost(S) * (whole(S) ? 0.95 : 1.0);  // (a tie goes to whole rounds)
-                if (c < best) {
-                    best = c;
-                    S_best = S;
+            const double cost_of_fast = 2.9 + load * f.KTg * (0.245 * std::min(per_wave, 8L) + 0.268 * std::max(per_wave - 8, 0L)) +
+                                        0.741 * f.S * mb + 0.81e-6 * g.B * (g.Cout + g.Cin) * (double)g.To;
+            const bool room = (whole > 0 ? whole : parts_of_fast) <= most;  // (without it what is estimated to be fastest)
+            long parts = room ? whole : 0;                                  // 0: the other kernel
+            if ((g.Cin >= 64 && g.Cout >= 64) || !room) {
+                double best = room ? 0.95 * (parts ? cost(parts) : cost_of_fast) - 2.0 : cost_of_fast;
+                if (parts && cost_of_fast < best && per_wave <= longest) {
+                    best = cost_of_fast;
+                    parts = 0;
                 }
+                for (long S = 1; S <= std::min(limit, (long)most); ++S)
+                    if (cost(S) < best) {
+                        best = cost(S);
+                        parts = S;
+                    }
             }
-            if (S_best > 0) {
+            if (parts > 0) {
                 f.shared = true;
                 f.KTg = KG;
                 f.ntg = ntg;
-                f.S = (int)S_best;
-                f.chain = (units + S_best - 1) / S_best > std::max(2L, chain) ? (int)std::max(1L, chain / 2) : 0;
+                f.S = (int)parts;
+                f.chain = (int)chain_pairs(parts);
                 f.lds = 3 * 128 * kFastXRowBytes;
             }
         }
@@ -1450,31 +1460,38 @@ bool mfma_wgrad_supported(const Geom &g0)
 }
 
 namespace {
-size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide);
+size_t wgrad_workspace16(const Geom &g, bool need_dz, int most);
 }
-size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, bool wide)
+size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, int most)
 {
-    return wgrad_workspace16(pitched(g), need_dz || g.To % 8 != 0, wide) + pitched_x_bytes(g);
+    return wgrad_workspace16(pitched(g), need_dz || g.To % 8 != 0, most) + pitched_x_bytes(g);
 }
-size_t mfma_wgrad_x_offset(const Geom &g, bool wide) { return mfma_wgrad_workspace(g, true, wide) - pitched_x_bytes(g); }
+size_t mfma_wgrad_x_offset(const Geom &g, int most) { return mfma_wgrad_workspace(g, true, most) - pitched_x_bytes(g); }
+int mfma_wgrad_parts(const Geom &g, bool need_dz, size_t bytes)
+{
+    if (mfma_wgrad_workspace(g, need_dz, kAllParts) <= bytes) return kAllParts;
+    int most = 8;  // (the most that the kernels of stride 1 take; the general one has eight or room for all)
+    while (most > 0 && mfma_wgrad_workspace(g, need_dz, most) > bytes) --most;
+    return most;
+}
 
 namespace {
-size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide)
+size_t wgrad_workspace16(const Geom &g, bool need_dz, int most)
 {
     // (sized without looking at lengths: a call with lengths never takes the pointwise kernel)
     Geom g0 = g;
     g0.len = nullptr;
     if (wgrad_k1_supported(g0)) {
-        const FastPlan f = make_fast_plan(g, wide);
+        const FastPlan f = make_fast_plan(g, most);
         const size_t fast = part_bytes(g, f.S) + dzf_bytes(g, f);
         const size_t k1 = wgrad_k1_part_bytes(g0) + dz_buf_bytes(g);
         return fast > k1 ? fast : k1;
     }
     if (fast_ok(g)) {
-        const FastPlan f = make_fast_plan(g, wide);
+        const FastPlan f = make_fast_plan(g, most);
         return part_bytes(g, f.S) + dzf_bytes(g, f);
     }
-    const WPlan w = make_wplan(g, wide);
+    const WPlan w = make_wplan(g, most == kAllParts);
     if (!w.ok) return 0;
     return part_bytes(g, w.S) + (need_dz ? dz_buf_bytes(g) : 0);
 }
@@ -1483,10 +1500,10 @@ size_t wgrad_workspace16(const Geom &g, bool need_dz, bool wide)
 // ---- stride-1 kernel with dz already in fragment order (dz_pack_kernel's layout) ----------------
 bool mfma_wgrad_fast_supported(const Geom &g) { return fast_ok(pitched(g)); }
 
-DzfLayout mfma_wgrad_dzf_layout(const Geom &g0, bool wide)
+DzfLayout mfma_wgrad_dzf_layout(const Geom &g0, int most)
 {
     const Geom g = pitched(g0);
-    const FastPlan f = make_fast_plan(g, wide);
+    const FastPlan f = make_fast_plan(g, most);
     DzfLayout l;
     l.ncm = f.ncm;
     l.nst = f.nst;
@@ -1496,10 +1513,10 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g0, bool wide)
 }
 
 hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float *scale, float *dw, bool accumulate, void *ws,
-                                      hipStream_t s, bool wide, const DefinedDw *defined)
+                                      hipStream_t s, int most, const DefinedDw *defined)
 {
     const Geom g = pitched(g0);
-    const FastPlan f = make_fast_plan(g, wide);
+    const FastPlan f = make_fast_plan(g, most);
     float *part = (float *)ws;
     const u32x4 *dzf = (const u32x4 *)((unsigned char *)ws + part_bytes(g, f.S));
     WgradParams p = {};
@@ -1554,7 +1571,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
 {
     const Geom g = pitched(g0);
     const bool copies = !rows16(g0);  // x, g or both are made into 16-byte rows first
-    const bool wide = ws_bytes >= mfma_wgrad_workspace(g0, relu || copies, true);
+    const int most = std::max(1, mfma_wgrad_parts(g0, relu || copies, ws_bytes));
     const DefinedDw tensors = {false, x, dy, relu ? y : nullptr}, *defined = copies ? &tensors : nullptr;
     RowPrep prep = {};
     if (copies) {
@@ -1563,7 +1580,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
         prep.relu = relu;
         if (g0.T % 8 != 0) {
             prep.x = x;
-            prep.xp = (unsigned char *)ws + mfma_wgrad_x_offset(g0, wide);
+            prep.xp = (unsigned char *)ws + mfma_wgrad_x_offset(g0, most);
             x = prep.xp;
         }
     }
@@ -1584,7 +1601,7 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
         return launch_wgrad_k1(g, x, gplain, scale, dw, accumulate, ws, s);
     }
     if (fast_ok(g)) {
-        const FastPlan f = make_fast_plan(g, wide);
+        const FastPlan f = make_fast_plan(g, most);
         u32x4 *dzf = (u32x4 *)((unsigned char *)ws + part_bytes(g, f.S));
         hipError_t e;
         if (copies) {
@@ -1598,9 +1615,9 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
             e = hipGetLastError();
         }
         if (e != hipSuccess) return e;
-        return launch_mfma_wgrad_prepared(g0, x, scale, dw, accumulate, ws, s, wide, defined);
+        return launch_mfma_wgrad_prepared(g0, x, scale, dw, accumulate, ws, s, most, defined);
     }
-    const WPlan w = make_wplan(g, wide);
+    const WPlan w = make_wplan(g, most == kAllParts);
     if (!w.ok) return hipErrorInvalidValue;
     float *part = (float *)ws;
     const void *dz = dy;
@@ -1645,17 +1662,17 @@ hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, cons
 void name_mfma_wgrad(const Geom &g0, bool relu, size_t ws_bytes, char *name, size_t n)
 {
     const Geom g = pitched(g0);
-    const bool wide = ws_bytes >= mfma_wgrad_workspace(g0, relu || !rows16(g0), true);
+    const int most = std::max(1, mfma_wgrad_parts(g0, relu || !rows16(g0), ws_bytes));
     if (wgrad_k1_supported(g)) {
         snprintf(name, n, "wgrad_k1_kernel");
     } else if (fast_ok(g)) {
-        const FastPlan f = make_fast_plan(g, wide);
+        const FastPlan f = make_fast_plan(g, most);
         if (f.shared)
             snprintf(name, n, "wgrad_shared_kernel<%d, %d, %s> in %d parts", f.KTg, g.dil, g.len ? "true" : "false", f.S);
         else
             snprintf(name, n, "wgrad_fast_kernel<%d, %d> in %d parts", f.KTg, g.dil, f.S);
     } else {
-        const WPlan w = make_wplan(g, wide);
+        const WPlan w = make_wplan(g, most == kAllParts);
         snprintf(name, n, "wgrad_kernel<%d> in %d parts", w.KTg, w.S);
     }
 }

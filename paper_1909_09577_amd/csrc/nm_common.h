@@ -308,9 +308,11 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
                              size_t ws_bytes, hipStream_t s, const void **g_used = nullptr);
 
 bool mfma_wgrad_supported(const Geom &g);
-// wide: with room for as many parts as are fastest; less serves too
-size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, bool wide = true);
-size_t mfma_wgrad_x_offset(const Geom &g, bool wide = true);  // where the pitched copy of x lies in a workspace sized with need_dz
+// most: the parts there is room for (no more than are fastest are used)
+constexpr int kAllParts = 32;
+size_t mfma_wgrad_workspace(const Geom &g, bool need_dz, int most = kAllParts);
+int mfma_wgrad_parts(const Geom &g, bool need_dz, size_t bytes);  // that `bytes` have room for; 0: too little for one
+size_t mfma_wgrad_x_offset(const Geom &g, int most = kAllParts);  // where the pitched copy of x lies in a workspace sized with need_dz
 hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const void *y,
                              const float *scale, float *dw, bool relu, bool accumulate, void *ws,
                              size_t ws_bytes, hipStream_t s);
@@ -372,11 +374,11 @@ struct DzfLayout {
     size_t offset, bytes;
 };
 bool mfma_wgrad_fast_supported(const Geom &g);
-DzfLayout mfma_wgrad_dzf_layout(const Geom &g, bool wide);
+DzfLayout mfma_wgrad_dzf_layout(const Geom &g, int most);
 // weight gradient from a workspace whose fragment-order g has been written already; scale[co] (or NULL)
 // multiplies the float32 sums; defined: for rows of any length
 hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float *scale, float *dw, bool accumulate,
-                                      void *ws, hipStream_t s, bool wide, const DefinedDw *defined = nullptr);
+                                      void *ws, hipStream_t s, int most, const DefinedDw *defined = nullptr);
 // packs the flipped weights times scale into ws (as launch_mfma_dgrad does; where `pack`) and, in the same launch, forms
 // g plain (into dres, else behind the packed weights in ws, else nowhere) and in fragment order (gf);
 // *g_plain: the tensor the input gradient contracts

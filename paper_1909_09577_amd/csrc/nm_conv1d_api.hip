@@ -210,7 +210,7 @@ size_t workspace_for(int op, const Geom &g, int dtype, bool mfma, bool scale_or_
     if (mfma) {
         if (op == NM_OP_FWD) return least ? mfma_fwd_workspace_least(g) : mfma_fwd_workspace(g);
         if (op == NM_OP_BWD_DATA) return least ? mfma_dgrad_workspace_least(g) : mfma_dgrad_workspace(g);
-        return mfma_wgrad_workspace(g, scale_or_relu, !least);
+        return mfma_wgrad_workspace(g, scale_or_relu, least ? 1 : kAllParts);
     }
     if (op == NM_OP_FWD) return 0;
     return scale_or_relu ? align_up((size_t)g.B * g.Cout * g.To * elt(dtype), kWsAlign) : 0;
@@ -284,7 +284,13 @@ Route route_pass(int op, const Geom &g, int dtype, unsigned flags, bool aligned,
         return workspace_for(op, g, dtype, r.mfma, dz, least);
     };
     r.need = room(false);
-    if (r.mfma && have < r.need) r.need = room(true);
+    if (r.mfma && have < r.need) {
+        r.need = room(true);
+        if (op == NM_OP_BWD_WEIGHT && have > r.need) {  // more than one part
+            const bool dz = dzneeded || !rows16(g);
+            r.need = mfma_wgrad_workspace(g, dz, mfma_wgrad_parts(g, dz, have));
+        }
+    }
     const bool plain_too = !rows16(g) || (op == NM_OP_BWD_DATA && g.stride == 2);
     if (r.mfma && plain_too && check_workspace(ws, have, r.need) != NM_OK) {
         r.mfma = false;  // no room for the copies
@@ -650,13 +656,14 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     whole = whole && !own_checks;
     // the matrix-core kernels of both gradients, and the workspace they can do with: what is more goes to the input gradient
     const bool both_mfma = use_mfma(NM_OP_BWD_DATA, g, dtype, flags) && use_mfma(NM_OP_BWD_WEIGHT, g, dtype, flags);
-    const size_t wgrad_least = both_mfma ? mfma_wgrad_workspace(g, true, false) : 0;
-    const bool fits = whole || (both_mfma && !own_checks && workspace_bytes >= mfma_dgrad_workspace_least(g) + wgrad_least);
+    const size_t dgrad_least = both_mfma ? mfma_dgrad_workspace_least(g) : 0;
+    const int most = !both_mfma ? 0 : whole ? kAllParts : workspace_bytes < dgrad_least ? 0 : mfma_wgrad_parts(g, true, workspace_bytes - dgrad_least);
+    const bool fits = whole || (both_mfma && !own_checks && most > 0);
     const bool fused = fits && both_mfma && !(lengths && (flags & NM_ACCUM_DX)) && g.stride == 1 && mfma_wgrad_fast_supported(g) &&
                        !wgrad_k1_supported(pitched(g)) && aligned16(x) && aligned16(dy) && aligned16(dx) && (!relu || aligned16(y)) &&
                        (!dres || aligned16(dres));
     // only meaningful when fused
-    const size_t ws_data = whole ? mfma_dgrad_workspace(g) : fits ? (workspace_bytes - wgrad_least) / kWsAlign * kWsAlign : 0;
+    const size_t ws_data = whole ? mfma_dgrad_workspace(g) : fits ? (workspace_bytes - mfma_wgrad_workspace(g, true, most)) / kWsAlign * kWsAlign : 0;
     // pointwise layers: the input gradient's masked g = dy*[y>0] also feeds the K=1 weight-gradient GEMM
     const bool fused_k1 = fits && both_mfma && !lengths && g.stride == 1 && wgrad_k1_supported(pitched(g)) && aligned16(x) &&
                           aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
@@ -668,7 +675,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         hipError_t err;
         if (!rows16(g)) {  // (K = 1 without padding: To == T)
             unsigned char *ws_w = (unsigned char *)workspace + ws_data;
-            void *xp = ws_w + mfma_wgrad_x_offset(g);
+            void *xp = ws_w + mfma_wgrad_x_offset(g, most);
             const DzfLayout none = {};
             err = launch_bwd_prepare(g, dy, y, scale, w, true, relu, workspace, nullptr, none, dres, &g_plain, s, x, xp);
             if (err != hipSuccess) return NM_ERR_DEVICE;
@@ -744,10 +751,9 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     if (clash) return NM_ERR_BAD_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     void *ws_w = (unsigned char *)workspace + ws_data;  // the weight gradient's workspace: partials, then dz fragments
-    const bool wide = workspace_bytes - ws_data >= mfma_wgrad_workspace(g, true);
-    const DzfLayout layout = mfma_wgrad_dzf_layout(g, wide);
+    const DzfLayout layout = mfma_wgrad_dzf_layout(g, most);
     const void *g_plain = nullptr;
-    void *xp = g.T % 8 == 0 ? nullptr : (unsigned char *)ws_w + mfma_wgrad_x_offset(g, wide);  // pitched copy of x
+    void *xp = g.T % 8 == 0 ? nullptr : (unsigned char *)ws_w + mfma_wgrad_x_offset(g, most);  // pitched copy of x
     hipError_t err = launch_bwd_prepare(g, dy, y, scale, w, !mfma_dgrad_unpacked(g, w, ws_data), relu, workspace, (unsigned char *)ws_w + layout.offset, layout,
                                         dres, &g_plain, s, x, xp);
     if (err != hipSuccess) return NM_ERR_DEVICE;
@@ -756,7 +762,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
     const DefinedDw defined = {false, x, dy, relu ? y : nullptr};
-    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, wide, rows16(g) ? nullptr : &defined));
+    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, most, rows16(g) ? nullptr : &defined));
 }
 
 int nm_conv1d_bwd(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const void *x,
