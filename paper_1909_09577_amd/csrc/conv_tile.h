@@ -285,7 +285,8 @@ __device__ __forceinline__ int clipped_len(const int *len, int b, int T)
 struct UnpackedPlan {
     int nt, nsplit, ngroups;  // nt = 0: none
     size_t lds, part_bytes;
-    double cost;              // estimated time on the device (us)
+    double cost;              // estimated time on the device (us), by which plans are compared
+    double device;            // the same, fitted to forward calls on the plans taken
 };
 bool unpacked_supported(int M, int R, int K, int stride, bool flip);
 UnpackedPlan unpacked_plan(int B, int M, int R, int Tout, int K, int dil, bool flip, size_t part_limit);

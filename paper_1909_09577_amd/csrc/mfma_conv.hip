@@ -1655,8 +1655,18 @@ double packed_cost(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int
     if (flip) return run + 4.0 + 0.73 * w;
     return run + 4.9 + 0.43 * w + (Tin % 8 != 0 ? 1.0 + 2.4e-6 * B * R * Tin : 0.0);
 }
-// The plan on unpacked weights where it is the better one by more than the estimates err.  Chosen over those 345 (fewer than
-// one in a hundred of them slower, 14 % at most): 1.25 times as fast on average.
+// The same for a forward call on the engine for few tiles, fitted to 3248 calls that the estimates above send to unpacked
+// weights, timed on both (rms 8 %): in one part that engine has no second launch.
+double packed_split_device(const SplitPlan &sp, int B, int M, int R, int Tin, int K)
+{
+    const double w = 2e-6 * M * R * K, odd = Tin % 8 != 0 ? 1.0 : 0.0;
+    if (sp.nsplit == 1) return 7.5 + 0.81 * sp.device + 0.66 * w + 1.6 * odd;
+    return 13.0 + 0.71 * sp.device + 0.31 * w + odd * 1.1e-6 * B * R * Tin;
+}
+// The plan on unpacked weights where it is the better one by more than the estimates err (over those 345).  Against the engine
+// for few tiles also with three parts at least (in two it lost in 37 of 66 calls), and in forward calls by that later fit
+// too: 128 -> 1024 channels, K=11, B=10, T=203 20.3 us packed, 31.1 unpacked; 256 -> 512, K=13, B=23, T=203 34 / 47.  187
+// calls that these two keep packed: 8 % faster so on average, 12 of them slower by more than 4 %.
 UnpackedPlan better_unpacked(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int Tin, int Tout, int K, int dil, bool flip, size_t part_limit)
 {
     if (!pl.ok || !unpacked_supported(M, R, K, pl.stride, flip)) return UnpackedPlan{};
@@ -1664,7 +1674,8 @@ UnpackedPlan better_unpacked(const Plan &pl, const SplitPlan &sp, int B, int M, 
     // (whatever the plan, its multiplications spread evenly: most large calls need not be looked at any further)
     if (10.7 + 0.69 * 0.0444 / 4 / 256 * ((M + kTileM - 1) / kTileM) * (R / 16) * (double)B * ((Tout + 31) / 32) * K > most) return UnpackedPlan{};
     const UnpackedPlan up = unpacked_plan(B, M, R, Tout, K, dil, flip, part_limit);
-    return up.nt && up.cost < most ? up : UnpackedPlan{};
+    if (!up.nt || up.cost >= most || (sp.nt && up.nsplit < 3)) return UnpackedPlan{};
+    return flip || !sp.nt || up.device < packed_split_device(sp, B, M, R, Tin, K) ? up : UnpackedPlan{};
 }
 
 size_t packed_bytes(int M, int R, int K)

@@ -361,6 +361,10 @@ UnpackedPlan make_unpacked_plan(int B, int M, int R, int Tout, int K, int dil, b
             const double cost = 10.7 + (resident == 2 ? per_cu / 2 * pair + per_cu % 2 * alone : per_cu * alone) +
                                 0.36e-6 * 4 * ns * M * (double)cols * nt * 32 + 0.01e-6 * M * R * K;
             if (best.nt && cost >= best.cost) continue;
+            // (forward calls on the plans taken, 6164 of them: rms 8 %; two workgroups on a CU overlap far less there than the fit above has it)
+            const double mult = K * (0.036 + 0.0337 * nt), one = chunks * (0.4 + mult);
+            best.device = 8.4 + per_cu % 2 * one + per_cu / 2 * (resident == 2 ? std::max(one, 1.86 * chunks * mult) : 2 * one) +
+                          0.576e-6 * 4 * ns * M * (double)cols * nt * 32 + 0.5e-6 * B * M * (double)Tout;
             best.nt = nt;
             best.nsplit = ns;
             best.ngroups = ngroups;

@@ -51,6 +51,13 @@ def test_calls_it_does_not_take():
     assert 0 < nm.nm_conv1d_workspace_bytes(FWD, *c.dims()) - packed <= nm.NM_STATIC_SCRATCH_BYTES
 
 
+def test_calls_that_are_faster_on_packed_weights():
+    """The engine for few tiles in one part has no second launch: 20 us there, 31 here; two parts here: 34 there, 47 here."""
+    for c in (L(10, 128, 1024, 203, 11), L(6, 128, 512, 935, 13), L(23, 256, 512, 203, 13), L(7, 192, 1024, 369, 13)):
+        assert width(FWD, c) == 0, c.dims()
+    assert width(FWD, L(23, 320, 768, 132, 13)) == 2  # (against the large engine two parts gain: 52 here, 72 there)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
 @pytest.mark.parametrize("cfg", [c for c, _, _ in CASES], ids=lambda c: "x".join(map(str, c.dims())))
