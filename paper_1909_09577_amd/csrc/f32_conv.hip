@@ -400,15 +400,18 @@ hipError_t launch_f32_conv_nt(const F32ConvParams &p, const F32ConvPlan &q, hipS
         return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 16, 2, SPLIT>(p, q, s) : launch_f32_conv_t<NT, FLIP, 16, kXIter, SPLIT>(p, q, s);
     return q.W <= 128 ? launch_f32_conv_t<NT, FLIP, 8, 2, SPLIT>(p, q, s) : launch_f32_conv_t<NT, FLIP, 8, kXIter, SPLIT>(p, q, s);
 }
-// Workgroups that share a tile's reduction channels where the tiles are too few to fill the chip (NT = 1 there): a
-// workgroup takes 3 us per chunk of channels, 16 chunks at 256 channels, K=11, and the second launch 4.
-// Channels, K, B, T: 256 -> 384, 13, 1, 260 50.9 -> 20.7 us; 256, 11, 1, 60 46.5 -> 12.2; 256, 11, 4, 250 47.1 -> 29.7; from half of
-// the chip on there is nothing to share out.
+// Workgroups that share a tile's reduction channels where the tiles are too few to fill the chip (NT = 1 there) and that saves
+// more than the second launch takes.  A chunk of channels takes 0.9 us and 0.15 a tap (with eight channels 1.1 and 0.065), the
+// launch 1.8 and 0.7 per MB of parts (of 1587 calls 3 that share and 6 that do not are slower by 4 %, 13 at most).  Channels, K,
+// B, T: 256 -> 384, 13, 1, 260 50.9 -> 20.7 us; 256, 11, 1, 60 46.5 -> 12.2; 256, 11, 4, 250 47.1 -> 29.7; but 32 -> 16, 1, 2, 165
+// 7.0 -> 8.3, so in one part.  From half of the chip on there is nothing to share out.
 int f32_splits(int B, int M, int R, int Tout, int K)
 {
     const size_t tiles = (size_t)((M + kTileM - 1) / kTileM) * ((Tout + 31) / 32) * B;
     const int cc = 16 * K <= kRun ? 16 : 8, chunks = (R + cc - 1) / cc;
-    return tiles > 128 ? 1 : std::max(1, std::min({(int)(256 / tiles), chunks, 8}));
+    const int n = tiles > 128 ? 1 : std::max(1, std::min({(int)(256 / tiles), chunks, 8}));
+    const double saved = (chunks - (chunks + n - 1) / n) * (cc == 16 ? 0.9 + 0.15 * K : 1.1 + 0.065 * K);
+    return saved > 1.8 + 0.7 * 4e-6 * n * B * M * (double)Tout ? n : 1;
 }
 size_t f32_split_bytes(int B, int M, int R, int Tout, int K)
 {
