@@ -257,14 +257,18 @@ __global__ __launch_bounds__(256) void decoder_plain_kernel(int B, int Cin, int 
 
 }  // namespace
 
-// Wavefronts that share the channels of the same 32 frames.  A workgroup's row segments get shorter with them (256 / 128 /
-// 64 bytes), which costs more than it gains once there are wavefronts enough.  1024 channels, 29 classes, 1 / 2 / 4
-// (us, replayed in a graph, cold x): B=1, T=88 11.4 / 9.7 / 7.8; B=1, T=600 13.9 / 10.2 / 8.7; B=8, T=800 14.5 / 11.1 / 10.0;
-// B=16, T=800 15.1 / 12.4 / 14.4; B=32, T=800 19.5 / 22.3 / 28.0; odd rows B=2, T=265 17.3 / 12.6 / 10.7.
-int decoder_split(int B, int T)
+// Wavefronts that share the channels of the same 32 frames.  Up to 256 channels a wavefront is through them before the sharing
+// has paid (K=1 with 128 channels: 3 to 10 % longer).  A workgroup's row segments get shorter with shares (256 / 128 / 64
+// bytes), which costs more than it gains once a second workgroup goes to a CU, and that is counted in workgroups: an item's
+// last one may be all but empty.  25536 calls (1 to 64 items, 8 to 1200 frames, 16 to 1280 channels; cold x): 0.833 of the time
+// without shares, 0.3 % from the best choice, 198 slower by more than 4 %, 14 % at most.  1024 channels, 29 classes, 1 / 2 / 4 (us):
+// B=1, T=88 11.4 / 9.7 / 7.8; B=1, T=600 13.9 / 10.2 / 8.7; B=8, T=800 14.5 / 11.1 / 10.0; B=16, T=800 15.1 / 12.4 / 14.4; B=32,
+// T=800 19.5 / 22.3 / 28.0; odd rows B=2, T=265 17.3 / 12.6 / 10.7; five classes, B=34, T=473 13.7 / 20.5 / 20.2.
+int decoder_split(int B, int Cin, int T)
 {
-    const long waves = (long)B * ((T + kFramesPerWave - 1) / kFramesPerWave);
-    return waves <= 256 ? 4 : waves <= 512 ? 2 : 1;
+    auto workgroups = [&](int split) { return (long)B * ((T + 4 / split * kFramesPerWave - 1) / (4 / split * kFramesPerWave)); };
+    if (Cin <= 256) return 1;
+    return Cin > 512 && workgroups(4) <= 208 ? 4 : workgroups(2) <= 224 ? 2 : 1;
 }
 
 // Forward of a pointwise sub-block with few output channels on the decoder's load stream.
@@ -277,7 +281,7 @@ bool skinny_fwd_supported(const Geom &g)
 hipError_t launch_skinny_fwd(const Geom &g, const void *x, const void *w, const float *scale, const float *shift,
                              const void *res, void *y, bool relu, hipStream_t s)
 {
-    const int split = decoder_split(g.B, g.T), frames = 4 / split * kFramesPerWave;
+    const int split = decoder_split(g.B, g.Cin, g.T), frames = 4 / split * kFramesPerWave;
     dim3 grid((g.T + frames - 1) / frames, g.B);
     MainKernelTimer timer(s);
     auto kern = split == 4 ? decoder_mfma_kernel<true, false, 4> : split == 2 ? decoder_mfma_kernel<true, false, 2> : decoder_mfma_kernel<true>;
@@ -305,7 +309,7 @@ extern "C" int nm_decoder_logsoftmax_fwd(int B, int Cin, int Ncls, int T, const 
                       ((uintptr_t)w % 16) == 0 && ((uintptr_t)x % 2) == 0 &&
                       (size_t)B * Cin * T * 2 <= ((size_t)1 << 30);
     if (fast) {
-        const int split = decoder_split(B, T), frames = 4 / split * kFramesPerWave;
+        const int split = decoder_split(B, Cin, T), frames = 4 / split * kFramesPerWave;
         dim3 grid((T + frames - 1) / frames, B);
         // 1024 channels, 29 classes: B=2, T=265 6034 us on the plain kernel, 17.4 here; B=32, T=777 19.9 (T=776 18.4)
         const bool rows16 = T % 8 == 0 && ((uintptr_t)x % 16) == 0;

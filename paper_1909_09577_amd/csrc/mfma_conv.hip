@@ -2134,7 +2134,7 @@ void name_unpacked(const UnpackedPlan &up, int K, bool flip, char *name, size_t 
 void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n)
 {
     if (skinny_fwd_supported(g)) {
-        snprintf(name, n, "decoder_mfma_kernel<true, false, %d>", decoder_split(g.B, g.T));
+        snprintf(name, n, "decoder_mfma_kernel<true, false, %d>", decoder_split(g.B, g.Cin, g.T));
         return;
     }
     static float affine;

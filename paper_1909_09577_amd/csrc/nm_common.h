@@ -294,7 +294,7 @@ int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes);
 
 // pointwise forward with at most 32 output channels: bound by reading x once (decoder_logsoftmax.hip)
 bool skinny_fwd_supported(const Geom &g);
-int decoder_split(int B, int T);  // its last template argument
+int decoder_split(int B, int Cin, int T);  // its last template argument
 hipError_t launch_skinny_fwd(const Geom &g, const void *x, const void *w, const float *scale, const float *shift,
                              const void *res, void *y, bool relu, hipStream_t s);
 

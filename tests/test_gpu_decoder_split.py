@@ -1,4 +1,4 @@
-"""The decoder's kernel where wavefronts share the channels of the same frames: fewer steps than shares, shares of unequal length,
+"""The decoder's kernel where wavefronts share the channels of the same frames: shares of unequal length,
 both sides of the lines between one, two and four, rows of any length, and the block forward on the same kernel."""
 import numpy as np
 import pytest
@@ -8,8 +8,8 @@ from oracle import decoder_oracle as dorc
 from paper_1909_09577_amd import binding as nm
 from paper_1909_09577_amd import inputs as syn
 
-CASES = [(1, 16, 29, 40, 4), (1, 48, 32, 33, 4), (3, 1024, 29, 77, 4), (2, 80, 5, 9, 4), (32, 64, 29, 256, 4), (32, 64, 29, 264, 2), (43, 16, 29, 161, 2),
-         (64, 80, 29, 256, 2), (64, 80, 29, 257, 1), (64, 48, 29, 264, 1)]
+CASES = [(1, 16, 29, 40, 1), (3, 256, 29, 96, 1), (1, 528, 32, 33, 4), (3, 1024, 29, 77, 4), (2, 272, 5, 9, 2), (8, 528, 29, 832, 4), (8, 528, 29, 840, 2),
+         (16, 272, 29, 896, 2), (16, 272, 29, 904, 1), (16, 272, 29, 889, 2), (34, 608, 16, 456, 1), (1, 512, 7, 64, 2)]
 
 
 def _bf16(a):
