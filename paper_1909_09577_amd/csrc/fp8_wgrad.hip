@@ -248,9 +248,12 @@ WgLayout wg_layout(int B, int Cin, int Cout, int To, int K, int dil)
     l.TG = K > 20 ? 2 : 1;
     // Workgroups per (tile, tap group): the count whose estimated time (us) is least.  A round over the 2*cus slots takes 0.053
     // per unit and tap of a workgroup, a last one of no more than a workgroup per CU 0.73 of that; every part is written, read
-    // and added, 0.3 per MB.  Fitted to 12300 calls of 1929 geometries (rms 11 %); 1.27 times as fast on average as rounds and a
-    // fixed charge per part, and within 1 % of the best count.  That / this one: 768 channels K=25, B=7, T=112 103 / 58; B=32,
-    // T=800 438 / 418; 512 channels K=17, B=4, T=56 42 / 29; 768 -> 896 K=29, B=2, T=162 113 / 58.
+    // and added, 0.3 per MB, and waited for, 0.8 a part, eight of them at once 2 (wgrad_reduce4_kernel).  Fitted to 12300 calls
+    // of 1929 geometries of 256 channels and more (rms 11 %), what the parts are waited for to 3022 of 64 to 896: against rounds and
+    // a fixed charge per part 1.27 times as fast on average over those, 1.16 over these, 105 of these slower by more than 4 %
+    // (297 without the waiting: 192 -> 64 channels, K=25, B=21, T=60 26 us in four parts, 33 in the seven it chose).  Fixed charge /
+    // this: 768 channels K=25, B=7, T=112 103 / 58; B=32, T=800 438 / 418; 512 channels K=17, B=4, T=56 42 / 29; 768 -> 896
+    // K=29, B=2, T=162 113 / 58.
     const int items = l.ntiles * l.TG, slots = 2 * cus, units = B * l.nu;
     const double mb = 4e-6 * Cout * Cin * K;
     double best = 1e30;
@@ -258,7 +261,7 @@ WgLayout wg_layout(int B, int Cin, int Cout, int To, int K, int dil)
     for (int sc = 1; sc <= 8; ++sc) {
         const int full = items * sc / slots, last = items * sc - full * slots;
         const double rounds = full + (last == 0 ? 0.0 : last <= cus ? 0.73 : 1.0);
-        const double cost = rounds * ((units + sc - 1) / sc) * 0.0526 * K / l.TG + 0.3 * sc * mb;
+        const double cost = rounds * ((units + sc - 1) / sc) * 0.0526 * K / l.TG + 0.3 * sc * mb + (sc < 8 ? 0.8 * sc : 2.0);
         if (cost < best) {
             best = cost;
             l.S = sc;

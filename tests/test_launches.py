@@ -66,3 +66,12 @@ def test_the_timer_counts_the_sum_of_the_parts():
         a, b = ([i for i, (kind, what, _) in enumerate(seq) if (kind, what) == ("event", e)] for e in (la.START, la.STOP))
         assert len(a) == len(b) == 1, (name, seq)
         assert [k for _, k, _ in seq[a[0] + 1:b[0]]] == kernels, (name, op)
+
+
+@pytest.mark.parametrize("dims,tiles,parts", [((21, 192, 64, 60, 25, 1, 1, 12), 6 * 2, 8), ((13, 64, 192, 69, 25, 1, 1, 12), 6 * 2, 8),
+                                              ((3, 448, 64, 535, 17, 1, 1, 8), 14, 8), ((32, 768, 768, 800, 25, 1, 1, 12), 288 * 2, 3)], ids=str)
+def test_parts_of_an_8_bit_weight_gradient(dims, tiles, parts):
+    """Parts are waited for one after the other, eight at once: seven were chosen for the first three."""
+    ((status, seq),) = la.run([{"call": "fp8_bwd", "dims": dims}])
+    assert status == nm.NM_OK
+    assert [grid[0] for _, kernel, grid in seq if kernel == "fp8_wgrad_kernel"] == [tiles * parts]
