@@ -2065,7 +2065,7 @@ size_t mfma_fwd_workspace(const Geom &g)
 
 // Whether the forward pass of this geometry runs on a kernel instance that can also write the statistics of its
 // outputs, and into how many (batch item, time tile) parts: the unrolled engine, wide tile, no lengths, 16-byte rows.
-int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes)
+int mfma_fwd_stats_parts(const Geom &g, const void *w, size_t ws_bytes)
 {
     if (!rows16(g)) return 0;
     const Plan pl = make_plan(g.T, g.To, g.Cin, g.K, g.stride, g.dil);
@@ -2074,7 +2074,7 @@ int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes)
     // few tiles: z is small and read again instead, where the engine for those saves more than that takes
     const SplitPlan sp = fwd_split_plan(g, pl, ws_bytes);
     if (sp.nt && sp.gain > 3.0) return 0;
-    const UnpackedPlan up = fwd_unpacked_plan(g, pl, ws_bytes);
+    const UnpackedPlan up = ((uintptr_t)w % 16) == 0 ? fwd_unpacked_plan(g, pl, ws_bytes) : UnpackedPlan{};
     if (up.nt && packed_cost(pl, SplitPlan{}, g.B, g.Cout, g.Cin, g.T, g.To, g.K, false) - up.cost > 5.0) return 0;
     return g.B * ((g.To + 159) / 160);
 }
@@ -2084,7 +2084,7 @@ hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const fl
 {
     const Plan pl = make_plan(row_pitch(g.T), g.To, g.Cin, g.K, g.stride, g.dil);
     if (!pl.ok || !mfma_fwd_supported(g)) return hipErrorInvalidValue;
-    if (stats && mfma_fwd_stats_parts(g, ws_bytes) == 0) return hipErrorInvalidValue;
+    if (stats && mfma_fwd_stats_parts(g, w, ws_bytes) == 0) return hipErrorInvalidValue;
     // a pointwise layer with a handful of output channels is a stream over x: no packing, no tiles
     if (skinny_fwd_supported(g) && ((uintptr_t)w % 16) == 0) return launch_skinny_fwd(g, x, w, scale, shift, res, y, relu, s);
     hipError_t e;
@@ -2144,7 +2144,7 @@ void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_
     fill_common(p, pl, g.B, g.Cout, g.Cin, row_pitch(g.T), g.To, g.K, g.dil, g.pad, !rows16(g));
     p.len_in = g.len;
     p.scale = &affine;
-    if (stats && mfma_fwd_stats_parts(g, ws_bytes) > 0) p.stats = &some_stats;
+    if (stats && mfma_fwd_stats_parts(g, nullptr, ws_bytes) > 0) p.stats = &some_stats;
     const UnpackedPlan up = p.stats ? UnpackedPlan{} : fwd_unpacked_plan(g, pl, ws_bytes);
     if (up.nt) return name_unpacked(up, g.K, false, name, n);
     name_conv(pl, fwd_split_plan(g, pl, ws_bytes), p, name, n);

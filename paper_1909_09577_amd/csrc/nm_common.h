@@ -284,13 +284,13 @@ bool mfma_fwd_supported(const Geom &g);
 // (the least is what a call needs; with the full size calls of few tiles run on the split engine)
 size_t mfma_fwd_workspace(const Geom &g);
 size_t mfma_fwd_workspace_least(const Geom &g);
-// stats (optional, only where mfma_fwd_stats_parts(g, ws_bytes) > 0): [parts][Cout][3] doubles that receive count, mean and
+// stats (optional, only where mfma_fwd_stats_parts(g, w, ws_bytes) > 0): [parts][Cout][3] doubles that receive count, mean and
 // centred second moment of the stored outputs of every (batch item, 160-step time tile) part and channel.
 // in_rounds: the results of a call with the workspace it asks for, to the last bit, in any workspace from the least on
 hipError_t launch_mfma_fwd(const Geom &g, const void *x, const void *w, const float *scale,
                            const float *shift, const void *res, void *y, bool relu, void *ws,
                            size_t ws_bytes, hipStream_t s, double *stats = nullptr, bool in_rounds = false);
-int mfma_fwd_stats_parts(const Geom &g, size_t ws_bytes);
+int mfma_fwd_stats_parts(const Geom &g, const void *w, size_t ws_bytes);
 
 // pointwise forward with at most 32 output channels: bound by reading x once (decoder_logsoftmax.hip)
 bool skinny_fwd_supported(const Geom &g);

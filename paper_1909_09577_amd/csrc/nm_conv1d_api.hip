@@ -428,7 +428,7 @@ static int block_fwd_impl(int B, int Cin, int Cout, int T, int K, int stride, in
     const bool relu = (flags & NM_RELU) != 0;
     t_current_op = NM_OP_FWD;
     if (r.mfma) {
-        const int parts = (stats && stats_parts) ? mfma_fwd_stats_parts(g, workspace_bytes) : 0;
+        const int parts = (stats && stats_parts) ? mfma_fwd_stats_parts(g, w, workspace_bytes) : 0;
         const hipError_t err = launch_mfma_fwd(g, x, w, scale, shift, residual, y, relu, workspace, workspace_bytes, s, parts > 0 ? stats : nullptr, in_rounds);
         if (err == hipSuccess && parts > 0) *stats_parts = parts;
         return dev(err);

@@ -75,3 +75,12 @@ def test_parts_of_an_8_bit_weight_gradient(dims, tiles, parts):
     ((status, seq),) = la.run([{"call": "fp8_bwd", "dims": dims}])
     assert status == nm.NM_OK
     assert [grid[0] for _, kernel, grid in seq if kernel == "fp8_wgrad_kernel"] == [tiles * parts]
+
+
+def test_batch_statistics_with_weights_at_any_address():
+    """Weights at an address that is no multiple of 16 bytes, a view into a flat buffer, run on packed weights whatever the estimates
+    say; the statistics then come from that engine's epilogue and not from a pass over its output."""
+    d = (2, 256, 384, 240, 13, 1, 1, 6)
+    (_, aligned), (_, odd) = la.run([{"call": "bn_fwd", "dims": d}, {"call": "bn_fwd", "dims": d, "w_offset": 2}])
+    assert [k for _, k, _ in aligned][0] == "conv_unpacked_kernel"
+    assert [k for _, k, _ in odd] == ["prepack_kernel", "conv_gemm_kernel", "bn_finalize_kernel", "bn_apply_fwd_kernel"]
