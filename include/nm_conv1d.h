@@ -216,7 +216,7 @@ int nm_decoder_logsoftmax_fwd(int B, int Cin, int Ncls, int T, const void *x, co
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation, arguments,
  * results (bit for bit) and error behaviour as nm_conv1d_block_fwd with the workspace it asks for, without the
  * workspace arguments: the scratch its kernels need (the weights in matrix-core fragment order, 16-byte copies of
- * rows of other lengths, partial sums) lives in a fixed array of NM_STATIC_SCRATCH_BYTES inside the library, one
+ * rows of other lengths, partial sums, also in NM_F32 mode) lives in a fixed array of NM_STATIC_SCRATCH_BYTES inside the library, one
  * copy per GPU, held until the process ends.  The call allocates and frees nothing.
  * A geometry whose weights in fragment order exceed NM_STATIC_SCRATCH_BYTES returns NM_ERR_SCRATCH_LIMIT before
  * anything is launched; one whose nm_conv1d_workspace_bytes(NM_OP_FWD, ...) does not exceed it is always served.
