@@ -715,7 +715,7 @@ constexpr int total_blocks(int KG) { return (2 * KG + kWaves - 1) / kWaves < 8 ?
 // CUT: a float32 sum is a chain of one product after the other, and its error grows with the root of the chain's length.
 // Where a workgroup has more units than a part of the plan in whole rounds would (make_fast_plan), its sums are added to
 // totals and begun again every p.chain pairs of units, which keeps the chains as short as that plan's: error of dw against
-// 64 bits, 640 -> 768 channels, K=25, B=5, T=528 9.5e-8 in eight parts, 2.4e-7 in one, 9.8e-8 in one that is cut; 303 layers
+// 64 bits, 640 -> 768 channels, K=25, B=5, T=528 9.5e-8 in eight parts, 2.4e-7 in one, 9.8e-8 in one that is cut; 270 layers
 // of the encoder 0.99 times those parts' on average, 1.11 at most (5.0e-8 -> 5.6e-8: a chain has two units at least).  The
 // totals lie in LDS, the registers being taken; adding to them costs 0.17 us per block and chain (LDS atomics took 30 times
 // as long), 13 us of a step of 644 at 640 channels, K=21, B=16, T=800.  An instance of its own: the others keep their registers.
