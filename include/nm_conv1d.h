@@ -41,6 +41,8 @@
  *    also multiply the zeros they put for padding, so that an infinite weight, or, where T and T_out are
  *    multiples of eight, an infinite sample or gradient can make a NaN of a result near it that the
  *    definition leaves finite.
+ *  - NM_F32 mode works on float32 operands whole (as they are, or as exact sums of three bfloat16 terms); operands
+ *    smaller than 2^-109 may lose digits below 2^-133.
  *  - Each tensor must hold fewer than 2^31 elements.
  */
 #ifndef NM_CONV1D_H
@@ -114,7 +116,7 @@ int nm_conv1d_block_fwd(int B, int Cin, int Cout, int T, int K, int stride, int 
  * In NM_BF16 mode the matrix-core kernels contract g = dy*m (exact in bfloat16) with the weights
  * bf16(w[co,ci,k]*scale[co]): the affine factor is folded into the weight operand, rounded once per weight.
  * The weight gradient contracts the same g and multiplies its float32 sums by scale[co].  The matrix-core
- * kernels of NM_F32 mode fold scale in the same places.  The plain kernels (NM_FORCE_DIRECT, and what the
+ * kernels of NM_F32 mode fold scale in the same places, or multiply g by it in float32.  The plain kernels (NM_FORCE_DIRECT, and what the
  * others do not serve: strides from 3 on, misaligned tensors, the smallest calls) form dz = g*scale in the
  * storage type instead.
  * With lengths and NM_ACCUM_DX, positions at or beyond a sample's length keep their old value.

@@ -10,94 +10,22 @@
 // few staged chunks (at most 64 terms), and the partial sums of the wavefronts and of the splits are added last, in a
 // fixed order.
 //
-// Measured (4 x 256 -> 256 channels, K = 11, T = 400, forward and both gradients): 141 us, 2732 us on the plain kernels
-// (2.5 TFLOP/s); relative error against 64 bits 1.3e-7, 1.6e-7 on those.  Of a 42 us convolution launch the products alone
-// take 28 (19 at the full clock), the LDS reads 5 and the staging 9.
-#include "nm_common.h"
+// Convolutions of 11 and 13 taps and most weight gradients run on the bfloat16 instructions instead (f32_terms.hip), which also
+// says what these measured on the same call.  2732 us on the plain kernels, 141 here (4 x 256 -> 256 channels, K = 11, T = 400,
+// forward and both gradients); relative error against 64 bits 1.3e-7, 1.6e-7 on those.  Of a 42 us convolution launch the
+// products alone take 28 (19 at the full clock), the LDS reads 5 and the staging 9.
+#include "f32_conv.h"
 
 #include <algorithm>
 
 namespace nm {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kTileM = 64;
 constexpr int kConvWaves = 8;     // wavefronts of a workgroup: two per SIMD, one stages while the other multiplies
 constexpr int kRun = 256;         // floats of a chunk's weight row: one 16-byte load per lane
 constexpr int kXIter = 4;         // window columns per lane: windows of at most 256 samples
 constexpr int kMaxLds = 160 * 1024;
-
-// All staging loads are buffer loads without branches (a branch around a load makes the next one wait for it): what a
-// lane does not want lies beyond the tensor and reads zeros.  The host keeps weights, dz and batch items below 2 GiB.
-constexpr uint32_t kFar = 0x80000000u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const float *p, size_t n)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)(n * sizeof(float)), 0x00020000);
-}
-__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-
-struct F32ConvParams {
-    int B, M, R, Tin, Tout, K, stride, dil, padL;
-    int nmt, ntt;
-    int w_stride;   // LDS: floats per output channel (forward), per reduction channel (input gradient)
-    int x_stride;   // LDS: floats per reduction channel of the window
-    int W;          // window length
-    int flush;      // chunks between two additions to the second accumulators
-    int relu;
-    const float *in;               // [B][R][Tin]
-    const float *w;                // forward [M][R][K]; input gradient [R][M][K], taps flipped here
-    const float *rscale;           // input gradient: optional factors of the reduction channels, folded into the weights
-    const float *scale, *shift;    // optional [M]
-    const float *res;              // optional, layout of out
-    float *out;                    // [B][M][Tout]
-    const int *len_in, *len_out;   // optional [B]
-    int nsplit;                    // workgroups that share a tile's reduction channels
-    float *part;                   // their sums [nsplit][B][M][Tout] (nsplit > 1)
-};
-
-// One output as the definition has it, the sums as the plain kernels take them.  The kernel below also multiplies zeros for
-// the padding: with a non-finite weight that makes a NaN of a sum that has no such product, so a NaN is made again here.
-template <bool FLIP>
-__device__ __forceinline__ float defined_sum(const F32ConvParams &p, const float *in, int len, int m, int t)
-{
-    float z = 0.f;
-#pragma clang loop unroll(disable)
-    for (int r0 = 0; r0 < p.R && z == z; r0 += 8) {
-        float part = 0.f;
-#pragma clang loop unroll(disable)
-        for (int r = r0; r < min(r0 + 8, p.R); ++r) {
-            const float *w = p.w + ((size_t)(FLIP ? r : m) * (FLIP ? p.M : p.R) + (FLIP ? m : r)) * p.K;
-            const float f = p.rscale ? p.rscale[r] : 1.f;
-#pragma clang loop unroll(disable)
-            for (int k = 0; k < p.K; ++k) {
-                const int j = FLIP ? p.K - 1 - k : k, tau = t * p.stride - p.padL + j * p.dil;
-                if (tau >= 0 && tau < len) part = fmaf(w[k], in[(size_t)r * p.Tin + tau] * f, part);
-            }
-        }
-        z += part;
-    }
-    return z;
-}
-
-// there: not behind the outputs' valid length, where they are zero
-__device__ __forceinline__ void finish_output(const F32ConvParams &p, float v, bool there, int m, size_t o)
-{
-    if (p.scale) v *= p.scale[m];
-    if (p.shift) v += p.shift[m];
-    if (!there) v = 0.f;
-    if (p.res) v += p.res[o];
-    if (p.relu) v = v > 0.f ? v : 0.f;
-    p.out[o] = v;
-}
 
 // A workgroup owns 64 output channels x 32*NT time steps of one batch item.  The reduction channels are staged in chunks
 // of CC (16 up to 16 taps, 8 up to 32) and split over the eight wavefronts in pairs (lane half h takes the pair's channel
@@ -350,6 +278,12 @@ __global__ __launch_bounds__(256) void f32_split_finish_kernel(const F32ConvPara
     finish_output(p, v, t < lim, m, o);
 }
 
+template <bool FLIP>
+void launch_finish(const F32ConvParams &p, hipStream_t s)
+{
+    hipLaunchKernelGGL(f32_split_finish_kernel<FLIP>, dim3((unsigned)(((size_t)p.B * p.M * p.Tout + 255) / 256)), dim3(256), 0, s, p);
+}
+
 struct F32ConvPlan {
     bool ok;
     int cc, W, w_stride, x_stride;
@@ -389,8 +323,7 @@ hipError_t launch_f32_conv_t(F32ConvParams p, const F32ConvPlan &q, hipStream_t 
     if (e != hipSuccess) return e;
     MainKernelTimer timer(s);  // (the sum of the parts counts with the kernel)
     hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)p.nmt * p.ntt * p.B), (unsigned)p.nsplit), dim3(64 * kConvWaves), q.lds, s, p);
-    if (SPLIT)
-        hipLaunchKernelGGL(f32_split_finish_kernel<FLIP>, dim3((unsigned)(((size_t)p.B * p.M * p.Tout + 255) / 256)), dim3(256), 0, s, p);
+    if (SPLIT) launch_finish<FLIP>(p, s);
     return hipGetLastError();
 }
 template <int NT, bool FLIP, bool SPLIT>
@@ -425,6 +358,14 @@ hipError_t launch_f32_conv(F32ConvParams p, void *part, size_t room, hipStream_t
     const size_t bytes = f32_split_bytes(p.B, p.M, p.R, p.Tout, p.K);
     p.nsplit = bytes > 0 && part && bytes <= room ? f32_splits(p.B, p.M, p.R, p.Tout, p.K) : 1;
     p.part = (float *)part;
+    if (f32_terms_conv_supported(p.R, p.K, p.stride, p.dil)) {
+        int nt;
+        f32_terms_plan(p.B, p.M, p.R, p.Tout, p.K, p.nsplit, &nt, &p.nsplit);
+        MainKernelTimer timer(s);
+        const hipError_t e = launch_f32_terms_conv(p, FLIP, nt, s);
+        if (e == hipSuccess && p.nsplit > 1) launch_finish<FLIP>(p, s);
+        return e == hipSuccess ? hipGetLastError() : e;
+    }
     // the wide tile from two workgroups per CU on (and where its window fits)
     const size_t wide = (size_t)((p.M + kTileM - 1) / kTileM) * ((p.Tout + 63) / 64) * p.B;
     const F32ConvPlan q2 = f32_conv_plan(p.K, p.stride, p.dil, 2, FLIP), q1 = f32_conv_plan(p.K, p.stride, p.dil, 1, FLIP);
@@ -566,7 +507,7 @@ __global__ __launch_bounds__(64 * kConvWaves) void f32_wgrad_kernel(const F32Wgr
 }
 
 struct F32WgradPlan {
-    bool ok;
+    bool ok, terms;  // terms: on the kernel of f32_terms.hip
     int ntg, KG, TPW, S, nchunk, units, W, x_stride;
 };
 F32WgradPlan f32_wgrad_plan(const Geom &g)
@@ -591,6 +532,15 @@ F32WgradPlan f32_wgrad_plan(const Geom &g)
     const long each = (q.units + S - 1) / S;  // no split whose last round is nearly empty
     q.S = (int)((q.units + each - 1) / each);
     q.ok = true;
+    if (f32_terms_wgrad_supported(g)) {
+        // that kernel's tiles are half as large: where they take a round more for little work this one is faster (384 channels, K=13,
+        // B=1, T=50: 20.0 us here, 23.3 there; T=300: 37.8, 35.1)
+        double cost;
+        const int parts = f32_terms_wgrad_parts(g, &cost);
+        const double rounds = (double)((tiles * q.S + 255) / 256), mb = 4e-6 * g.Cout * g.Cin * (double)g.K;
+        q.terms = cost < rounds * (8.2 + each * (0.8 + 1.8 * q.TPW)) + 0.5 * mb * q.S;
+        if (q.terms) q.S = parts;
+    }
     return q;
 }
 
@@ -646,6 +596,15 @@ hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *dz, cons
 {
     const F32WgradPlan q = f32_wgrad_plan(g);
     if (!q.ok) return hipErrorInvalidValue;
+    const DefinedDw fix = {true, x, dz, nullptr};
+    if (q.terms) {
+        hipError_t e;
+        {
+            MainKernelTimer timer(s);
+            e = launch_f32_terms_wgrad(g, x, dz, (float *)part, s);
+        }
+        return e == hipSuccess ? launch_wgrad_reduce(g, (const float *)part, dw, scale, q.S, accumulate, s, &g, &fix) : e;
+    }
     F32WgradParams p = {};
     p.B = g.B; p.Cin = g.Cin; p.Cout = g.Cout; p.T = g.T; p.To = g.To;
     p.K = g.K; p.stride = g.stride; p.dil = g.dil; p.pad = g.pad;
@@ -671,7 +630,6 @@ hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *dz, cons
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const DefinedDw fix = {true, x, dz, nullptr};
     return launch_wgrad_reduce(g, (const float *)part, dw, scale, q.S, accumulate, s, &g, &fix);
 }
 
