@@ -159,9 +159,11 @@ struct Epilogue {
             const bool ok = m < M && t < Tout;
             ld.ooff[q] = ok ? (uint32_t)((((size_t)b * M + m) * Tout + t) * 2) : kOutOfRange;
             const uint32_t moff = ok ? (uint32_t)m * 4u : kOutOfRange;
-            if (ANYROW && anyrow)
-                ld.rvec[q] = load8_any(res_p + ld.ooff[q] / 2, ok && res_p ? Tout - t : 0);
-            else
+            if (ANYROW && anyrow) {
+                if (!res_p) ld.rvec[q] = u32x4{0u, 0u, 0u, 0u};
+                else if (Tout >= 8) ld.rvec[q] = load8_row(res_p + ((size_t)b * M + min(m, M - 1)) * Tout, t, Tout);  // moved down in finish_rows
+                else ld.rvec[q] = load8_any(res_p + ld.ooff[q] / 2, ok ? Tout - t : 0);
+            } else
                 ld.rvec[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_res, ld.ooff[q], 0, 0);
             ld.scv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_scale, moff, 0, 0));
             ld.shv[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_shift, moff, 0, 0));
@@ -179,12 +181,13 @@ struct Epilogue {
             const f32x4 lo = *reinterpret_cast<const f32x4 *>(tp + r * TN + c8 * 8);
             const f32x4 hi = *reinterpret_cast<const f32x4 *>(tp + r * TN + c8 * 8 + 4);
             const float sc = has_scale ? ld.scv[q] : 1.f;
-            u32x4 o;
+            u32x4 rv = ld.rvec[q], o;
+            if (ANYROW && anyrow && res_p && Tout >= 8) rv = shift8_down(rv, c8 * 8, ld.tout_rel);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float a0 = (e < 2 ? lo[2 * e] : hi[2 * e - 4]), a1 = (e < 2 ? lo[2 * e + 1] : hi[2 * e - 3]);
-                float v0 = a0 * sc + ld.shv[q] + __uint_as_float(ld.rvec[q][e] << 16);
-                float v1 = a1 * sc + ld.shv[q] + __uint_as_float(ld.rvec[q][e] & 0xffff0000u);
+                float v0 = a0 * sc + ld.shv[q] + __uint_as_float(rv[e] << 16);
+                float v1 = a1 * sc + ld.shv[q] + __uint_as_float(rv[e] & 0xffff0000u);
                 if (relu) {
                     v0 = v0 > 0.f ? v0 : 0.f;
                     v1 = v1 > 0.f ? v1 : 0.f;

@@ -1455,7 +1455,10 @@ __global__ __launch_bounds__(256) void prepare_rows_kernel(const PrepareRowsArgs
         const int l = a.len[row / (unsigned)a.Cin];
         n = l < 0 ? 0 : (l < n ? l : n);
     }
-    a.xp[i] = load8_any(a.x + row * a.T + t, n - t);
+    if (a.T >= 8)
+        a.xp[i] = first_of8(shift8_down(load8_row(a.x + row * a.T, t, a.T), t, a.T), n - t);
+    else
+        a.xp[i] = load8_any(a.x + row * a.T + t, n - t);
 }
 
 // A stride-2 input gradient's: the parities' filters (M = 2*Cin rows cut out of w [R][Cin][ld]) and the pass over dy and y
