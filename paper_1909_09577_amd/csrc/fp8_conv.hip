@@ -31,7 +31,7 @@
 // takes every fourth chunk of the tile and the partial tiles are summed through LDS in a fixed order.
 #include "../../include/nm_conv1d.h"
 #include "../../include/nm_conv1d_fp8.h"
-#include "nm_common.h"
+#include "fp8_prepare.h"
 
 #include <type_traits>
 #include <utility>
@@ -56,21 +56,6 @@ constexpr int kFragBytes = 64 * 32;        // one A fragment
 constexpr int kTapBytes = 2 * kFragBytes;  // the two fragments (rows 0-31, 32-63) of one tap and chunk
 constexpr int kAhead = 4;                  // taps between the request of a window piece and its LDS write
 constexpr size_t kSlack = 8192;            // bytes behind each quantised tensor that prefetches may read
-constexpr float kE4M3Max = 448.0f;
-
-// ---------------------------------------------------------------------------------------------
-// E4M3 conversion: round to nearest, ties to even, saturating at +-448.  The hardware conversion
-// (v_cvt_pk_fp8_f32, two values per instruction) rounds to nearest even; the saturation is made explicit by
-// clamping first.  Inputs are finite by contract (a NaN gives a NaN code).
-__device__ __forceinline__ float clamp_e4m3(float v) { return __builtin_fminf(__builtin_fmaxf(v, -448.0f), 448.0f); }
-// codes of a, b, c, d in bytes 0..3
-__device__ __forceinline__ uint32_t e4m3_pack4(float a, float b, float c, float d)
-{
-    int r = __builtin_amdgcn_cvt_pk_fp8_f32(clamp_e4m3(a), clamp_e4m3(b), 0, false);
-    r = __builtin_amdgcn_cvt_pk_fp8_f32(clamp_e4m3(c), clamp_e4m3(d), r, true);
-    return (uint32_t)r;
-}
-__device__ __forceinline__ uint32_t f32_to_e4m3(float f) { return e4m3_pack4(f, 0.f, 0.f, 0.f) & 0xffu; }
 
 __device__ __forceinline__ float wave_max(float v)
 {
@@ -114,124 +99,6 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__rest
     q[i] = (unsigned char)f32_to_e4m3(bf16_to_f32(x[i]) * inv);
 }
 
-// x [B][Cin][T] bf16 -> xq[B][Cin/64][Tp][64] codes; row r stands for input time r - pad, zero outside [0,T).
-// grid (ceil(Tp/64), Cin/64, B); thread (tl, cg): row blockIdx.x*64 + tl, channels 16*cg .. 16*cg+15.
-__global__ __launch_bounds__(256) void quant_x_kernel(const bf16_t *__restrict__ x, const float *__restrict__ xs,
-                                                      unsigned char *__restrict__ xq, int Cin, int T, int Tp, int pad)
-{
-    const int tl = threadIdx.x & 63, cg = threadIdx.x >> 6;
-    const int r = blockIdx.x * 64 + tl;
-    if (r >= Tp) return;
-    const int c = blockIdx.y, b = blockIdx.z;
-    const int t = r - pad;
-    u32x4 out = {0u, 0u, 0u, 0u};
-    if (t >= 0 && t < T) {
-        const float inv = 1.0f / xs[0];
-        const bf16_t *src = x + ((size_t)b * Cin + c * 64 + cg * 16) * T + t;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            out[j] = e4m3_pack4(bf16_to_f32(src[(size_t)(4 * j) * T]) * inv, bf16_to_f32(src[(size_t)(4 * j + 1) * T]) * inv,
-                                bf16_to_f32(src[(size_t)(4 * j + 2) * T]) * inv, bf16_to_f32(src[(size_t)(4 * j + 3) * T]) * inv);
-    }
-    *reinterpret_cast<u32x4 *>(xq + (((size_t)b * gridDim.y + c) * Tp + r) * 64 + cg * 16) = out;
-}
-
-// The same for T % 8 == 0 and 16-byte aligned x: 16-byte loads along T, the transposition to time-major rows goes
-// through LDS.  grid (ceil(T/128), Cin/64, B); a block converts 64 channels x 128 time steps.  Thread (g, tv) loads 8
-// time steps of the four channels 4g..4g+3 and writes eight dwords (four channel codes of one time step each); then
-// every thread copies 16-byte pieces of finished rows out.  The first and the last block of a row of blocks also
-// write the zero rows before time 0 and behind time T.
-constexpr int kQxT = 128;
-__global__ __launch_bounds__(256) void quant_x_vec_kernel(const bf16_t *__restrict__ x, const float *__restrict__ xs,
-                                                          unsigned char *__restrict__ xq, int Cin, int T, int Tp, int pad)
-{
-    __shared__ __align__(16) unsigned char tile[kQxT * kRowBytes];
-    const int c = blockIdx.y, b = blockIdx.z, nck = gridDim.y;
-    const int t0 = blockIdx.x * kQxT;
-    const int g = threadIdx.x & 15, tv = threadIdx.x >> 4;
-    const float inv = 1.0f / xs[0];
-    const int t = t0 + tv * 8;
-    if (t < T) {
-        const bf16_t *src = x + ((size_t)b * Cin + c * 64 + g * 4) * T + t;
-        u32x4 raw[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) raw[j] = *reinterpret_cast<const u32x4 *>(src + (size_t)j * T);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = bf16_to_f32((bf16_t)((raw[j][e >> 1] >> (16 * (e & 1))) & 0xffffu)) * inv;
-            *reinterpret_cast<uint32_t *>(tile + (tv * 8 + e) * kRowBytes + g * 4) = e4m3_pack4(v[0], v[1], v[2], v[3]);
-        }
-    }
-    __syncthreads();
-    unsigned char *const slab = xq + ((size_t)b * nck + c) * Tp * 64;
-    const int rows = min(kQxT, T - t0);
-    for (int i = threadIdx.x; i < rows * 4; i += 256) {
-        const int row = i >> 2, q = i & 3;
-        *reinterpret_cast<u32x4 *>(slab + (size_t)(t0 + row + pad) * 64 + q * 16) =
-            *reinterpret_cast<const u32x4 *>(tile + row * kRowBytes + q * 16);
-    }
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < pad * 4; i += 256) *reinterpret_cast<u32x4 *>(slab + (size_t)i * 16) = zero;
-    if (blockIdx.x == gridDim.x - 1)
-        for (int i = threadIdx.x; i < (Tp - T - pad) * 4; i += 256)
-            *reinterpret_cast<u32x4 *>(slab + (size_t)(T + pad) * 64 + (size_t)i * 16) = zero;
-}
-
-// w [Cout][Cin][K] bf16 -> wq[Cout/64][Cin/64][K][2][64][32] codes.  One block per (channel tile, chunk,
-// row half): its 32 rows of 64*K weights are contiguous pieces of memory; they go through LDS as codes.
-// Lane l of a fragment holds row l%32 and the 32 channels 32*(l/32) .. +31 of the chunk.
-constexpr int kPackThreads = 1024;
-__global__ __launch_bounds__(kPackThreads) void pack_w_kernel(const bf16_t *__restrict__ w, const float *__restrict__ wsc,
-                                                              unsigned char *__restrict__ wq, int Cin, int K)
-{
-    extern __shared__ __align__(16) unsigned char codes[];  // [32][pitch]
-    const int mi = blockIdx.x & 1, c = blockIdx.y, cot = blockIdx.z;
-    const int nck = gridDim.y;
-    const int rowlen = 64 * K;       // codes per row
-    const int pitch = rowlen + 8;    // keeps the 8-byte writes aligned
-    const int vec_per_row = rowlen / 8;
-    const int nvec = 32 * vec_per_row;
-    for (int base = 0; base < nvec; base += 4 * kPackThreads) {
-        u32x4 raw[4];
-        int row[4], col[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {  // four loads in flight
-            const int v = base + u * kPackThreads + threadIdx.x;
-            row[u] = v / vec_per_row;
-            col[u] = v - row[u] * vec_per_row;
-            if (v < nvec)
-                raw[u] = *reinterpret_cast<const u32x4 *>(w + ((size_t)(cot * 64 + mi * 32 + row[u]) * Cin + c * 64) * K + col[u] * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (base + u * kPackThreads + (int)threadIdx.x >= nvec) continue;
-            const float inv = 1.0f / wsc[cot * 64 + mi * 32 + row[u]];
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = bf16_to_f32((bf16_t)((raw[u][j >> 1] >> (16 * (j & 1))) & 0xffffu)) * inv;
-            const u32x2 o = {e4m3_pack4(v[0], v[1], v[2], v[3]), e4m3_pack4(v[4], v[5], v[6], v[7])};
-            *reinterpret_cast<u32x2 *>(codes + row[u] * pitch + col[u] * 8) = o;
-        }
-    }
-    __syncthreads();
-    for (int it = threadIdx.x; it < K * 64; it += kPackThreads) {
-        const int k = it >> 6, lane = it & 63;
-        const unsigned char *src = codes + (lane & 31) * pitch + (32 * (lane >> 5)) * K + k;
-        u32x4 lo = {0u, 0u, 0u, 0u}, hi = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            lo[j >> 2] |= (uint32_t)src[j * K] << (8 * (j & 3));
-            hi[j >> 2] |= (uint32_t)src[(16 + j) * K] << (8 * (j & 3));
-        }
-        u32x4 *dst = reinterpret_cast<u32x4 *>(wq + ((((size_t)(cot * nck + c) * K + k) * 2 + mi) * 64 + lane) * 32);
-        dst[0] = lo;
-        dst[1] = hi;
-    }
-}
-
 // ---- operands of the input gradient ------------------------------------------------------------
 // out[ci] = max over (co, k) of |w[co,ci,k]*scale[co]| / 448 (1 if that maximum is 0); one block per input channel
 __global__ __launch_bounds__(256) void dgrad_wscale_kernel(const bf16_t *__restrict__ w, const float *__restrict__ scale,
@@ -251,143 +118,6 @@ __global__ __launch_bounds__(256) void dgrad_wscale_kernel(const bf16_t *__restr
     if (threadIdx.x == 0) {
         const float a = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
         out[ci] = a == 0.f ? 1.f : a / kE4M3Max;
-    }
-}
-
-// g = dy*[y>0] -> codes in the time-major layout of the activations (row r stands for time r - pad), and g itself
-// to dres when that is wanted.  Same structure as quant_x_vec_kernel; T % 8 == 0 and 16-byte aligned tensors.
-__global__ __launch_bounds__(256) void quant_g_vec_kernel(const bf16_t *__restrict__ dy, const bf16_t *__restrict__ y,
-                                                          const float *__restrict__ gs, unsigned char *__restrict__ gq,
-                                                          bf16_t *__restrict__ dres, int C, int T, int Tp, int pad)
-{
-    __shared__ __align__(16) unsigned char tile[kQxT * kRowBytes];
-    const int c = blockIdx.y, b = blockIdx.z, nck = gridDim.y;
-    const int t0 = blockIdx.x * kQxT;
-    const int g4 = threadIdx.x & 15, tv = threadIdx.x >> 4;
-    const float inv = 1.0f / gs[0];
-    const int t = t0 + tv * 8;
-    if (t < T) {
-        const size_t off = ((size_t)b * C + c * 64 + g4 * 4) * T + t;
-        u32x4 raw[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) raw[j] = *reinterpret_cast<const u32x4 *>(dy + off + (size_t)j * T);
-        if (y) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) raw[j] = masked_grad8(raw[j], *reinterpret_cast<const u32x4 *>(y + off + (size_t)j * T));
-        }
-        if (dres) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4 *>(dres + off + (size_t)j * T) = raw[j];
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = bf16_to_f32((bf16_t)((raw[j][e >> 1] >> (16 * (e & 1))) & 0xffffu)) * inv;
-            *reinterpret_cast<uint32_t *>(tile + (tv * 8 + e) * kRowBytes + g4 * 4) = e4m3_pack4(v[0], v[1], v[2], v[3]);
-        }
-    }
-    __syncthreads();
-    unsigned char *const slab = gq + ((size_t)b * nck + c) * Tp * 64;
-    const int rows = min(kQxT, T - t0);
-    for (int i = threadIdx.x; i < rows * 4; i += 256) {
-        const int row = i >> 2, q = i & 3;
-        *reinterpret_cast<u32x4 *>(slab + (size_t)(t0 + row + pad) * 64 + q * 16) =
-            *reinterpret_cast<const u32x4 *>(tile + row * kRowBytes + q * 16);
-    }
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < pad * 4; i += 256) *reinterpret_cast<u32x4 *>(slab + (size_t)i * 16) = zero;
-    if (blockIdx.x == gridDim.x - 1)
-        for (int i = threadIdx.x; i < (Tp - T - pad) * 4; i += 256)
-            *reinterpret_cast<u32x4 *>(slab + (size_t)(T + pad) * 64 + (size_t)i * 16) = zero;
-}
-
-// The same element by element (any T and alignment); grid (ceil(Tp/64), C/64, B) as quant_x_kernel.
-__global__ __launch_bounds__(256) void quant_g_kernel(const bf16_t *__restrict__ dy, const bf16_t *__restrict__ y,
-                                                      const float *__restrict__ gs, unsigned char *__restrict__ gq,
-                                                      bf16_t *__restrict__ dres, int C, int T, int Tp, int pad)
-{
-    const int tl = threadIdx.x & 63, cg = threadIdx.x >> 6;
-    const int r = blockIdx.x * 64 + tl;
-    if (r >= Tp) return;
-    const int c = blockIdx.y, b = blockIdx.z;
-    const int t = r - pad;
-    u32x4 out = {0u, 0u, 0u, 0u};
-    if (t >= 0 && t < T) {
-        const float inv = 1.0f / gs[0];
-        const size_t off = ((size_t)b * C + c * 64 + cg * 16) * T + t;
-        float v[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            bf16_t gb = dy[off + (size_t)j * T];
-            if (y && !((uint32_t)y[off + (size_t)j * T] - 1u < 0x7f80u)) gb = 0;
-            if (dres) dres[off + (size_t)j * T] = gb;
-            v[j] = bf16_to_f32(gb) * inv;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = e4m3_pack4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
-    }
-    *reinterpret_cast<u32x4 *>(gq + (((size_t)b * gridDim.y + c) * Tp + r) * 64 + cg * 16) = out;
-}
-
-// Weight operand of the input gradient: W'[ci][co][k'] = w[co][ci][K-1-k'] * scale[co], quantised with the scale of
-// its row ci, in fragment order wtq[Cin/64][Cout/64][K][2][64][32].  One block per (input-channel tile, chunk of 64
-// output channels, row half): for every output channel of the chunk the 32*K weights of the block's 32 input
-// channels are one contiguous piece of memory; they go through LDS as codes [co][ci*K + k].
-__global__ __launch_bounds__(kPackThreads) void pack_wt_kernel(const bf16_t *__restrict__ w, const float *__restrict__ scale,
-                                                               const float *__restrict__ wts, unsigned char *__restrict__ wtq,
-                                                               int Cin, int K)
-{
-    extern __shared__ __align__(16) unsigned char codes[];  // [64][pitch]
-    const int mi = blockIdx.x & 1, c = blockIdx.y, cit = blockIdx.z;
-    const int nck = gridDim.y;
-    const int rowlen = 32 * K;       // codes per output channel
-    const int pitch = rowlen + 8;
-    const int vec_per_row = rowlen / 8;
-    const int nvec = 64 * vec_per_row;
-    const int ci0 = cit * 64 + mi * 32;
-    // the inverse scales of the 32 input channels once (a division per element: 36 us at 768 channels, K=25; 29 so)
-    __shared__ float inv_scale[32];
-    if (threadIdx.x < 32) inv_scale[threadIdx.x] = 1.0f / wts[ci0 + threadIdx.x];
-    __syncthreads();
-    for (int base = 0; base < nvec; base += 4 * kPackThreads) {
-        u32x4 raw[4];
-        int row[4], col[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int v = base + u * kPackThreads + threadIdx.x;
-            row[u] = v / vec_per_row;
-            col[u] = v - row[u] * vec_per_row;
-            if (v < nvec) raw[u] = *reinterpret_cast<const u32x4 *>(w + ((size_t)(c * 64 + row[u]) * Cin + ci0) * K + col[u] * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (base + u * kPackThreads + (int)threadIdx.x >= nvec) continue;
-            const float f = scale ? scale[c * 64 + row[u]] : 1.f;
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int e = col[u] * 8 + j;  // element (ci_l, k) = (e / K, e % K) of this output channel's piece
-                v[j] = (bf16_to_f32((bf16_t)((raw[u][j >> 1] >> (16 * (j & 1))) & 0xffffu)) * f) * inv_scale[e / K];
-            }
-            const u32x2 o = {e4m3_pack4(v[0], v[1], v[2], v[3]), e4m3_pack4(v[4], v[5], v[6], v[7])};
-            *reinterpret_cast<u32x2 *>(codes + row[u] * pitch + col[u] * 8) = o;
-        }
-    }
-    __syncthreads();
-    for (int it = threadIdx.x; it < K * 64; it += kPackThreads) {
-        const int k = it >> 6, lane = it & 63;  // fragment of tap k' = k: row ci_l = lane % 32, output channels 32*(lane/32) .. +31
-        const unsigned char *src = codes + (32 * (lane >> 5)) * pitch + (lane & 31) * K + (K - 1 - k);
-        u32x4 lo = {0u, 0u, 0u, 0u}, hi = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            lo[j >> 2] |= (uint32_t)src[j * pitch] << (8 * (j & 3));
-            hi[j >> 2] |= (uint32_t)src[(16 + j) * pitch] << (8 * (j & 3));
-        }
-        u32x4 *dst = reinterpret_cast<u32x4 *>(wtq + ((((size_t)(cit * nck + c) * K + k) * 2 + mi) * 64 + lane) * 32);
-        dst[0] = lo;
-        dst[1] = hi;
     }
 }
 
@@ -903,47 +633,14 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb)
 
 }  // namespace
 
-// ---- quantisation passes shared with the weight-gradient kernel (fp8_wgrad.hip) ------------------
 bool fp8_taps_supported(int K, int dil) { return taps_supported(K, dil); }
 
-// x [B][C][T] -> codes [B][C/64][Tp][64], row r standing for time r - pad, zero rows elsewhere
-hipError_t fp8_launch_quant_x(const void *x, const float *xs, unsigned char *xq, int B, int C, int T, int Tp, int pad,
-                              hipStream_t s)
-{
-    if (T % 8 == 0 && !((uintptr_t)x & 15))
-        hipLaunchKernelGGL(quant_x_vec_kernel, dim3((T + kQxT - 1) / kQxT, C / 64, B), dim3(256), 0, s, (const bf16_t *)x, xs, xq,
-                           C, T, Tp, pad);
-    else
-        hipLaunchKernelGGL(quant_x_kernel, dim3((Tp + 63) / 64, C / 64, B), dim3(256), 0, s, (const bf16_t *)x, xs, xq, C, T, Tp,
-                           pad);
-    return hipGetLastError();
-}
-
-// g = dy*[y>0] (y NULL: dy) -> codes in the same layout; g itself to dres when that is given
-hipError_t fp8_launch_quant_g(const void *dy, const void *y, const float *gs, unsigned char *gq, void *dres, int B, int C,
-                              int T, int Tp, int pad, hipStream_t s)
-{
-    const bool vec = T % 8 == 0 && !((uintptr_t)dy & 15) && !((uintptr_t)y & 15) && !((uintptr_t)dres & 15);
-    if (vec)
-        hipLaunchKernelGGL(quant_g_vec_kernel, dim3((T + kQxT - 1) / kQxT, C / 64, B), dim3(256), 0, s, (const bf16_t *)dy,
-                           (const bf16_t *)y, gs, gq, (bf16_t *)dres, C, T, Tp, pad);
-    else
-        hipLaunchKernelGGL(quant_g_kernel, dim3((Tp + 63) / 64, C / 64, B), dim3(256), 0, s, (const bf16_t *)dy, (const bf16_t *)y,
-                           gs, gq, (bf16_t *)dres, C, T, Tp, pad);
-    return hipGetLastError();
-}
-
-// Input gradient behind the quantisation of g: packs the flipped, scale-folded weights (quantised per input
-// channel) into wtq and runs the matrix-core kernel on the codes gq (time-major, Tp rows per batch item and
-// 64-channel group, row r standing for output time r - (dil*(K-1) - pad)).
+// Input gradient behind fp8_prepare: runs the matrix-core kernel on the flipped, scale-folded weights wtq and the codes
+// gq (time-major, Tp rows per batch item and 64-channel group, row r standing for output time r - (dil*(K-1) - pad)).
 hipError_t fp8_dgrad_run(int B, int Cin, int Cout, int T, int K, int dil, const unsigned char *gq, int Tp, const float *g_scale,
-                         const void *w, const float *scale, const float *wt_scales, void *dx, unsigned char *wtq, hipStream_t s)
+                         const float *wt_scales, void *dx, const unsigned char *wtq, hipStream_t s)
 {
     const int ncit = Cin / kTileCo, nck = Cout / kChunk, ntt = (T + kTileT - 1) / kTileT;
-    hipLaunchKernelGGL(pack_wt_kernel, dim3(2, nck, ncit), dim3(kPackThreads), (size_t)64 * (32 * K + 8), s, (const bf16_t *)w,
-                       scale, wt_scales, wtq, Cin, K);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     Fp8Params p;
     p.B = B; p.Cin = Cout; p.Cout = Cin; p.To = T; p.K = K;
     p.ncot = ncit; p.nck = nck; p.ntt = ntt; p.Tp = Tp;
@@ -1029,15 +726,9 @@ extern "C" int nm_conv1d_block_fwd_fp8(int B, int Cin, int Cout, int T, int K, i
     hipStream_t s = (hipStream_t)hip_stream;
     unsigned char *xq = (unsigned char *)workspace;
     unsigned char *wq = xq + l.xq_bytes;
-    if (T % 8 == 0 && !((uintptr_t)x & 15))
-        hipLaunchKernelGGL(quant_x_vec_kernel, dim3((T + kQxT - 1) / kQxT, l.nck, B), dim3(256), 0, s, (const bf16_t *)x,
-                           x_scale, xq, Cin, T, l.Tp, pad);
-    else
-        hipLaunchKernelGGL(quant_x_kernel, dim3((l.Tp + 63) / 64, l.nck, B), dim3(256), 0, s, (const bf16_t *)x, x_scale, xq,
-                           Cin, T, l.Tp, pad);
-    hipLaunchKernelGGL(pack_w_kernel, dim3(2, l.nck, l.ncot), dim3(kPackThreads), (size_t)32 * (64 * K + 8), s,
-                       (const bf16_t *)w, w_scales, wq, Cin, K);
-    if (hipGetLastError() != hipSuccess) return NM_ERR_DEVICE;
+    const Fp8Pack pack = {w, nullptr, w_scales, wq, Cin, Cout, K, false};
+    const Fp8Quant quant = {x, nullptr, x_scale, xq, nullptr, B, Cin, T, l.Tp, pad};
+    if (fp8_prepare(pack, quant, {}, s) != hipSuccess) return NM_ERR_DEVICE;
 
     Fp8Params p;
     p.B = B; p.Cin = Cin; p.Cout = Cout; p.To = To; p.K = K;
@@ -1118,15 +809,10 @@ extern "C" int nm_conv1d_bwd_data_fp8(int B, int Cin, int Cout, int T, int K, in
     unsigned char *wtq = gq + l.xq_bytes;
     const int padL = dilation * (K - 1) - pad;
     const bf16_t *ym = relu ? (const bf16_t *)y : nullptr;
-    const bool vec = To % 8 == 0 && !((uintptr_t)dy & 15) && !((uintptr_t)y & 15) && !((uintptr_t)dres & 15);
-    if (vec)
-        hipLaunchKernelGGL(quant_g_vec_kernel, dim3((To + kQxT - 1) / kQxT, l.nck, B), dim3(256), 0, s, (const bf16_t *)dy, ym,
-                           g_scale, gq, (bf16_t *)dres, Cout, To, l.Tp, padL);
-    else
-        hipLaunchKernelGGL(quant_g_kernel, dim3((l.Tp + 63) / 64, l.nck, B), dim3(256), 0, s, (const bf16_t *)dy, ym, g_scale, gq,
-                           (bf16_t *)dres, Cout, To, l.Tp, padL);
-    if (hipGetLastError() != hipSuccess) return NM_ERR_DEVICE;
-    return fp8_dgrad_run(B, Cin, Cout, T, K, dilation, gq, l.Tp, g_scale, w, scale, wt_scales, dx, wtq, s) == hipSuccess
+    const Fp8Pack pack = {w, scale, wt_scales, wtq, Cin, Cout, K, true};
+    const Fp8Quant quant = {dy, ym, g_scale, gq, dres, B, Cout, To, l.Tp, padL};
+    if (fp8_prepare(pack, quant, {}, s) != hipSuccess) return NM_ERR_DEVICE;
+    return fp8_dgrad_run(B, Cin, Cout, T, K, dilation, gq, l.Tp, g_scale, wt_scales, dx, wtq, s) == hipSuccess
                ? NM_OK
                : NM_ERR_DEVICE;
 }

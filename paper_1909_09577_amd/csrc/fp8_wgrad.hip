@@ -24,20 +24,16 @@
 // per-channel factor and writes dw[co][ci][k]: deterministic.
 #include "../../include/nm_conv1d.h"
 #include "../../include/nm_conv1d_fp8.h"
-#include "nm_common.h"
+#include "fp8_prepare.h"
 
 #include <type_traits>
 #include <utility>
 
 namespace nm {
-// quantisation passes of fp8_conv.hip
-hipError_t fp8_launch_quant_x(const void *x, const float *xs, unsigned char *xq, int B, int C, int T, int Tp, int pad,
-                              hipStream_t s);
-hipError_t fp8_launch_quant_g(const void *dy, const void *y, const float *gs, unsigned char *gq, void *dres, int B, int C,
-                              int T, int Tp, int pad, hipStream_t s);
+// fp8_conv.hip
 bool fp8_taps_supported(int K, int dil);
 hipError_t fp8_dgrad_run(int B, int Cin, int Cout, int T, int K, int dil, const unsigned char *gq, int Tp, const float *g_scale,
-                         const void *w, const float *scale, const float *wt_scales, void *dx, unsigned char *wtq, hipStream_t s);
+                         const float *wt_scales, void *dx, const unsigned char *wtq, hipStream_t s);
 size_t fp8_packed_weight_bytes(int Cin, int Cout, int K);
 
 namespace {
@@ -306,18 +302,16 @@ hipError_t launch_wgrad(const WgParams &p, int grid, hipStream_t s)
     return hipGetLastError();
 }
 
-// The weight gradient behind the quantisation of g: quantises x into `rest`, runs the matrix-core kernel on the
-// codes gq (Tpg rows per batch item and channel group, row g_row0 standing for output time 0) and reduces the
+// The weight gradient behind fp8_prepare: runs the matrix-core kernel on the codes xq (`rest`) and gq (Tpg rows per batch item and channel group, row g_row0 standing for output time 0) and reduces the
 // partial tiles into dw.  `rest`: xq, partial tiles, per-channel factors (sizes of `l`).
 hipError_t wgrad_run(int B, int Cin, int Cout, int T, int To, int K, int dil, int pad, const WgLayout &l, const unsigned char *gq,
-                     int Tpg, int g_row0, const void *x, const float *x_scale, const float *g_scale, const float *scale, float *dw,
+                     int Tpg, int g_row0, const float *x_scale, const float *g_scale, const float *scale, float *dw,
                      bool accumulate, unsigned char *rest, hipStream_t s)
 {
     unsigned char *xq = rest;
     float *part = reinterpret_cast<float *>(xq + l.xq_bytes);
     float *eff = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(part) + l.part_bytes);
-    hipError_t e = fp8_launch_quant_x(x, x_scale, xq, B, Cin, T, l.Tpx, pad, s);
-    if (e != hipSuccess) return e;
+    hipError_t e;
     WgParams p;
     p.B = B; p.Cin = Cin; p.Cout = Cout; p.K = K;
     p.ncit = Cin / kTileCi; p.S = l.S;
@@ -373,8 +367,10 @@ extern "C" int nm_conv1d_bwd_weight_fp8(int B, int Cin, int Cout, int T, int K, 
     hipStream_t s = (hipStream_t)hip_stream;
     unsigned char *gq = (unsigned char *)workspace;
     unsigned char *rest = gq + l.gq_bytes;
-    if (fp8_launch_quant_g(dy, relu ? y : nullptr, g_scale, gq, nullptr, B, Cout, To, l.Tpg, 0, s) != hipSuccess) return NM_ERR_DEVICE;
-    return wgrad_run(B, Cin, Cout, T, To, K, dilation, pad, l, gq, l.Tpg, 0, x, x_scale, g_scale, scale, dw,
+    const Fp8Quant qg = {dy, relu ? y : nullptr, g_scale, gq, nullptr, B, Cout, To, l.Tpg, 0};
+    const Fp8Quant qx = {x, nullptr, x_scale, rest, nullptr, B, Cin, T, l.Tpx, pad};
+    if (fp8_prepare({}, qg, qx, s) != hipSuccess) return NM_ERR_DEVICE;
+    return wgrad_run(B, Cin, Cout, T, To, K, dilation, pad, l, gq, l.Tpg, 0, x_scale, g_scale, scale, dw,
                      (flags & NM_ACCUM_DW) != 0, rest, s) == hipSuccess
                ? NM_OK
                : NM_ERR_DEVICE;
@@ -444,11 +440,14 @@ extern "C" int nm_conv1d_bwd_fp8(int B, int Cin, int Cout, int T, int K, int str
     unsigned char *wtq = gq + l.gq_bytes;
     unsigned char *rest = wtq + l.wtq_bytes;
     const int padL = dilation * (K - 1) - pad;
-    // one pass over dy and y: dres and the codes of g, laid out for the input gradient (row = time + padL)
-    if (fp8_launch_quant_g(dy, relu ? y : nullptr, g_scale, gq, dres, B, Cout, To, l.Tp, padL, s) != hipSuccess) return NM_ERR_DEVICE;
-    if (fp8_dgrad_run(B, Cin, Cout, T, K, dilation, gq, l.Tp, g_scale, w, scale, wt_scales, dx, wtq, s) != hipSuccess)
+    // one launch: the packed weights, the codes of x, and in one pass over dy and y dres and the codes of g, laid out for the input gradient (row = time + padL)
+    const Fp8Pack pack = {w, scale, wt_scales, wtq, Cin, Cout, K, true};
+    const Fp8Quant qg = {dy, relu ? y : nullptr, g_scale, gq, dres, B, Cout, To, l.Tp, padL};
+    const Fp8Quant qx = {x, nullptr, x_scale, rest, nullptr, B, Cin, T, l.wg.Tpx, pad};
+    if (fp8_prepare(pack, qg, qx, s) != hipSuccess) return NM_ERR_DEVICE;
+    if (fp8_dgrad_run(B, Cin, Cout, T, K, dilation, gq, l.Tp, g_scale, wt_scales, dx, wtq, s) != hipSuccess)
         return NM_ERR_DEVICE;
-    return wgrad_run(B, Cin, Cout, T, To, K, dilation, pad, l.wg, gq, l.Tp, padL, x, x_scale, g_scale, scale, dw,
+    return wgrad_run(B, Cin, Cout, T, To, K, dilation, pad, l.wg, gq, l.Tp, padL, x_scale, g_scale, scale, dw,
                      (flags & NM_ACCUM_DW) != 0, rest, s) == hipSuccess
                ? NM_OK
                : NM_ERR_DEVICE;
