@@ -1561,6 +1561,59 @@ unsigned split_rounds(unsigned cols, size_t col_bytes, size_t room)
     return fit == 0 ? ~0u : (unsigned)((cols + fit - 1) / fit);
 }
 
+// Padded work of a shape: MFMAs of all its tiles over the MFMAs of the contraction, times the rounds the
+// workgroups need over the rounds a perfectly divisible launch would need.
+template <int MI, int NT>
+double pointwise_waste(const ConvGemmParams &p, int cus)
+{
+    const int rows = kWaves * MI * 32, cols = NT * 32;
+    const long tr = (p.M + rows - 1) / rows, tc = (p.Tout + cols - 1) / cols;
+    const long tiles = tr * tc * p.B;
+    const double pad = (double)(tr * rows) * (double)(tc * cols) / ((double)p.M * p.Tout);
+    const double rounds = (double)((tiles + cus - 1) / cus) * cus / (double)tiles;
+    return pad * rounds;
+}
+
+bool pointwise_big_tile(const ConvGemmParams &p, int cus)
+{
+    // the 512 x 128 tile does half the LDS and staging work per MFMA and has half as many epilogue rounds per
+    // output (measured 1.1 to 1.2 times faster per MFMA issued at 896 <-> 1024 channels); it is taken unless
+    // its padding and last-round losses outweigh that
+    return pointwise_waste<4, 4>(p, cus) <= 1.12 * pointwise_waste<2, 5>(p, cus);
+}
+
+// Pointwise layers of whole tiles and chunks have estimates of their own, fitted to all plans of 101 forward calls (256 to 1024
+// channels, 56 to 13000 steps; on the device, tensors that no cache holds, weight packing left out; rms 6.5 %).  The plan
+// taken is 1.9 % from the fastest on average, 7.4 % by the rates of the other calls, which hold parts too dear and the large
+// kernels too cheap: 512 -> 640 channels, B=1, T=600: pointwise_gemm_kernel 22.8 us, two parts 16.5; 896 -> 1024, B=1, T=56: tap-pair
+// kernel 19.9, parts 14.8.  Two workgroups share a CU from the 257th on.
+bool whole_pointwise(const Plan &pl, int M, int R, int K)
+{
+    return K == 1 && pl.stride == 1 && M >= 256 && R >= 256 && M % kTileM == 0 && R % kChunk == 0;
+}
+double layer_split_cost(int nt, int ns, unsigned wgs, unsigned chunks, double mb)
+{
+    const unsigned last = wgs % 512, pairs = wgs / 512 + (last > 256 ? 1 : 0);
+    const double one = last > 0 && last <= 256 ? (0.155 + 0.162 * nt) * chunks - 0.95 : 0.0;
+    return 8.5 + one + pairs * ((0.136 + 0.141 * nt) * chunks + 0.5) + 0.46 * mb + (ns > 1 ? 1.3 + 0.5 * ns * mb : 0.0);
+}
+double layer_engine_cost(const Plan &pl, int B, int M, int R, int Tout)
+{
+    const long cus = 256;
+    const int nmt = M / kTileM;
+    const double base = 6.2 + 0.26 * 4e-6 * B * M * (double)Tout;
+    if (pl.nt != 5) {
+        const long tiles = (long)nmt * ((Tout + pl.nt * 32 - 1) / (pl.nt * 32)) * B;
+        return base + (double)((tiles + cus - 1) / cus) * 1.47 * ((R + 127) / 128);
+    }
+    ConvGemmParams p = {};
+    p.M = M; p.B = B; p.Tout = Tout;
+    const bool big = pointwise_big_tile(p, cus);
+    const long tiles = big ? (long)((nmt + 7) / 8) * ((Tout + 127) / 128) * B : (long)((nmt + 3) / 4) * ((Tout + 159) / 160) * B;
+    const double tile = big ? 1.75 * ((R + 63) / 64) + 0.1 : 1.83 * ((R + 127) / 128) + 6.9;
+    return base + (double)((tiles + cus - 1) / cus) * (tile + (Tout % 8 != 0 ? 4.7 : 0.0));  // (that instance's epilogue)
+}
+
 double engine_cost(const Plan &pl, int B, int M, int R, int Tout, int K)
 {
     const long cus = 256;
@@ -1588,7 +1641,9 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
     const int nmt = (M + kTileM - 1) / kTileM, nch = (R + kChunk - 1) / kChunk;
     if (!pl.ok || (K == 1 && nch == 1)) return best;
     const double mb = 4e-6 * B * M * (double)Tout;
-    double best_cost = 0.9 * engine_cost(pl, B, M, R, Tout, K), best_on_device = 0.0;  // (a tie with another engine goes to that)
+    const bool layer = whole_pointwise(pl, M, R, K);
+    // (a tie with another engine goes to that)
+    double best_cost = layer ? 0.96 * layer_engine_cost(pl, B, M, R, Tout) : 0.9 * engine_cost(pl, B, M, R, Tout, K), best_on_device = 0.0;
     // (whatever the shape, the MFMAs at 256 CUs' full rate: most large calls need not be looked at any further)
     if (0.0205 / 4096 * nmt * 2 * (double)B * ((Tout + 31) / 32) * nch * 2 * K > best_cost) return best;
     for (int nt = pl.stride == 1 ? 4 : 3; nt >= 2; --nt) {
@@ -1604,6 +1659,7 @@ SplitPlan make_split_plan(const Plan &pl, int B, int M, int R, int Tout, int K, 
             double cost = (double)(rounds * chunks) *
                           ((rounds > 1 ? 0.0205 : 0.027) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.3 : 0.8));
             if (ns > 1) cost = std::max(cost + 6.0 + 0.42 * ns * mb, 15.0);
+            if (layer) cost = layer_split_cost(nt, ns, wgs, chunks, mb);
             const double on_device = (double)(rounds * chunks) *
                                          ((rounds > 1 ? 0.026 : 0.032) * ((K + 1) / 2) * 2 * nt + (rounds > 1 ? 0.25 : 0.62)) +
                                      0.78 * rounds + 1.4 + 0.79 * ns * mb;
@@ -1728,27 +1784,6 @@ hipError_t launch_pointwise_shape(const ConvGemmParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-// Padded work of a shape: MFMAs of all its tiles over the MFMAs of the contraction, times the rounds the
-// workgroups need over the rounds a perfectly divisible launch would need.
-template <int MI, int NT>
-double pointwise_waste(const ConvGemmParams &p, int cus)
-{
-    const int rows = kWaves * MI * 32, cols = NT * 32;
-    const long tr = (p.M + rows - 1) / rows, tc = (p.Tout + cols - 1) / cols;
-    const long tiles = tr * tc * p.B;
-    const double pad = (double)(tr * rows) * (double)(tc * cols) / ((double)p.M * p.Tout);
-    const double rounds = (double)((tiles + cus - 1) / cus) * cus / (double)tiles;
-    return pad * rounds;
-}
-
-bool pointwise_big_tile(const ConvGemmParams &p)
-{
-    // the 512 x 128 tile does half the LDS and staging work per MFMA and has half as many epilogue rounds per
-    // output (measured 1.1 to 1.2 times faster per MFMA issued at 896 <-> 1024 channels); it is taken unless
-    // its padding and last-round losses outweigh that
-    const int cus = current_device_info().cus;
-    return pointwise_waste<4, 4>(p, cus) <= 1.12 * pointwise_waste<2, 5>(p, cus);
-}
 hipError_t launch_pointwise(const ConvGemmParams &p, bool big, bool len, hipStream_t s)
 {
     if (len)
@@ -1831,7 +1866,7 @@ ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
     // (worth it from two 64-channel row tiles on: a single one would leave three wavefronts idle)
     if (p.K == 1 && p.nmt >= 2 && pl.nt == 5 && pl.stride == 1 && p.padL == 0 && p.Tin == row_pitch(p.Tout)) {
         c.kind = ConvChoice::kPointwise;
-        c.big = pointwise_big_tile(p);
+        c.big = pointwise_big_tile(p, current_device_info().cus);
         c.len = p.len_in || c.any;
         return c;
     }
@@ -2137,7 +2172,7 @@ void name_unpacked(const UnpackedPlan &up, int K, bool flip, char *name, size_t 
 void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n)
 {
     if (skinny_fwd_supported(g)) {
-        snprintf(name, n, "decoder_mfma_kernel<true, false, %d>", decoder_split(g.B, g.Cin, g.T));
+        snprintf(name, n, "decoder_mfma_kernel<true, %s, %d>", g.T % 8 == 0 ? "false" : "true", decoder_split(g.B, g.Cin, g.T));
         return;
     }
     static float affine;
