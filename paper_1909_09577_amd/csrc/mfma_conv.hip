@@ -776,6 +776,144 @@ __global__ __launch_bounds__(kThreads, 2) void conv_split_kernel(const ConvGemmP
     epi.template finish_rows<false, true>(lane, tp, ld);
 }
 
+// ---- the strided first layer, enough tiles ----------------------------------------------------------------
+// The encoder's first layer (64 channels, stride 2, K = 11) has 22 MFMA steps per chunk and two chunks, its input gradient (both
+// parities at once, six taps) 12 and eight: in conv_split_kernel a workgroup spends more time waiting for its first window, adding its wavefronts' sums and finishing than multiplying.  Here
+// the wavefronts of a workgroup share the staged window too, but each has rows (WM of them 64 rows each) and columns (4/WM of them
+// 64 steps each) of its own, over all taps and channels: nothing is exchanged, and a window is staged once for 64*WM rows.
+// Windows are double buffered, one barrier per chunk; weights come in fragment order from L2, six register sets in rotation, all
+// steps of a chunk in a straight line (in a loop over the taps a step took 45 ns an MFMA instead of 20).  Columns of 96 and 128 steps
+// were slower everywhere: two workgroups share a CU and cover each other's waits.  64 -> 256 channels, K=11, B=32, T=1600:
+// forward 26.2 -> 16.3 us, the gradient's contraction 21.5 -> 17.3.
+template <int STRIDE, int WM, int KT>
+struct RowsShape {
+    static constexpr int NT = 2, TN = NT * 32, WC = kWaves / WM, COLS = WC * TN;
+    static constexpr int GROUPS = ((COLS - 1) * STRIDE + KT + 7 + 7) / 8;      // 8-row groups of a window
+    static constexpr int kItems = (GROUPS * 16 + kThreads - 1) / kThreads;      // staging items per lane and chunk
+    static constexpr int BUF = GROUPS * 8 * kRowBytes, TILE = kWaves * 16 * TN * 4;
+    static constexpr int LDS = 2 * BUF > TILE ? 2 * BUF : TILE;
+};
+
+template <int STRIDE, int WM, int KT>
+__global__ __launch_bounds__(kThreads, 2) void conv_rows_kernel(const ConvGemmParams p)
+{
+    using Sh = RowsShape<STRIDE, WM, KT>;
+    constexpr int NT = Sh::NT;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WM, wc = wave / WM;
+    const int nmg = (p.nmt + WM - 1) / WM;
+    const int col = (int)blockIdx.x / nmg, mt = ((int)blockIdx.x - col * nmg) * WM + wm;
+    const int b = col / p.ntt, tw = (col - b * p.ntt) * Sh::COLS, t0 = tw + wc * Sh::TN;  // of the workgroup, of the wavefront
+
+    Epilogue<NT> epi;
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div);
+    const __amdgpu_buffer_rsrc_t rs_in =
+        __builtin_amdgcn_make_buffer_rsrc((void *)p.in, 0, (int)((size_t)p.B * p.R * p.Tin * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)p.wp, 0, (int)p.wp_bytes, 0x00020000);
+    const int ws = tw * STRIDE - p.padL, ws_al = (ws >> 3) * 8;
+    const int tlen = __builtin_amdgcn_readfirstlane(clipped_len(p.len_in, b, p.Tin));
+
+    u32x4 sxa[Sh::kItems], sxb[Sh::kItems];
+    auto stage_load = [&](int c) {
+        const uint32_t soff = (uint32_t)(((size_t)b * p.R + (size_t)c * kChunk) * p.Tin * 2);
+        const int rem = p.R - c * kChunk;
+#pragma unroll
+        for (int q = 0; q < Sh::kItems; ++q) {
+            const int idx = (int)threadIdx.x + kThreads * q;
+            const int pp = idx & 15, grp = idx >> 4;
+            const int t = ws_al + 8 * grp;
+            const bool ok = grp < Sh::GROUPS && (unsigned)t < (unsigned)tlen;
+            const uint32_t at = (uint32_t)(((2 * pp) * p.Tin + t) * 2);
+            sxa[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, ok && 2 * pp < rem ? at : kOutOfRange, soff, 0);
+            sxb[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, ok && 2 * pp + 1 < rem ? at + (uint32_t)(p.Tin * 2) : kOutOfRange, soff, 0);
+        }
+    };
+    auto stage_write = [&](unsigned char *buf) {
+#pragma unroll
+        for (int q = 0; q < Sh::kItems; ++q) {
+            const int idx = (int)threadIdx.x + kThreads * q;
+            const int pp = idx & 15, grp = idx >> 4;
+            if (kThreads * (q + 1) > Sh::GROUPS * 16 && grp >= Sh::GROUPS) continue;
+            const int nv = tlen - (ws_al + 8 * grp);  // valid steps of the group (a group before the row holds zeros)
+            uint32_t *dst = reinterpret_cast<uint32_t *>(buf + (size_t)(8 * grp) * kRowBytes + pp * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t keep = nv >= 2 * j + 2 ? 0xffffffffu : (nv == 2 * j + 1 ? 0x0000ffffu : 0u);
+                const uint32_t a = sxa[q][j] & keep, c = sxb[q][j] & keep;
+                dst[(2 * j) * kRowDwords] = zip_lo16(a, c);
+                dst[(2 * j + 1) * kRowDwords] = zip_hi16(a, c);
+            }
+        }
+    };
+
+    // steps of a chunk: step j is tap j / 2, channel half j % 2
+    constexpr int steps = 2 * KT;
+    constexpr uint32_t kStep = 2048;
+    const uint32_t chunk_bytes = (uint32_t)p.Kp * 4096u;
+    auto chunk_off = [&](int c) { return (uint32_t)(min(mt, p.nmt - 1) * p.nch + c) * chunk_bytes; };
+    constexpr int NS = 6;  // register sets
+    bf16x8 wf[NS][2];
+    auto w_load = [&](uint32_t soff, int mi) {
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs_w, (uint32_t)lane * 16 + (uint32_t)mi * 1024u, soff, 0));
+    };
+    f32x16 acc[2][NT];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+    // (uniform over the workgroup: a window that lies wholly in the padding, or columns that are zero whatever the sums)
+    const bool dead = (p.len_in && ws >= tlen) || (p.len_out && tw >= epi.out_limit(b));
+    if (!dead) {
+        stage_load(0);
+        uint32_t w_cur = chunk_off(0);
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) wf[j][mi] = w_load(w_cur + (uint32_t)j * kStep, mi);
+        stage_write(smem);
+        __syncthreads();
+        const uint32_t lane_off = (uint32_t)((((lane & 31) + wc * Sh::TN) * STRIDE + ws - ws_al) * kRowBytes + (lane >> 5) * 16);
+        for (int c = 0; c < p.nch; ++c) {
+            const bool more = c + 1 < p.nch;
+            const uint32_t w_nxt = more ? chunk_off(c + 1) : w_cur;
+            const unsigned char *bbase = smem + (c & 1) * Sh::BUF + lane_off;
+            if (more) stage_load(c + 1);
+            bf16x8 bf[2][NT];
+            auto read_b = [&](bf16x8(&dst)[NT], int j) {
+                const unsigned char *at = bbase + (j >> 1) * kRowBytes + (j & 1) * 32;
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni) dst[ni] = *reinterpret_cast<const bf16x8 *>(at + ni * 32 * STRIDE * kRowBytes);
+            };
+            read_b(bf[0], 0);
+            for_each_index([&](auto index) __attribute__((always_inline)) {
+                constexpr int j = decltype(index)::value, set = j % NS;
+                if constexpr (j + 1 < steps) read_b(bf[(j & 1) ^ 1], j + 1);
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NT; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][mi], bf[j & 1][ni], acc[mi][ni], 0, 0, 0);
+                // (its next use: NS steps on, or the next chunk's step of the same set)
+                const uint32_t src = j + NS < steps ? w_cur + (j + NS) * kStep : w_nxt + set * kStep;
+                wf[set][0] = w_load(src, 0);
+                wf[set][1] = w_load(src, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }, std::make_integer_sequence<int, steps>{});
+            if (more) stage_write(smem + ((c + 1) & 1) * Sh::BUF);
+            w_cur = w_nxt;
+            __syncthreads();
+        }
+    }
+    if (mt >= p.nmt || t0 >= p.Tout) return;
+    float *tp = reinterpret_cast<float *>(smem) + wave * 16 * Sh::TN;
+    epi.template store_private_tile<false, true>(acc, tp, lane, b, t0, mt * kTileM);
+}
+
 // Adds the nsplit parts of 16 rows x 32 steps in order and finishes them: a wavefront of its own for each of the
 // kWaves x nt such pieces of a tile (with whole 16-row quarters, a quarter of the wavefronts: 11 us instead of 4 for
 // 768 channels x 600 steps in four parts, too few loads in flight).
@@ -1841,11 +1979,34 @@ hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int strid
     return launch_split_t<2, 2>(p, at_once, sp.lds, s);
 }
 
+// Calls of conv_rows_kernel: those that have an instance (stride 2, K = 11; the six taps of its gradient, two row tiles) and enough
+// workgroups.  In a sweep over 32 to 256 input and 192 to 512 output channels, 50 to 51200 steps, the lines below
+// separate gains (forward 1.1 to 1.5 times, gradient up to 1.5) from losses but for a few per cent: forward 64 -> 256, B=24,
+// T=1000, 192 workgroups 15.2 us on conv_split_kernel, 15.6 here; B=20, T=1203, 200 of them 23.2 / 17.6; gradient, 64
+// workgroups 24.8 / 24.9, 84 29.4 / 28.2.
+bool takes_rows(const Plan &pl, int B, int M, int Tout, int K, int dil)
+{
+    const int nmt = (M + kTileM - 1) / kTileM;
+    if (!pl.ok || dil != 1) return false;
+    if (pl.stride == 2) return K == 11 && nmt >= 3 && (long)B * ((Tout + 63) / 64) * nmt >= 4 * 200;
+    return K == 6 && nmt == 2 && M >= 96 && (long)B * ((Tout + 127) / 128) >= 80;  // (a second tile that is at least half full)
+}
+template <int STRIDE, int WM, int KT>
+hipError_t launch_rows_t(ConvGemmParams p, hipStream_t s)
+{
+    using Sh = RowsShape<STRIDE, WM, KT>;
+    static_assert(Sh::LDS <= 64 * 1024, "LDS without an opt-in");
+    p.ntt = (p.Tout + Sh::COLS - 1) / Sh::COLS;
+    MainKernelTimer timer(s);
+    hipLaunchKernelGGL((conv_rows_kernel<STRIDE, WM, KT>), dim3((unsigned)((p.nmt + WM - 1) / WM * p.ntt * p.B)), dim3(kThreads), Sh::LDS, s, p);
+    return hipGetLastError();
+}
+
 // Which kernel makes a contraction.
 struct ConvChoice {
-    enum Kind { kFew, kSplit, kPointwise, kGemm } kind;
+    enum Kind { kFew, kSplit, kPointwise, kRows, kGemm } kind;
     bool big;                                // kPointwise: the 512 x 128 tile
-    int nt, stride, kt;                      // kGemm: the template arguments
+    int nt, stride, kt;                      // kGemm: the template arguments (stride: of kRows too)
     bool len, stats, any, pad_pair;          // (len: of kPointwise too)
 };
 ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p)
@@ -1856,6 +2017,11 @@ ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
     if (p.K == 1 && p.R <= kChunk && pl.stride == 1 && p.padL == 0 && p.Tin == p.Tout && p.Tout % 8 == 0 && !p.res &&
         !p.scale && !p.shift && !p.relu && !p.len_in && !p.len_out) {
         c.kind = ConvChoice::kFew;
+        return c;
+    }
+    if (!p.stats && takes_rows(pl, p.B, p.M, p.Tout, p.K, p.dil)) {
+        c.kind = ConvChoice::kRows;
+        c.stride = pl.stride;
         return c;
     }
     if (!p.stats && sp.nt) {
@@ -1911,6 +2077,7 @@ hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
     case ConvChoice::kFew: return launch_few_channels(p, s);
     case ConvChoice::kSplit: return launch_split(sp, p, pl.stride, part, part_room, s);
     case ConvChoice::kPointwise: return launch_pointwise(p, c.big, c.len, s);
+    case ConvChoice::kRows: return c.stride == 2 ? launch_rows_t<2, 4, 11>(p, s) : launch_rows_t<1, 2, 6>(p, s);
     case ConvChoice::kGemm: break;
     }
     if (c.stats) return launch_unrolled<false, true, false>(c.kt, p, pl.lds, s);
@@ -1932,6 +2099,7 @@ void name_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, cha
     case ConvChoice::kPointwise:
         snprintf(name, n, "pointwise_gemm_kernel<%s, %s>", b(c.len), c.big ? "4, 4, 64" : "2, 5, 128");
         break;
+    case ConvChoice::kRows: snprintf(name, n, "conv_rows_kernel<%s>", c.stride == 1 ? "1, 2, 6" : "2, 4, 11"); break;
     case ConvChoice::kGemm:
         snprintf(name, n, "conv_gemm_kernel<%d, %d, %d, %s, %s, %s, %s>", c.nt, c.stride, c.kt, b(c.len), b(c.stats), b(c.any), b(c.pad_pair));
         break;
