@@ -276,6 +276,37 @@ struct Epilogue {
     }
 };
 
+// Adds the nsplit parts of 16 rows x 32 steps in order and finishes them: one wavefront's work, tp its LDS tile of 16 x 32 floats.
+__device__ __forceinline__ void split_reduce_piece(const ConvGemmParams &p, int nt, int piece, int lane, float *tp)
+{
+    const int ni = piece % nt, quarter = piece / nt;
+    const int wave = quarter & 3, tile = quarter >> 2;
+    const int col = tile / p.nmt, mt = tile - col * p.nmt;
+    const int b = (p.col0 + col) / p.ntt, t0 = ((p.col0 + col - b * p.ntt) * nt + ni) * 32;
+    Epilogue<1> epi;
+    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div);
+    const auto ld = epi.template request_rows<true>(lane, b, t0, mt * kTileM + 8 * wave, true);
+    const size_t pitch = (size_t)p.nmt * p.ncols * kWaves * 2 * nt * 64;
+    const f32x4 *src = p.part + ((size_t)quarter * 2 * nt + ni) * 64 + lane;
+    f32x4 own[2][1] = {};
+#pragma unroll 8
+    for (int s = 0; s < p.nsplit; ++s) {
+        own[0][0] += src[(size_t)s * pitch];
+        own[1][0] += src[(size_t)s * pitch + (size_t)nt * 64];
+    }
+    epi.put_quarter(tp, lane, own);
+    wave_lds_fence();
+    epi.template finish_rows<false, true>(lane, tp, ld);
+}
+
+// Such a sum that is still to be launched.
+struct SplitSum {
+    bool set = false;
+    ConvGemmParams p;
+    int nt;
+    unsigned pieces() const { return (unsigned)(p.nmt * p.ncols * kWaves * nt); }
+};
+
 // valid length of batch item b from an optional device array, clipped to [0, T]
 __device__ __forceinline__ int clipped_len(const int *len, int b, int T)
 {
@@ -295,8 +326,8 @@ bool unpacked_supported(int M, int R, int K, int stride, bool flip);
 UnpackedPlan unpacked_plan(int B, int M, int R, int Tout, int K, int dil, bool flip, size_t part_limit);
 // p: as for the other engines, without the packed weights; w 16-byte aligned; part: plan.part_bytes of scratch
 hipError_t launch_unpacked_conv(const UnpackedPlan &plan, const ConvGemmParams &p, const void *w, bool flip, const float *rscale,
-                                void *part, hipStream_t s);
-// adds p.nsplit parts in a fixed order and finishes the tiles (mfma_conv.hip)
-hipError_t launch_split_reduce(const ConvGemmParams &p, int nt, hipStream_t s);
+                                void *part, hipStream_t s, SplitSum *later = nullptr);
+// adds p.nsplit parts in a fixed order and finishes the tiles (mfma_conv.hip); later: leaves that to the caller
+hipError_t launch_split_reduce(const ConvGemmParams &p, int nt, hipStream_t s, SplitSum *later = nullptr);
 
 }  // namespace nm

@@ -920,25 +920,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_rows_kernel(const ConvGemmPa
 __global__ __launch_bounds__(64) void split_reduce_kernel(const ConvGemmParams p, int nt)
 {
     __shared__ __align__(16) float tp[16 * 32];
-    const int lane = threadIdx.x;
-    const int ni = (int)blockIdx.x % nt, quarter = (int)blockIdx.x / nt;
-    const int wave = quarter & 3, tile = quarter >> 2;
-    const int col = tile / p.nmt, mt = tile - col * p.nmt;
-    const int b = (p.col0 + col) / p.ntt, t0 = ((p.col0 + col - b * p.ntt) * nt + ni) * 32;
-    Epilogue<1> epi;
-    epi.init(p.out, p.res, p.scale, p.shift, p.B, p.M, p.Tout, p.relu, p.len_out, p.len_out_div);
-    const auto ld = epi.template request_rows<true>(lane, b, t0, mt * kTileM + 8 * wave, true);
-    const size_t pitch = (size_t)p.nmt * p.ncols * kWaves * 2 * nt * 64;
-    const f32x4 *src = p.part + ((size_t)quarter * 2 * nt + ni) * 64 + lane;
-    f32x4 own[2][1] = {};
-#pragma unroll 8
-    for (int s = 0; s < p.nsplit; ++s) {
-        own[0][0] += src[(size_t)s * pitch];
-        own[1][0] += src[(size_t)s * pitch + (size_t)nt * 64];
-    }
-    epi.put_quarter(tp, lane, own);
-    wave_lds_fence();
-    epi.template finish_rows<false, true>(lane, tp, ld);
+    split_reduce_piece(p, nt, (int)blockIdx.x, (int)threadIdx.x, tp);
 }
 
 // ---- K = 1 (pointwise convolution: a plain GEMM  out[b] = W' . in[b]) ----------------------------
@@ -1944,21 +1926,21 @@ hipError_t launch_few_channels(const ConvGemmParams &p, hipStream_t s)
 }
 
 template <int NT, int STRIDE>
-hipError_t launch_split_t(ConvGemmParams p, int cols_at_once, size_t lds, hipStream_t s)
+hipError_t launch_split_t(ConvGemmParams p, int cols_at_once, size_t lds, hipStream_t s, SplitSum *later)
 {
     MainKernelTimer timer(s);
     const int cols = p.ntt * p.B;
     for (p.col0 = 0; p.col0 < cols; p.col0 += cols_at_once) {
         p.ncols = std::min(cols_at_once, cols - p.col0);
         hipLaunchKernelGGL((conv_split_kernel<NT, STRIDE>), dim3(p.nmt * p.ncols * p.nsplit), dim3(kThreads), lds, s, p);
-        const hipError_t e = p.nsplit > 1 ? launch_split_reduce(p, NT, s) : hipGetLastError();
+        const hipError_t e = p.nsplit > 1 ? launch_split_reduce(p, NT, s, cols_at_once >= cols && !timer.stop ? later : nullptr) : hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 // [part, part + part_room): room for the parts of one column of tiles at least
-hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int stride, void *part, size_t part_room, hipStream_t s)
+hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int stride, void *part, size_t part_room, hipStream_t s, SplitSum *later)
 {
     ConvGemmParams p = p0;
     p.ntt = (p.Tout + sp.nt * 32 - 1) / (sp.nt * 32);
@@ -1971,12 +1953,12 @@ hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int strid
     const int at_once = sp.part_bytes <= part_room ? cols : (int)(part_room / sp.col_bytes);
     if (at_once < 1) return hipErrorInvalidValue;  // (no such plan is made)
     if (stride == 1) {
-        if (sp.nt == 4) return launch_split_t<4, 1>(p, at_once, sp.lds, s);
-        if (sp.nt == 3) return launch_split_t<3, 1>(p, at_once, sp.lds, s);
-        return launch_split_t<2, 1>(p, at_once, sp.lds, s);
+        if (sp.nt == 4) return launch_split_t<4, 1>(p, at_once, sp.lds, s, later);
+        if (sp.nt == 3) return launch_split_t<3, 1>(p, at_once, sp.lds, s, later);
+        return launch_split_t<2, 1>(p, at_once, sp.lds, s, later);
     }
-    if (sp.nt == 3) return launch_split_t<3, 2>(p, at_once, sp.lds, s);
-    return launch_split_t<2, 2>(p, at_once, sp.lds, s);
+    if (sp.nt == 3) return launch_split_t<3, 2>(p, at_once, sp.lds, s, later);
+    return launch_split_t<2, 2>(p, at_once, sp.lds, s, later);
 }
 
 // Calls of conv_rows_kernel: those that have an instance (stride 2, K = 11; the six taps of its gradient, two row tiles) and enough
@@ -2070,12 +2052,13 @@ hipError_t launch_tap_pairs(const ConvChoice &c, const ConvGemmParams &p, size_t
 }
 
 // [part, part + part_room): room for the partial sums of the split engine, whose plan is sp
-hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room)
+hipError_t launch_plan(const Plan &pl, const SplitPlan &sp, const ConvGemmParams &p, hipStream_t s, void *part, size_t part_room,
+                       SplitSum *later = nullptr)
 {
     const ConvChoice c = choose_conv(pl, sp, p);
     switch (c.kind) {
     case ConvChoice::kFew: return launch_few_channels(p, s);
-    case ConvChoice::kSplit: return launch_split(sp, p, pl.stride, part, part_room, s);
+    case ConvChoice::kSplit: return launch_split(sp, p, pl.stride, part, part_room, s, later);
     case ConvChoice::kPointwise: return launch_pointwise(p, c.big, c.len, s);
     case ConvChoice::kRows: return c.stride == 2 ? launch_rows_t<2, 4, 11>(p, s) : launch_rows_t<1, 2, 6>(p, s);
     case ConvChoice::kGemm: break;
@@ -2225,8 +2208,14 @@ void fill_common(ConvGemmParams &p, const Plan &pl, int B, int M, int R, int Tin
 }  // namespace
 
 // (also reports a refused launch before it: asking clears it)
-hipError_t launch_split_reduce(const ConvGemmParams &p, int nt, hipStream_t s)
+hipError_t launch_split_reduce(const ConvGemmParams &p, int nt, hipStream_t s, SplitSum *later)
 {
+    if (later) {
+        later->set = true;
+        later->p = p;
+        later->nt = nt;
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(split_reduce_kernel, dim3(p.nmt * p.ncols * kWaves * nt), dim3(64), 0, s, p, nt);
     return hipGetLastError();
 }
@@ -2557,7 +2546,7 @@ void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name
 // accumulate (stride 1 only): dx = bf16(dx + gradient), one rounding.
 hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const float *scale, const void *w,
                              void *dx, void *dres, bool relu, bool accumulate, void *ws, size_t ws_bytes, hipStream_t s,
-                             const void **g_used)
+                             const void **g_used, SplitSum *later)
 {
     const size_t least = mfma_dgrad_workspace_least(g);
     void *part = (unsigned char *)ws + least;
@@ -2604,7 +2593,7 @@ hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const
         if (e != hipSuccess) return e;
     }
     if (g_used) *g_used = gin;
-    return launch_mfma_dgrad_prepared(g, gin, scale, w, dx, accumulate, ws, ws_bytes, s);
+    return launch_mfma_dgrad_prepared(g, gin, scale, w, dx, accumulate, ws, ws_bytes, s, later);
 }
 
 // ---- fused backward -------------------------------------------------------------------------
@@ -2653,7 +2642,7 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
 }
 
 hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, const float *scale, const void *w, void *dx, bool accumulate,
-                                      void *ws, size_t ws_bytes, hipStream_t s)
+                                      void *ws, size_t ws_bytes, hipStream_t s, SplitSum *later)
 {
     const Plan pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
     if (!pl.ok || !mfma_dgrad_supported(g)) return hipErrorInvalidValue;
@@ -2661,8 +2650,8 @@ hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, const 
     fill_dgrad(p, pl, g, g_plain, ws, dx, accumulate);
     const size_t least = mfma_dgrad_workspace_least(g);
     if (mfma_dgrad_unpacked(g, w, ws_bytes))
-        return launch_unpacked_conv(dgrad_unpacked_plan(g, pl, ws_bytes), p, w, true, scale, (unsigned char *)ws + least, s);
-    return launch_plan(pl, dgrad_split_plan(g, pl, ws_bytes), p, s, (unsigned char *)ws + least, ws_bytes - least);
+        return launch_unpacked_conv(dgrad_unpacked_plan(g, pl, ws_bytes), p, w, true, scale, (unsigned char *)ws + least, s, later);
+    return launch_plan(pl, dgrad_split_plan(g, pl, ws_bytes), p, s, (unsigned char *)ws + least, ws_bytes - least, later);
 }
 
 }  // namespace nm

@@ -22,7 +22,7 @@
 // by a vectorised elementwise kernel) and the affine factor scale[co] multiplies the float32 sums in
 // the final reduction, so the operand carries no rounding of its own:
 //   dw[co,ci,k] = scale[co] * sum_b sum_t g[b,co,t] * x[b,ci,tau(t,k)].
-#include "nm_common.h"
+#include "wgrad_reduce.h"
 
 #include <stdio.h>
 
@@ -1073,38 +1073,6 @@ __global__ __launch_bounds__(kThreads) void wgrad_shared_kernel(const WgradParam
     }
 }
 
-// One sum as the definition has it (see DefinedDw), in the plain kernel's blocks.
-template <typename TS>
-__device__ __forceinline__ float defined_dw(const Geom &g, const TS *x, const TS *dy, const TS *y, int co, int ci, int k)
-{
-    const int off = k * g.dil - g.pad;
-    float z = 0.f;
-#pragma clang loop unroll(disable)
-    for (int b = 0; b < g.B && z == z; ++b) {
-        const int len = valid_len(g, b);
-        const size_t at = ((size_t)b * g.Cout + co) * g.To;
-        const TS *xr = x + ((size_t)b * g.Cin + ci) * g.T;
-#pragma clang loop unroll(disable)
-        for (int t0 = 0; t0 < g.To && z == z; t0 += 64) {
-            float part = 0.f;
-#pragma clang loop unroll(disable)
-            for (int t = t0; t < min(t0 + 64, g.To); ++t) {
-                const int tau = t * g.stride + off;
-                if (tau < 0 || tau >= len) continue;
-                const float gv = y && !(load_as_f32(y, at + t) > 0.f) ? 0.f : load_as_f32(dy, at + t);
-                part = fmaf(gv, load_as_f32(xr, (size_t)tau), part);
-            }
-            z += part;
-        }
-    }
-    return z;
-}
-__device__ __forceinline__ float defined_dw(const Geom &g, const DefinedDw &q, int co, int ci, int k)
-{
-    return q.f32 ? defined_dw(g, (const float *)q.x, (const float *)q.dy, (const float *)q.y, co, ci, k)
-                 : defined_dw(g, (const bf16_t *)q.x, (const bf16_t *)q.dy, (const bf16_t *)q.y, co, ci, k);
-}
-
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci]; one block per (co, 64 ci).
 // MEND: the instance that makes NaN sums again from the tensors of DefinedDw.  MANY: the instance for eight parts and more,
 // which requests eight at a time (one after the other, 16 parts of 64 -> 256 channels, K=11, took 15 us, 6 so); for fewer it
@@ -1142,57 +1110,14 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
     }
 }
 
-// The same for Cin % 4 == 0 and 16-byte aligned dw: one block per (co, 256 ci), 16-byte loads along ci
-// (a wavefront reads 1 KiB contiguous per partial row) and 16-byte stores of the transposed tile.
-constexpr int kReduce4Ci = 256;
+// The same for Cin % 4 == 0 and 16-byte aligned dw: one block per (co, 256 ci), see reduce4_block.
 template <bool MEND, bool MANY>
 __global__ __launch_bounds__(256) void wgrad_reduce4_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                             const float *__restrict__ scale, int S, int K, int Cout,
                                                             int Cin, int accumulate, const Geom own, const DefinedDw defined)
 {
     extern __shared__ float tile[];  // [256][K+1]
-    const int co = blockIdx.y;
-    const int ci0 = blockIdx.x * kReduce4Ci;
-    const int l = threadIdx.x & 63, kq = threadIdx.x >> 6;
-    const int ci = ci0 + 4 * l;
-    const size_t plane = (size_t)Cout * Cin;
-    const float factor = scale ? scale[co] : 1.f;
-    for (int k = kq; k < K; k += 4) {
-        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-        if (ci < Cin) {
-            const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
-#pragma unroll MANY ? 8 : 1
-            for (int sp = 0; sp < S; ++sp) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)sp * K * plane);
-            if constexpr (MEND) {
-                const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);  // a NaN if one of them is
-                if (__builtin_expect(all != all, 0)) {
-#pragma clang loop unroll(disable)
-                    for (int e = 0; e < 4; ++e) {
-                        const float one = e == 0 ? sum[0] : e == 1 ? sum[1] : e == 2 ? sum[2] : sum[3];
-                        if (one == one) continue;
-                        const float z = defined_dw(own, defined, co, ci + e, k);
-                        if (e == 0) sum[0] = z; else if (e == 1) sum[1] = z; else if (e == 2) sum[2] = z; else sum[3] = z;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) tile[(4 * l + e) * (K + 1) + k] = sum[e] * factor;
-    }
-    __syncthreads();
-    const int nci = min(kReduce4Ci, Cin - ci0);
-    const int n = nci * K;  // a multiple of 4
-    float *dst = dw + ((size_t)co * Cin + ci0) * K;
-    for (int e0 = threadIdx.x * 4; e0 < n; e0 += 1024) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = (e0 + e) / K, k = (e0 + e) - c * K;
-            v[e] = tile[c * (K + 1) + k];
-        }
-        f32x4 *o = reinterpret_cast<f32x4 *>(dst + e0);
-        *o = accumulate ? *o + v : v;
-    }
+    reduce4_block<MEND, MANY>(tile, (int)blockIdx.x, (int)blockIdx.y, part, dw, scale, S, K, Cout, Cin, accumulate, own, defined);
 }
 
 constexpr long kPlanCUs = 256;  // the planning below aims at this many CUs (a heuristic only: any count works)
@@ -1432,17 +1357,22 @@ constexpr int kMaxReduceTaps = 64 * 1024 / (64 * (int)sizeof(float)) - 1;  // 25
 }  // namespace
 
 hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, const float *scale, int S, bool accumulate,
-                         hipStream_t s, const Geom *own, const DefinedDw *defined)
+                         hipStream_t s, const Geom *own, const DefinedDw *defined, const SplitSum *first)
 {
     const bool mend = own && defined;
     const Geom og = mend ? *own : g;
     const DefinedDw d = mend ? *defined : DefinedDw{};
     if (g.Cin % 4 == 0 && ((uintptr_t)dw % 16) == 0 && (size_t)kReduce4Ci * (g.K + 1) * sizeof(float) <= 64 * 1024) {
+        if (first) return launch_both_sums(*first, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate, mend, og, d, s);
         dim3 grid4((g.Cin + kReduce4Ci - 1) / kReduce4Ci, g.Cout);
         auto kern = S >= 8 ? (mend ? wgrad_reduce4_kernel<true, true> : wgrad_reduce4_kernel<false, true>)
                            : (mend ? wgrad_reduce4_kernel<true, false> : wgrad_reduce4_kernel<false, false>);
         hipLaunchKernelGGL(kern, grid4, dim3(256), kReduce4Ci * (g.K + 1) * sizeof(float), s, part, dw, scale, S, g.K, g.Cout, g.Cin, accumulate ? 1 : 0, og, d);
         return hipGetLastError();
+    }
+    if (first) {
+        const hipError_t e = launch_split_sum(*first, s);
+        if (e != hipSuccess) return e;
     }
     dim3 rgrid((g.Cin + 63) / 64, g.Cout);
     auto kern = S >= 8 ? (mend ? wgrad_reduce_kernel<true, true> : wgrad_reduce_kernel<false, true>)
@@ -1513,7 +1443,7 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g0, int most)
 }
 
 hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float *scale, float *dw, bool accumulate, void *ws,
-                                      hipStream_t s, int most, const DefinedDw *defined)
+                                      hipStream_t s, int most, const DefinedDw *defined, const SplitSum *first)
 {
     const Geom g = pitched(g0);
     const FastPlan f = make_fast_plan(g, most);
@@ -1563,7 +1493,7 @@ hipError_t launch_mfma_wgrad_prepared(const Geom &g0, const void *x, const float
         }
     }
     if (e != hipSuccess) return e;
-    return launch_wgrad_reduce(g, part, dw, scale, f.S, accumulate, s, &g0, defined);
+    return launch_wgrad_reduce(g, part, dw, scale, f.S, accumulate, s, &g0, defined, first);
 }
 
 hipError_t launch_mfma_wgrad(const Geom &g0, const void *x, const void *dy, const void *y, const float *scale,

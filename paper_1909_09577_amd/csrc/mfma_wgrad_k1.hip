@@ -197,7 +197,7 @@ size_t wgrad_k1_part_bytes(const Geom &g)
 
 // gplain: g = dy*[y>0] in the layout of dy (dy itself without a ReLU).  ws: wgrad_k1_part_bytes(g) bytes.
 hipError_t launch_wgrad_k1(const Geom &g, const void *x, const void *gplain, const float *scale, float *dw, bool accumulate,
-                           void *ws, hipStream_t s)
+                           void *ws, hipStream_t s, const SplitSum *first)
 {
     const K1Plan q = make_k1_plan(g);
     K1Params p = {};
@@ -215,7 +215,7 @@ hipError_t launch_wgrad_k1(const Geom &g, const void *x, const void *gplain, con
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
-    return launch_wgrad_reduce(g, (const float *)ws, dw, scale, q.S, accumulate, s);
+    return launch_wgrad_reduce(g, (const float *)ws, dw, scale, q.S, accumulate, s, nullptr, nullptr, first);
 }
 
 }  // namespace nm

@@ -342,11 +342,14 @@ hipError_t launch_skinny_fwd(const Geom &g, const void *x, const void *w, const 
 bool mfma_dgrad_supported(const Geom &g);
 size_t mfma_dgrad_workspace(const Geom &g);
 size_t mfma_dgrad_workspace_least(const Geom &g);
+// later (optional, where it appears): the sum of an input gradient's parts is left to the caller, who hands it to the weight gradient's
+// sum (first), with which it shares a launch
+struct SplitSum;
 // g_used (optional, stride 1): receives the tensor the kernel contracted, g = dy*[y>0] -- dy itself without
 // ReLU, else dres or a buffer inside ws -- so that a weight gradient launched next need not form it again
 hipError_t launch_mfma_dgrad(const Geom &g, const void *dy, const void *y, const float *scale,
                              const void *w, void *dx, void *dres, bool relu, bool accumulate, void *ws,
-                             size_t ws_bytes, hipStream_t s, const void **g_used = nullptr);
+                             size_t ws_bytes, hipStream_t s, const void **g_used = nullptr, SplitSum *later = nullptr);
 
 bool mfma_wgrad_supported(const Geom &g);
 // most: the parts there is room for (no more than are fastest are used)
@@ -374,12 +377,13 @@ void name_mfma_wgrad(const Geom &g, bool relu, size_t ws_bytes, char *name, size
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci] (scale NULL: 1), fixed order
 // (own, defined: optional; the call's geometry and tensors)
 hipError_t launch_wgrad_reduce(const Geom &g, const float *part, float *dw, const float *scale, int S, bool accumulate,
-                               hipStream_t s, const Geom *own = nullptr, const DefinedDw *defined = nullptr);
+                               hipStream_t s, const Geom *own = nullptr, const DefinedDw *defined = nullptr,
+                               const SplitSum *first = nullptr);
 // pointwise (K = 1) weight gradient as a GEMM over plain rows (mfma_wgrad_k1.hip); never with lengths
 bool wgrad_k1_supported(const Geom &g);
 size_t wgrad_k1_part_bytes(const Geom &g);
 hipError_t launch_wgrad_k1(const Geom &g, const void *x, const void *gplain, const float *scale, float *dw, bool accumulate,
-                           void *ws, hipStream_t s);
+                           void *ws, hipStream_t s, const SplitSum *first = nullptr);
 
 // ---- rows of any length -------------------------------------------------------------------------
 // What a call on rows that are no multiple of eight long needs before its main kernel, in one launch; each part is
@@ -419,7 +423,7 @@ DzfLayout mfma_wgrad_dzf_layout(const Geom &g, int most);
 // weight gradient from a workspace whose fragment-order g has been written already; scale[co] (or NULL)
 // multiplies the float32 sums; defined: for rows of any length
 hipError_t launch_mfma_wgrad_prepared(const Geom &g, const void *x, const float *scale, float *dw, bool accumulate,
-                                      void *ws, hipStream_t s, int most, const DefinedDw *defined = nullptr);
+                                      void *ws, hipStream_t s, int most, const DefinedDw *defined = nullptr, const SplitSum *first = nullptr);
 // packs the flipped weights times scale into ws (as launch_mfma_dgrad does; where `pack`) and, in the same launch, forms
 // g plain (into dres, else behind the packed weights in ws, else nowhere) and in fragment order (gf);
 // *g_plain: the tensor the input gradient contracts
@@ -430,7 +434,7 @@ hipError_t launch_bwd_prepare(const Geom &g, const void *dy, const void *y, cons
 bool mfma_dgrad_unpacked(const Geom &g, const void *w, size_t ws_bytes);
 // input gradient from a workspace prepared by launch_bwd_prepare
 hipError_t launch_mfma_dgrad_prepared(const Geom &g, const void *g_plain, const float *scale, const void *w, void *dx, bool accumulate,
-                                      void *ws, size_t ws_bytes, hipStream_t s);
+                                      void *ws, size_t ws_bytes, hipStream_t s, SplitSum *later = nullptr);
 
 // ---- training-mode BatchNorm passes (bn_train.hip) ---------------------------------------------
 size_t bn_fwd_scratch_bytes(int B, int C, int T);

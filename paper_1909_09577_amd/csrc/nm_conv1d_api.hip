@@ -3,7 +3,7 @@
 // launches.  Validation never touches the HIP runtime, so it behaves the same on a
 // host without a device.
 #include "../../include/nm_conv1d.h"
-#include "nm_common.h"
+#include "conv_tile.h"
 
 #include <stdio.h>
 
@@ -667,6 +667,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     // pointwise layers: the input gradient's masked g = dy*[y>0] also feeds the K=1 weight-gradient GEMM
     const bool fused_k1 = fits && both_mfma && !lengths && g.stride == 1 && wgrad_k1_supported(pitched(g)) && aligned16(x) &&
                           aligned16(dy) && aligned16(dx) && (!relu || aligned16(y));
+    SplitSum dx_sum;  // of the input gradient's parts: launched with the weight gradient's
     if (fused_k1) {
         DisarmOnExit disarm;
         if (clash) return NM_ERR_BAD_ARG;
@@ -680,16 +681,17 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
             err = launch_bwd_prepare(g, dy, y, scale, w, true, relu, workspace, nullptr, none, dres, &g_plain, s, x, xp);
             if (err != hipSuccess) return NM_ERR_DEVICE;
             t_current_op = NM_OP_BWD_DATA;
-            err = launch_mfma_dgrad_prepared(g, g_plain, scale, w, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
+            err = launch_mfma_dgrad_prepared(g, g_plain, scale, w, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s, &dx_sum);
             if (err != hipSuccess) return NM_ERR_DEVICE;
             t_current_op = NM_OP_BWD_WEIGHT;
-            return dev(launch_wgrad_k1(pitched(g), xp, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s));
+            return dev(launch_wgrad_k1(pitched(g), xp, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, dx_sum.set ? &dx_sum : nullptr));
         }
         t_current_op = NM_OP_BWD_DATA;
-        err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s, &g_plain);
+        err = launch_mfma_dgrad(g, dy, y, scale, w, dx, dres, relu, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s, &g_plain, &dx_sum);
         if (err != hipSuccess || !g_plain) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
-        return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s));
+        return dev(launch_wgrad_k1(g, x, g_plain, scale, dw, (flags & NM_ACCUM_DW) != 0, (unsigned char *)workspace + ws_data, s,
+                                   dx_sum.set ? &dx_sum : nullptr));
     }
     // stride 2: the input gradient's g is plain too, and what the general weight-gradient kernel reads
     const bool fused_s2 = fits && both_mfma && !clash && g.stride == 2 && rows16(g) && !(flags & NM_ACCUM_DX) && masked_on_mfma(g, NM_OP_BWD_WEIGHT) && aligned16(x) &&
@@ -758,11 +760,12 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
                                         dres, &g_plain, s, x, xp);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_DATA;
-    err = launch_mfma_dgrad_prepared(g, g_plain, scale, w, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s);
+    err = launch_mfma_dgrad_prepared(g, g_plain, scale, w, dx, (flags & NM_ACCUM_DX) != 0, workspace, ws_data, s, &dx_sum);
     if (err != hipSuccess) return NM_ERR_DEVICE;
     t_current_op = NM_OP_BWD_WEIGHT;
     const DefinedDw defined = {false, x, dy, relu ? y : nullptr};
-    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, most, rows16(g) ? nullptr : &defined));
+    return dev(launch_mfma_wgrad_prepared(g, xp ? xp : x, scale, dw, (flags & NM_ACCUM_DW) != 0, ws_w, s, most, rows16(g) ? nullptr : &defined,
+                                          dx_sum.set ? &dx_sum : nullptr));
 }
 
 int nm_conv1d_bwd(int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, const void *x,

@@ -408,7 +408,7 @@ UnpackedPlan unpacked_plan(int B, int M, int R, int Tout, int K, int dil, bool f
 }
 
 hipError_t launch_unpacked_conv(const UnpackedPlan &plan, const ConvGemmParams &p, const void *w, bool flip, const float *rscale,
-                                void *part, hipStream_t s)
+                                void *part, hipStream_t s, SplitSum *later)
 {
     UnpackedParams q = {};
     q.c = p;
@@ -424,6 +424,6 @@ hipError_t launch_unpacked_conv(const UnpackedPlan &plan, const ConvGemmParams &
     const unsigned grid = (unsigned)(p.nmt * plan.nsplit * q.ncolgroups);
     MainKernelTimer timer(s);
     const hipError_t e = flip ? launch_columns<true>(plan.nt, q, grid, plan.lds, s) : launch_columns<false>(plan.nt, q, grid, plan.lds, s);
-    return e != hipSuccess ? e : launch_split_reduce(q.c, plan.nt, s);
+    return e != hipSuccess ? e : launch_split_reduce(q.c, plan.nt, s, timer.stop ? nullptr : later);
 }
 }  // namespace nm
