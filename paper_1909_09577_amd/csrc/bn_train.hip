@@ -8,108 +8,123 @@
 //
 // All of these are bandwidth-bound passes over [B][C][T] tensors.  Sums are deterministic: every block
 // owns one channel and a fixed subset of the batch items, reduces in a fixed tree (in double, so that
-// var = M2/N does not cancel), and a one-thread-per-channel kernel combines the per-block results in a
-// fixed order (block means and centred second moments, merged pairwise as in a streaming variance).
-// Elements move in groups of VEC: 8 bf16 (16 bytes) when rows are 16-byte aligned, else one at a time.
+// var = M2/N does not cancel), and the per-block results are combined in a fixed order (block means and
+// centred second moments, merged pairwise as in a streaming variance).
+// Elements move in groups of 16 bytes, 8 bf16 or 4 float, whatever the row length and the address: the last
+// group of a row ends with the row and begins inside the one before it (the elements that both hold are
+// counted once, and written twice with the same value); rows shorter than a group go element by element.
+// Rows that are no multiple of a group used to go element by element throughout: 384 channels, B=10, T=711 six launches of 41.8 us,
+// 24.4 in four now (640 channels, B=16, T=800, where nothing but the last merge went: 47.1 and 43.4).
 #include "nm_common.h"
 
-#include <initializer_list>
+#include <type_traits>
 
 namespace nm {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxParts = 8;  // of a channel, where a pass over the tensor makes them
+template <int N>
+using Vec = std::integral_constant<int, N>;
+
+// Group i of the rows of channel c that a block handles: row i / ng of them, first element at(..), of which the first `skip`
+// belong to the group before.
+struct Rows {
+    int C, T, ng;
+    __device__ __forceinline__ size_t at(int vec, unsigned i, int c, int b0, int step, int &skip) const
+    {
+        const unsigned r = i / (unsigned)ng;
+        const int t = (int)(i - r * (unsigned)ng) * vec, from = min(t, T - vec);
+        skip = t - from;
+        return ((size_t)(b0 + (int)r * step) * C + c) * T + from;
+    }
+};
 
 template <typename TS, int VEC>
 struct Group {
-    float v[VEC];
+    TS raw[VEC] __attribute__((aligned(VEC > 1 ? 16 : sizeof(TS))));
+    __device__ __forceinline__ void load(const TS *p) { __builtin_memcpy(raw, p, sizeof raw); }
+    __device__ __forceinline__ float operator[](int e) const { return load_as_f32(raw, e); }
 };
 template <typename TS, int VEC>
-__device__ __forceinline__ Group<TS, VEC> load_group(const TS *p, size_t group)
+__device__ __forceinline__ void store_group(TS *p, const float *v)
 {
-    Group<TS, VEC> r;
-    if constexpr (VEC == 8) {
-        const u32x4_t raw = reinterpret_cast<const u32x4_t *>(p)[group];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            r.v[2 * j] = __uint_as_float(raw[j] << 16);
-            r.v[2 * j + 1] = __uint_as_float(raw[j] & 0xffff0000u);
-        }
-    } else {
-        r.v[0] = load_as_f32(p, group);
-    }
-    return r;
-}
-template <typename TS, int VEC>
-__device__ __forceinline__ void store_group(TS *p, size_t group, const Group<TS, VEC> &g)
-{
-    if constexpr (VEC == 8) {
+    if constexpr (sizeof(TS) == 2 && VEC == 8) {
         u32x4_t raw;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) raw[j] = pack_bf16x2(g.v[2 * j], g.v[2 * j + 1]);
-        reinterpret_cast<u32x4_t *>(p)[group] = raw;
+        for (int j = 0; j < 4; ++j) raw[j] = pack_bf16x2(v[2 * j], v[2 * j + 1]);
+        __builtin_memcpy(p, &raw, 16);
     } else {
-        store_from_f32(p, group, g.v[0]);
+        TS raw[VEC] __attribute__((aligned(16)));
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) store_from_f32(raw, e, v[e]);
+        __builtin_memcpy(p, raw, sizeof raw);
     }
 }
 
 // Sum of `a` and of `b` over the block, in a fixed tree, returned to thread 0.
 __device__ __forceinline__ void block_sum2(double &a, double &b)
 {
-    __shared__ double red[2][kThreads];
-    red[0][threadIdx.x] = a;
-    red[1][threadIdx.x] = b;
-    __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + s];
-            red[1][threadIdx.x] += red[1][threadIdx.x + s];
-        }
-        __syncthreads();
+    __shared__ double red[2][kThreads / 64];
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_down(a, off, 64);
+        b += __shfl_down(b, off, 64);
     }
-    a = red[0][0];
-    b = red[1][0];
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        red[0][wave] = a;
+        red[1][wave] = b;
+    }
+    __syncthreads();
+    a = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+    b = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
 }
 
 // Block (c, g): batch items g, g+G, ... of channel c -> part[(g*C + c)*3] = {count, mean, centred second moment}.
 template <typename TS, int VEC>
-__global__ __launch_bounds__(kThreads) void bn_stats_kernel(const TS *__restrict__ z, int B, int C, int T, int G,
+__global__ __launch_bounds__(kThreads) void bn_stats_kernel(const TS *__restrict__ z, int B, Rows rows, int G,
                                                             double *__restrict__ part)
 {
     const int c = blockIdx.x, g = blockIdx.y;
-    const int ng = T / VEC;
-    float s1 = 0.f, s2 = 0.f;
-    int rows = 0;
-    for (int b = g; b < B; b += G, ++rows) {
-        const size_t row = ((size_t)b * C + c) * ng;
-        for (int i = threadIdx.x; i < ng; i += kThreads) {
-            const Group<TS, VEC> v = load_group<TS, VEC>(z, row + i);
+    const int nrows = (B - g + G - 1) / G;
+    const unsigned n = (unsigned)nrows * rows.ng;
+    double a = 0.0, q = 0.0;
+    for (unsigned i = threadIdx.x; i < n; i += kThreads) {
+        int skip;
+        Group<TS, VEC> v;
+        v.load(z + rows.at(VEC, i, c, g, G, skip));
+        float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                s1 += v.v[e];
-                s2 = fmaf(v.v[e], v.v[e], s2);
-            }
+        for (int e = 0; e < VEC; ++e) {
+            const float f = e < skip ? 0.f : v[e];
+            s1 += f;
+            s2 = fmaf(f, f, s2);
         }
+        a += s1;
+        q += s2;
     }
-    double a = s1, q = s2;
     block_sum2(a, q);
     if (threadIdx.x == 0) {
-        const double n = (double)rows * T;
-        double *o = part + ((size_t)g * C + c) * 3;
-        o[0] = n;
-        o[1] = n > 0 ? a / n : 0.0;
-        o[2] = n > 0 ? q - a * a / n : 0.0;
+        const double cnt = (double)nrows * rows.T;
+        double *o = part + ((size_t)g * rows.C + c) * 3;
+        o[0] = cnt;
+        o[1] = cnt > 0 ? a / cnt : 0.0;
+        o[2] = cnt > 0 ? q - a * a / cnt : 0.0;
     }
 }
 
-// One wavefront per channel: lane l merges parts l, l+64, ... in order (Chan's update), then the lanes merge in a
-// fixed tree; mean, invstd, and the affine they imply.
-__global__ __launch_bounds__(64) void bn_finalize_kernel(const double *__restrict__ part, int G, int C,
-                                                         const float *__restrict__ gamma, const float *__restrict__ beta,
-                                                         float eps, float *__restrict__ mean, float *__restrict__ invstd,
-                                                         float *__restrict__ scale, float *__restrict__ shift)
+struct BnFinal {
+    const double *part;
+    int G;
+    const float *gamma, *beta;
+    float eps;
+    float *mean, *invstd, *scale, *shift;
+};
+
+// A wavefront's merge of the parts of channel c: lane l merges parts l, l+64, ... in order (Chan's update), then the lanes
+// merge in a fixed tree; lane 0 has the mean, 1/std and the affine that they imply.
+__device__ __forceinline__ void bn_merge(const BnFinal &f, int C, int c, int lane, float (&out)[4])
 {
-    const int c = blockIdx.x, lane = threadIdx.x;
     double n = 0.0, mu = 0.0, m2 = 0.0;
     auto merge = [&](double nb, double mb, double qb) {
         if (nb <= 0.0) return;
@@ -118,145 +133,217 @@ __global__ __launch_bounds__(64) void bn_finalize_kernel(const double *__restric
         m2 += qb + delta * delta * n * nb / tot;
         n = tot;
     };
-    for (int g = lane; g < G; g += 64) {
-        const double *p = part + ((size_t)g * C + c) * 3;
+    for (int g = lane; g < f.G; g += 64) {
+        const double *p = f.part + ((size_t)g * C + c) * 3;
         merge(p[0], p[1], p[2]);
     }
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int off = f.G > kMaxParts ? 32 : kMaxParts / 2; off > 0; off >>= 1) {
         const double nb = __shfl_down(n, off, 64), mb = __shfl_down(mu, off, 64), qb = __shfl_down(m2, off, 64);
         if (lane < off) merge(nb, mb, qb);
     }
-    if (lane != 0) return;
     const double var = n > 0 ? (m2 > 0 ? m2 / n : 0.0) : 0.0;
-    const double is = 1.0 / sqrt(var + (double)eps);
-    const double ga = gamma ? (double)gamma[c] : 1.0, be = beta ? (double)beta[c] : 0.0;
-    mean[c] = (float)mu;
-    invstd[c] = (float)is;
-    scale[c] = (float)(ga * is);
-    shift[c] = (float)(be - mu * ga * is);
+    const double is = 1.0 / sqrt(var + (double)f.eps);
+    const double ga = f.gamma ? (double)f.gamma[c] : 1.0, be = f.beta ? (double)f.beta[c] : 0.0;
+    out[0] = (float)mu;
+    out[1] = (float)is;
+    out[2] = (float)(ga * is);
+    out[3] = (float)(be - mu * ga * is);
 }
 
-// y = relu?(scale[c]*z + shift[c] + residual)
-template <typename TS, int VEC>
-__global__ __launch_bounds__(kThreads) void bn_apply_fwd_kernel(size_t ngroups, int C, int ng, const TS *__restrict__ z,
-                                                                const float *__restrict__ scale,
-                                                                const float *__restrict__ shift,
-                                                                const TS *__restrict__ res, int relu, TS *__restrict__ y)
+// One wavefront per channel.
+__global__ __launch_bounds__(64) void bn_finalize_kernel(BnFinal f, int C)
 {
-    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= ngroups) return;
-    const int c = (int)((i / (size_t)ng) % (size_t)C);
-    const float sc = scale[c], sh = shift[c];
-    const Group<TS, VEC> zv = load_group<TS, VEC>(z, i);
-    Group<TS, VEC> out;
-    if (res) {
-        const Group<TS, VEC> rv = load_group<TS, VEC>(res, i);
+    float o[4];
+    bn_merge(f, C, blockIdx.x, threadIdx.x, o);
+    if (threadIdx.x != 0) return;
+    f.mean[blockIdx.x] = o[0];
+    f.invstd[blockIdx.x] = o[1];
+    f.scale[blockIdx.x] = o[2];
+    f.shift[blockIdx.x] = o[3];
+}
+
+// Block j*C + c: groups j*per, ... of channel c: y = relu?(scale[c]*z + shift[c] + residual).  MERGE: the parts of the statistics are
+// merged here while z and the residual are under way, by the block's first wavefront, and block c writes mean and invstd.
+// That goes for the at most eight parts of bn_stats_kernel (a launch of 4.9 us before); the parts that
+// a convolution's epilogue writes are one per tile of time, some hundred, and merging them is longer than a launch.
+constexpr int kApplyGroups = 2;  // a thread's, read at once (four: 5.9 -> 7.0 us at 384 channels, B=10, T=711)
+template <typename TS, int VEC, bool MERGE>
+__global__ __launch_bounds__(kThreads) void bn_apply_fwd_kernel(unsigned n, unsigned per, Rows rows, const TS *__restrict__ z,
+                                                                BnFinal f, const TS *__restrict__ res, int relu,
+                                                                TS *__restrict__ y)
+{
+    const int c = blockIdx.x % (unsigned)rows.C;
+    const unsigned j = blockIdx.x / (unsigned)rows.C, first = j * per, last = min(n, first + per);
+    Group<TS, VEC> zv[kApplyGroups], rv[kApplyGroups];
+    size_t at[kApplyGroups];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) out.v[e] = fmaf(zv.v[e], sc, sh) + rv.v[e];
+    for (int u = 0; u < kApplyGroups; ++u) {
+        const unsigned i = first + u * kThreads + threadIdx.x;
+        int skip;
+        at[u] = rows.at(VEC, min(i, n - 1), c, 0, 1, skip);
+        if (i < last) {
+            zv[u].load(z + at[u]);
+            if (res) rv[u].load(res + at[u]);
+        }
+    }
+    float sc, sh;
+    if constexpr (MERGE) {
+        __shared__ float affine[2];
+        if (threadIdx.x < 64) {
+            float o[4];
+            bn_merge(f, rows.C, c, threadIdx.x, o);
+            if (threadIdx.x == 0) {
+                affine[0] = o[2];
+                affine[1] = o[3];
+                if (j == 0) {
+                    f.mean[c] = o[0];
+                    f.invstd[c] = o[1];
+                }
+            }
+        }
+        __syncthreads();
+        sc = affine[0];
+        sh = affine[1];
     } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) out.v[e] = fmaf(zv.v[e], sc, sh);
+        sc = f.scale[c];
+        sh = f.shift[c];
     }
-    if (relu) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) out.v[e] = out.v[e] > 0.f ? out.v[e] : 0.f;
+    for (int u = 0; u < kApplyGroups; ++u) {
+        if (first + u * kThreads + threadIdx.x >= last) break;
+        float out[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            out[e] = fmaf(zv[u][e], sc, sh);
+            if (res) out[e] += rv[u][e];
+            if (relu) out[e] = out[e] > 0.f ? out[e] : 0.f;
+        }
+        store_group<TS, VEC>(y + at[u], out);
     }
-    store_group<TS, VEC>(y, i, out);
 }
 
 // Block (c, g): part[(g*C + c)*2] = {sum g, sum g*zhat} over its batch items, g = dy*[y>0].
 template <typename TS, int VEC>
 __global__ __launch_bounds__(kThreads) void bn_bwd_stats_kernel(const TS *__restrict__ dy, const TS *__restrict__ y,
                                                                 const TS *__restrict__ z, const float *__restrict__ mean,
-                                                                const float *__restrict__ invstd, int relu, int B, int C,
-                                                                int T, int G, double *__restrict__ part)
+                                                                const float *__restrict__ invstd, int relu, int B, Rows rows,
+                                                                int G, double *__restrict__ part)
 {
     const int c = blockIdx.x, g = blockIdx.y;
-    const int ng = T / VEC;
+    const unsigned n = (unsigned)((B - g + G - 1) / G) * rows.ng;
     const float mu = mean[c], is = invstd[c];
-    float s1 = 0.f, s2 = 0.f;
-    for (int b = g; b < B; b += G) {
-        const size_t row = ((size_t)b * C + c) * ng;
-        for (int i = threadIdx.x; i < ng; i += kThreads) {
-            const Group<TS, VEC> dv = load_group<TS, VEC>(dy, row + i);
-            const Group<TS, VEC> zv = load_group<TS, VEC>(z, row + i);
-            Group<TS, VEC> yv;
-            if (relu) yv = load_group<TS, VEC>(y, row + i);
+    double a = 0.0, q = 0.0;
+    for (unsigned i = threadIdx.x; i < n; i += kThreads) {
+        int skip;
+        const size_t at = rows.at(VEC, i, c, g, G, skip);
+        Group<TS, VEC> dv, zv, yv;
+        dv.load(dy + at);
+        zv.load(z + at);
+        if (relu) yv.load(y + at);
+        float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const float gv = (!relu || yv.v[e] > 0.f) ? dv.v[e] : 0.f;
-                s1 += gv;
-                s2 = fmaf(gv, (zv.v[e] - mu) * is, s2);
-            }
+        for (int e = 0; e < VEC; ++e) {
+            const bool counts = e >= skip;
+            const float gv = counts && (!relu || yv[e] > 0.f) ? dv[e] : 0.f;
+            s1 += gv;
+            s2 = fmaf(gv, counts ? (zv[e] - mu) * is : 0.f, s2);
         }
+        a += s1;
+        q += s2;
     }
-    double a = s1, q = s2;
     block_sum2(a, q);
     if (threadIdx.x == 0) {
-        double *o = part + ((size_t)g * C + c) * 2;
+        double *o = part + ((size_t)g * rows.C + c) * 2;
         o[0] = a;
         o[1] = q;
     }
 }
 
-// One thread per channel: dbeta, dgamma (added to the old values when accumulating) and the three
-// per-channel numbers the elementwise pass needs: coef[c] = {gamma*invstd, dbeta/N, dgamma/N}.
-__global__ void bn_bwd_finalize_kernel(const double *__restrict__ part, int G, int C, double N,
-                                       const float *__restrict__ gamma, const float *__restrict__ invstd,
-                                       float *__restrict__ dgamma, float *__restrict__ dbeta, int accumulate,
-                                       float *__restrict__ coef)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    double sb = 0.0, sg = 0.0;
-    for (int g = 0; g < G; ++g) {
-        sb += part[((size_t)g * C + c) * 2];
-        sg += part[((size_t)g * C + c) * 2 + 1];
-    }
-    if (dbeta) dbeta[c] = accumulate ? dbeta[c] + (float)sb : (float)sb;
-    if (dgamma) dgamma[c] = accumulate ? dgamma[c] + (float)sg : (float)sg;
-    coef[3 * c] = (gamma ? gamma[c] : 1.f) * invstd[c];
-    coef[3 * c + 1] = (float)(sb / N);
-    coef[3 * c + 2] = (float)(sg / N);
-}
+struct BnBwdFinal {
+    const double *part;
+    int G;
+    double N;
+    const float *gamma, *mean, *invstd;
+    float *dgamma, *dbeta;
+    int accumulate;
+};
 
-// dz = coef0*(g - coef1 - zhat*coef2) in the storage type; dres = g (optional).
+// Block j*C + c: groups j*per, ... of channel c: dz = gamma*invstd*(g - dbeta/N - zhat*dgamma/N) in the storage type; dres = g
+// (optional).  Every block adds up the at most eight parts of its channel itself, behind its loads; block c also writes dbeta and
+// dgamma (added to the old values when accumulating).  A launch of its own took 4.8 us for that.
 template <typename TS, int VEC>
-__global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(size_t ngroups, int C, int ng, const TS *__restrict__ dy,
+__global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(unsigned n, unsigned per, Rows rows, const TS *__restrict__ dy,
                                                                 const TS *__restrict__ y, const TS *__restrict__ z,
-                                                                const float *__restrict__ mean,
-                                                                const float *__restrict__ invstd,
-                                                                const float *__restrict__ coef, int relu,
-                                                                TS *__restrict__ dz, TS *__restrict__ dres)
+                                                                BnBwdFinal f, int relu, TS *__restrict__ dz,
+                                                                TS *__restrict__ dres)
 {
-    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= ngroups) return;
-    const int c = (int)((i / (size_t)ng) % (size_t)C);
-    const float mu = mean[c], is = invstd[c];
-    const float k0 = coef[3 * c], k1 = coef[3 * c + 1], k2 = coef[3 * c + 2];
-    const Group<TS, VEC> dv = load_group<TS, VEC>(dy, i);
-    const Group<TS, VEC> zv = load_group<TS, VEC>(z, i);
-    Group<TS, VEC> yv, gout, zout;
-    if (relu) yv = load_group<TS, VEC>(y, i);
+    const int c = blockIdx.x % (unsigned)rows.C;
+    const unsigned j = blockIdx.x / (unsigned)rows.C, first = j * per, last = min(n, first + per);
+    Group<TS, VEC> dv[kApplyGroups], zv[kApplyGroups], yv[kApplyGroups];
+    size_t at[kApplyGroups];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        const float gv = (!relu || yv.v[e] > 0.f) ? dv.v[e] : 0.f;
-        gout.v[e] = gv;
-        zout.v[e] = k0 * (gv - k1 - (zv.v[e] - mu) * is * k2);
+    for (int u = 0; u < kApplyGroups; ++u) {
+        const unsigned i = first + u * kThreads + threadIdx.x;
+        int skip;
+        at[u] = rows.at(VEC, min(i, n - 1), c, 0, 1, skip);
+        if (i < last) {
+            dv[u].load(dy + at[u]);
+            zv[u].load(z + at[u]);
+            if (relu) yv[u].load(y + at[u]);
+        }
     }
-    store_group<TS, VEC>(dz, i, zout);
-    if (dres) store_group<TS, VEC>(dres, i, gout);
+    double sb = 0.0, sg = 0.0;
+    double pb[kMaxParts], pg[kMaxParts];
+#pragma unroll
+    for (int g = 0; g < kMaxParts; ++g) {
+        const double *o = f.part + ((size_t)min(g, f.G - 1) * rows.C + c) * 2;
+        pb[g] = o[0];
+        pg[g] = o[1];
+    }
+#pragma unroll
+    for (int g = 0; g < kMaxParts; ++g) {
+        if (g < f.G) sb += pb[g], sg += pg[g];
+    }
+    if (threadIdx.x == 0 && j == 0) {
+        if (f.dbeta) f.dbeta[c] = f.accumulate ? f.dbeta[c] + (float)sb : (float)sb;
+        if (f.dgamma) f.dgamma[c] = f.accumulate ? f.dgamma[c] + (float)sg : (float)sg;
+    }
+    const float mu = f.mean[c], is = f.invstd[c];
+    const float k0 = (f.gamma ? f.gamma[c] : 1.f) * is, k1 = (float)(sb / f.N), k2 = (float)(sg / f.N);
+#pragma unroll
+    for (int u = 0; u < kApplyGroups; ++u) {
+        if (first + u * kThreads + threadIdx.x >= last) break;
+        float gout[VEC], zout[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float gv = (!relu || yv[u][e] > 0.f) ? dv[u][e] : 0.f;
+            gout[e] = gv;
+            zout[e] = k0 * (gv - k1 - (zv[u][e] - mu) * is * k2);
+        }
+        store_group<TS, VEC>(dz + at[u], zout);
+        if (dres) store_group<TS, VEC>(dres + at[u], gout);
+    }
 }
 
-int batch_groups(int B) { return B < 8 ? B : 8; }
+int batch_groups(int B) { return B < kMaxParts ? B : kMaxParts; }
 
-bool vec8_ok(bool is_bf16, int T, std::initializer_list<const void *> ptrs)
+// elements of a group: 16 bytes, one in rows that are shorter
+int group_size(bool is_bf16, int T)
 {
-    if (!is_bf16 || T % 8 != 0) return false;
-    for (const void *p : ptrs)
-        if (p && ((uintptr_t)p % 16) != 0) return false;
-    return true;
+    const int vec = is_bf16 ? 8 : 4;
+    return T >= vec ? vec : 1;
 }
+
+// The groups of a channel in as many blocks as a thread's kApplyGroups need, of equal work.
+struct ApplySplit {
+    unsigned n, per, blocks;
+    ApplySplit(int B, int ng)
+    {
+        n = (unsigned)B * ng;
+        blocks = (n + kApplyGroups * kThreads - 1) / (kApplyGroups * kThreads);
+        per = (n + blocks - 1) / blocks;
+    }
+};
 
 // parts of a channel's statistics: the groups of batch items of bn_stats_kernel, or one per (batch item, 160-step
 // time tile) when the convolution kernel writes them from its epilogue
@@ -273,10 +360,47 @@ size_t bn_fwd_scratch_bytes(int B, int C, int T)
     return align_up(bn_parts_cap(B, T) * C * 3 * sizeof(double), 256) + 2 * align_up((size_t)C * sizeof(float), 256);
 }
 
-size_t bn_bwd_scratch_bytes(int B, int C)
+size_t bn_bwd_scratch_bytes(int B, int C) { return align_up((size_t)batch_groups(B) * C * 2 * sizeof(double), 256); }
+
+namespace {
+
+template <typename TS, int VEC>
+hipError_t fwd_passes(int B, int C, int T, const TS *z, const BnFinal &f, bool given, const TS *res, bool relu, TS *y, hipStream_t s)
 {
-    return align_up((size_t)batch_groups(B) * C * 2 * sizeof(double), 256) + align_up((size_t)3 * C * sizeof(float), 256);
+    const Rows rows{C, T, (T + VEC - 1) / VEC};
+    if (given)
+        hipLaunchKernelGGL(bn_finalize_kernel, dim3(C), dim3(64), 0, s, f, C);
+    else
+        hipLaunchKernelGGL((bn_stats_kernel<TS, VEC>), dim3(C, f.G), dim3(kThreads), 0, s, z, B, rows, f.G, (double *)f.part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const ApplySplit a(B, rows.ng);
+    const dim3 grid(C * a.blocks);
+    if (given)
+        hipLaunchKernelGGL((bn_apply_fwd_kernel<TS, VEC, false>), grid, dim3(kThreads), 0, s, a.n, a.per, rows, z, f, res,
+                           relu ? 1 : 0, y);
+    else
+        hipLaunchKernelGGL((bn_apply_fwd_kernel<TS, VEC, true>), grid, dim3(kThreads), 0, s, a.n, a.per, rows, z, f, res,
+                           relu ? 1 : 0, y);
+    return hipGetLastError();
 }
+
+template <typename TS, int VEC>
+hipError_t bwd_passes(int B, int C, int T, const TS *dy, const TS *y, const TS *z, const BnBwdFinal &f, bool relu, TS *dz, TS *dres,
+                      hipStream_t s)
+{
+    const Rows rows{C, T, (T + VEC - 1) / VEC};
+    hipLaunchKernelGGL((bn_bwd_stats_kernel<TS, VEC>), dim3(C, f.G), dim3(kThreads), 0, s, dy, y, z, f.mean, f.invstd, relu ? 1 : 0,
+                       B, rows, f.G, (double *)f.part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const ApplySplit a(B, rows.ng);
+    hipLaunchKernelGGL((bn_bwd_apply_kernel<TS, VEC>), dim3(C * a.blocks), dim3(kThreads), 0, s, a.n, a.per, rows, dy, y, z, f,
+                       relu ? 1 : 0, dz, dres);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 // Statistics of z [B][C][T], then y = relu?(gamma*zhat + beta + residual).  scratch: bn_fwd_scratch_bytes.
 hipError_t launch_bn_fwd(int B, int C, int T, bool is_bf16, const void *z, const float *gamma, const float *beta, float eps,
@@ -285,37 +409,16 @@ hipError_t launch_bn_fwd(int B, int C, int T, bool is_bf16, const void *z, const
 {
     // given_parts > 0: the part array already holds that many parts per channel (written by the convolution kernel)
     const int G = given_parts > 0 ? given_parts : batch_groups(B);
-    double *part = (double *)scratch;
     float *scale = (float *)((unsigned char *)scratch + align_up(bn_parts_cap(B, T) * C * 3 * sizeof(double), 256));
     float *shift = (float *)((unsigned char *)scale + align_up((size_t)C * sizeof(float), 256));
-    const bool v8 = vec8_ok(is_bf16, T, {z, residual, y});
-    const dim3 sgrid(C, G);
-    if (given_parts > 0)
-        ;
-    else if (v8)
-        hipLaunchKernelGGL((bn_stats_kernel<bf16_t, 8>), sgrid, dim3(kThreads), 0, s, (const bf16_t *)z, B, C, T, G, part);
-    else if (is_bf16)
-        hipLaunchKernelGGL((bn_stats_kernel<bf16_t, 1>), sgrid, dim3(kThreads), 0, s, (const bf16_t *)z, B, C, T, G, part);
-    else
-        hipLaunchKernelGGL((bn_stats_kernel<float, 1>), sgrid, dim3(kThreads), 0, s, (const float *)z, B, C, T, G, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bn_finalize_kernel, dim3(C), dim3(64), 0, s, part, G, C, gamma, beta, eps, mean, invstd, scale, shift);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int ng = v8 ? T / 8 : T;
-    const size_t ngroups = (size_t)B * C * ng;
-    const dim3 agrid((unsigned)((ngroups + kThreads - 1) / kThreads));
-    if (v8)
-        hipLaunchKernelGGL((bn_apply_fwd_kernel<bf16_t, 8>), agrid, dim3(kThreads), 0, s, ngroups, C, ng, (const bf16_t *)z,
-                           scale, shift, (const bf16_t *)residual, relu ? 1 : 0, (bf16_t *)y);
-    else if (is_bf16)
-        hipLaunchKernelGGL((bn_apply_fwd_kernel<bf16_t, 1>), agrid, dim3(kThreads), 0, s, ngroups, C, ng, (const bf16_t *)z,
-                           scale, shift, (const bf16_t *)residual, relu ? 1 : 0, (bf16_t *)y);
-    else
-        hipLaunchKernelGGL((bn_apply_fwd_kernel<float, 1>), agrid, dim3(kThreads), 0, s, ngroups, C, ng, (const float *)z,
-                           scale, shift, (const float *)residual, relu ? 1 : 0, (float *)y);
-    return hipGetLastError();
+    const BnFinal f{(const double *)scratch, G, gamma, beta, eps, mean, invstd, scale, shift};
+    auto run = [&](auto type, auto vec) {
+        using TS = decltype(type);
+        return fwd_passes<TS, decltype(vec)::value>(B, C, T, (const TS *)z, f, given_parts > 0, (const TS *)residual, relu, (TS *)y, s);
+    };
+    const bool whole = group_size(is_bf16, T) > 1;
+    if (is_bf16) return whole ? run(bf16_t{}, Vec<8>{}) : run(bf16_t{}, Vec<1>{});
+    return whole ? run(float{}, Vec<4>{}) : run(float{}, Vec<1>{});
 }
 
 // dgamma, dbeta, dres and the corrected dz (storage type) from dy, the saved y and z and the saved statistics.
@@ -323,39 +426,15 @@ hipError_t launch_bn_bwd(int B, int C, int T, bool is_bf16, const void *dy, cons
                          const float *mean, const float *invstd, bool relu, void *dz, void *dres, float *dgamma,
                          float *dbeta, bool accumulate, void *scratch, hipStream_t s)
 {
-    const int G = batch_groups(B);
-    double *part = (double *)scratch;
-    float *coef = (float *)((unsigned char *)scratch + align_up((size_t)G * C * 2 * sizeof(double), 256));
-    const bool v8 = vec8_ok(is_bf16, T, {dy, y, z, dz, dres});
-    const dim3 sgrid(C, G);
-    if (v8)
-        hipLaunchKernelGGL((bn_bwd_stats_kernel<bf16_t, 8>), sgrid, dim3(kThreads), 0, s, (const bf16_t *)dy, (const bf16_t *)y,
-                           (const bf16_t *)z, mean, invstd, relu ? 1 : 0, B, C, T, G, part);
-    else if (is_bf16)
-        hipLaunchKernelGGL((bn_bwd_stats_kernel<bf16_t, 1>), sgrid, dim3(kThreads), 0, s, (const bf16_t *)dy, (const bf16_t *)y,
-                           (const bf16_t *)z, mean, invstd, relu ? 1 : 0, B, C, T, G, part);
-    else
-        hipLaunchKernelGGL((bn_bwd_stats_kernel<float, 1>), sgrid, dim3(kThreads), 0, s, (const float *)dy, (const float *)y,
-                           (const float *)z, mean, invstd, relu ? 1 : 0, B, C, T, G, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bn_bwd_finalize_kernel, dim3((C + 127) / 128), dim3(128), 0, s, part, G, C, (double)B * T, gamma, invstd,
-                       dgamma, dbeta, accumulate ? 1 : 0, coef);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int ng = v8 ? T / 8 : T;
-    const size_t ngroups = (size_t)B * C * ng;
-    const dim3 agrid((unsigned)((ngroups + kThreads - 1) / kThreads));
-    if (v8)
-        hipLaunchKernelGGL((bn_bwd_apply_kernel<bf16_t, 8>), agrid, dim3(kThreads), 0, s, ngroups, C, ng, (const bf16_t *)dy,
-                           (const bf16_t *)y, (const bf16_t *)z, mean, invstd, coef, relu ? 1 : 0, (bf16_t *)dz, (bf16_t *)dres);
-    else if (is_bf16)
-        hipLaunchKernelGGL((bn_bwd_apply_kernel<bf16_t, 1>), agrid, dim3(kThreads), 0, s, ngroups, C, ng, (const bf16_t *)dy,
-                           (const bf16_t *)y, (const bf16_t *)z, mean, invstd, coef, relu ? 1 : 0, (bf16_t *)dz, (bf16_t *)dres);
-    else
-        hipLaunchKernelGGL((bn_bwd_apply_kernel<float, 1>), agrid, dim3(kThreads), 0, s, ngroups, C, ng, (const float *)dy,
-                           (const float *)y, (const float *)z, mean, invstd, coef, relu ? 1 : 0, (float *)dz, (float *)dres);
-    return hipGetLastError();
+    const BnBwdFinal f{(const double *)scratch, batch_groups(B), (double)B * T, gamma, mean, invstd, dgamma, dbeta, accumulate ? 1 : 0};
+    auto run = [&](auto type, auto vec) {
+        using TS = decltype(type);
+        return bwd_passes<TS, decltype(vec)::value>(B, C, T, (const TS *)dy, (const TS *)y, (const TS *)z, f, relu, (TS *)dz, (TS *)dres,
+                                                    s);
+    };
+    const bool whole = group_size(is_bf16, T) > 1;
+    if (is_bf16) return whole ? run(bf16_t{}, Vec<8>{}) : run(bf16_t{}, Vec<1>{});
+    return whole ? run(float{}, Vec<4>{}) : run(float{}, Vec<1>{});
 }
 
 }  // namespace nm
