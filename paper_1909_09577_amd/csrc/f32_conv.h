@@ -83,7 +83,7 @@ bool f32_terms_conv_supported(int R, int K, int stride, int dil);
 void f32_terms_plan(int B, int M, int R, int Tout, int K, int most_parts, int *nt, int *nsplit);
 hipError_t launch_f32_terms_conv(const F32ConvParams &p, bool flip, int nt, hipStream_t s);
 bool f32_terms_wgrad_supported(const Geom &g);
-int f32_terms_wgrad_parts(const Geom &g, double *cost);  // cost: estimated us
-hipError_t launch_f32_terms_wgrad(const Geom &g, const float *x, const float *dz, float *part, hipStream_t s);
+int f32_terms_wgrad_parts(const Geom &g, int most, double *cost);  // at most `most`; cost: estimated us
+hipError_t launch_f32_terms_wgrad(const Geom &g, int S, const float *x, const float *dz, float *part, hipStream_t s);
 
 }  // namespace nm

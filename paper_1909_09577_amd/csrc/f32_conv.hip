@@ -337,7 +337,8 @@ hipError_t launch_f32_conv_nt(const F32ConvParams &p, const F32ConvPlan &q, hipS
 // more than the second launch takes.  A chunk of channels takes 0.9 us and 0.15 a tap (with eight channels 1.1 and 0.065), the
 // launch 1.8 and 0.7 per MB of parts (of 1587 calls 3 that share and 6 that do not are slower by 4 %, 13 at most).  Channels, K,
 // B, T: 256 -> 384, 13, 1, 260 50.9 -> 20.7 us; 256, 11, 1, 60 46.5 -> 12.2; 256, 11, 4, 250 47.1 -> 29.7; but 32 -> 16, 1, 2, 165
-// 7.0 -> 8.3, so in one part.  From half of the chip on there is nothing to share out.
+// 7.0 -> 8.3, so in one part.  From half of the chip on there is nothing to share out.  (Times of this file's kernel; that of f32_terms.hip
+// chooses again, at most as many parts as this: the room is asked for before it is known which of them runs.)
 int f32_splits(int B, int M, int R, int Tout, int K)
 {
     const size_t tiles = (size_t)((M + kTileM - 1) / kTileM) * ((Tout + 31) / 32) * B;
@@ -510,7 +511,8 @@ struct F32WgradPlan {
     bool ok, terms;  // terms: on the kernel of f32_terms.hip
     int ntg, KG, TPW, S, nchunk, units, W, x_stride;
 };
-F32WgradPlan f32_wgrad_plan(const Geom &g)
+// most: parts that there is room for; fewer than this file's kernel takes are no reason to leave it (its parts are what is asked for at least)
+F32WgradPlan f32_wgrad_plan(const Geom &g, long most = 8)
 {
     F32WgradPlan q = {};
     if (g.K > 255) return q;  // the reduction kernel's LDS tile
@@ -536,7 +538,7 @@ F32WgradPlan f32_wgrad_plan(const Geom &g)
         // that kernel's tiles are half as large: where they take a round more for little work this one is faster (384 channels, K=13,
         // B=1, T=50: 20.0 us here, 23.3 there; T=300: 37.8, 35.1)
         double cost;
-        const int parts = f32_terms_wgrad_parts(g, &cost);
+        const int parts = f32_terms_wgrad_parts(g, (int)std::max(most, (long)q.S), &cost);
         const double rounds = (double)((tiles * q.S + 255) / 256), mb = 4e-6 * g.Cout * g.Cin * (double)g.K;
         q.terms = cost < rounds * (8.2 + each * (0.8 + 1.8 * q.TPW)) + 0.5 * mb * q.S;
         if (q.terms) q.S = parts;
@@ -586,22 +588,24 @@ hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, 
     return launch_f32_conv<true>(p, part, room, s);
 }
 
-size_t f32_wgrad_part_bytes(const Geom &g)
-{
-    return align_up((size_t)f32_wgrad_plan(g).S * g.K * g.Cout * g.Cin * sizeof(float), 256);
-}
+namespace {
+size_t wgrad_part(const Geom &g) { return (size_t)g.K * g.Cout * g.Cin * sizeof(float); }
+F32WgradPlan wgrad_plan_within(const Geom &g, size_t room) { return f32_wgrad_plan(g, (long)std::min<size_t>(8, room / wgrad_part(g))); }
+}  // namespace
+
+size_t f32_wgrad_part_bytes(const Geom &g, size_t room) { return align_up(wgrad_plan_within(g, room).S * wgrad_part(g), 256); }
 
 hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *dz, const float *scale, float *dw, bool accumulate,
-                            void *part, hipStream_t s)
+                            void *part, size_t room, hipStream_t s)
 {
-    const F32WgradPlan q = f32_wgrad_plan(g);
+    const F32WgradPlan q = wgrad_plan_within(g, room);
     if (!q.ok) return hipErrorInvalidValue;
     const DefinedDw fix = {true, x, dz, nullptr};
     if (q.terms) {
         hipError_t e;
         {
             MainKernelTimer timer(s);
-            e = launch_f32_terms_wgrad(g, x, dz, (float *)part, s);
+            e = launch_f32_terms_wgrad(g, q.S, x, dz, (float *)part, s);
         }
         return e == hipSuccess ? launch_wgrad_reduce(g, (const float *)part, dw, scale, q.S, accumulate, s, &g, &fix) : e;
     }

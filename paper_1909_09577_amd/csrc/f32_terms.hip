@@ -477,9 +477,9 @@ struct TermsWgradPlan {
     int ntg, KG, TPW, S, nchunk, units, ncot, ncit;
     double cost;
 };
-// Estimated in microseconds: rounds of workgroups over the CUs (one each: the registers), their units, the sum of at most eight
+// At most most_parts parts.  Estimated in microseconds: rounds of workgroups over the CUs (one each: the registers), their units, the sum of at most eight
 // parts by their bytes.
-TermsWgradPlan wgrad_plan(const Geom &g)
+TermsWgradPlan wgrad_plan(const Geom &g, int most_parts)
 {
     TermsWgradPlan q = {};
     q.ntg = (g.K + 2 * kMostTaps - 1) / (2 * kMostTaps);
@@ -490,7 +490,7 @@ TermsWgradPlan wgrad_plan(const Geom &g)
     q.ncot = (g.Cout + kRows - 1) / kRows;
     q.ncit = (g.Cin + kRows - 1) / kRows;
     const double tiles = (double)q.ncot * q.ncit * q.ntg, mb = 4e-6 * g.Cout * g.Cin * (double)g.K;
-    for (int S = 1; S <= 8 && S <= q.units; ++S) {
+    for (int S = 1; S <= most_parts && S <= q.units; ++S) {
         const int each = (q.units + S - 1) / S;
         if (S > (q.units + each - 1) / each) continue;  // the last part of it would be empty
         const double rounds = (double)((long)(tiles * S + 255) / 256);
@@ -542,19 +542,20 @@ hipError_t launch_f32_terms_conv(const F32ConvParams &p, bool flip, int nt, hipS
 }
 
 bool f32_terms_wgrad_supported(const Geom &g) { return g.stride == 1 && g.dil == 1; }
-int f32_terms_wgrad_parts(const Geom &g, double *cost)
+int f32_terms_wgrad_parts(const Geom &g, int most, double *cost)
 {
-    const TermsWgradPlan q = wgrad_plan(g);
+    const TermsWgradPlan q = wgrad_plan(g, most);
     *cost = q.cost;
     return q.S;
 }
 
-hipError_t launch_f32_terms_wgrad(const Geom &g, const float *x, const float *dz, float *part, hipStream_t s)
+// S: what f32_terms_wgrad_parts chose
+hipError_t launch_f32_terms_wgrad(const Geom &g, int S, const float *x, const float *dz, float *part, hipStream_t s)
 {
-    const TermsWgradPlan q = wgrad_plan(g);
+    const TermsWgradPlan q = wgrad_plan(g, 1);
     TermsWgradParams p = {};
     p.B = g.B; p.Cin = g.Cin; p.Cout = g.Cout; p.T = g.T; p.To = g.To; p.K = g.K; p.pad = g.pad;
-    p.ncot = q.ncot; p.ncit = q.ncit; p.ntg = q.ntg; p.KG = q.KG; p.S = q.S; p.nchunk = q.nchunk; p.units = q.units;
+    p.ncot = q.ncot; p.ncit = q.ncit; p.ntg = q.ntg; p.KG = q.KG; p.S = S; p.nchunk = q.nchunk; p.units = q.units;
     p.x = x; p.dz = dz; p.len = g.len; p.part = part;
     const unsigned grid = (unsigned)((size_t)p.ncot * p.ncit * p.ntg * p.S);
     auto go = [&](void (*kern)(const TermsWgradParams)) { hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kTermWaves), 0, s, p); };

@@ -311,12 +311,13 @@ hipError_t launch_f32_fwd(const Geom &g, const float *x, const float *w, const f
 size_t f32_fwd_part_bytes(const Geom &g);
 size_t f32_dgrad_part_bytes(const Geom &g);
 // gy = dy*[y>0] for both gradients (scale[co] is folded into the weights, resp. multiplies the sums);
-// part: f32_wgrad_part_bytes(g) bytes
+// part: f32_wgrad_part_bytes(g, room) bytes
 hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, const float *w, float *dx, bool accumulate,
                             void *part, size_t room, hipStream_t s);
-size_t f32_wgrad_part_bytes(const Geom &g);
+// room: that there is for the parts; where it is less than all that are wanted, but not less than the fewest, as many as fit
+size_t f32_wgrad_part_bytes(const Geom &g, size_t room = (size_t)-1);
 hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *gy, const float *scale, float *dw, bool accumulate,
-                            void *part, hipStream_t s);
+                            void *part, size_t room, hipStream_t s);
 
 // ---- matrix-core kernels (mfma_*.hip), bf16 storage only -------------------------------
 // Each *_supported says whether the matrix-core path can serve the geometry; the

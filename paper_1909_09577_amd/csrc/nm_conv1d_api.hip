@@ -299,8 +299,9 @@ Route route_pass(int op, const Geom &g, int dtype, unsigned flags, bool aligned,
     r.part_at = r.need;
     r.f32 = use_f32(op, g, dtype, flags);
     if (r.f32 && op == NM_OP_BWD_WEIGHT) {
-        r.f32 = check_workspace(ws, have, r.need + f32_wgrad_part_bytes(g)) == NM_OK;
-        if (r.f32) r.need += f32_wgrad_part_bytes(g);
+        const size_t part = f32_wgrad_part_bytes(g, have > r.part_at ? have - r.part_at : 0);
+        r.f32 = check_workspace(ws, have, r.need + part) == NM_OK;
+        if (r.f32) r.need += part;
     }
     r.status = check_workspace(ws, have, r.need);
     return r;
@@ -532,7 +533,8 @@ static int bwd_weight_impl(int B, int Cin, int Cout, int T, int K, int stride, i
         dz = workspace;
     }
     if (r.f32)
-        return dev(launch_f32_wgrad(g, (const float *)x, (const float *)dz, scale, dw, accum, (unsigned char *)workspace + r.part_at, s));
+        return dev(launch_f32_wgrad(g, (const float *)x, (const float *)dz, scale, dw, accum, (unsigned char *)workspace + r.part_at,
+                                    workspace_bytes - r.part_at, s));
     MainKernelTimer timer(s);
     return dev(launch_direct_wgrad(g, bf, x, dz, scale, dw, accum, s));
 }
@@ -709,9 +711,10 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
     }
     // float32 on the matrix cores: the masked gradient is formed once for both
     // (a workspace without room for the input gradient's parts serves it too)
+    const size_t f32_taken = dtype == NM_F32 ? workspace_for(NM_OP_BWD_DATA, g, dtype, false, true) + workspace_for(NM_OP_BWD_WEIGHT, g, dtype, false, true) : 0;
+    const size_t f32_parts_room = workspace_bytes > f32_taken ? workspace_bytes - f32_taken : 0;
     const bool f32_room = whole || (!own_checks && dtype == NM_F32 &&
-                                    check_workspace(workspace, workspace_bytes, workspace_for(NM_OP_BWD_DATA, g, dtype, false, true) +
-                                                                                    asked_workspace(NM_OP_BWD_WEIGHT, g, dtype, flags)) == NM_OK);
+                                    check_workspace(workspace, workspace_bytes, f32_taken + f32_wgrad_part_bytes(g, f32_parts_room)) == NM_OK);
     const bool fused_f32 = f32_room && use_f32(NM_OP_BWD_DATA, g, dtype, flags) && use_f32(NM_OP_BWD_WEIGHT, g, dtype, flags);
     if (fused_f32) {
         DisarmOnExit disarm;
@@ -730,7 +733,7 @@ static int bwd_impl(int B, int Cin, int Cout, int T, int K, int stride, int dila
         if (err != hipSuccess) return NM_ERR_DEVICE;
         t_current_op = NM_OP_BWD_WEIGHT;
         return dev(launch_f32_wgrad(g, (const float *)x, (const float *)gy, scale, dw, (flags & NM_ACCUM_DW) != 0,
-                                    (unsigned char *)workspace + workspace_for(NM_OP_BWD_DATA, g, dtype, false, true), s));
+                                    (unsigned char *)workspace + behind, f32_parts_room, s));
     }
     if (!fused) {
         // two calls sharing the workspace one after the other (their own argument checks apply)
