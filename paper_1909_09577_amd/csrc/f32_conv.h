@@ -39,12 +39,13 @@ struct F32ConvParams {
     const float *res;              // optional, layout of out
     float *out;                    // [B][M][Tout]
     const int *len_in, *len_out;   // optional [B]
+    bool infinities;               // infinite sums are made again too
     int nsplit;                    // workgroups that share a tile's reduction channels
     float *part;                   // their sums [nsplit][B][M][Tout] (nsplit > 1)
 };
 
-// One output as the definition has it, the sums as the plain kernels take them.  The kernel below also multiplies zeros for
-// the padding: with a non-finite weight that makes a NaN of a sum that has no such product, so a NaN is made again here.
+// One output as the definition has it, the sums as the plain kernels take them.  The kernels of both engines also multiply zeros
+// for the padding: with a non-finite weight that makes a NaN of a sum that has no such product, so a NaN is made again here.
 template <bool FLIP>
 __device__ __forceinline__ float defined_sum(const F32ConvParams &p, const float *in, int len, int m, int t)
 {

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void f32_split_finish_kernel(const F32ConvPara
         return l < 0 ? 0 : (l < most ? l : most);
     };
     const int lim = limit(p.len_out, p.Tout);
-    if (v != v && t < lim) v = defined_sum<FLIP>(p, p.in + (size_t)b * p.R * p.Tin, limit(p.len_in, p.Tin), m, t);
+    if (made_again(v, p.infinities) && t < lim) v = defined_sum<FLIP>(p, p.in + (size_t)b * p.R * p.Tin, limit(p.len_in, p.Tin), m, t);
     finish_output(p, v, t < lim, m, o);
 }
 
@@ -361,6 +361,7 @@ hipError_t launch_f32_conv(F32ConvParams p, void *part, size_t room, hipStream_t
     p.part = (float *)part;
     if (f32_terms_conv_supported(p.R, p.K, p.stride, p.dil)) {
         int nt;
+        p.infinities = true;
         f32_terms_plan(p.B, p.M, p.R, p.Tout, p.K, p.nsplit, &nt, &p.nsplit);
         MainKernelTimer timer(s);
         const hipError_t e = launch_f32_terms_conv(p, FLIP, nt, s);
@@ -600,7 +601,7 @@ hipError_t launch_f32_wgrad(const Geom &g, const float *x, const float *dz, cons
 {
     const F32WgradPlan q = wgrad_plan_within(g, room);
     if (!q.ok) return hipErrorInvalidValue;
-    const DefinedDw fix = {true, x, dz, nullptr};
+    const DefinedDw fix = {true, x, dz, nullptr, q.terms};
     if (q.terms) {
         hipError_t e;
         {

@@ -5,7 +5,9 @@
 // h*h' and the five corrections are summed in accumulators of their own, so that the rounding of the small terms costs
 // nothing, and a chain of additions has one link per 16 products where the float32 instruction has eight.
 // (Terms below 2^-126 keep an absolute precision of 2^-133: operands smaller than 2^-109 lose digits.)
-// An operand that is infinite, or rounds to infinity, makes a NaN here; NaN sums are made again from the definition's products.
+// An operand that is infinite, or rounds to infinity, makes a NaN here, and leading products of rounded values can add up to an infinity
+// where the sum is finite (x = w = 2^64*(1 - 2^-10): 2^128 less the corrections).  Sums that are not finite are made again from the
+// definition's products.
 //
 // Measured (4 x 256 -> 256 channels, K = 11, T = 400; the float32 instructions of f32_conv.hip before): forward 50.0 -> 24.4 us,
 // input gradient 49.9 -> 21.9, weight gradient 34.2 -> 24.7 and its sum of four parts instead of seven 9.2 -> 6.7.  What bounds a
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(64 * kTermWaves) __attribute__((amdgpu_waves_per_eu
         if constexpr (SPLIT) {
             p.part[(size_t)blockIdx.y * p.B * p.M * p.Tout + ((size_t)b * p.M + m) * p.Tout + t] = v;
         } else {
-            if (v != v && t < lim) v = defined_sum<FLIP>(p, xb, len, m, t);
+            if (made_again(v, true) && t < lim) v = defined_sum<FLIP>(p, xb, len, m, t);
             finish_output(p, v, t < lim, m, ((size_t)b * p.M + m) * p.Tout + t);
         }
     }

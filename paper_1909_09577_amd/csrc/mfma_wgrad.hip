@@ -1074,7 +1074,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_shared_kernel(const WgradParam
 }
 
 // dw[co][ci][k] = (accumulate ? dw : 0) + scale[co] * sum_s part[s][k][co][ci]; one block per (co, 64 ci).
-// MEND: the instance that makes NaN sums again from the tensors of DefinedDw.  MANY: the instance for eight parts and more,
+// MEND: the instance that makes NaN sums (and infinities, where that is asked for) again from the tensors of DefinedDw.  MANY: the instance for eight parts and more,
 // which requests eight at a time (one after the other, 16 parts of 64 -> 256 channels, K=11, took 15 us, 6 so); for fewer it
 // only costs registers (one part of 1024 -> 512 channels, K=17: 55.6 us for the gradient, 60.5 with it).
 template <bool MEND, bool MANY>
@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
             const float *src = part + ((size_t)k * Cout + co) * Cin + ci;
 #pragma unroll MANY ? 8 : 1
             for (int sp = 0; sp < S; ++sp) s += src[(size_t)sp * K * plane];
-            if (MEND && __builtin_expect(s != s, 0)) s = defined_dw(own, defined, co, ci, k);
+            if (MEND && __builtin_expect(made_again(s, defined.infinities), 0)) s = defined_dw(own, defined, co, ci, k);
         }
         tile[l * (K + 1) + k] = s * factor;
     }

@@ -368,7 +368,14 @@ hipError_t launch_mfma_wgrad(const Geom &g, const void *x, const void *dy, const
 struct DefinedDw {
     bool f32;
     const void *x, *dy, *y;
+    bool infinities = false;  // infinite sums are made again too
 };
+// Whether a sum is made again: a NaN, and an infinity where the kernel can make one of a finite sum.
+__device__ __forceinline__ bool made_again(float sum, bool infinities)
+{
+    const float t = infinities ? sum - sum : sum;
+    return t != t;
+}
 // Names, as a profiler lists them, of the kernels that the three passes' launches above would run (tensors 16-byte
 // aligned, a forward pass with an affine; stats: the forward pass of a BatchNorm call).
 void name_mfma_fwd(const Geom &g, bool stats, size_t ws_bytes, char *name, size_t n);

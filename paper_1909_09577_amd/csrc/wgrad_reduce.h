@@ -59,12 +59,12 @@ __device__ __forceinline__ void reduce4_block(float *tile, int cb, int co, const
 #pragma unroll MANY ? 8 : 1
             for (int sp = 0; sp < S; ++sp) sum += *reinterpret_cast<const f32x4 *>(src + (size_t)sp * K * plane);
             if constexpr (MEND) {
-                const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);  // a NaN if one of them is
-                if (__builtin_expect(all != all, 0)) {
+                const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);  // a NaN (or an infinity) if one of them is
+                if (__builtin_expect(made_again(all, defined.infinities), 0)) {
 #pragma clang loop unroll(disable)
                     for (int e = 0; e < 4; ++e) {
                         const float one = e == 0 ? sum[0] : e == 1 ? sum[1] : e == 2 ? sum[2] : sum[3];
-                        if (one == one) continue;
+                        if (!made_again(one, defined.infinities)) continue;
                         const float z = defined_dw(own, defined, co, ci + e, k);
                         if (e == 0) sum[0] = z; else if (e == 1) sum[1] = z; else if (e == 2) sum[2] = z; else sum[3] = z;
                     }
