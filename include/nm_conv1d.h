@@ -41,8 +41,8 @@
  *    also multiply the zeros they put for padding, so that an infinite weight, or, where T and T_out are
  *    multiples of eight, an infinite sample or gradient can make a NaN of a result near it that the
  *    definition leaves finite.
- *  - NM_F32 mode works on float32 operands whole (as they are, or as exact sums of three bfloat16 terms); operands
- *    smaller than 2^-109 may lose digits below 2^-133.
+ *  - NM_F32 mode works on float32 operands whole (as they are, or as exact sums of three bfloat16 terms).  Operands
+ *    from 2^112 on and results from 2^96 on are served like infinities: right, but slowly.
  *  - Each tensor must hold fewer than 2^31 elements.
  */
 #ifndef NM_CONV1D_H

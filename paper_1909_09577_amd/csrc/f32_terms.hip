@@ -4,10 +4,11 @@
 // bfloat16 values are exact in float32.  Six v_mfma_f32_32x32x16_bf16 of 32 cycles do what eight v_mfma_f32_32x32x2_f32 of 64 do.
 // h*h' and the five corrections are summed in accumulators of their own, so that the rounding of the small terms costs
 // nothing, and a chain of additions has one link per 16 products where the float32 instruction has eight.
-// (Terms below 2^-126 keep an absolute precision of 2^-133: operands smaller than 2^-109 lose digits.)
+// Operands are multiplied by 2^16 first and the sums by 2^-32 last: every float32 number, the denormal ones included, is then a multiple
+// of 2^-133, which is what bfloat16 terms resolve (unscaled, operands below 2^-109 lost digits, those of 2^-126 all but nine).
 // An operand that is infinite, or rounds to infinity, makes a NaN here, and leading products of rounded values can add up to an infinity
-// where the sum is finite (x = w = 2^64*(1 - 2^-10): 2^128 less the corrections).  Sums that are not finite are made again from the
-// definition's products.
+// where the sum is finite (unscaled, x = w = 2^64*(1 - 2^-10): 2^128 less the corrections).  Sums that are not finite are made again from
+// the definition's products; so are, then, those of operands from 2^112 on and those that reach 2^96.
 //
 // Measured (4 x 256 -> 256 channels, K = 11, T = 400; the float32 instructions of f32_conv.hip before): forward 50.0 -> 24.4 us,
 // input gradient 49.9 -> 21.9, weight gradient 34.2 -> 24.7 and its sum of four parts instead of seven 9.2 -> 6.7.  What bounds a
@@ -23,6 +24,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTermWaves = 8;  // two per SIMD: one splits and reads while the other multiplies
 constexpr int kRows = 32;      // output channels of a tile
+constexpr float kLift = 65536.f, kDrop = 1.f / (kLift * kLift);  // of an operand, of a sum
 
 // two floats -> three packed pairs of terms
 __device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
@@ -160,19 +162,18 @@ __global__ __launch_bounds__(64 * kTermWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int i = 0; i < Q::WCOLS; ++i)
                 if (i + 1 < Q::WCOLS || wlast)
-                    *reinterpret_cast<f32x4 *>(ws + (8 * g + wrow) * Q::WSTRIDE + 4 * (wcol + 8 * i)) = wv[g][i];
-        if constexpr (Q::WREST) *reinterpret_cast<f32x4 *>(ws + rrow * Q::WSTRIDE + 4 * rcol) = wr;
-        if (FLIP && p.rscale) {
+                    *reinterpret_cast<f32x4 *>(ws + (8 * g + wrow) * Q::WSTRIDE + 4 * (wcol + 8 * i)) = wv[g][i] * kLift;
+        if constexpr (Q::WREST) *reinterpret_cast<f32x4 *>(ws + rrow * Q::WSTRIDE + 4 * rcol) = wr * kLift;
+        auto factor = [&](int r) { return FLIP && p.rscale ? p.rscale[min(r, p.R - 1)] * kLift : kLift; };
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float f = p.rscale[min(c * 8 + j, p.R - 1)];
+        for (int j = 0; j < 8; ++j) {
+            const float f = factor(c * 8 + j);
 #pragma unroll
-                for (int q = 0; q < kFullGroups; ++q) xv[q][j] *= f;
-            }
-            if constexpr (kTailPairs) {
+            for (int q = 0; q < kFullGroups; ++q) xv[q][j] *= f;
+        }
+        if constexpr (kTailPairs) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i) xt[i] *= p.rscale[min(c * 8 + 2 * (lane >> 4) + i, p.R - 1)];
-            }
+            for (int i = 0; i < 2; ++i) xt[i] *= factor(c * 8 + 2 * (lane >> 4) + i);
         }
 #pragma unroll
         for (int f = 0; f < kFullGroups; ++f)
@@ -274,6 +275,7 @@ __global__ __launch_bounds__(64 * kTermWaves) __attribute__((amdgpu_waves_per_eu
         float v = 0.f;
 #pragma unroll
         for (int q = 0; q < kTermWaves; ++q) v += lds[q * kRows * TN + e];
+        v *= kDrop;
         if constexpr (SPLIT) {
             p.part[(size_t)blockIdx.y * p.B * p.M * p.Tout + ((size_t)b * p.M + m) * p.Tout + t] = v;
         } else {
@@ -410,8 +412,8 @@ __global__ __launch_bounds__(64 * kTermWaves) __attribute__((amdgpu_waves_per_eu
     auto store_unit = [&](unsigned char *buf) {
         auto put = [&](const float(&f)[4], unsigned char *to, int plane) {
             uint32_t a[3], b[3];
-            split2(f[0], f[1], a[0], a[1], a[2]);
-            split2(f[2], f[3], b[0], b[1], b[2]);
+            split2(f[0] * kLift, f[1] * kLift, a[0], a[1], a[2]);
+            split2(f[2] * kLift, f[3] * kLift, b[0], b[1], b[2]);
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 reinterpret_cast<uint32_t *>(to + q * plane)[0] = a[q];
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(64 * kTermWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
                 for (int q = 1; q < 4; ++q) z += red[(2 * q + half) * kTile + at];
                 if (co0 + co < p.Cout && ci0 + l32 < p.Cin)
-                    p.part[(((size_t)sp * p.K + k0 + tap) * p.Cout + co0 + co) * p.Cin + ci0 + l32] = z;
+                    p.part[(((size_t)sp * p.K + k0 + tap) * p.Cout + co0 + co) * p.Cin + ci0 + l32] = z * kDrop;
             }
         }
     }

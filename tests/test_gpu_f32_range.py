@@ -56,3 +56,30 @@ def test_infinities_and_overflow(dims):
         # (rows with a finite 3e38 in them have finite results of that size: scaled by each channel's largest)
         top = np.abs(np.where(fin, ref, 0)).max()
         assert np.abs(np.where(fin, got, 0) - np.where(fin, ref, 0)).max() <= 1e-5 * top
+
+
+# sizes of the two operands of a pass: float32's smallest normal numbers, denormal ones, the edges of what bfloat16 terms hold as they are
+SIZES = [(-126, 100), (-140, 120), (-109, 90), (-115, 20), (110, -100), (120, -126), (-70, -60)]
+
+
+@pytest.mark.parametrize("swap", [False, True], ids=["", "swapped"])
+@pytest.mark.parametrize("sizes", SIZES, ids=str)
+def test_operands_of_any_size(sizes, swap):
+    """The error stays that of float32 sums (1e-6 of the result, 2e-7 being measured) wherever the results are normal numbers; of
+    results below 2^-126 it stays below the sum of their roundings, half of 2^-149 for each of a few hundred products."""
+    import torch
+    from oracle import conv1d_oracle as orc
+    a, b = (2.0 ** e for e in (sizes[::-1] if swap else sizes))
+    rng = np.random.default_rng(4)
+    B, C, M, T, K = 2, 64, 48, 70, 11
+    kw = dict(stride=1, dilation=1, pad=5)
+    draw = lambda size, *s: (rng.standard_normal(s) * size).astype(np.float32)
+    dev = lambda v: torch.from_numpy(v).cuda()
+    x, dy, w_x, w_dy, dy_x = draw(a, B, C, T), draw(a, B, M, T), draw(b, M, C, K), draw(b, M, C, K), draw(b, B, M, T)
+    for got, ref in ((nm.nm_conv1d_block_fwd(dev(x), dev(w_x), None, None, None, relu=False, **kw), orc.block_fwd(x, w_x, None, None, None, False, **kw)),
+                     (nm.nm_conv1d_bwd_data(dev(dy), dev(w_dy), T, relu=False, **kw)[0], orc.bwd_data(dy, w_dy, T, **kw)),
+                     (nm.nm_conv1d_bwd_weight(dev(x), dev(dy_x), K, relu=False, **kw), orc.bwd_weight(x, dy_x, K, **kw))):
+        ref = np.asarray(ref, dtype=np.float64)
+        assert np.isfinite(ref).all() and np.linalg.norm(ref) > 0
+        off = np.linalg.norm(got.double().cpu().numpy() - ref)
+        assert off <= 1e-6 * np.linalg.norm(ref) + (2.0 ** -149 * 500 * ref.size ** 0.5 if sum(sizes) < -100 else 0), (off / np.linalg.norm(ref))
