@@ -591,7 +591,8 @@ hipError_t launch_f32_dgrad(const Geom &g, const float *gy, const float *scale, 
 
 namespace {
 size_t wgrad_part(const Geom &g) { return (size_t)g.K * g.Cout * g.Cin * sizeof(float); }
-F32WgradPlan wgrad_plan_within(const Geom &g, size_t room) { return f32_wgrad_plan(g, (long)std::min<size_t>(8, room / wgrad_part(g))); }
+// (the parts' room is rounded up to 256 bytes, so what there is counts rounded down)
+F32WgradPlan wgrad_plan_within(const Geom &g, size_t room) { return f32_wgrad_plan(g, (long)std::min<size_t>(8, room / 256 * 256 / wgrad_part(g))); }
 }  // namespace
 
 size_t f32_wgrad_part_bytes(const Geom &g, size_t room) { return align_up(wgrad_plan_within(g, room).S * wgrad_part(g), 256); }

@@ -42,3 +42,22 @@ def test_results(dims, room, both):
     guard = torch.full((both + 512,), 255, dtype=torch.uint8, device="cuda")
     dx, _, dw = nm.nm_conv1d_bwd(xd, dyd, wd, workspace=guard[:both], **kw)
     assert near(dw, ref_dw) and near(dx, ref_dx) and (guard[both:] == 255).all()
+
+
+@pytest.mark.parametrize("dims", [(8, 205, 268, 393, 25, 1, 1, 12), (10, 250, 169, 668, 25, 1, 1, 12), (3, 97, 130, 500, 13, 1, 1, 6), (5, 33, 65, 711, 7, 2, 1, 3)],
+                         ids=str)
+def test_more_room_is_never_served_by_a_slower_kernel(dims):
+    """Parts that are no multiple of 256 bytes: at every byte around the size of each number of parts."""
+    import ctypes
+    L, name = nm.lib(), ctypes.create_string_buffer(100)
+    asked = nm.nm_conv1d_workspace_bytes(nm.NM_OP_BWD_WEIGHT, *dims, nm.NM_F32, 1)
+    T_out = nm.nm_conv1d_out_len(dims[3], *dims[4:])
+    g, part = -(-4 * dims[0] * dims[2] * T_out // 256) * 256, 4 * dims[1] * dims[2] * dims[4]
+    assert part % 256 != 0
+    fast = []
+    for parts in range(1, 9):
+        for n in range(g + parts * part - 300, g + parts * part + 301):
+            assert L.nm_conv1d_kernel_name(nm.NM_OP_BWD_WEIGHT, *dims, nm.NM_F32, 1, 0, n, name, 100) == nm.NM_OK
+            fast.append(name.value.startswith(b"f32_"))
+            assert n < asked or fast[-1]
+    assert fast == sorted(fast) and fast[-1] and not fast[0]
