@@ -1966,13 +1966,24 @@ hipError_t launch_split(const SplitPlan &sp, const ConvGemmParams &p0, int strid
 // workgroups.  In a sweep over 32 to 256 input and 192 to 512 output channels, 50 to 51200 steps, the lines below
 // separate gains (forward 1.1 to 1.5 times, gradient up to 1.5) from losses but for a few per cent: forward 64 -> 256, B=24,
 // T=1000, 192 workgroups 15.2 us on conv_split_kernel, 15.6 here; B=20, T=1203, 200 of them 23.2 / 17.6; gradient, 64
-// workgroups 24.8 / 24.9, 84 29.4 / 28.2.
-bool takes_rows(const Plan &pl, int B, int M, int Tout, int K, int dil)
+// workgroups 24.8 / 24.9, 84 29.4 / 28.2.  The wavefronts of a row group that is
+// half full or less wait for the others, which costs most where a last round of workgroups is nearly empty: 600 calls of up to 1024 input
+// channels take 0.85 of the time on average, the worst 1.06, where that goes to the engine for few tiles (638 -> 384, B=28, T=528, 24 workgroups
+// in the last round, 60.0 us there, 91.5 here; 118 -> 300, B=24, T=1352, 16 of them, 39.1 / 45.8; 273 -> 257, B=24, T=800, 80 of them
+// 53.6 / 48.8).  Layers of six taps and stride 1 run the gradient's instance; with few chunks it needs more workgroups for its longer start (50
+// channels and 90 workgroups 11.5 / 13.0, 96 and 138 13.3 / 14.7, 50 and 387 20.4 / 19.2).
+// (phases: both parities of a strided gradient)
+bool takes_rows(const Plan &pl, const SplitPlan &sp, int B, int M, int R, int Tout, int K, int dil, bool phases)
 {
     const int nmt = (M + kTileM - 1) / kTileM;
     if (!pl.ok || dil != 1) return false;
-    if (pl.stride == 2) return K == 11 && nmt >= 3 && (long)B * ((Tout + 63) / 64) * nmt >= 4 * 200;
-    return K == 6 && nmt == 2 && M >= 96 && (long)B * ((Tout + 127) / 128) >= 80;  // (a second tile that is at least half full)
+    if (pl.stride == 2) {
+        const long cols = (long)B * ((Tout + 63) / 64), wgs = cols * ((nmt + 3) / 4);
+        const bool idle = (nmt & 3) == 1 || (nmt & 3) == 2, thin = wgs > 256 && wgs % 256 > 0 && wgs % 256 <= 96;
+        return K == 11 && nmt >= 3 && cols * nmt >= 4 * 200 && !(sp.nt && idle && thin);
+    }
+    const int least = phases ? 80 : std::max(80, 256 - 32 * ((R + kChunk - 1) / kChunk));
+    return K == 6 && nmt == 2 && M >= 96 && (long)B * ((Tout + 127) / 128) >= least;  // (a second tile that is at least half full)
 }
 template <int STRIDE, int WM, int KT>
 hipError_t launch_rows_t(ConvGemmParams p, hipStream_t s)
@@ -2002,7 +2013,7 @@ ConvChoice choose_conv(const Plan &pl, const SplitPlan &sp, const ConvGemmParams
         c.kind = ConvChoice::kFew;
         return c;
     }
-    if (!p.stats && takes_rows(pl, p.B, p.M, p.Tout, p.K, p.dil)) {
+    if (!p.stats && takes_rows(pl, sp, p.B, p.M, p.R, p.Tout, p.K, p.dil, p.len_out_div == 2)) {
         c.kind = ConvChoice::kRows;
         c.stride = pl.stride;
         return c;
@@ -2535,6 +2546,7 @@ void name_mfma_dgrad(const Geom &g, bool accumulate, size_t ws_bytes, char *name
         pl = make_plan(row_pitch(g.To), ph.Up, g.Cout, ph.K, 1, 1);
         fill_common(p, pl, g.B, 2 * g.Cin, g.Cout, row_pitch(g.To), ph.Up, ph.K, 1, ph.padL, false);
         p.len_out = g.len;
+        p.len_out_div = 2;
     } else {
         pl = make_plan(row_pitch(g.To), g.T, g.Cout, g.K, 1, g.dil);
         fill_dgrad(p, pl, g, nullptr, nullptr, &dx, accumulate);
