@@ -250,8 +250,9 @@ int nm_conv1d_time_next_kernel_of(void *start_event, void *stop_event, int op);
 /* Which kernel a pass runs on, for tests and profiles: the name of the main kernel of pass `op` (NM_OP_FWD, NM_OP_BWD_DATA,
  * NM_OP_BWD_WEIGHT, or NM_OP_BN_FWD for the forward pass of a BatchNorm call) of this geometry, dtype and flags, with
  * (masked != 0) or without lengths, given workspace_bytes of workspace for the pass itself.  Tensors are taken to be
- * 16-byte aligned, a forward pass to have scale or shift.  Kernels whose reduction is shared are named with the number of
- * its parts: "conv_split_kernel<2, 1> in 12 parts".  The name is cut to name_bytes.  Host only.
+ * 16-byte aligned, a forward pass to have scale or shift.  The bfloat16 kernels whose reduction is shared are named with
+ * the number of its parts: "conv_split_kernel<2, 1> in 12 parts"; those of NM_F32 mode by "f32_conv_kernel" and "f32_wgrad_kernel" alone,
+ * whichever instructions, tile and parts they work with.  The name is cut to name_bytes.  Host only.
  * NM_ERR_WORKSPACE where the pass would return that. */
 int nm_conv1d_kernel_name(int op, int B, int Cin, int Cout, int T, int K, int stride, int dilation, int pad, int dtype,
                           unsigned flags, int masked, size_t workspace_bytes, char *name, size_t name_bytes);

@@ -509,9 +509,11 @@ TermsWgradPlan wgrad_plan(const Geom &g, int most_parts)
 
 }  // namespace
 
-// The tap counts whose weights fit the LDS in this form, and sums of no more links (products of a wavefront to one accumulator)
-// than leave the error below that of the float32 instructions' short sums: 42 of 384 channels, K=13, where it is the same
-// (1.25e-7 against 64 bits; 20 to 35 % smaller with fewer).
+// The tap counts that have instances: 11 and 13, those of the encoder's first three blocks, whose layers the estimates below are fitted to.
+// The LDS does not draw that line (3 to 14 taps fit with all three tiles, 15 with two, 17 with one): other counts have not been measured
+// here and run on the float32 instructions.  And sums of no more links (products of a wavefront to one accumulator) than leave the error
+// below that of those instructions' short sums: 42 of 384 channels, K=13, where it is the same (1.25e-7 against 64 bits; 20 to 35 %
+// smaller with fewer).
 bool f32_terms_conv_supported(int R, int K, int stride, int dil)
 {
     const int links = ((R + 7) / 8 + kTermWaves - 1) / kTermWaves * ((K + 1) / 2);

@@ -56,8 +56,9 @@ def _serve(recorder):
     json.dump(out, sys.stdout)
 
 
-def run(calls):
-    """[(status, [(kind, kernel or event handle, grid), ...]), ...]; kind: launch, refused, event."""
+def run(calls, instances=False):
+    """[(status, [(kind, kernel or event handle, grid), ...]), ...]; kind: launch, refused, event.  instances: kernels with their template
+    arguments, ("f32_conv_kernel", 1, 0, 11, 1)."""
     with tempfile.TemporaryDirectory() as tmp:
         rec = os.path.join(tmp, "librecorder.so")
         subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", rec, os.path.join(ROOT, "tests", "launch_recorder.c")], check=True)
@@ -68,8 +69,11 @@ def run(calls):
         seq = []
         for l in lines:
             kind, name, *grid = l.rsplit(" ", 4) if l.count(" ") == 4 else l.split(" ")
-            k = re.search(r"\d([a-z][a-z0-9_]*_kernel)", name)
-            seq.append((kind, int(name) if kind == "event" else k.group(1) if k else name, tuple(map(int, grid))))
+            k = re.search(r"\d([a-z][a-z0-9_]*_kernel)(?:I((?:L[ib]\d+E)+)E)?", name)
+            what = k.group(1) if k else name
+            if k and instances:
+                what = (what, *map(int, re.findall(r"L[ib](\d+)E", k.group(2) or "")))
+            seq.append((kind, int(name) if kind == "event" else what, tuple(map(int, grid))))
         res.append((status, seq))
     return res
 

@@ -1,5 +1,5 @@
 """Float32 weight gradients with room for fewer parts than are asked for, but for those of the kernel on the float32 instructions (what was
-asked for when it was the only one): they stay on the matrix cores, with as many parts as fit.  Without room for any the plain kernel runs."""
+asked for when it was the only one): they stay on the matrix cores, with no more parts than fit.  Without room for any the plain kernel runs."""
 import numpy as np
 import pytest
 

@@ -10,11 +10,12 @@ from paper_1909_09577_amd import binding as nm
 
 pytestmark = pytest.mark.gpu
 
-# tiles of 32 channels x 32, 64 and 96 steps, in one part and in several; chunks of eight channels, the last one short; 64-step units of
-# the weight gradient, its slices of 16 and its groups of 4, 8 and 12 taps
-CASES = [base.L("t32", 1, 70, 40, 33, 11, pad=5, residual=True), base.L("t32_one", 9, 61, 230, 97, 13, pad=6),
-         base.L("t64", 4, 200, 131, 193, 11, pad=5, residual=True), base.L("t64_parts", 1, 130, 97, 127, 13, pad=6),
-         base.L("t96", 5, 136, 257, 289, 11, pad=5), base.L("t96_k13", 6, 97, 300, 311, 13, pad=6, residual=True),
+# around the edges of tiles of 32 channels x 32, 64 and 96 steps (test_f32_terms_instances.py says which tile and parts a size runs on, and
+# reaches all of them); chunks of eight channels, the last one short; 64-step units of the weight gradient, its slices of 16 and its groups
+# of 4, 8 and 12 taps
+CASES = [base.L("cols_33", 1, 70, 40, 33, 11, pad=5, residual=True), base.L("cols_97", 9, 61, 230, 97, 13, pad=6),
+         base.L("cols_193", 4, 200, 131, 193, 11, pad=5, residual=True), base.L("cols_127", 1, 130, 97, 127, 13, pad=6),
+         base.L("cols_289", 5, 136, 257, 289, 11, pad=5), base.L("cols_311", 6, 97, 300, 311, 13, pad=6, residual=True),
          base.L("pad_wide", 2, 33, 34, 64, 11, pad=10), base.L("pad_none", 2, 40, 32, 80, 13, pad=0),
          base.L("taps_4", 2, 40, 48, 65, 4, pad=1), base.L("taps_8", 3, 31, 33, 129, 8, pad=3), base.L("taps_25", 2, 65, 32, 90, 25, pad=12)]
 
