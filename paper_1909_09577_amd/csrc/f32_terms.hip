@@ -10,8 +10,8 @@
 // where the sum is finite (unscaled, x = w = 2^64*(1 - 2^-10): 2^128 less the corrections).  Sums that are not finite are made again from
 // the definition's products; so are, then, those of operands from 2^112 on and those that reach 2^96.
 //
-// Measured (4 x 256 -> 256 channels, K = 11, T = 400; the float32 instructions of f32_conv.hip before): forward 50.0 -> 24.4 us,
-// input gradient 49.9 -> 21.9, weight gradient 34.2 -> 24.7 and its sum of four parts instead of seven 9.2 -> 6.7.  What bounds a
+// Measured (4 x 256 -> 256 channels, K = 11, T = 400; the float32 instructions of f32_conv.hip before): forward 50.0 -> 24.5 us,
+// input gradient 49.9 -> 22.9, weight gradient 34.2 -> 24.7 and its sum of four parts instead of seven 9.2 -> 6.7.  What bounds a
 // convolution: its products alone take 11 us of that (at the 1.65 GHz these phases run at), splitting and LDS accesses alone as
 // long; two wavefronts per SIMD overlap them to 16, the rest is the first loads and the sum of the wavefronts.
 #include "f32_conv.h"
