@@ -3,6 +3,7 @@ instance."""
 import pytest
 
 import test_gpu_any_rows as rows
+import test_gpu_rows_kernel as strided
 from paper_1909_09577_amd import binding as nm
 
 
@@ -39,3 +40,19 @@ CASES = [rows.L("six", 25, 36, 103, 968, 6, pad=3, residual=True), rows.L("six_o
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
 def test_six_taps_results(cfg, masked):
     rows.test_rows_of_any_length(cfg, masked)
+
+
+# row groups of two, one and three tiles that stay on the kernel, the last chunk short
+PARTIAL = [strided.L(45, 70, 330, 386, False), strided.L(45, 40, 270, 389), strided.L(90, 33, 180, 257)]
+
+
+@pytest.mark.parametrize("cfg", PARTIAL, ids=lambda c: "x".join(map(str, c.dims())))
+def test_half_empty_row_groups(cfg):
+    assert nm.nm_conv1d_kernel_name(nm.NM_OP_FWD, *cfg.dims(), flags=nm.NM_RELU).startswith("conv_rows_kernel<2, 4, 11>")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("masked", [False, True], ids=["full", "lengths"])
+@pytest.mark.parametrize("cfg", PARTIAL, ids=lambda c: "x".join(map(str, c.dims())))
+def test_half_empty_row_groups_results(cfg, masked):
+    strided.test_passes(cfg, masked)
